@@ -143,7 +143,7 @@ struct demon_vae {
     const float* head_alpha = nullptr;  const float* head_inv_beta = nullptr;
     int head_cin = 0;
 
-    // fp32 path: residual stream ping/pong + Snake scratch, all fp32.
+    // fp32 path: residual stream, activated operand of the next layer, branch tensor / next residual stream, all fp32.
     // bf16 path: buf[0], buf[1] residual stream ping/pong (half), buf[2] bf16 activated branch tensor,
     // buf[3], buf[4] bf16 activated operand of the next layer (each bf16 buffer: hi plane + lo plane).
     // head_out: planar window waveforms [out_channels, cap_frames*S]; slot_gated: per-call copy of a window table with
@@ -400,7 +400,6 @@ demon_status run_pass(demon_vae* v, const Workspace& ws, const Plan* plan, const
     auto conv_args = [&](const ConvLayer& L, const void* x, void* y, const void* res) {
         ConvArgs a;
         a.x = x; a.y = y; a.res = res; a.w = L.w; a.bias = L.bias;
-        a.in_alpha = L.in_alpha; a.in_inv_beta = L.in_inv_beta;
         a.out_alpha = L.out_alpha; a.out_inv_beta = L.out_inv_beta;
         a.slots = gs; a.n_slots = gn; a.max_len = ml; a.max_int = plan->max_int; a.margin = L.margin; a.r_in = r;
         a.cin = L.cin; a.cout = L.cout; a.ntaps = L.ntaps; a.dil = L.dil; a.stride = L.stride; a.down = L.down;
@@ -414,38 +413,42 @@ demon_status run_pass(demon_vae* v, const Workspace& ws, const Plan* plan, const
     auto resampled = [](int rate, const ConvLayer& L) { return L.down > 0 ? rate / L.down : rate * L.stride; };
 
     if (!bf) {
-        // ---- fp32 path: Snake on a layer's input runs as its own kernel into buf[2]
-        if (enc)
-            HIP_TRY(launch_stem(io.d_wave, cur, false, nullptr, 0, v->stem_w, v->stem_bias, nullptr, nullptr, v->st.out_channels,
+        // ---- fp32 path.  Three buffers in rotation: `cur` holds the residual stream h, `act` the activated operand of the
+        // next layer (written by the producer of h with that layer's Snake), `other` is free.
+        void* act = ws.buf[2];
+        if (enc) {
+            const ConvLayer& C = *v->first_consumer;
+            HIP_TRY(launch_stem(io.d_wave, cur, false, act, 0, v->stem_w, v->stem_bias, C.in_alpha, C.in_inv_beta, v->st.out_channels,
                                 v->stem_cout, v->st.head_kernel, S, n_frames, v->stem_margin, slots, ns, ml, plan->max_int, stream), "stem");
-        else
-            HIP_TRY(launch_gather(io.d_latent, (float*)cur, v->st.c0, n_frames, false, slots, ns, ml, stream), "gather");
+        } else {
+            const ConvLayer& C = *v->first_consumer;
+            HIP_TRY(launch_gather(io.d_latent, (float*)act, v->st.c0, n_frames, false, slots, ns, ml, stream, nullptr, 0, 0,
+                                  C.in_alpha, C.in_inv_beta), "gather");
+        }
         HIP_TRY(mark(1), "event");
-        auto run_conv = [&](const ConvLayer& L, const void* x, void* y, const void* res) -> hipError_t {
-            ConvArgs a = conv_args(L, x, y, res);
-            if (L.in_alpha) {
-                hipError_t e = launch_snake_f32((const float*)x, (float*)ws.buf[2], L.in_alpha, L.in_inv_beta, L.cin,
-                                                (size_t)plan->total_frames * r * L.cin, stream);
-                if (e != hipSuccess) return e;
-                a.x = ws.buf[2];
-                a.in_alpha = a.in_inv_beta = nullptr;
-            }
-            return launch_conv_f32(a, stream);
-        };
         for (size_t si = 0; si < n_steps; ++si) {
             const Step& T = v->steps[si];
+            const ConvLayer* C = T.consumer;
             const bool last = si + 1 == n_steps;
+            auto emit_to = [&](ConvArgs& a, void* ya) { if (C) { a.ya = ya; a.out_alpha = C->in_alpha; a.out_inv_beta = C->in_inv_beta; } };
             if (T.conv) {
-                HIP_TRY(run_conv(*T.conv, cur, other, nullptr), "resampling convolution");
+                ConvArgs a = conv_args(*T.conv, act, other, nullptr);
+                emit_to(a, cur);                                       // the old h is not needed any more
+                HIP_TRY(launch_conv_f32(a, stream), "resampling convolution");
                 HIP_TRY(mark(last ? 1 : 2), "event");
-                std::swap(cur, other);
+                void* const old = cur;
+                cur = other; other = act; act = old;
                 r = resampled(r, *T.conv);
                 HIP_TRY(tap(cur, T.conv->cout), "debug tap");
             } else {
                 const ResUnit& U = *T.unit;
-                HIP_TRY(run_conv(U.dilated, cur, other, nullptr), "dilated convolution");
+                ConvArgs d = conv_args(U.dilated, act, nullptr, nullptr);
+                d.ya = other;                                          // Snake between the convolutions: the layer's own out_alpha
+                HIP_TRY(launch_conv_f32(d, stream), "dilated convolution");
                 HIP_TRY(mark(2), "event");
-                HIP_TRY(run_conv(U.pointwise, other, cur, cur), "pointwise convolution");   // in place on the residual stream
+                ConvArgs q = conv_args(U.pointwise, other, cur, cur);  // in place on the residual stream
+                emit_to(q, act);
+                HIP_TRY(launch_conv_f32(q, stream), "pointwise convolution");
                 HIP_TRY(mark(last ? 1 : 2), "event");
                 HIP_TRY(tap(cur, U.pointwise.cout), "debug tap");
             }

@@ -56,14 +56,13 @@ enum OperandFmt { OP_BF16 = 0,     // one bf16 plane
                   OP_F16 = 2 };    // one IEEE half plane, f16 MFMA
 
 struct ConvArgs {
-    const void* x;        // input activation [rows_in, cin] (fp32 path: fp32; bf16 path: activated bf16 operand)
+    const void* x;        // activated input [rows_in, cin] (fp32 path: fp32; bf16 path: 16-bit operand)
     void* y;              // output activation [rows_out, cout] (fp32 path: fp32; bf16 path: half); bf16 dilated conv: unused
-    void* ya = nullptr;   // bf16 path: activated bf16 copy of the output for the next layer (Snake out_alpha/out_inv_beta)
+    void* ya = nullptr;   // activated copy of the output for the next layer (Snake out_alpha/out_inv_beta); fp32 path: fp32
     const void* res;      // residual (same layout as y) or nullptr; bf16 path: must equal y (in place)
     const void* w;        // packed weights (layout private to each kernel family)
     const float* bias;    // [cout]
-    const float* in_alpha;   const float* in_inv_beta;    // Snake on the input, or nullptr
-    const float* out_alpha;  const float* out_inv_beta;   // Snake on the output, or nullptr
+    const float* out_alpha;  const float* out_inv_beta;   // Snake applied before writing ya, or nullptr
     const Slot* slots;    // device
     int n_slots;
     int max_len;          // longest slot (frames)
@@ -83,9 +82,8 @@ struct ConvArgs {
     bool wide_tile_ok = true;                    // bf16 path: dilated convs with many columns may use the 128 x 256 tile
 };
 
-hipError_t launch_conv_f32(const ConvArgs& a, hipStream_t stream);   // in_alpha must be nullptr (see launch_snake_f32)
-hipError_t launch_snake_f32(const float* x, float* y, const float* alpha, const float* inv_beta, int C,
-                            size_t n, hipStream_t stream);
+// fp32 implicit GEMM on an activated input; y: the residual stream (or nullptr), ya: fp32 operand of the next layer (or nullptr)
+hipError_t launch_conv_f32(const ConvArgs& a, hipStream_t stream);
 // bf16 MFMA implicit GEMM.  `variant` is the tile configuration chosen when the weights were packed.
 hipError_t launch_conv_bf16(const ConvArgs& a, int variant, hipStream_t stream);
 
@@ -140,16 +138,16 @@ void pack_w1_wide(const float* w /*[256][256]*/, uint16_t* dst);
 struct IoArgs {
     const Slot* slots; int n_slots; int max_len;
 };
-// latent [n_clips, c0, n_frames] (fp32 or bf16) -> level-0 activation [frames, c0] fp32; with `xa` (bf16 path) the
-// activated operand snake(x; alpha, inv_beta) instead, in operand format xa_fmt (lo plane at xa + xa_lo_off)
+// latent [n_clips, c0, n_frames] (fp32 or bf16) -> activated operand snake(x; alpha, inv_beta) of the first layer, [frames, c0]:
+// fp32 in x0 or, with `xa` (bf16 path), in operand format xa_fmt (lo plane at xa + xa_lo_off)
 hipError_t launch_gather(const void* latent, float* x0, int c0, int n_frames, bool bf16,
                          const Slot* slots, int n_slots, int max_len, hipStream_t stream,
                          uint16_t* xa = nullptr, int xa_fmt = OP_BF16, long long xa_lo_off = 0,
                          const float* alpha = nullptr, const float* inv_beta = nullptr);
 // encoder stem: Conv1d(k, ch -> C) + bias from the planar fp32 waveform [n_clips, ch, n_frames * S] into the residual
-// stream y (half or fp32) of the rows each window needs (interior widened by `margin`); with ya (half path only) also
-// the activated operand snake(y; alpha, inv_beta) in format ya_fmt.  w: fp32 [k][ch][C].
-hipError_t launch_stem(const float* wave, void* y, bool y_half, uint16_t* ya, int ya_fmt, const float* w, const float* bias,
+// stream y (half or fp32) of the rows each window needs (interior widened by `margin`); with ya also the activated
+// operand snake(y; alpha, inv_beta), fp32 or (half path) in format ya_fmt.  w: fp32 [k][ch][C].
+hipError_t launch_stem(const float* wave, void* y, bool y_half, void* ya, int ya_fmt, const float* w, const float* bias,
                        const float* alpha, const float* inv_beta, int ch, int C, int k, int S, int n_frames, int margin,
                        const Slot* slots, int n_slots, int max_len, int max_int, hipStream_t stream);
 // encoder: moments of the windows' interior frames -> moments_out fp32 [n_clips, 2 C0, n_frames] and the sampled latent

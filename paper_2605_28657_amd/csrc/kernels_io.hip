@@ -6,6 +6,7 @@
 // stitch : step 3 (trim the margins, keep the frame-aligned interior) plus the side-by-side write
 //          of the interiors into the clip's waveform.
 #include <algorithm>
+#include <type_traits>
 
 #include "device_common.h"
 
@@ -20,7 +21,7 @@ template <> __device__ __forceinline__ float load_act<_Float16>(const _Float16* 
 // The latent is [clip, channel, frame] (frames fastest), the slots are time-major [frame, channel]: a workgroup moves a
 // tile of 64 frames x 64 channels through LDS, reading runs of consecutive frames of one channel and writing runs of
 // consecutive channels of one frame, so both sides are coalesced.  With `xa` (bf16 path) it writes the first layer's
-// MFMA operand directly, snake(latent) in operand format fmt, instead of the fp32 copy.
+// MFMA operand directly, snake(latent) in operand format fmt; without it (fp32 path) the same in fp32.
 constexpr int GATHER_TILE = 64;
 
 template <typename T>
@@ -42,13 +43,13 @@ __global__ __launch_bounds__(256) void gather_kernel(const T* __restrict__ laten
     __syncthreads();
     const int c = cbase + lane;
     if (c >= c0) return;
-    const float al = xa ? alpha[c] : 0.f, ib = xa ? inv_beta[c] : 0.f;
+    const float al = alpha[c], ib = inv_beta[c];
     for (int rr = sub; rr < GATHER_TILE; rr += 256 / GATHER_TILE) {
         const int r = r0 + rr;
         if (r >= s.len) break;
         const float raw = tile[lane][rr];
         const size_t idx = ((size_t)s.row0 + r) * c0 + c;
-        if (!xa) { x0[idx] = raw; continue; }
+        if (!xa) { x0[idx] = snake_precise(raw, al, ib); continue; }
         const float v = snake_fast(raw, al, ib);
         if (fmt == OP_F16) {
             xa[idx] = __builtin_bit_cast(uint16_t, (_Float16)v);
@@ -64,7 +65,7 @@ hipError_t launch_gather(const void* latent, float* x0, int c0, int n_frames, bo
                          const Slot* slots, int n_slots, int max_len, hipStream_t stream,
                          uint16_t* xa, int xa_fmt, long long xa_lo_off, const float* alpha, const float* inv_beta)
 {
-    if (xa && (!alpha || !inv_beta)) return hipErrorInvalidValue;
+    if (!alpha || !inv_beta) return hipErrorInvalidValue;
     dim3 grid((unsigned)((max_len + GATHER_TILE - 1) / GATHER_TILE), (unsigned)n_slots, (unsigned)((c0 + GATHER_TILE - 1) / GATHER_TILE));
     if (bf16)
         hipLaunchKernelGGL(gather_kernel<uint16_t>, grid, dim3(256), 0, stream, (const uint16_t*)latent, x0, xa, xa_fmt, xa_lo_off, alpha, inv_beta, c0, n_frames, slots);
@@ -83,13 +84,14 @@ hipError_t launch_gather(const void* latent, float* x0, int c0, int n_frames, bo
 constexpr int STEM_MAXK = 15 * 8;                 // taps x channels held in registers
 
 template <typename TY, int KCH>
-__global__ __launch_bounds__(256) void stem_kernel(const float* __restrict__ wave, TY* __restrict__ y, uint16_t* __restrict__ ya,
+__global__ __launch_bounds__(256) void stem_kernel(const float* __restrict__ wave, TY* __restrict__ y, void* __restrict__ ya_,
                                                    int ya_fmt, const float* __restrict__ w /*[k][ch][C]*/,
                                                    const float* __restrict__ bias, const float* __restrict__ alpha,
                                                    const float* __restrict__ inv_beta, int ch, int C, int k, int S,
                                                    int n_frames, int margin, const Slot* __restrict__ slots)
 {
     if (sizeof(TY) == 2) fp16_saturate_on();
+    std::conditional_t<sizeof(TY) == 4, float, uint16_t>* __restrict__ ya = static_cast<std::conditional_t<sizeof(TY) == 4, float, uint16_t>*>(ya_);
     const Slot s = slots[blockIdx.y];
     const long long nrows = (long long)s.len * S;
     const long long out_lo = max(0ll, (long long)s.crop * S - margin);
@@ -121,6 +123,12 @@ __global__ __launch_bounds__(256) void stem_kernel(const float* __restrict__ wav
         if constexpr (sizeof(TY) == 4) {
             *reinterpret_cast<float4*>(&y[idx]) = make_float4(acc[0], acc[1], acc[2], acc[3]);
             *reinterpret_cast<float4*>(&y[idx + 4]) = make_float4(acc[4], acc[5], acc[6], acc[7]);
+            if (ya) {
+#pragma unroll
+                for (int e = 0; e < 8; ++e) acc[e] = snake_precise(acc[e], alpha[8 * g + e], inv_beta[8 * g + e]);
+                *reinterpret_cast<float4*>(&ya[idx]) = make_float4(acc[0], acc[1], acc[2], acc[3]);
+                *reinterpret_cast<float4*>(&ya[idx + 4]) = make_float4(acc[4], acc[5], acc[6], acc[7]);
+            }
         } else {
             f16x8 hv;
 #pragma unroll
@@ -141,12 +149,12 @@ __global__ __launch_bounds__(256) void stem_kernel(const float* __restrict__ wav
     }
 }
 
-hipError_t launch_stem(const float* wave, void* y, bool y_half, uint16_t* ya, int ya_fmt, const float* w, const float* bias,
+hipError_t launch_stem(const float* wave, void* y, bool y_half, void* ya, int ya_fmt, const float* w, const float* bias,
                        const float* alpha, const float* inv_beta, int ch, int C, int k, int S, int n_frames, int margin,
                        const Slot* slots, int n_slots, int max_len, int max_int, hipStream_t stream)
 {
     if (C % 8 != 0 || k < 1 || (k & 1) == 0 || margin < 0 || k * ch > STEM_MAXK) return hipErrorInvalidValue;
-    if (ya && (ya_fmt == OP_BF16X2 || !alpha || !inv_beta || !y_half)) return hipErrorInvalidValue;
+    if (ya && (ya_fmt == OP_BF16X2 || !alpha || !inv_beta)) return hipErrorInvalidValue;
     const long long rows = std::min((long long)max_int * S + 2ll * margin, (long long)max_len * S);
     dim3 grid((unsigned)((rows + 255) / 256), (unsigned)n_slots);
     // stereo with a 7-tap stem holds 14 samples per thread; anything up to 15 taps x 8 channels takes the large form
@@ -205,25 +213,26 @@ hipError_t launch_sample(const void* m, bool m_half, const float* eps, float* mo
 // Only the interior rows of every window are produced (the halo is trimmed right after).  Rows outside
 // the window read as zero (the conv's zero padding at a clip edge); Snake is applied while staging.
 //
-// Fast kernel (OC output channels, K taps as template arguments): a workgroup owns HEAD_NT = 1024
-// consecutive samples, each thread 4 of them.  Channels go through LDS in chunks of 16, transposed to
+// Fast kernel (OC output channels, K taps as template arguments): a workgroup owns 256 SPT
+// consecutive samples, each thread SPT of them.  Channels go through LDS in chunks of 16, transposed to
 // [channel][row] so that a thread's 4 + K - 1 input rows are consecutive words (three 16-byte reads per
 // channel for K = 7) and feed 4*K*OC FMAs; the weights are wave-uniform (scalar loads).  The row
-// length HEAD_LDR = 4 mod 16 keeps both the transposing stores and the reads free of bank conflicts.
-constexpr int HEAD_SPT = 4;                    // samples per thread
-constexpr int HEAD_NT = 256 * HEAD_SPT;
+// length LDR = 4 mod 16 keeps both the transposing stores and the reads free of bank conflicts.  SPT = 4 reads
+// the fewest LDS words per sample; a launch that would leave CUs idle that way (a few windows) takes SPT = 1, which adds
+// in the same order.
 constexpr int HEAD_KC = 16;
 constexpr int HEAD_MAXK = 15;
 constexpr int HEAD_MAXOC = 8;
-constexpr int HEAD_LDR = 1044;                 // >= HEAD_NT + HEAD_MAXK - 1, = 4 (mod 16)
 
-template <typename TX, bool FAST, int OC, int K>
+template <typename TX, bool FAST, int OC, int K, int HEAD_SPT>
 __global__ __launch_bounds__(256) void head_fast_kernel(const TX* __restrict__ x, float* __restrict__ y,
                                                         const float* __restrict__ w, const float* __restrict__ bias,
                                                         const float* __restrict__ alpha, const float* __restrict__ inv_beta,
                                                         int cin, int r, long long total_rows,
                                                         const Slot* __restrict__ slots)
 {
+    constexpr int HEAD_NT = 256 * HEAD_SPT;
+    constexpr int HEAD_LDR = HEAD_NT + 20;                  // >= HEAD_NT + HEAD_MAXK - 1, = 4 (mod 16)
     __shared__ __attribute__((aligned(16))) float xs[HEAD_KC * HEAD_LDR];
     constexpr int HALF = (K - 1) / 2;
     constexpr int XR = HEAD_NT + K - 1;
@@ -277,8 +286,14 @@ __global__ __launch_bounds__(256) void head_fast_kernel(const TX* __restrict__ x
             float xv[NV * 4];
 #pragma unroll
             for (int i = 0; i < NV; ++i) {
-                const float4 t4 = *reinterpret_cast<const float4*>(&xs[c * HEAD_LDR + HEAD_SPT * tid + 4 * i]);
-                xv[4 * i] = t4.x; xv[4 * i + 1] = t4.y; xv[4 * i + 2] = t4.z; xv[4 * i + 3] = t4.w;
+                const float* src = &xs[c * HEAD_LDR + HEAD_SPT * tid + 4 * i];
+                if constexpr (HEAD_SPT == 4) {
+                    const float4 t4 = *reinterpret_cast<const float4*>(src);
+                    xv[4 * i] = t4.x; xv[4 * i + 1] = t4.y; xv[4 * i + 2] = t4.z; xv[4 * i + 3] = t4.w;
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) xv[4 * i + e] = 4 * i + e < HEAD_SPT + K - 1 ? src[e] : 0.f;
+                }
             }
 #pragma unroll
             for (int t = 0; t < K; ++t)
@@ -295,9 +310,9 @@ __global__ __launch_bounds__(256) void head_fast_kernel(const TX* __restrict__ x
     for (int o = 0; o < OC; ++o) {
         const float b = bias[o];
         float* dst = y + (size_t)o * total_rows + rowbase + n;
-        if (n + HEAD_SPT <= hi && (r % 4) == 0) {
-            *reinterpret_cast<float4*>(dst) = make_float4(tanhf(acc[0][o] + b), tanhf(acc[1][o] + b),
-                                                          tanhf(acc[2][o] + b), tanhf(acc[3][o] + b));
+        if (HEAD_SPT == 4 && n + HEAD_SPT <= hi && (r % 4) == 0) {
+            *reinterpret_cast<float4*>(dst) = make_float4(tanhf(acc[0][o] + b), tanhf(acc[HEAD_SPT / 4][o] + b),
+                                                          tanhf(acc[HEAD_SPT / 2][o] + b), tanhf(acc[HEAD_SPT - 1][o] + b));
         } else {
 #pragma unroll
             for (int i = 0; i < HEAD_SPT; ++i)
@@ -533,13 +548,14 @@ hipError_t launch_head(const void* x, bool x_half, float* y, const float* w, con
     if (k > HEAD_MAXK || oc > HEAD_MAXOC || (x_half && !fast)) return hipErrorInvalidValue;
     const long long rows = (long long)max_int * r;
     if (oc == 2 && k == 7 && cin % HEAD_KC == 0) {
-        dim3 grid((unsigned)((rows + HEAD_NT - 1) / HEAD_NT), (unsigned)n_slots);
-        if (x_half)
-            hipLaunchKernelGGL((head_fast_kernel<_Float16, true, 2, 7>), grid, dim3(256), 0, stream, (const _Float16*)x, y, w, bias, alpha, inv_beta, cin, r, total_rows, slots);
-        else if (fast)
-            hipLaunchKernelGGL((head_fast_kernel<float, true, 2, 7>), grid, dim3(256), 0, stream, (const float*)x, y, w, bias, alpha, inv_beta, cin, r, total_rows, slots);
-        else
-            hipLaunchKernelGGL((head_fast_kernel<float, false, 2, 7>), grid, dim3(256), 0, stream, (const float*)x, y, w, bias, alpha, inv_beta, cin, r, total_rows, slots);
+        const bool few = (rows + 1023) / 1024 * n_slots < 512;        // two 1024-sample workgroups per CU
+        const int nt = few ? 256 : 1024;
+        dim3 grid((unsigned)((rows + nt - 1) / nt), (unsigned)n_slots);
+#define DEMON_HEADF(TX_, FAST_, SPT_) hipLaunchKernelGGL((head_fast_kernel<TX_, FAST_, 2, 7, SPT_>), grid, dim3(256), 0, stream, (const TX_*)x, y, w, bias, alpha, inv_beta, cin, r, total_rows, slots)
+        if (x_half) { if (few) DEMON_HEADF(_Float16, true, 1); else DEMON_HEADF(_Float16, true, 4); }
+        else if (fast) { if (few) DEMON_HEADF(float, true, 1); else DEMON_HEADF(float, true, 4); }
+        else { if (few) DEMON_HEADF(float, false, 1); else DEMON_HEADF(float, false, 4); }
+#undef DEMON_HEADF
         return hipGetLastError();
     }
     dim3 grid((unsigned)((rows + HEADG_NT - 1) / HEADG_NT), (unsigned)n_slots);
