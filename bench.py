@@ -238,7 +238,7 @@ def main():
                    if wl.bf16 else "fp32"},
         "roofline": {
             "kernel": "MFMA convolution kernels (conv_mfma_kernel, res_unit_wide_kernel, res_unit_fused_kernel): all %d "
-                      "convolution layers of a step, launched once per window group (two groups on two streams)" % n_conv_launches,
+                      "convolution layers of a step" % n_conv_launches,
             "bound": "mfma", "achieved": achieved, "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
             "frac": achieved / PEAK_BF16_TFLOPS,
             # L2 miss traffic of these kernels per step from rocprofv3 FETCH_SIZE + WRITE_SIZE (bytes, scaled by a plain

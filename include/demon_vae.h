@@ -34,7 +34,6 @@
  * process (read once when the library is loaded):
  *   DEMON_VAE_WIDE_OPERANDS=bf16x2  default of wide_operands becomes 2
  *   DEMON_VAE_NO_FUSED=1            as if DEMON_VAE_FLAG_NO_FUSED were set in every config
- *   DEMON_VAE_ONE_STREAM=1          as if DEMON_VAE_FLAG_ONE_STREAM were set in every config
  *   DEMON_VAE_SMALL_TILE_WGS=n      default of small_tile_wgs becomes n (0 = never)
  */
 #ifndef DEMON_VAE_H
@@ -74,8 +73,8 @@ typedef enum {
 
 /* demon_vae_config.flags */
 #define DEMON_VAE_FLAG_NO_FUSED   1   /* every residual unit as two kernels (no fused units)          */
-#define DEMON_VAE_FLAG_ONE_STREAM 2   /* no internal second stream: all launches on the given stream  */
-#define DEMON_VAE_FLAG_NO_WIDE_TILE 4 /* dilated convs never use the 128 x 256 tile (bit-identical results) */
+#define DEMON_VAE_FLAG_ONE_STREAM 2   /* accepted, without effect: all launches are on the given stream */
+#define DEMON_VAE_FLAG_NO_WIDE_TILE 4 /* accepted, without effect: the 128 x 256 tile it switched off is gone */
 #define DEMON_VAE_FLAG_NO_HEAD_FUSION 8 /* the head always runs as its own kernel (bit-identical results) */
 
 /* Layer stack and workspace limits.  Arrays are read during the call only. */
@@ -99,8 +98,8 @@ typedef struct {
                              2 = hi + lo bf16 pairs on the bf16 MFMA (two MFMAs per k-step in the transposed and 1x1
                              convolutions) for stacks whose wide-level activations may leave the half range */
     int flags;            /* DEMON_VAE_FLAG_* */
-    int small_tile_wgs;   /* launches of at most this many 128 x 128 tiles use 64 x 64 tiles instead (bit-identical
-                             results, more workgroups for a single playback window); default 192, negative = never */
+    int small_tile_wgs;   /* launches of at most this many 128 x 128 tiles may use smaller tiles instead (bit-identical
+                             results, more workgroups for a single playback window); default 1024, negative = never */
 } demon_vae_config;
 
 /* One window of the grid: interior latent frames [begin, end) of clip `clip`, decoded from the

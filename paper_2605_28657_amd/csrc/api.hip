@@ -33,10 +33,9 @@ const int g_env_wide_fmt = [] {
     return (e && strcmp(e, "bf16x2") == 0) ? (int)OP_BF16X2 : (int)OP_F16;
 }();
 const bool g_env_no_fused = getenv("DEMON_VAE_NO_FUSED") != nullptr;
-const bool g_env_one_stream = getenv("DEMON_VAE_ONE_STREAM") != nullptr;
 const long long g_env_small_tile_wgs = [] {
     const char* e = getenv("DEMON_VAE_SMALL_TILE_WGS");
-    return e ? atoll(e) : 192ll;
+    return e ? atoll(e) : 1024ll;
 }();
 
 struct ConvLayer {
@@ -65,13 +64,6 @@ struct Plan {
     int n_clips = 0, n_frames = 0, frame_begin = 0, frame_end = 0, window = 0, halo = 0;
     int n_slots = 0, max_len = 0, max_int = 0;
     long long total_frames = 0;
-    // The windows form one or two groups of consecutive table entries.  A group owns the workspace region that starts
-    // at frame0 x (largest per-frame activation size), and the rows of its windows count from the region's start: two
-    // groups can then be at different layers at the same time without touching each other's bytes (the bytes a window
-    // occupies depend on the layer's rate x width).
-    int n_groups = 1;
-    int g_first[2] = {0, 0}, g_count[2] = {0, 0};
-    long long g_frame0[2] = {0, 0}, g_frames[2] = {0, 0};
     Slot* d_slots = nullptr;
     unsigned long long last_use = 0;
     // A call on this grid was recorded into a HIP graph: the graph holds the address of this entry's table (and the
@@ -127,8 +119,7 @@ struct demon_vae {
     int rf_left = 0, rf_right = 0;
     int device = 0;
     bool has_split_operands = false;   // bf16 path: some layer carries its operand as hi + lo planes
-    long long small_tile_wgs = 192;    // bf16 path: launches of at most this many 128 x 128 tiles use 64 x 64 tiles
-    bool wide_tile_ok = true;          // bf16 path: dilated convs with many columns may use the 128 x 256 tile
+    long long small_tile_wgs = 1024;   // bf16 path: launches of more 128 x 128 tiles than this take that tile
     bool head_fusable = false;         // bf16 path: the last layer is a fused 64-channel unit that can run the head in its kernel
 
     void* d_params = nullptr;          // one allocation: all packed weights, biases, Snake parameters
@@ -151,8 +142,6 @@ struct demon_vae {
     Workspace ws;
     unsigned char* scratch = nullptr;              // this device's copy of the static scratch array
     Slot* d_slot_arena = nullptr;
-    hipStream_t stream2 = nullptr;                 // second lane of the bf16 layer sequence (default priority, non-blocking)
-    hipEvent_t ev_fork = nullptr, ev_join = nullptr;
     Plan plans[kPlanCache];
     unsigned long long use_counter = 0;
 
@@ -209,6 +198,9 @@ size_t pack_conv(Arena& ar, const float* w, ConvLayer& L, bool bf16)
         const size_t n = packed_bf16_count(L.cin, L.cout, L.ntaps, L.stride, L.variant);
         const size_t off = ar.reserve(n * 2);
         pack_bf16(w, L.cin, L.cout, L.ntaps, L.stride, L.variant, L.in_fmt == OP_F16, L.generic, reinterpret_cast<uint16_t*>(ar.bytes.data() + off), L.down);
+        int rows = 0, kc = 0;
+        variant_block(L.variant, &rows, &kc);
+        to_fragment_order(reinterpret_cast<uint16_t*>(ar.bytes.data() + off), n, rows, kc);
         return off;
     }
     const size_t n = packed_f32_count(L.cin, L.cout, L.ntaps, L.stride);
@@ -255,7 +247,7 @@ demon_status check_plane(const demon_vae* v, int max_len)
 // Looks the window grid up in the plan cache; on a miss the table of the least recently used entry that no graph holds is
 // rewritten by a small kernel on the decode stream, so the call stays asynchronous (kernels of earlier calls that still
 // read the replaced table precede that kernel on the stream) and can itself be recorded into a graph.
-demon_status get_plan(demon_vae* v, int n_clips, int n_frames, int fb, int fe, int window, int halo, bool two_groups,
+demon_status get_plan(demon_vae* v, int n_clips, int n_frames, int fb, int fe, int window, int halo,
                       hipStream_t stream, Plan** out)
 {
     ++v->use_counter;
@@ -265,13 +257,12 @@ demon_status get_plan(demon_vae* v, int n_clips, int n_frames, int fb, int fe, i
     Plan* victim = nullptr;
     for (Plan& p : v->plans) {
         if (p.valid && p.n_clips == n_clips && p.n_frames == n_frames && p.frame_begin == fb && p.frame_end == fe &&
-            p.window == window && p.halo == halo && (p.n_groups == 2) == (two_groups && p.n_slots >= 2)) {
+            p.window == window && p.halo == halo) {
             p.last_use = v->use_counter;
             if (capturing) p.pinned = true;
             if (p.table_pending) {
-                const int split = p.n_groups == 2 ? p.g_first[1] : p.n_slots;
                 HIP_TRY(launch_plan_slots(p.d_slots, p.n_clips, p.n_slots / p.n_clips, (int)(p.total_frames / p.n_clips), p.n_frames,
-                                          p.frame_begin, p.frame_end, p.window, p.halo, split, (int)p.g_frame0[1], stream), "window table");
+                                          p.frame_begin, p.frame_end, p.window, p.halo, stream), "window table");
                 if (!capturing) p.table_pending = false;
             }
             *out = &p;
@@ -291,26 +282,10 @@ demon_status get_plan(demon_vae* v, int n_clips, int n_frames, int fb, int fe, i
         return fail(DEMON_ERR_WORKSPACE, "extended windows need %lld frames, the workspace holds %lld", total, v->cap_frames);
     const demon_status prc = check_plane(v, gc.max_len);
     if (prc != DEMON_OK) return prc;
-    // two groups of about equal size (in frames) for the bf16 path, whose layer sequence can run on two streams: the
-    // second group starts at the window whose first row is nearest to half of the rows
-    int n_groups = 1, split = (int)n_slots;
-    long long frame0_b = 0;
-    if (two_groups && n_slots >= 2) {
-        long long best = -1, row = 0, i = 0;
-        for (int c = 0; c < n_clips; ++c)
-            for (long long b = fb; b < fe; b += window, ++i) {
-                const long long e = std::min<long long>(b + window, fe);
-                const long long d = row > total - row ? row - (total - row) : (total - row) - row;
-                if (i >= 1 && (best < 0 || d < best)) { best = d; split = (int)i; frame0_b = row; }
-                row += std::min<long long>(n_frames, e + halo) - std::max<long long>(0, b - halo);
-            }
-        n_groups = 2;
-    }
     const int idx = (int)(victim - v->plans);
     Slot* d = v->d_slot_arena + (size_t)idx * kMaxSlots;
     victim->valid = false;
-    HIP_TRY(launch_plan_slots(d, n_clips, (int)gc.per_clip, (int)gc.clip_frames, n_frames, fb, fe, window, halo, split, (int)frame0_b, stream),
-            "window table");
+    HIP_TRY(launch_plan_slots(d, n_clips, (int)gc.per_clip, (int)gc.clip_frames, n_frames, fb, fe, window, halo, stream), "window table");
     victim->valid = true;
     victim->pinned = capturing;
     victim->table_pending = capturing;
@@ -318,18 +293,8 @@ demon_status get_plan(demon_vae* v, int n_clips, int n_frames, int fb, int fe, i
     victim->window = window; victim->halo = halo;
     victim->n_slots = (int)n_slots; victim->max_len = gc.max_len; victim->max_int = gc.max_int;
     victim->total_frames = total; victim->d_slots = d; victim->last_use = v->use_counter;
-    victim->n_groups = n_groups;
-    victim->g_first[0] = 0; victim->g_count[0] = split; victim->g_frame0[0] = 0; victim->g_frames[0] = n_groups == 2 ? frame0_b : total;
-    victim->g_first[1] = split; victim->g_count[1] = (int)n_slots - split; victim->g_frame0[1] = frame0_b; victim->g_frames[1] = total - frame0_b;
     *out = victim;
     return DEMON_OK;
-}
-
-
-// two window groups on two streams unless a mode wants one ordered launch sequence (per-launch timing, debug tap)
-bool wants_two_groups(const demon_vae* v)
-{
-    return v->dtype == DEMON_BF16 && v->stream2 && v->timing < 2 && !(v->tap_layer >= 0 && v->tap_dst);
 }
 
 // What one call reads and writes besides the handle's own memory.
@@ -347,7 +312,6 @@ demon_status run_pass(demon_vae* v, const Workspace& ws, const Plan* plan, const
 {
     const bool bf = v->dtype == DEMON_BF16;
     const bool enc = v->encoder;
-    const bool dual = wants_two_groups(v);
     // the head inside the last unit's kernel, unless the debug tap wants that unit's output in memory
     // (bit-identical either way).  Only for calls of a few windows, where a launch less is what counts: for a whole clip
     // the fused launch takes as long as the two it replaces.
@@ -361,22 +325,10 @@ demon_status run_pass(demon_vae* v, const Workspace& ws, const Plan* plan, const
         slots = ws.slot_gated;
     }
 
-    // the convolution launches address a group of windows (gs, gn) on a stream gst: all windows on the caller's
-    // stream, or two halves on two streams (see the bf16 path below)
-    const Slot* gs = slots;
-    int gn = ns, g = 0;
-    hipStream_t gst = stream;
-    bool marks_on = true;
-    auto select_group = [&](int which, hipStream_t on) {
-        g = which; gs = slots + plan->g_first[which]; gn = plan->g_count[which]; gst = on;
-    };
-    // element offset of the current group's region in every activation buffer
-    auto goff = [&]() -> size_t { return (size_t)plan->g_frame0[g] * (size_t)v->per_frame; };
-
     v->n_marks = 0;
     const int ring_base = (v->timed_calls % kTimingRing) * v->marks_per_call;
     auto mark = [&](int level) -> hipError_t {
-        if (!marks_on || v->timing < level || v->n_marks >= v->marks_per_call) return hipSuccess;
+        if (v->timing < level || v->n_marks >= v->marks_per_call) return hipSuccess;
         return hipEventRecord(v->events[ring_base + v->n_marks++], stream);
     };
     // level 1 marks: start, after gather (stem), after the last convolution, after head (sampling step), after stitch.
@@ -392,21 +344,18 @@ demon_status run_pass(demon_vae* v, const Workspace& ws, const Plan* plan, const
     auto tap = [&](const void* x, int c) -> hipError_t {
         const int id = layer_id++;
         if (id != v->tap_layer || !v->tap_dst) return hipSuccess;
-        // the groups' regions are apart in the workspace; the tap lays them end to end
-        const size_t first = (size_t)plan->g_frame0[g] * r * c, want = (size_t)plan->g_frames[g] * r * c;
-        if (first >= v->tap_cap) return hipSuccess;
-        return launch_to_f32(x, v->tap_dst + first, std::min(want, v->tap_cap - first), bf ? 2 : 0, gst);
+        const size_t want = (size_t)plan->total_frames * r * c;
+        return launch_to_f32(x, v->tap_dst, std::min(want, v->tap_cap), bf ? 2 : 0, stream);
     };
     auto conv_args = [&](const ConvLayer& L, const void* x, void* y, const void* res) {
         ConvArgs a;
         a.x = x; a.y = y; a.res = res; a.w = L.w; a.bias = L.bias;
         a.out_alpha = L.out_alpha; a.out_inv_beta = L.out_inv_beta;
-        a.slots = gs; a.n_slots = gn; a.max_len = ml; a.max_int = plan->max_int; a.margin = L.margin; a.r_in = r;
+        a.slots = slots; a.n_slots = ns; a.max_len = ml; a.max_int = plan->max_int; a.margin = L.margin; a.r_in = r;
         a.cin = L.cin; a.cout = L.cout; a.ntaps = L.ntaps; a.dil = L.dil; a.stride = L.stride; a.down = L.down;
         a.in_fmt = L.in_fmt;
         a.in_lo_off = a.out_lo_off = lo_off;
         a.small_tile_wgs = v->small_tile_wgs;
-        a.wide_tile_ok = v->wide_tile_ok;
         return a;
     };
     // samples per frame after a resampling layer
@@ -460,25 +409,17 @@ demon_status run_pass(demon_vae* v, const Workspace& ws, const Plan* plan, const
         uint16_t* acur = (uint16_t*)ws.buf[3];
         uint16_t* aoth = (uint16_t*)ws.buf[4];
         uint16_t* mid = (uint16_t*)ws.buf[2];
-        for (int gi = 0; gi < plan->n_groups; ++gi) {
-            select_group(gi, stream);
-            if (enc) {
-                const ConvLayer* C = v->first_consumer;
-                HIP_TRY(launch_stem(io.d_wave, (uint16_t*)ws.buf[0] + goff(), true, C ? (uint16_t*)ws.buf[3] + goff() : nullptr,
-                                    C ? C->in_fmt : 0, v->stem_w, v->stem_bias, C ? C->in_alpha : nullptr, C ? C->in_inv_beta : nullptr,
-                                    v->st.out_channels, v->stem_cout, v->st.head_kernel, S, n_frames, v->stem_margin, gs, gn, ml,
-                                    plan->max_int, stream), "stem");
-            } else {
-                const ConvLayer& U0 = *v->first_consumer;
-                HIP_TRY(launch_gather(io.d_latent, nullptr, v->st.c0, n_frames, true, gs, gn, ml, stream, (uint16_t*)ws.buf[3] + goff(),
-                                      U0.in_fmt, lo_off, U0.in_alpha, U0.in_inv_beta), "gather");
-            }
+        if (enc) {
+            const ConvLayer* C = v->first_consumer;
+            HIP_TRY(launch_stem(io.d_wave, ws.buf[0], true, C ? ws.buf[3] : nullptr, C ? C->in_fmt : 0, v->stem_w, v->stem_bias,
+                                C ? C->in_alpha : nullptr, C ? C->in_inv_beta : nullptr, v->st.out_channels, v->stem_cout,
+                                v->st.head_kernel, S, n_frames, v->stem_margin, slots, ns, ml, plan->max_int, stream), "stem");
+        } else {
+            const ConvLayer& U0 = *v->first_consumer;
+            HIP_TRY(launch_gather(io.d_latent, nullptr, v->st.c0, n_frames, true, slots, ns, ml, stream, (uint16_t*)ws.buf[3],
+                                  U0.in_fmt, lo_off, U0.in_alpha, U0.in_inv_beta), "gather");
         }
         HIP_TRY(mark(1), "event");
-        auto layers = [&]() -> demon_status {
-        cur = (uint16_t*)ws.buf[0] + goff(); other = (uint16_t*)ws.buf[1] + goff();      // half: 2 bytes
-        acur = (uint16_t*)ws.buf[3] + goff(); aoth = (uint16_t*)ws.buf[4] + goff(); mid = (uint16_t*)ws.buf[2] + goff();
-        r = enc ? S : 1; layer_id = 0;
         for (size_t si = 0; si < n_steps; ++si) {
             const Step& T = v->steps[si];
             const bool last = si + 1 == n_steps;
@@ -488,7 +429,7 @@ demon_status run_pass(demon_vae* v, const Workspace& ws, const Plan* plan, const
             if (T.conv) {
                 ConvArgs a = conv_args(*T.conv, acur, other, nullptr);
                 if (C) { a.ya = aoth; a.out_alpha = C->in_alpha; a.out_inv_beta = C->in_inv_beta; a.out_fmt = C->in_fmt; }
-                HIP_TRY(launch_conv_bf16(a, T.conv->variant, gst), "resampling convolution");
+                HIP_TRY(launch_conv_bf16(a, T.conv->variant, stream), "resampling convolution");
                 if (C) std::swap(acur, aoth);
                 HIP_TRY(mark(last ? 1 : 2), "event");
                 std::swap(cur, other);
@@ -505,15 +446,15 @@ demon_status run_pass(demon_vae* v, const Workspace& ws, const Plan* plan, const
                 f.b7 = U.dilated.bias; f.b1 = U.pointwise.bias;
                 f.a1 = U.dilated.in_alpha; f.ib1 = U.dilated.in_inv_beta;
                 f.a2 = U.dilated.out_alpha; f.ib2 = U.dilated.out_inv_beta;
-                f.slots = gs; f.n_slots = gn; f.max_len = ml; f.max_int = plan->max_int; f.margin = U.pointwise.margin;
+                f.slots = slots; f.n_slots = ns; f.max_len = ml; f.max_int = plan->max_int; f.margin = U.pointwise.margin;
                 f.r = r; f.c = U.dilated.cin; f.ntaps = U.dilated.ntaps; f.dil = U.dilated.dil;
                 if (C && C->in_fmt != OP_BF16) return fail(DEMON_ERR_UNSUPPORTED, "a fused unit cannot feed a layer with wide operands");
                 if (last && head_in_unit) {
                     f.hw = v->head_wfrag; f.hb = v->head_bias; f.ha = v->head_alpha; f.hib = v->head_inv_beta;
-                    f.hy = ws.head_out + plan->g_frame0[g] * r; f.total_rows = plan->total_frames * r;
+                    f.hy = ws.head_out; f.total_rows = plan->total_frames * r;
                     f.oc = v->st.out_channels; f.hk = v->st.head_kernel;
                 }
-                HIP_TRY(launch_res_unit_fused(f, gst), "fused residual unit");
+                HIP_TRY(launch_res_unit_fused(f, stream), "fused residual unit");
                 std::swap(cur, other);
                 HIP_TRY(mark(2), "event");
             } else if (U.wide) {
@@ -523,88 +464,47 @@ demon_status run_pass(demon_vae* v, const Workspace& ws, const Plan* plan, const
                 f.w7 = (const uint16_t*)U.dilated.w; f.w1 = U.w1_fused;
                 f.b7 = U.dilated.bias; f.b1 = U.pointwise.bias;
                 f.a2 = U.dilated.out_alpha; f.ib2 = U.dilated.out_inv_beta;
-                f.slots = gs; f.n_slots = gn; f.max_len = ml; f.max_int = plan->max_int; f.margin = U.pointwise.margin;
+                f.slots = slots; f.n_slots = ns; f.max_len = ml; f.max_int = plan->max_int; f.margin = U.pointwise.margin;
                 f.r = r; f.c = U.dilated.cin; f.ntaps = U.dilated.ntaps; f.dil = U.dilated.dil;
                 if (C && C->in_fmt != OP_BF16) return fail(DEMON_ERR_UNSUPPORTED, "a fused unit cannot feed a layer with wide operands");
-                HIP_TRY(launch_res_unit_wide(f, gst), "fused residual unit (256 channels)");
+                HIP_TRY(launch_res_unit_wide(f, stream), "fused residual unit (256 channels)");
                 if (C) std::swap(acur, aoth);
                 HIP_TRY(mark(2), "event");
             } else {
                 ConvArgs d = conv_args(U.dilated, acur, nullptr, nullptr);
                 d.ya = mid; d.out_fmt = U.pointwise.in_fmt;   // Snake between the convolutions: the layer's own out_alpha
-                HIP_TRY(launch_conv_bf16(d, U.dilated.variant, gst), "dilated convolution");
+                HIP_TRY(launch_conv_bf16(d, U.dilated.variant, stream), "dilated convolution");
                 HIP_TRY(mark(2), "event");
                 ConvArgs q = conv_args(U.pointwise, mid, cur, cur);   // in place on the residual stream
                 if (C) { q.ya = acur; q.out_alpha = C->in_alpha; q.out_inv_beta = C->in_inv_beta; q.out_fmt = C->in_fmt; }
-                HIP_TRY(launch_conv_bf16(q, U.pointwise.variant, gst), "pointwise convolution");
+                HIP_TRY(launch_conv_bf16(q, U.pointwise.variant, stream), "pointwise convolution");
             }
             HIP_TRY(mark(last ? 1 : 2), "event");
             HIP_TRY(tap(cur, U.pointwise.cout), "debug tap");
         }
-        return DEMON_OK;
-        };
-        // Windows are independent through the whole stack, so the layer sequence can run as two sequences over half of
-        // the windows each, on two streams: the ramp and tail of one sequence's launches (a last round of workgroups
-        // that fills a fraction of the CUs, prologues, epilogues) overlap with the other's.  Not with per-launch
-        // timing or the debug tap, which want one ordered sequence.
-        const bool two = dual && plan->n_groups == 2;
-        if (two) {
-            marks_on = false;
-            HIP_TRY(hipEventRecord(v->ev_fork, stream), "event");
-            HIP_TRY(hipStreamWaitEvent(v->stream2, v->ev_fork, 0), "hipStreamWaitEvent");
-        }
-        demon_status lrc = DEMON_OK;
-        for (int gi = 0; gi < plan->n_groups && lrc == DEMON_OK; ++gi) {
-            select_group(gi, two && gi == 1 ? v->stream2 : stream);
-            lrc = layers();
-        }
-        if (two) {
-            // also after a failed launch: the second stream joins the caller's again (an open capture stays well-formed)
-            const hipError_t e1 = hipEventRecord(v->ev_join, v->stream2);
-            const hipError_t e2 = e1 == hipSuccess ? hipStreamWaitEvent(stream, v->ev_join, 0) : e1;
-            if (lrc != DEMON_OK) return lrc;
-            HIP_TRY(e2, "joining the second stream");
-            marks_on = true;
-            HIP_TRY(mark(1), "event");                       // after the last convolution
-        }
-        if (lrc != DEMON_OK) return lrc;
     }
-    const size_t hbytes = bf ? 2 : sizeof(float);                           // half or fp32 residual stream
-    const char* final_base = (const char*)cur - goff() * hbytes;           // the buffer the last layer wrote, without the group offset
     if (enc) {
         // sampling step on the moments, trim and scatter into the caller's [clip, channel, frame] arrays
-        for (int gi = 0; gi < plan->n_groups; ++gi) {
-            select_group(gi, stream);
-            HIP_TRY(launch_sample(final_base + goff() * hbytes, bf, io.d_eps, io.d_moments, io.d_zout, bf, v->st.c0, n_frames, gs, gn,
-                                  plan->max_int, stream), "sampling step");
-        }
+        HIP_TRY(launch_sample(cur, bf, io.d_eps, io.d_moments, io.d_zout, bf, v->st.c0, n_frames, slots, ns, plan->max_int, stream), "sampling step");
         HIP_TRY(mark(1), "event");
         if (v->timing > 0) ++v->timed_calls;
         return DEMON_OK;
     }
-    // head and stitch, group by group on the caller's stream; the window waveforms are planar [channel][all rows]
+    // head and stitch; the window waveforms are planar [channel][all rows]
     const long long total_rows = plan->total_frames * r;
-    for (int gi = 0; gi < plan->n_groups && !head_in_unit; ++gi) {
-        select_group(gi, stream);
-        const void* x = final_base + goff() * hbytes;
-        float* y = ws.head_out + plan->g_frame0[gi] * r;
-        if (v->head_wfrag) {
-            HIP_TRY(launch_head_mfma(x, y, v->head_wfrag, v->head_bias, v->head_alpha, v->head_inv_beta, v->head_cin,
-                                     v->st.out_channels, v->st.head_kernel, r, total_rows, gs, gn, ml, plan->max_int, stream), "head");
-        } else {
-            HIP_TRY(launch_head(x, bf, y, v->head_w, v->head_bias, v->head_alpha, v->head_inv_beta, v->head_cin,
-                                v->st.out_channels, v->st.head_kernel, r, total_rows, bf, gs, gn, plan->max_int, stream), "head");
-        }
+    if (!head_in_unit) {
+        if (v->head_wfrag)
+            HIP_TRY(launch_head_mfma(cur, ws.head_out, v->head_wfrag, v->head_bias, v->head_alpha, v->head_inv_beta, v->head_cin,
+                                     v->st.out_channels, v->st.head_kernel, r, total_rows, slots, ns, ml, plan->max_int, stream), "head");
+        else
+            HIP_TRY(launch_head(cur, bf, ws.head_out, v->head_w, v->head_bias, v->head_alpha, v->head_inv_beta, v->head_cin,
+                                v->st.out_channels, v->st.head_kernel, r, total_rows, bf, slots, ns, plan->max_int, stream), "head");
     }
     HIP_TRY(mark(1), "event");
-    for (int gi = 0; gi < plan->n_groups; ++gi) {
-        select_group(gi, stream);
-        const float* y = ws.head_out + plan->g_frame0[gi] * r;
-        if (io.d_pcm)
-            HIP_TRY(launch_stitch_pcm16(y, io.d_pcm, v->st.out_channels, r, n_frames, total_rows, gs, gn, plan->max_int, stream), "stitch");
-        else
-            HIP_TRY(launch_stitch(y, io.d_out, v->st.out_channels, r, n_frames, total_rows, gs, gn, plan->max_int, stream), "stitch");
-    }
+    if (io.d_pcm)
+        HIP_TRY(launch_stitch_pcm16(ws.head_out, io.d_pcm, v->st.out_channels, r, n_frames, total_rows, slots, ns, plan->max_int, stream), "stitch");
+    else
+        HIP_TRY(launch_stitch(ws.head_out, io.d_out, v->st.out_channels, r, n_frames, total_rows, slots, ns, plan->max_int, stream), "stitch");
     HIP_TRY(mark(1), "event");
     if (v->timing > 0) ++v->timed_calls;
     return DEMON_OK;
@@ -630,7 +530,6 @@ demon_status create_impl(const demon_vae_config* cfg, const float* host_weights,
     // 0 in a field = the default, which the environment may have changed (see the header)
     const int g_wide_fmt = cfg->wide_operands == 1 ? (int)OP_F16 : cfg->wide_operands == 2 ? (int)OP_BF16X2 : g_env_wide_fmt;
     const bool g_allow_fused = !((cfg->flags & DEMON_VAE_FLAG_NO_FUSED) || g_env_no_fused);
-    const bool g_dual_stream = !((cfg->flags & DEMON_VAE_FLAG_ONE_STREAM) || g_env_one_stream);
     if (bf) {
         if (st.c0 % 16) return fail(DEMON_ERR_UNSUPPORTED, "bf16 path: latent_channels %d is not a multiple of 16", st.c0);
         for (int c : st.widths)
@@ -656,7 +555,6 @@ demon_status create_impl(const demon_vae_config* cfg, const float* host_weights,
     v->cap_frames = cfg->max_extended_frames > 0 ? cfg->max_extended_frames : 3ll * cfg->max_frames * cfg->max_clips;
     if (encoder) stack_encoder_receptive_field(st, &v->rf_left, &v->rf_right, nullptr, nullptr);
     else stack_receptive_field(st, &v->rf_left, &v->rf_right);
-    v->wide_tile_ok = !(cfg->flags & DEMON_VAE_FLAG_NO_WIDE_TILE);
     v->small_tile_wgs = cfg->small_tile_wgs > 0 ? cfg->small_tile_wgs : cfg->small_tile_wgs < 0 ? 0 : g_env_small_tile_wgs;
     if (hipGetDevice(&v->device) != hipSuccess) return fail(DEMON_ERR_HIP, "hipGetDevice failed");
     {
@@ -706,8 +604,10 @@ demon_status create_impl(const demon_vae_config* cfg, const float* host_weights,
         Pending pp{&P, 0, 0, {}, {}, false, false};
         if (U.fused || U.wide) {
             const size_t off = ar.reserve((size_t)c * c * 2);
-            if (U.wide) pack_w1_wide(w, reinterpret_cast<uint16_t*>(ar.bytes.data() + off));
-            else pack_w1_fused(w, c, reinterpret_cast<uint16_t*>(ar.bytes.data() + off));
+            uint16_t* w1 = reinterpret_cast<uint16_t*>(ar.bytes.data() + off);
+            if (U.wide) pack_w1_wide(w, w1);
+            else pack_w1_fused(w, c, w1);
+            to_fragment_order(w1, (size_t)c * c, c, U.wide ? 32 : c);
             fused_fix.push_back({&U, off});
         }
         pp.w = pack_conv(ar, w, P, bf);              w += (size_t)c * c;
@@ -871,9 +771,6 @@ demon_status create_impl(const demon_vae_config* cfg, const float* host_weights,
         if (v->ws.head_out) (void)hipFree(v->ws.head_out);
         if (v->d_slot_arena) (void)hipFree(v->d_slot_arena);
         if (v->ws.slot_gated) (void)hipFree(v->ws.slot_gated);
-        if (v->ev_fork) (void)hipEventDestroy(v->ev_fork);
-        if (v->ev_join) (void)hipEventDestroy(v->ev_join);
-        if (v->stream2) (void)hipStreamDestroy(v->stream2);
     };
     hipError_t e = hipMalloc(&v->d_params, ar.bytes.size());
     // fp32 path: 4 bytes per element; bf16 path: half residual stream (2 bytes), bf16 operand buffers with hi and lo planes (4)
@@ -881,11 +778,6 @@ demon_status create_impl(const demon_vae_config* cfg, const float* host_weights,
     if (e == hipSuccess) e = hipMalloc((void**)&v->ws.head_out, head_bytes);
     if (e == hipSuccess) e = hipMalloc((void**)&v->d_slot_arena, sizeof(Slot) * kMaxSlots * kPlanCache);
     if (e == hipSuccess) e = hipMalloc((void**)&v->ws.slot_gated, sizeof(Slot) * kMaxSlots);
-    if (e == hipSuccess && bf && g_dual_stream) {
-        e = hipStreamCreateWithFlags(&v->stream2, hipStreamNonBlocking);
-        if (e == hipSuccess) e = hipEventCreateWithFlags(&v->ev_fork, hipEventDisableTiming);
-        if (e == hipSuccess) e = hipEventCreateWithFlags(&v->ev_join, hipEventDisableTiming);
-    }
     if (e == hipSuccess) e = hipMemcpy(v->d_params, ar.bytes.data(), ar.bytes.size(), hipMemcpyHostToDevice);
     if (e != hipSuccess) { cleanup(); return hip_fail(e, "allocating device memory"); }
 
@@ -955,9 +847,6 @@ void demon_vae_destroy(demon_vae* v)
     (void)hipFree(v->d_slot_arena);
     (void)hipFree(v->ws.slot_gated);
     for (hipEvent_t e : v->events) (void)hipEventDestroy(e);
-    if (v->ev_fork) (void)hipEventDestroy(v->ev_fork);
-    if (v->ev_join) (void)hipEventDestroy(v->ev_join);
-    if (v->stream2) (void)hipStreamDestroy(v->stream2);
     delete v;
 }
 
@@ -986,7 +875,7 @@ static demon_status decode_checked(demon_vae* v, const void* d_latent, int n_cli
     if (n_clips > v->max_clips) return fail(DEMON_ERR_WORKSPACE, "n_clips %d exceeds max_clips %d", n_clips, v->max_clips);
     if (halo == -1) halo = std::max(v->rf_left, v->rf_right);
     Plan* plan = nullptr;
-    const demon_status rc = get_plan(v, n_clips, n_frames, frame_begin, frame_end, window, halo, wants_two_groups(v), (hipStream_t)stream, &plan);
+    const demon_status rc = get_plan(v, n_clips, n_frames, frame_begin, frame_end, window, halo, (hipStream_t)stream, &plan);
     if (rc != DEMON_OK) return rc;
     Io io;
     io.d_latent = d_latent; io.d_skip = d_skip; io.d_out = d_out; io.d_pcm = d_pcm; io.n_frames = n_frames;
@@ -1069,11 +958,8 @@ demon_status demon_vae_decode_windowed_static(demon_vae* v, const void* d_latent
     plan.window = window; plan.halo = halo;
     plan.n_slots = (int)(per_clip * n_clips); plan.max_len = max_len; plan.max_int = max_int;
     plan.total_frames = total;
-    plan.n_groups = 1;
-    plan.g_first[0] = 0; plan.g_count[0] = plan.n_slots; plan.g_frame0[0] = 0; plan.g_frames[0] = total;
     plan.d_slots = reinterpret_cast<Slot*>(v->scratch + at_slots);
-    HIP_TRY(launch_plan_slots(plan.d_slots, n_clips, (int)per_clip, (int)clip_frames, n_frames, frame_begin, frame_end, window, halo,
-                              plan.n_slots, 0, stream),
+    HIP_TRY(launch_plan_slots(plan.d_slots, n_clips, (int)per_clip, (int)clip_frames, n_frames, frame_begin, frame_end, window, halo, stream),
             "window table");
     Io io;
     io.d_latent = d_latent; io.d_out = d_out; io.n_frames = n_frames;
@@ -1099,7 +985,7 @@ demon_status demon_vae_encode_windowed(demon_vae* v, const float* d_wave, int n_
     if ((long long)n_frames * v->st.total_stride() > 0x7fffffffll) return fail(DEMON_ERR_UNSUPPORTED, "clips longer than 2^31 samples");
     if (halo == -1) halo = std::max(v->rf_left, v->rf_right);
     Plan* plan = nullptr;
-    const demon_status rc = get_plan(v, n_clips, n_frames, frame_begin, frame_end, window, halo, wants_two_groups(v), (hipStream_t)stream, &plan);
+    const demon_status rc = get_plan(v, n_clips, n_frames, frame_begin, frame_end, window, halo, (hipStream_t)stream, &plan);
     if (rc != DEMON_OK) return rc;
     Io io;
     io.d_wave = d_wave; io.d_eps = d_eps; io.d_moments = d_moments; io.d_zout = d_latent; io.n_frames = n_frames;

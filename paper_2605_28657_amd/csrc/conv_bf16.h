@@ -1,0 +1,41 @@
+// Parameters and modes shared by the implicit-GEMM convolution kernels of the bf16 path (kernels_bf16.hip: tiles staged
+// through LDS for shapes that kernels_bf16_stream.hip, which streams the weights to registers, turns away).
+#pragma once
+
+#include "device_common.h"
+
+namespace demon {
+
+constexpr int MAXSPAN = 64;    // largest (max tap offset - min tap offset) the LDS tiles are sized for
+
+enum { MODE_ACT = 0,   // bias + Snake, bf16 out only                     (dilated conv of a residual unit)
+       MODE_RES = 1,   // bias + residual add in fp32, half out in place  (1x1 conv of a residual unit)
+       MODE_UP  = 2,   // bias, polyphase scatter, half out               (ConvTranspose1d)
+       MODE_DOWN = 3 };// bias, half out; columns step two input rows     (strided Conv1d on merged rows)
+// MODE_RES, MODE_UP and MODE_DOWN may in addition emit the activated operand of the next layer: EMIT = 0 none, else the
+// operand format + 1 (1 bf16, 2 bf16 hi + lo, 3 half).  IN is the operand format of the input.
+
+struct MfmaParams {
+    const uint16_t* xa;      // activated input, 16-bit [rows][cin] in the kernel's IN format; lo plane at xa + in_lo_off
+    const uint16_t* w;       // packed weight blocks
+    const float* bias;
+    hres_t* y;               // residual-stream output; MODE_RES: also the residual source (in place); unused in MODE_ACT
+    uint16_t* ya;            // activated output in the kernel's EMIT format; lo plane at ya + out_lo_off
+    const float* out_alpha; const float* out_inv_beta;   // Snake applied before writing ya
+    const Slot* slots;
+    int r_in, cin, cout, ntaps, tap0, tap_step, stride, nchunks, margin;
+    int mtiles_x;            // > 0: blockIdx.x enumerates (column tile, row tile), see the kernel; 0: blockIdx.z = row tile
+    int xcd_group;           // with mtiles_x: 1 = all row tiles of a column tile on one XCD, 0 = row tiles dealt over the XCDs
+    unsigned w_bytes;
+    long long in_lo_off, out_lo_off;     // element offsets of the lo planes
+};
+
+// kernels_bf16_stream.hip: weights streamed to registers, on weights packed for the 128 x 128 tile (variant 0).  `rows` is the
+// GEMM's M, `ncols` the most columns a window needs, `mode`, `in_fmt` and `emit` as the template arguments of the
+// other kernels; launches of more than `max_small` 128 x 128 tiles do not look for a smaller tile.
+// stream_conv_ok: whether it has a kernel for the call.
+bool stream_conv_ok(const MfmaParams& p, int mode, int in_fmt);
+hipError_t launch_conv_stream(MfmaParams p, int mode, int in_fmt, int emit, int rows, long long ncols, int n_slots, long long max_small,
+                              hipStream_t stream);
+
+}  // namespace demon

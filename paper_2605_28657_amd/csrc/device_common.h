@@ -89,4 +89,8 @@ __device__ __forceinline__ uint32_t pack_f16x2(float lo, float hi)
     return __builtin_bit_cast(uint32_t, v);
 }
 
+// LDS row and 16-byte piece of the q-th piece of a packed weight block of KC-value rows (see to_fragment_order)
+template <int KC> __device__ __forceinline__ int frag_row(int q) { return KC % 32 ? q / (KC / 8) : q / (2 * KC) * 16 + (q & 15); }
+template <int KC> __device__ __forceinline__ int frag_piece(int q) { return KC % 32 ? q % (KC / 8) : q / 64 % (KC / 32) * 4 + (q >> 4 & 3); }
+
 }  // namespace demon

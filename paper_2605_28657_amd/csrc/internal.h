@@ -78,8 +78,7 @@ struct ConvArgs {
     // bf16 path only: format of the MFMA operand read (x) and of the one emitted (ya), see kernels_bf16.hip
     int in_fmt = OP_BF16, out_fmt = OP_BF16;
     long long in_lo_off = 0, out_lo_off = 0;     // OP_BF16X2: element offset of the lo plane
-    long long small_tile_wgs = 192;              // bf16 path: a launch of at most this many 128 x 128 tiles uses 64 x 64 tiles (0: never)
-    bool wide_tile_ok = true;                    // bf16 path: dilated convs with many columns may use the 128 x 256 tile
+    long long small_tile_wgs = 1024;             // bf16 path: launches of more 128 x 128 tiles than this take that tile
 };
 
 // fp32 implicit GEMM on an activated input; y: the residual stream (or nullptr), ya: fp32 operand of the next layer (or nullptr)
@@ -97,6 +96,10 @@ size_t packed_bf16_count(int cin, int cout, int ntaps, int stride, int variant);
 // `down` = s > 0: a strided Conv1d [cout, cin, 2s] in its merged-row form (see kernels_bf16.hip); ntaps, stride unused.
 void pack_bf16(const float* w_src, int cin, int cout, int ntaps, int stride, int variant, bool as_half, bool permute_rows,
                uint16_t* dst, int down = 0);
+// The layouts of pack_bf16 / pack_w1_* are row-major within a block; the kernels read every block in fragment order.
+// variant_block: rows and K values of a block of a variant's layout.
+void to_fragment_order(uint16_t* w, size_t count, int rows, int kc);
+void variant_block(int variant, int* rows, int* kc);
 uint16_t f32_to_bf16_rne(float v);
 uint16_t f32_to_f16_rne(float v);
 
@@ -174,9 +177,8 @@ hipError_t launch_stitch(const float* y, float* out, int oc, int S, int n_frames
 hipError_t launch_stitch_pcm16(const float* y, int16_t* pcm, int oc, int S, int n_frames, long long total_rows,
                                const Slot* slots, int n_slots, int max_int, hipStream_t stream);
 // window table written on the device (no host copy); per_clip windows and clip_frames extended frames per clip.
-// Windows from index `split` on form the second group: their rows count from `split_row0` (n_clips * per_clip, 0: one group).
 hipError_t launch_plan_slots(Slot* dst, int n_clips, int per_clip, int clip_frames, int n_frames, int frame_begin,
-                             int frame_end, int window, int halo, int split, int split_row0, hipStream_t stream);
+                             int frame_end, int window, int halo, hipStream_t stream);
 // decode gate: dst = src with the windows of clips whose skip flag is set emptied
 hipError_t launch_gate_slots(const Slot* src, Slot* dst, int n, const int* skip, hipStream_t stream);
 // latent similarity filter: per clip mse = mean((a-b)^2) over n elements and the gate mse < threshold

@@ -40,39 +40,15 @@
 //
 // Accumulation is fp32 in a fixed order (chunk-major, then tap, then channel), independent of where the
 // tile sits in the window, so a windowed decode reproduces the full decode bit for bit.
-#include <stdlib.h>
+#include <string.h>
 
 #include <algorithm>
 #include <type_traits>
+#include <vector>
 
-#include "device_common.h"
+#include "conv_bf16.h"
 
 namespace demon {
-
-constexpr int MAXSPAN = 64;    // largest (max tap offset - min tap offset) the LDS tile is sized for
-
-enum { MODE_ACT = 0,   // bias + Snake, bf16 out only                     (dilated conv of a residual unit)
-       MODE_RES = 1,   // bias + residual add in fp32, half out in place  (1x1 conv of a residual unit)
-       MODE_UP  = 2,   // bias, polyphase scatter, half out               (ConvTranspose1d)
-       MODE_DOWN = 3 };// bias, half out; columns step two input rows     (strided Conv1d on merged rows)
-// MODE_RES, MODE_UP and MODE_DOWN may in addition emit the activated operand of the next layer: EMIT = 0 none, else the
-// operand format + 1 (1 bf16, 2 bf16 hi + lo, 3 half).  IN is the operand format of the input.
-
-struct MfmaParams {
-    const uint16_t* xa;      // activated input, 16-bit [rows][cin] in the kernel's IN format; lo plane at xa + in_lo_off
-    const uint16_t* w;       // packed weight blocks
-    const float* bias;
-    hres_t* y;               // residual-stream output; MODE_RES: also the residual source (in place); unused in MODE_ACT
-    uint16_t* ya;            // activated output in the kernel's EMIT format; lo plane at ya + out_lo_off
-    const float* out_alpha; const float* out_inv_beta;   // Snake applied before writing ya
-    const Slot* slots;
-    int r_in, cin, cout, ntaps, tap0, tap_step, stride, nchunks, margin;
-    int mtiles_x;            // > 0: blockIdx.x enumerates (column tile, row tile), see the kernel; 0: blockIdx.z = row tile
-    int xcd_group;           // with mtiles_x: 1 = all row tiles of a column tile on one XCD, 0 = row tiles dealt over the XCDs
-    unsigned w_bytes;
-    int pack_ratio;          // the weights are packed in blocks of pack_ratio * MT rows (1, or 2 for the small-grid tile)
-    long long in_lo_off, out_lo_off;     // element offsets of the lo planes
-};
 
 struct Variant { int MT, NT, KC; };
 // variant 3 only names a weight layout: blocks of 256 x 32 for the fused 256-channel unit (kernels_bf16_wide.hip)
@@ -172,6 +148,25 @@ void pack_bf16(const float* w, int cin, int cout, int ntaps, int stride, int var
                     }
 }
 
+// The kernels read the packed blocks in the order of the 16 x 16 x 32 MFMA's fragments: within a block of `rows` x kc values,
+// 16-byte piece (tile * kc/32 + ks) * 64 + 16 q + i holds row 16 tile + i, values 32 ks + 8 q .. + 7.  A wave that loads a
+// fragment reads 1 KB in a row; a workgroup that stages a block in LDS copies it linearly and scatters the pieces over its
+// padded rows.  Blocks of 16 values per row stay row-major.
+void to_fragment_order(uint16_t* w, size_t count, int rows, int kc)
+{
+    if (kc % 32 != 0) return;
+    std::vector<uint16_t> blk((size_t)rows * kc);
+    for (size_t b = 0; b + blk.size() <= count; b += blk.size()) {
+        memcpy(blk.data(), w + b, blk.size() * 2);
+        for (int piece = 0; piece < rows * kc / 8; ++piece) {
+            const int i = piece % 16, q = (piece / 16) % 4, ks = (piece / 64) % (kc / 32), tile = piece / 64 / (kc / 32);
+            memcpy(w + b + (size_t)piece * 8, blk.data() + (size_t)(16 * tile + i) * kc + 32 * ks + 8 * q, 16);
+        }
+    }
+}
+
+void variant_block(int variant, int* rows, int* kc) { *rows = kVariants[variant].MT; *kc = kVariants[variant].KC; }
+
 template <int MT, int NT, int KC, int WM, int WN, int MODE, int IN, int EMIT>
 __global__ __launch_bounds__(64 * WM * WN) void conv_mfma_kernel(MfmaParams p)
 {
@@ -192,11 +187,8 @@ __global__ __launch_bounds__(64 * WM * WN) void conv_mfma_kernel(MfmaParams p)
     constexpr bool SPLIT_IN = IN == OP_BF16X2;
     constexpr int NP = SPLIT_IN ? 2 : 1;        // operand planes (hi, lo)
     static_assert(WM * WN == 2 || WM * WN == 4 || WM * WN == 8, "two, four or eight waves per workgroup");
-    static_assert(TM == 1 || TM == 2 || TM == 4, "a lane owns one channel, or one or two pairs of consecutive channels");
-    // A wave's 32-row slot tiles come in pairs (the packed order: slot j of tile 2b + k of a wave is GEMM row 64 b + 2 j + k
-    // of the wave's rows): a lane owns the channel pairs mu0 + 64 b + {0, 1}.
-    constexpr int PW = TM >= 2 ? 2 : 1;         // channels per pair
-    constexpr int PR = TM / PW;                 // pairs per lane
+    static_assert(TM == 1 || TM == 2, "a lane owns one channel or a pair of consecutive channels");
+    constexpr int PW = TM;                      // channels per lane
     static_assert(MODE != MODE_ACT || EMIT > 0, "the dilated conv only has the activated output");
     static_assert(MODE != MODE_DOWN || IN != OP_BF16X2, "the strided conv takes one operand plane");
 
@@ -206,8 +198,6 @@ __global__ __launch_bounds__(64 * WM * WN) void conv_mfma_kernel(MfmaParams p)
     // residual values requested after the K loop instead of before it.
     constexpr int NBUF = (MT == 128) ? 1 : 2;
     constexpr bool LATE_RES = MT == 128;
-    constexpr bool PF2 = MT == 64 && NT == 64;     // the small-grid tile: weight blocks requested several stages ahead
-    constexpr int PFD = PF2 ? 4 : 1;               // weight blocks in flight: the block of stage t travels in register set t % PFD
     constexpr int AS_BYTES = NBUF * MT * LDK * 2, XS_BYTES = NP * XR_MAX * LDK * 2;
     constexpr int SMEM_BYTES = AS_BYTES + XS_BYTES;
     __shared__ __attribute__((aligned(16))) unsigned char smem[SMEM_BYTES];
@@ -262,35 +252,29 @@ __global__ __launch_bounds__(64 * WM * WN) void conv_mfma_kernel(MfmaParams p)
     const __amdgpu_buffer_rsrc_t rs_xl = make_rsrc(p.xa + p.in_lo_off + rowbase * p.cin, SPLIT_IN ? (unsigned)nrows * p.cin * 2u : 0u);
 
     const int nstages = p.nchunks * p.ntaps;
-    // a row tile's blocks are nstages apart in the packed order; with blocks packed for a tile of pack_ratio * MT rows
-    // this tile is a contiguous slice of every such block
-    const unsigned w_blk = (unsigned)p.pack_ratio * (A_CH * 16u);
-    const unsigned w_tile0 = (unsigned)(mtile / p.pack_ratio) * nstages * w_blk + (unsigned)(mtile % p.pack_ratio) * (A_CH * 16u);
+    const unsigned w_tile0 = (unsigned)mtile * nstages * (A_CH * 16u);       // a row tile's blocks are nstages apart
     const unsigned a_voff = tid * 16u;
     const unsigned x_voff = ((unsigned)((XS * n0 + minoff + xr0) * p.cin) + seg * 8u) * 2u;    // may wrap "negative": out of range
     const unsigned x_row_step = (unsigned)(RPP * p.cin) * 2u;
 
-    u32x4 rs[PFD][A_ITERS];
-    u32x4 (&ra)[A_ITERS] = rs[0];
+    u32x4 ra[A_ITERS];
     u32x4 rx[X_ITERS][NP];
 
-    auto load_a_to = [&](u32x4 (&r)[A_ITERS], int stage) __attribute__((always_inline)) {
-        const unsigned base = w_tile0 + (unsigned)stage * w_blk;
+    auto load_a = [&](int stage) __attribute__((always_inline)) {
+        const unsigned base = w_tile0 + (unsigned)stage * (A_CH * 16u);
 #pragma unroll
         for (int it = 0; it < A_ITERS; ++it)
             if (A_CH % NTH == 0 || tid + it * NTH < A_CH)
-                r[it] = __builtin_amdgcn_raw_buffer_load_b128(rs_w, a_voff, base + it * (NTH * 16u), 0);
+                ra[it] = __builtin_amdgcn_raw_buffer_load_b128(rs_w, a_voff, base + it * (NTH * 16u), 0);
     };
-    auto store_a_from = [&](const u32x4 (&r)[A_ITERS], int buf) __attribute__((always_inline)) {
+    auto store_a = [&](int buf) __attribute__((always_inline)) {
 #pragma unroll
         for (int it = 0; it < A_ITERS; ++it) {
             const int q = tid + it * NTH;
             if (A_CH % NTH == 0 || q < A_CH)
-                *reinterpret_cast<u32x4*>(&As[buf][(q / SEGS) * LDK + (q % SEGS) * 8]) = r[it];
+                *reinterpret_cast<u32x4*>(&As[buf][frag_row<KC>(q) * LDK + frag_piece<KC>(q) * 8]) = ra[it];
         }
     };
-    auto load_a = [&](int stage) __attribute__((always_inline)) { load_a_to(ra, stage); };
-    auto store_a = [&](int buf) __attribute__((always_inline)) { store_a_from(ra, buf); };
     auto load_x = [&](int chunk) __attribute__((always_inline)) {
         const unsigned coff = x_voff + (unsigned)(chunk * KC) * 2u;
 #pragma unroll
@@ -312,10 +296,10 @@ __global__ __launch_bounds__(64 * WM * WN) void conv_mfma_kernel(MfmaParams p)
         }
     };
 
-    // this lane's GEMM rows: accumulator tile mi holds row mu0 + 64 (mi / 2) + mi % 2; the accumulators start at their bias
+    // this lane's GEMM rows: accumulator tile mi holds row mu0 + mi; the accumulators start at their bias
     const int mu0 = m0 + wm * WTM + j * PW;
     auto chan = [&](int mi) -> int {            // output channel of accumulator tile mi
-        const int mu = mu0 + (mi >> 1) * 64 + (mi & 1);
+        const int mu = mu0 + mi;
         return (MODE == MODE_UP) ? mu % p.cout : mu;
     };
     f32x16 acc[TM][TN];
@@ -346,26 +330,21 @@ __global__ __launch_bounds__(64 * WM * WN) void conv_mfma_kernel(MfmaParams p)
     // issued in the epilogue where they are used, each of the loads would be waited for in turn (they cannot move
     // above the in-place stores), a chain of memory latencies per tile.
     using pack_t = std::conditional_t<PW == 2, uint32_t, uint16_t>;     // PW 16-bit values
-    pack_t resv[MODE == MODE_RES ? PR : 1][MODE == MODE_RES ? TN : 1][16];
+    pack_t resv[MODE == MODE_RES ? TN : 1][16];
     auto load_res = [&]() __attribute__((always_inline)) {
 #pragma unroll
-        for (int pr = 0; pr < PR; ++pr)
+        for (int ni = 0; ni < TN; ++ni)
 #pragma unroll
-            for (int ni = 0; ni < TN; ++ni)
-#pragma unroll
-                for (int gq = 0; gq < 16; ++gq) {
-                    const unsigned off = (elem(ni, gq) + 64u * pr) * 2u;
-                    if constexpr (PW == 2) resv[pr][ni][gq] = __builtin_amdgcn_raw_buffer_load_b32(rs_y, off, 0, 0);
-                    else resv[pr][ni][gq] = __builtin_amdgcn_raw_buffer_load_b16(rs_y, off, 0, 0);
-                }
+            for (int gq = 0; gq < 16; ++gq) {
+                if constexpr (PW == 2) resv[ni][gq] = __builtin_amdgcn_raw_buffer_load_b32(rs_y, elem(ni, gq) * 2u, 0, 0);
+                else resv[ni][gq] = __builtin_amdgcn_raw_buffer_load_b16(rs_y, elem(ni, gq) * 2u, 0, 0);
+            }
     };
     if (MODE == MODE_RES && !LATE_RES) load_res();
 
     load_a(0);
     load_x(0);
     store_a(0);
-#pragma unroll
-    for (int t = 1; t < PFD; ++t) load_a_to(rs[t], t);             // past the last stage: out of range, nothing is read
     store_x();
     __syncthreads();
 
@@ -412,20 +391,15 @@ __global__ __launch_bounds__(64 * WM * WN) void conv_mfma_kernel(MfmaParams p)
         __builtin_amdgcn_sched_group_barrier(0x008, M - PAIRS, 0);
         __builtin_amdgcn_s_setprio(0);
     };
-    // The weight block of stage s + PFD is requested before stage s is computed, into the register set whose block
-    // (stage s) went to LDS a stage ago.  U = s % PFD is a compile-time constant (the loop is unrolled by PFD), so the sets
-    // stay in registers.  One block in flight is enough where three workgroups share the CU and cover each other's loads
-    // (two blocks: the same step time, 16 more registers); launches with few workgroups (the small-grid tile: one wave per
-    // SIMD, nothing else to hide a load behind) keep four in flight (-3.5 % on a 3 s playback window).  The request is
-    // unconditional -- past the last stage its offset is outside the descriptor and nothing is read -- because behind a
-    // branch the compiler cannot count it, and every wait for an older block would then wait for all loads.
-    auto body = [&](int stage, auto U) __attribute__((always_inline)) {
-        constexpr int u = decltype(U)::value;
+    // One weight block in flight is enough where three workgroups share the CU and cover each other's loads (two blocks: the
+    // same step time, 16 more registers).  The request is unconditional -- past the last stage it reads another row tile's
+    // block or nothing -- because behind a branch the compiler cannot count it.
+    for (int stage = 0; stage < nstages; ++stage) {
         int ntap = tap + 1, nchunk = chunk;
         if (ntap == p.ntaps) { ntap = 0; ++nchunk; }
         const bool more = stage + 1 < nstages;
         const bool new_chunk = more && nchunk != chunk;
-        load_a_to(rs[u], stage + PFD);
+        load_a(stage + 1);
         if (new_chunk) load_x(nchunk);
         mma(stage);
         if (more) {
@@ -433,20 +407,11 @@ __global__ __launch_bounds__(64 * WM * WN) void conv_mfma_kernel(MfmaParams p)
                 __syncthreads();              // every wave is done with the old X tile (and the single weight buffer)
                 if (new_chunk) store_x();
             }
-            store_a_from(rs[(u + 1) % PFD], NBUF == 2 ? ((stage + 1) & 1) : 0);
+            store_a(NBUF == 2 ? ((stage + 1) & 1) : 0);
             __syncthreads();
         }
         tap = ntap; chunk = nchunk;
-    };
-    for (int stage = 0; stage < nstages; stage += PFD) {
-        body(stage, std::integral_constant<int, 0>{});
-        if constexpr (PFD == 4) {
-            if (stage + 1 < nstages) body(stage + 1, std::integral_constant<int, 1 % PFD>{});
-            if (stage + 2 < nstages) body(stage + 2, std::integral_constant<int, 2 % PFD>{});
-            if (stage + 3 < nstages) body(stage + 3, std::integral_constant<int, 3 % PFD>{});
-        }
     }
-    static_assert(PFD == 1 || PFD == 4, "the stage loop is unrolled by hand");
 
     if (MODE == MODE_RES && LATE_RES) load_res();
 
@@ -462,19 +427,17 @@ __global__ __launch_bounds__(64 * WM * WN) void conv_mfma_kernel(MfmaParams p)
         ob[mi] = EMIT > 0 ? p.out_inv_beta[chan(mi)] : 0.f;
     }
 #pragma unroll
-    for (int pr = 0; pr < PR; ++pr)
-#pragma unroll
     for (int ni = 0; ni < TN; ++ni)
 #pragma unroll
         for (int gq = 0; gq < 16; ++gq) {
-            const unsigned e = elem(ni, gq) + 64u * pr;
+            const unsigned e = elem(ni, gq);
             float v[PW];
 #pragma unroll
-            for (int k = 0; k < PW; ++k) v[k] = acc[PW * pr + k][ni][gq];
+            for (int k = 0; k < PW; ++k) v[k] = acc[k][ni][gq];
             if (MODE == MODE_RES) {
 #pragma unroll
                 for (int k = 0; k < PW; ++k)
-                    v[k] += (float)__builtin_bit_cast(_Float16, (uint16_t)(resv[pr][ni][gq] >> (16 * k)));
+                    v[k] += (float)__builtin_bit_cast(_Float16, (uint16_t)(resv[ni][gq] >> (16 * k)));
             }
             if (MODE != MODE_ACT) {
                 // half store of h; the next layer's operand is Snake of the STORED value
@@ -493,7 +456,7 @@ __global__ __launch_bounds__(64 * WM * WN) void conv_mfma_kernel(MfmaParams p)
                 float a[PW];
 #pragma unroll
                 for (int k = 0; k < PW; ++k) {
-                    a[k] = snake_fast(v[k], oa[PW * pr + k], ob[PW * pr + k]);
+                    a[k] = snake_fast(v[k], oa[k], ob[k]);
                     if (EMIT == 3) a[k] = keep_f32(a[k]);                 // fp32 Snake, then one rounding
                 }
                 if constexpr (PW == 2) {
@@ -523,10 +486,6 @@ static hipError_t launch_variant(const MfmaParams& p, int mode, int in_fmt, int 
 #define DEMON_CASE(MODE_, IN_, EM_) if (in_fmt == IN_ && emit == EM_) { DEMON_LAUNCH(MODE_, IN_, EM_); return hipGetLastError(); }
     if (mode == MODE_ACT) {
         DEMON_CASE(MODE_ACT, OP_BF16, 1) DEMON_CASE(MODE_ACT, OP_BF16, 2) DEMON_CASE(MODE_ACT, OP_F16, 3)
-    } else if constexpr (MT == 128 && NT == 256) {
-        if (mode != MODE_UP) return hipErrorInvalidValue;         // the 128 x 256 tile runs dilated and transposed convs
-        DEMON_CASE(MODE_UP, OP_BF16, 0) DEMON_CASE(MODE_UP, OP_BF16, 1) DEMON_CASE(MODE_UP, OP_BF16, 2) DEMON_CASE(MODE_UP, OP_BF16, 3)
-        DEMON_CASE(MODE_UP, OP_F16, 1) DEMON_CASE(MODE_UP, OP_F16, 3)
     } else if (mode == MODE_RES) {
         DEMON_CASE(MODE_RES, OP_BF16, 0) DEMON_CASE(MODE_RES, OP_BF16, 1) DEMON_CASE(MODE_RES, OP_BF16, 2) DEMON_CASE(MODE_RES, OP_BF16, 3)
         DEMON_CASE(MODE_RES, OP_BF16X2, 0) DEMON_CASE(MODE_RES, OP_BF16X2, 1) DEMON_CASE(MODE_RES, OP_BF16X2, 2)
@@ -546,9 +505,6 @@ static hipError_t launch_variant(const MfmaParams& p, int mode, int in_fmt, int 
     return hipErrorInvalidValue;
 }
 
-// Launches of the 128 x 128 tile that would leave most CUs without a workgroup (one playback window at the wide, low-rate
-// levels) use a 64 x 64 tile on the same packed weights instead: four times the workgroups, and the same K order, so
-// the results are bit-identical to the large tile's.  ConvArgs::small_tile_wgs is the threshold (0: never).
 hipError_t launch_conv_bf16(const ConvArgs& a, int variant, hipStream_t stream)
 {
     if (variant < 0 || variant > 2) return hipErrorInvalidValue;
@@ -596,23 +552,8 @@ hipError_t launch_conv_bf16(const ConvArgs& a, int variant, hipStream_t stream)
     //  * W larger, more than 8 row tiles: ids run over row tiles first, so XCD x owns the row tiles = x mod 8 (an
     //    eighth of W, resident) and reads all activations: about 8 X + W.
     //  * else column tiles fastest (blockIdx.x): workgroups in flight share one row tile of the weights: mtiles X + W.
-    p.pack_ratio = 1;
-    bool small_tile = false;
-    if (variant == 0 && ((ncols + v.NT - 1) / v.NT) * (M / v.MT) * a.n_slots <= a.small_tile_wgs) {
-        small_tile = true;
-        v.MT = 64; v.NT = 64; p.pack_ratio = 2;
-    }
-    // Dilated convs with enough columns run a 128 x 256 tile on the same packed weights (four waves side by side, every
-    // wave all 128 rows of its 64 columns: 0.75 instead of 1 fragment read per MFMA, half the weight staging per column, two
-    // workgroups per CU): -7 % on the 512-channel dilated convs.  Only when the launch still has 768 such workgroups (three per CU):
-    // with fewer the larger tile's last round costs more than the tile saves (+5 % on the 1024-channel level of a 60 s clip).
-    // Same K order, so the results are bit-identical to the 128 x 128 tile's.
-    // Transposed convs too where the weight matrix is small (at most four row tiles: -8 ... -12 % at 128 and 256 input
-    // channels; with more row tiles the square tile is as fast or faster).
-    const bool wide_n = a.wide_tile_ok && variant == 0 && !small_tile && a.in_fmt != OP_BF16X2 &&
-                        (mode == MODE_ACT || (mode == MODE_UP && M / v.MT <= 4)) &&
-                        ((ncols + 255) / 256) * (M / v.MT) * a.n_slots >= 768;
-    if (wide_n) v.NT = 256;
+    if (variant == 0 && stream_conv_ok(p, mode, a.in_fmt))
+        return launch_conv_stream(p, mode, a.in_fmt, emit, M, ncols, a.n_slots, a.small_tile_wgs, stream);
     const long long ntiles = (ncols + v.NT - 1) / v.NT;
     const int mtiles = M / v.MT;
     const long long ntiles8 = (ntiles + 7) / 8 * 8;           // whole groups of 8 column tiles; the surplus exits at once
@@ -622,9 +563,7 @@ hipError_t launch_conv_bf16(const ConvArgs& a, int variant, hipStream_t stream)
     p.xcd_group = w_fits_l2 ? 1 : 0;
     dim3 grid(m_fastest ? (unsigned)(ntiles8 * mtiles) : (unsigned)ntiles, (unsigned)a.n_slots, m_fastest ? 1u : (unsigned)mtiles);
     switch (variant) {
-        case 0: if (wide_n) return launch_variant<128, 256, 64, 1, 4>(p, mode, a.in_fmt, emit, grid, stream);
-                return small_tile ? launch_variant<64, 64, 64, 1, 2>(p, mode, a.in_fmt, emit, grid, stream)
-                                  : launch_variant<128, 128, 64, 2, 2>(p, mode, a.in_fmt, emit, grid, stream);
+        case 0: return launch_variant<128, 128, 64, 2, 2>(p, mode, a.in_fmt, emit, grid, stream);
         case 1: return launch_variant<64, 256, 64, 1, 4>(p, mode, a.in_fmt, emit, grid, stream);
         default: return launch_variant<32, 128, 16, 1, 4>(p, mode, a.in_fmt, emit, grid, stream);
     }

@@ -156,7 +156,7 @@ __global__ __launch_bounds__(256, (CH == 128 && TN == 2) ? 2 : 3) void res_unit_
 #pragma unroll
         for (int it = 0; it < A_ITERS; ++it) {
             const int q = tid + it * 256;
-            *reinterpret_cast<u32x4*>(&As[(q / SEGS) * LDK + (q % SEGS) * 8]) = ra[it];
+            *reinterpret_cast<u32x4*>(&As[frag_row<KC>(q) * LDK + frag_piece<KC>(q) * 8]) = ra[it];
         }
     };
     auto load_x = [&](int chunk) __attribute__((always_inline)) {
@@ -328,7 +328,7 @@ __global__ __launch_bounds__(256, (CH == 128 && TN == 2) ? 2 : 3) void res_unit_
 #pragma unroll
     for (int it = 0; it < W1_CH / 256; ++it) {
         const int q = tid + it * 256;
-        *reinterpret_cast<u32x4*>(&As[(q / (CH / 8)) * LD1 + (q % (CH / 8)) * 8]) = rw1[it];
+        *reinterpret_cast<u32x4*>(&As[frag_row<CH>(q) * LD1 + frag_piece<CH>(q) * 8]) = rw1[it];
     }
     __syncthreads();
 

@@ -1,0 +1,384 @@
+// Convolutions of the bf16 path with the weights streamed to registers.
+//
+// What bound the LDS-staged tiles: a launch of few workgroups (a playback window, a short clip) lasted as long as one
+// workgroup's walk over K, whatever their number -- two barriers per 8 KB weight block, four blocks in flight, 0.41 us per block
+// where its MFMAs take 0.1 -- and a launch that fills the chip read as many LDS bytes per MFMA as the LDS delivers.  Here
+//  * a wave streams the fragments of its own GEMM rows from global memory straight to registers, in the order the packed
+//    blocks hold them (no LDS, no barrier), RS k-steps ahead in a ring of registers with static indices;
+//  * the activation tile, shared by the workgroup's waves, is double-buffered in LDS in stages of SC 64-channel chunks and all
+//    their taps: one barrier per stage;
+//  * the MFMA is the 16 x 16 x 32 form: half the dependent accumulations of the 32 x 32 x 16 form and tiles small enough to
+//    give every SIMD a chain (a dependent 32 x 32 x 16 takes 19 ns, an independent one 13.5; 16 x 16 x 32: 22 and 7.5);
+//  * the output tile goes through LDS to 16-byte loads and stores of consecutive channels.
+// A CU takes some 45 bytes of weights per clock in, whether they hit its L1 or not, and reads 190 bytes per clock from LDS: the
+// large tile gives every wave 32 rows x 128 columns (8 KB of weights and 32 KB of LDS reads per 288 cycles of MFMAs).
+// Measured, LDS-staged tile -> here: 1024-channel dilated conv 46 -> 9.6 us (200 columns), 47 -> 17 (830), 258 -> 214 (17000);
+// 512 channels 34 -> 21 (4700), 333 -> 298 (100000: 1.23 PFLOP/s); 1x1 conv of 1024 channels 13 -> 5 (200), 14 -> 7.6 (830);
+// strided conv 1024 -> 128, stride 10: 146 -> 25 (75 columns).
+// Both MFMA forms add the products of 8 consecutive K values at a time, in K order, so with the K order (chunk, tap, channel)
+// of kernels_bf16.hip the results are bit-identical.
+#include <algorithm>
+
+#include "conv_bf16.h"
+
+namespace demon {
+
+namespace {
+
+struct StreamGrid {
+    int xm, xn;              // the 8 XCDs as xm groups of 128-row panels x xn groups of column tiles
+    int mper;                // row tiles of an XCD
+};
+
+// Tile: WM x WN waves of TM x TN accumulator tiles of 16 rows x 16 columns.
+// NB: activation buffers, 2, or 1 for layers of a single stage.
+template <int TM, int TN, int WM, int WN, int NTAPS, int SC, int SPAN, int MODE, int IN, int NB>
+__global__ __launch_bounds__(64 * WM * WN) void conv_stream_kernel(MfmaParams p, StreamGrid sg, int emit)
+{
+    fp16_saturate_on();
+    constexpr int NTH = 64 * WM * WN, MT = 16 * TM * WM, NT = 16 * TN * WN;
+    constexpr int XS = (MODE == MODE_DOWN) ? 2 : 1;        // input rows per GEMM column
+    constexpr int XROWS = XS * (NT - 1) + 1 + SPAN;
+    // channels of a stage; padded LDS row: 16-byte reads of 16 rows x 4 neighbouring pieces are free of bank conflicts (5.3 cycles
+    // a wave, else 8 or more) when the rows lie 2 (mod 4) pieces apart
+    constexpr int KX = 64 * SC, LDR = KX + 16 / XS;
+    constexpr int NP = IN == OP_BF16X2 ? 2 : 1;
+    constexpr int SEGS = KX / 8, RPP = NTH / SEGS, X_ITERS = (XROWS + RPP - 1) / RPP;
+    constexpr int XR = X_ITERS * RPP;                      // rows held (whole passes)
+    constexpr int F = SC * NTAPS * 2;                      // k-steps of a stage
+    // k-steps in flight: a step lasts TM x TN MFMAs of 8 ns, an L2 hit some 400 ns
+    constexpr int RS = TM >= 4 ? 2 : TM * F <= 32 ? F : F / 2;
+    static_assert(F % RS == 0, "static ring indices");
+    constexpr int LDO = MT + 4;                            // padded row of the fp32 output tile
+    constexpr int X_BYTES = NP * XR * LDR * 2;
+    constexpr int EP = NT * LDO * 4 > NB * X_BYTES && TN % 2 == 0 ? 2 : 1;      // passes of the epilogue
+    constexpr int O_BYTES = NT / EP * LDO * 4;
+    constexpr int SMEM = NB * X_BYTES > O_BYTES ? NB * X_BYTES : O_BYTES;
+    static_assert(NTH % SEGS == 0 && TN % EP == 0, "whole rows per pass");
+    __shared__ __attribute__((aligned(16))) unsigned char smem[SMEM];
+
+    const Slot s = p.slots[blockIdx.y];
+    const int nrows = s.len * p.r_in;
+    const int r_out = (MODE == MODE_UP) ? p.r_in * p.stride : (MODE == MODE_DOWN) ? p.r_in / 2 : p.r_in;
+    const int nrows_o = s.len * r_out;
+    const int out_lo = max(0, s.crop * r_out - p.margin);
+    const int out_hi = min(nrows_o, (s.crop + s.n_int) * r_out + p.margin);
+    if (out_hi <= out_lo) return;                           // an empty window (a gated clip)
+    const int col_lo = (MODE == MODE_UP) ? (out_lo + p.stride / 2) / p.stride : out_lo;
+    const int ncols = (MODE == MODE_UP) ? (out_hi - 1 + p.stride / 2) / p.stride + 1 : out_hi;
+    // Workgroups are dealt to the 8 XCDs round-robin by linear id (gridDim.x is a multiple of 8), each with its own L2.  XCD
+    // (x % xm, x / xm) takes every xm-th panel of 128 rows and every xn-th column tile (rotated by the window): it reads
+    // 1/xm of the weights and 1/xn of the activations.
+    constexpr int SUB = 128 / MT;                           // row tiles of a panel
+    const int xcd = (int)((blockIdx.x + blockIdx.y) & 7u), q8 = (int)(blockIdx.x >> 3), mi8 = q8 % sg.mper;
+    const int panel = xcd % sg.xm + sg.xm * (mi8 / SUB), ntile = xcd / sg.xm + sg.xn * (q8 / sg.mper);
+    const int n0 = col_lo + ntile * NT;
+    if (n0 >= ncols) return;
+    const int sub = mi8 % SUB, m0 = panel * 128 + sub * MT;
+    const long long rowbase = (long long)s.row0 * p.r_in, rowbase_o = (long long)s.row0 * r_out;
+    const int minoff = min(p.tap0, p.tap0 + (NTAPS - 1) * p.tap_step);
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int wm = wave / WN, wn = wave % WN;
+    const int i = lane & 15, q = lane >> 4;
+    const int seg = tid % SEGS, xr0 = tid / SEGS;
+
+    const __amdgpu_buffer_rsrc_t rs_w = make_rsrc(p.w, p.w_bytes);
+    const __amdgpu_buffer_rsrc_t rs_x = make_rsrc(p.xa + rowbase * p.cin, (unsigned)nrows * p.cin * 2u);
+    const __amdgpu_buffer_rsrc_t rs_xl = make_rsrc(p.xa + p.in_lo_off + rowbase * p.cin, NP == 2 ? (unsigned)nrows * p.cin * 2u : 0u);
+
+    // ---- weights: blocks of 128 x 64 (16 KB) in fragment order, [16-slot tile][2 k-steps][lane][8].  Slot 32 k + l of a group of
+    // 64 is row 2 l + k (the lane order of the 128 x 128 tile): slot tiles 0, 2 hold rows 0..31 of the group (even, odd), 1, 3
+    // rows 32..63.  Unit u of a panel takes them in the order 0, 2, 1, 3; its lane i is row 32 (u / 2) + 2 i + u % 2.
+    const int nblocks = p.nchunks * NTAPS;
+    const int unit0 = sub * (MT / 16) + wm * TM;                             // first unit of this wave in the panel
+    const unsigned w_voff = (unsigned)((unit0 & ~3) + (unit0 & 1) * 2 + (unit0 >> 1 & 1)) * 2048u + lane * 16u;
+    const unsigned w_tile = (unsigned)panel * (unsigned)nblocks * 16384u;
+    u32x4 a[RS][TM];
+    auto load_a = [&](int stage, int f) __attribute__((always_inline)) {     // f may run past the stage
+        // past the last stage: another panel's block or out of range; not used
+        const unsigned blk = w_tile + (unsigned)(stage * (F / 2) + f / 2) * 16384u;
+#pragma unroll
+        for (int mi = 0; mi < TM; ++mi) a[f % RS][mi] = __builtin_amdgcn_raw_buffer_load_b128(rs_w, w_voff + ((mi & 1) * 2 + (mi >> 1)) * 2048u + (f & 1) * 1024u, blk, 0);
+    };
+    auto lane_row = [&](int mi) __attribute__((always_inline)) -> int {      // GEMM row of this lane in the tile
+        const int u = unit0 + mi;
+        return (u >> 1) * 32 + 2 * i + (u & 1) - sub * MT;
+    };
+
+    // ---- activations
+    const unsigned x_voff = ((unsigned)((XS * n0 + minoff + xr0) * p.cin) + seg * 8u) * 2u;    // may wrap "negative": out of range
+    const unsigned x_row_step = (unsigned)(RPP * p.cin) * 2u;
+    const int nstages = p.nchunks / SC;
+    u32x4 rx[X_ITERS][NP];
+    auto load_x = [&](int stage) __attribute__((always_inline)) {
+        const unsigned off = stage < nstages ? x_voff + (unsigned)(stage * KX) * 2u : 0xf8000000u;      // past the last stage: out of range
+#pragma unroll
+        for (int it = 0; it < X_ITERS; ++it) {
+            rx[it][0] = __builtin_amdgcn_raw_buffer_load_b128(rs_x, off + it * x_row_step, 0, 0);
+            if (NP == 2) rx[it][NP - 1] = __builtin_amdgcn_raw_buffer_load_b128(rs_xl, off + it * x_row_step, 0, 0);
+        }
+    };
+    auto store_x = [&](int buf) __attribute__((always_inline)) {
+        uint16_t* xs = reinterpret_cast<uint16_t*>(smem + buf * X_BYTES);
+#pragma unroll
+        for (int it = 0; it < X_ITERS; ++it)
+#pragma unroll
+            for (int pl = 0; pl < NP; ++pl)
+                *reinterpret_cast<u32x4*>(&xs[pl * XR * LDR + (xr0 + it * RPP) * LDR + seg * 8]) = rx[it][pl];
+    };
+
+    // every request of the prologue in the order of use
+    load_x(0);
+#pragma unroll
+    for (int f = 0; f < RS; ++f) load_a(0, f);
+    float bv[TM];
+#pragma unroll
+    for (int mi = 0; mi < TM; ++mi) bv[mi] = p.bias[(MODE == MODE_UP) ? (m0 + lane_row(mi)) % p.cout : m0 + lane_row(mi)];
+
+    // ---- geometry of the epilogue: piece (row, 8 channels) of the output tile; residual values requested ahead where the
+    // registers allow it
+    constexpr int PPR = MT / 8, ERPP = NTH / PPR, E_ITERS = (NT / EP + ERPP - 1) / ERPP;
+    static_assert(NTH % PPR == 0, "whole rows per pass");
+    constexpr int WROWS = NT / EP / WN;                                 // rows of a pass that belong to one wave column
+    const int ec = m0 + (tid % PPR) * 8, er0 = tid / PPR;
+    auto eoff = [&](int ep, int it) __attribute__((always_inline)) -> unsigned {
+        const int r = er0 + it * ERPP;
+        if (NT / EP % ERPP != 0 && r >= NT / EP) return 0xf8000000u;         // out of range
+        const int n = n0 + r / WROWS * (16 * TN) + ep * WROWS + r % WROWS;
+        // transposed conv: column n, row mu lands on the run starting at (n s - p) cout + mu; a negative row wraps: out of range
+        return (MODE == MODE_UP ? (unsigned)((n * p.stride - p.stride / 2) * p.cout + ec) : (unsigned)(n * p.cout + ec)) * 2u;
+    };
+    const unsigned out_bytes = (unsigned)out_hi * p.cout * 2u;
+    const __amdgpu_buffer_rsrc_t rs_y = make_rsrc(MODE == MODE_ACT ? nullptr : p.y + rowbase_o * p.cout, MODE == MODE_ACT ? 0u : out_bytes);
+    u32x4 resv[MODE == MODE_RES ? EP : 1][MODE == MODE_RES ? E_ITERS : 1];
+    auto load_res = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int ep = 0; ep < EP; ++ep)
+#pragma unroll
+            for (int it = 0; it < E_ITERS; ++it) resv[ep][it] = __builtin_amdgcn_raw_buffer_load_b128(rs_y, eoff(ep, it), 0, 0);
+    };
+    constexpr bool EARLY_RES = MODE == MODE_RES && E_ITERS * EP <= 4;
+    if (EARLY_RES) load_res();
+
+    f32x4 acc[TM][TN];
+#pragma unroll
+    for (int mi = 0; mi < TM; ++mi)
+#pragma unroll
+        for (int ni = 0; ni < TN; ++ni) acc[mi][ni] = f32x4{bv[mi], bv[mi], bv[mi], bv[mi]};
+
+    store_x(0);
+    __syncthreads();
+
+    // The k-steps are a software pipeline held in source order by scheduling fences: activation fragments AHEAD steps before their
+    // MFMAs, the step's weight registers refilled right after them.  (Left to itself the compiler runs one accumulator's whole
+    // chain, then the next, waiting out the LDS latency of every fragment.)
+    constexpr int AHEAD = TM * TN <= 2 ? 6 : TM * TN <= 4 ? 3 : 1, XD = AHEAD + 1;
+    for (int stage = 0; stage < nstages; ++stage) {
+        if (NB == 2) load_x(stage + 1);
+        const uint16_t* xs = reinterpret_cast<const uint16_t*>(smem + (NB == 2 ? (stage & 1) * X_BYTES : 0)) + (wn * (16 * TN) + i) * XS * LDR + q * 8;
+        u32x4 x[XD][TN][NP];
+        auto read_x = [&](int f, int ni) __attribute__((always_inline)) {
+            const int ks = f & 1, tap = (f / 2) % NTAPS, c = f / (2 * NTAPS);
+            const uint16_t* xt = xs + (p.tap0 + tap * p.tap_step - minoff) * LDR + c * 64 + ks * 32 + ni * 16 * XS * LDR;
+#pragma unroll
+            for (int pl = 0; pl < NP; ++pl) x[f % XD][ni][pl] = *reinterpret_cast<const u32x4*>(xt + pl * XR * LDR);
+        };
+#pragma unroll
+        for (int f = 0; f < AHEAD && f < F; ++f)
+#pragma unroll
+            for (int ni = 0; ni < TN; ++ni) read_x(f, ni);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int f = 0; f < F; ++f) {
+#pragma unroll
+            for (int ni = 0; ni < TN; ++ni) {
+                if (f + AHEAD < F) read_x(f + AHEAD, ni);
+                // activations are the row operand: the accumulator tile is [time][GEMM row].  Two operand planes alternate per 16
+                // K values (hi, then lo: the order of the 32 x 32 x 16 form): the other half of the step's K slots are zero.
+#pragma unroll
+                for (int mi = 0; mi < TM; ++mi) {
+                    const u32x4 w = a[f % RS][mi];
+                    if constexpr (NP == 2) {
+                        const u32x4 z = {0, 0, 0, 0};
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) {
+                            const u32x4 xv = (q >> 1) == (k >> 1) ? x[f % XD][ni][k & 1] : z;
+                            acc[mi][ni] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, xv), __builtin_bit_cast(bf16x8, w), acc[mi][ni], 0, 0, 0);
+                        }
+                    } else if (IN == OP_F16)
+                        acc[mi][ni] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, x[f % XD][ni][0]), __builtin_bit_cast(f16x8, w), acc[mi][ni], 0, 0, 0);
+                    else
+                        acc[mi][ni] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, x[f % XD][ni][0]), __builtin_bit_cast(bf16x8, w), acc[mi][ni], 0, 0, 0);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            load_a(stage, f + RS);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if (NB == 2) store_x((stage + 1) & 1);
+        __syncthreads();
+        if (NB == 1) break;
+    }
+
+    // ---- epilogue: register e of lane (i, q) is time row 4 q + e, GEMM row lane_row(mi)
+    if (MODE == MODE_RES && !EARLY_RES) load_res();
+    float oa[8], ob[8];
+    if (emit > 0) {
+        const int c0 = (MODE == MODE_UP) ? ec % p.cout : ec;
+#pragma unroll
+        for (int e = 0; e < 8; e += 4) {
+            const f32x4 va = *reinterpret_cast<const f32x4*>(p.out_alpha + c0 + e), vb = *reinterpret_cast<const f32x4*>(p.out_inv_beta + c0 + e);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) { oa[e + k] = va[k]; ob[e + k] = vb[k]; }
+        }
+    }
+    const __amdgpu_buffer_rsrc_t rs_a = make_rsrc(p.ya + rowbase_o * p.cout, emit > 0 ? out_bytes : 0u);
+    const __amdgpu_buffer_rsrc_t rs_al = make_rsrc(p.ya + p.out_lo_off + rowbase_o * p.cout, emit == 2 ? out_bytes : 0u);
+    float* os = reinterpret_cast<float*>(smem);
+#pragma unroll
+    for (int ep = 0; ep < EP; ++ep) {
+        if (ep > 0) __syncthreads();
+#pragma unroll
+        for (int mi = 0; mi < TM; ++mi)
+#pragma unroll
+            for (int ni = 0; ni < TN / EP; ++ni)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) os[(wn * WROWS + ni * 16 + 4 * q + e) * LDO + lane_row(mi)] = acc[mi][ep * (TN / EP) + ni][e];
+        __syncthreads();
+#pragma unroll
+        for (int it = 0; it < E_ITERS; ++it) {
+            if (NT / EP % ERPP != 0 && er0 + it * ERPP >= NT / EP) break;
+            const float* src = &os[(er0 + it * ERPP) * LDO + (tid % PPR) * 8];
+            float v[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v[e] = src[e];
+            const unsigned off = eoff(ep, it);
+            if (MODE == MODE_RES) {
+                const f16x8 r = __builtin_bit_cast(f16x8, resv[ep][it]);
+#pragma unroll
+                for (int e = 0; e < 8; ++e) v[e] = keep_f32(v[e] + (float)r[e]);
+            }
+            if (MODE != MODE_ACT) {
+                // half store of h; the next layer's operand is Snake of the STORED value
+                f16x8 hv;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) { hv[e] = (_Float16)v[e]; v[e] = (float)hv[e]; }
+                __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, hv), rs_y, off, 0, 0);
+            }
+            if (emit == 0) continue;                                                  // uniform
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v[e] = keep_f32(snake_fast(v[e], oa[e], ob[e]));            // fp32 Snake, then one rounding
+            u32x4 o;
+            if (emit == 3) {
+#pragma unroll
+                for (int k = 0; k < 4; ++k) o[k] = pack_f16x2(v[2 * k], v[2 * k + 1]);
+            } else {
+#pragma unroll
+                for (int k = 0; k < 4; ++k) o[k] = pack_bf16x2(v[2 * k], v[2 * k + 1]);
+            }
+            __builtin_amdgcn_raw_buffer_store_b128(o, rs_a, off, 0, 0);
+            if (emit == 2) {                                                          // what the hi plane's rounding left over
+                u32x4 lo;
+#pragma unroll
+                for (int k = 0; k < 4; ++k) lo[k] = pack_bf16x2(v[2 * k] - __uint_as_float(o[k] << 16), v[2 * k + 1] - __uint_as_float(o[k] & 0xffff0000u));
+                __builtin_amdgcn_raw_buffer_store_b128(lo, rs_al, off, 0, 0);
+            }
+        }
+    }
+}
+
+template <int TM, int TN, int WM, int WN>
+hipError_t launch_tile(const MfmaParams& p, const StreamGrid& sg, int mode, int in_fmt, int emit, dim3 grid, hipStream_t stream)
+{
+    // SC: the more k-steps a stage holds, the deeper the weight ring of the small tiles and the fewer barriers; the chunk
+    // count of the layer must be a multiple
+    constexpr bool small = TM == 1;
+    constexpr int SA = small ? 2 : 1, SR = TN * WN <= 2 ? 8 : TN * WN <= 4 ? 4 : TN * WN <= 6 ? 2 : 1, SU = small ? 4 : TN * WN <= 6 ? 2 : 1, SD = small ? 2 : 1;
+#define DEMON_CASE(NTAPS_, SC_, SPAN_, MODE_, IN_, NB_) \
+    if (in_fmt == IN_) { \
+        hipLaunchKernelGGL((conv_stream_kernel<TM, TN, WM, WN, NTAPS_, SC_, SPAN_, MODE_, IN_, NB_>), grid, dim3(64 * WM * WN), 0, stream, p, sg, emit); \
+        return hipGetLastError(); \
+    }
+    if (mode == MODE_ACT) {
+        const int span = (p.ntaps - 1) * p.tap_step;
+        if (span <= 6) { DEMON_CASE(7, SA, 6, MODE_ACT, OP_BF16, 2) DEMON_CASE(7, SA, 6, MODE_ACT, OP_F16, 2) }
+        else if (span <= 18) { DEMON_CASE(7, SA, 18, MODE_ACT, OP_BF16, 2) DEMON_CASE(7, SA, 18, MODE_ACT, OP_F16, 2) }
+        else { DEMON_CASE(7, SA, MAXSPAN, MODE_ACT, OP_BF16, 2) DEMON_CASE(7, SA, MAXSPAN, MODE_ACT, OP_F16, 2) }
+    } else if (mode == MODE_RES) {
+        if (p.nchunks % SR == 0) { DEMON_CASE(1, SR, 0, MODE_RES, OP_BF16, 2) DEMON_CASE(1, SR, 0, MODE_RES, OP_F16, 2) }
+        else { DEMON_CASE(1, 2, 0, MODE_RES, OP_BF16, 2) DEMON_CASE(1, 2, 0, MODE_RES, OP_F16, 2) }
+        DEMON_CASE(1, 2, 0, MODE_RES, OP_BF16X2, 2)
+    } else if (mode == MODE_DOWN) {
+        if (p.nchunks == 1) { DEMON_CASE(4, 1, 3, MODE_DOWN, OP_BF16, 1) DEMON_CASE(4, 1, 3, MODE_DOWN, OP_F16, 1) }
+        else if (p.nchunks % SD == 0) { DEMON_CASE(4, SD, 3, MODE_DOWN, OP_BF16, 2) DEMON_CASE(4, SD, 3, MODE_DOWN, OP_F16, 2) }
+        else { DEMON_CASE(4, 1, 3, MODE_DOWN, OP_BF16, 2) DEMON_CASE(4, 1, 3, MODE_DOWN, OP_F16, 2) }
+    } else {
+        if (p.nchunks == 1) { DEMON_CASE(2, 1, 1, MODE_UP, OP_BF16, 1) DEMON_CASE(2, 1, 1, MODE_UP, OP_F16, 1) }
+        else if (p.nchunks % SU == 0) { DEMON_CASE(2, SU, 1, MODE_UP, OP_BF16, 2) DEMON_CASE(2, SU, 1, MODE_UP, OP_F16, 2) }
+        else { DEMON_CASE(2, 1, 1, MODE_UP, OP_BF16, 2) DEMON_CASE(2, 1, 1, MODE_UP, OP_F16, 2) }
+        DEMON_CASE(2, 1, 1, MODE_UP, OP_BF16X2, 2)
+    }
+#undef DEMON_CASE
+    return hipErrorInvalidValue;
+}
+
+}  // namespace
+
+bool stream_conv_ok(const MfmaParams& p, int mode, int in_fmt)
+{
+    if (p.cout % 8 != 0) return false;
+    switch (mode) {
+        case MODE_ACT: return p.ntaps == 7 && p.nchunks % 2 == 0 && in_fmt != OP_BF16X2;
+        case MODE_RES: return p.ntaps == 1 && p.nchunks % 2 == 0;
+        case MODE_DOWN: return p.ntaps == 4 && in_fmt != OP_BF16X2;
+        default: return p.ntaps == 2;
+    }
+}
+
+hipError_t launch_conv_stream(MfmaParams p, int mode, int in_fmt, int emit, int rows, long long ncols, int n_slots, long long max_small, hipStream_t stream)
+{
+    if (rows % 128 != 0 || ncols < 1 || !stream_conv_ok(p, mode, in_fmt)) return hipErrorInvalidValue;
+    // Tile of a launch: the cheapest by (workgroups on the busiest of 256 CUs) x (time of one K step of 32, in ns, with one
+    // workgroup on a CU or with several), as measured on the dilated convs of 256 to 1024 channels with 200 to 100000
+    // columns.  A CU takes weights in at some 45 bytes per clock, so small tiles are bound by that and large ones by their
+    // MFMAs.  Launches of more than `max_small` 128 x 128 tiles take that tile without further ado.
+    struct Tile { int mt, nt; double alone, shared; };
+    static const Tile kTiles[6] = {{32, 32, 25, 26}, {64, 64, 57, 70}, {64, 80, 65, 85}, {64, 96, 73, 97}, {128, 64, 90, 122}, {128, 128, 185, 212}};
+    int best = 5;
+    if ((ncols + 127) / 128 * (rows / 128) * n_slots <= max_small) {
+        double least = 0;
+        for (int t = 0; t < 6; ++t) {
+            const long long wgs = (ncols + kTiles[t].nt - 1) / kTiles[t].nt * (rows / kTiles[t].mt) * n_slots;
+            const double cost = wgs <= 256 ? kTiles[t].alone : wgs <= 1024 ? (double)((wgs + 255) / 256) * kTiles[t].shared : (wgs / 256.0 + 0.5) * kTiles[t].shared;
+            if (t == 0 || cost < least) { least = cost; best = t; }
+        }
+    }
+    const int mt = kTiles[best].mt, nt = kTiles[best].nt;
+    StreamGrid sg;
+    const int panels = rows / 128;
+    // split of the 8 XCDs over panels and column tiles with the least to read per XCD
+    const double w = (double)p.w_bytes, x = (double)ncols * n_slots * (mode == MODE_DOWN ? 2 : 1) * p.cin * 2.0;
+    double least = 0;
+    sg.xm = 0;
+    for (int xm = 1; xm <= 8; xm *= 2) {
+        if (panels % xm != 0) continue;
+        const double cost = w / xm + x * xm / 8;
+        if (sg.xm == 0 || cost < least) { sg.xm = xm; least = cost; }
+    }
+    sg.xn = 8 / sg.xm;
+    sg.mper = panels / sg.xm * (128 / mt);
+    const long long ntiles = ((ncols + nt - 1) / nt + sg.xn - 1) / sg.xn * sg.xn;
+    if (ntiles * (rows / mt) > 0x7fffffffll) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)(ntiles * (rows / mt)), (unsigned)n_slots);
+    switch (best) {
+        case 0: return launch_tile<1, 2, 2, 1>(p, sg, mode, in_fmt, emit, grid, stream);
+        case 1: return launch_tile<1, 4, 4, 1>(p, sg, mode, in_fmt, emit, grid, stream);
+        case 2: return launch_tile<1, 5, 4, 1>(p, sg, mode, in_fmt, emit, grid, stream);
+        case 3: return launch_tile<1, 6, 4, 1>(p, sg, mode, in_fmt, emit, grid, stream);
+        case 4: return launch_tile<2, 4, 4, 1>(p, sg, mode, in_fmt, emit, grid, stream);
+        default: return launch_tile<2, 8, 4, 1>(p, sg, mode, in_fmt, emit, grid, stream);
+    }
+}
+
+}  // namespace demon

@@ -86,12 +86,12 @@ __global__ __launch_bounds__(256) void res_unit_wide_kernel(WideParams p)
     const __amdgpu_buffer_rsrc_t rs_w7 = make_rsrc(p.w7, (unsigned)nstages * (W_A_CH * 16u));
     const __amdgpu_buffer_rsrc_t rs_w1 = make_rsrc(p.w1, (unsigned)W_NCHUNKS * (W_A_CH * 16u));
 
-    // Staging pattern.  An LDS row is 80 bytes (20 banks), so the 8 lanes that one cycle of a 16-byte LDS write serves
+    // Staging pattern of the activations.  An LDS row is 80 bytes (20 banks), so the 8 lanes that one cycle of a 16-byte LDS write serves
     // must not hold two neighbouring rows (rows r and r + 1 overlap in 4 banks): lanes 0..3 of each group of 8 take the
     // four pieces of row r, lanes 4..7 those of row r + 4, which starts 16 banks further.  A pass of 256 threads covers
     // 64 rows; srow is the thread's row within a pass.
     const int srow = 8 * (tid >> 5) + ((tid >> 3) & 3) + 4 * ((tid >> 2) & 1);
-    const unsigned a_voff = (unsigned)(srow * SEGS + seg) * 16u;
+    const unsigned a_voff = tid * 16u;
     const unsigned x_voff = ((unsigned)((n0 + minoff + srow) * CH) + seg * 8u) * 2u;     // may wrap "negative": out of range
     constexpr unsigned x_row_step = RPP * CH * 2u;
 
@@ -105,7 +105,7 @@ __global__ __launch_bounds__(256) void res_unit_wide_kernel(WideParams p)
     auto store_set = [&](const u32x4 (&r)[A_ITERS], int buf) __attribute__((always_inline)) {
 #pragma unroll
         for (int it = 0; it < A_ITERS; ++it)
-            *reinterpret_cast<u32x4*>(&As[buf * CH * LDK + (srow + it * RPP) * LDK + seg * 8]) = r[it];
+            *reinterpret_cast<u32x4*>(&As[buf * CH * LDK + frag_row<KC>(tid + it * 256) * LDK + frag_piece<KC>(tid + it * 256) * 8]) = r[it];
     };
     auto load_a = [&](__amdgpu_buffer_rsrc_t rs, int block) __attribute__((always_inline)) { load_set(ra, rs, block); };
     auto store_a = [&](int buf) __attribute__((always_inline)) { store_set(ra, buf); };

@@ -672,11 +672,10 @@ hipError_t launch_gate_slots(const Slot* src, Slot* dst, int n, const int* skip,
 
 // ---------------------------------------------------------------------------------- window table on the device
 // The window grid of section 3.6 written by a kernel: window k of a clip covers frames [begin + k window, ...), is
-// extended by the halo and clamped to the clip; its workspace rows follow those of the windows before it (the windows
-// from `split` on form a second group whose rows count from the group's first).  One thread per window; the prefix
+// extended by the halo and clamped to the clip; its workspace rows follow those of the windows before it.  One thread per window; the prefix
 // sum over the earlier windows of the clip is a short loop (at most 4096 windows per call).
 __global__ __launch_bounds__(256) void plan_slots_kernel(Slot* __restrict__ dst, int n, int per_clip, int clip_frames,
-                                                         int n_frames, int fb, int fe, int window, int halo, int split, int split_row0)
+                                                         int n_frames, int fb, int fe, int window, int halo)
 {
     const int i = blockIdx.x * 256 + threadIdx.x;
     if (i >= n) return;
@@ -696,17 +695,17 @@ __global__ __launch_bounds__(256) void plan_slots_kernel(Slot* __restrict__ dst,
     int lo, hi, b, e;
     extent(k, &lo, &hi, &b, &e);
     Slot s;
-    s.row0 = i >= split ? row - split_row0 : row; s.len = hi - lo; s.clip = clip; s.lo = lo; s.crop = b - lo; s.n_int = e - b; s.begin = b; s.pad = 0;
+    s.row0 = row; s.len = hi - lo; s.clip = clip; s.lo = lo; s.crop = b - lo; s.n_int = e - b; s.begin = b; s.pad = 0;
     dst[i] = s;
 }
 
 hipError_t launch_plan_slots(Slot* dst, int n_clips, int per_clip, int clip_frames, int n_frames, int frame_begin,
-                             int frame_end, int window, int halo, int split, int split_row0, hipStream_t stream)
+                             int frame_end, int window, int halo, hipStream_t stream)
 {
     const long long n = (long long)n_clips * per_clip;
     if (n < 1 || n > 65536) return hipErrorInvalidValue;
     hipLaunchKernelGGL(plan_slots_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream, dst, (int)n, per_clip, clip_frames,
-                       n_frames, frame_begin, frame_end, window, halo, split, split_row0);
+                       n_frames, frame_begin, frame_end, window, halo);
     return hipGetLastError();
 }
 

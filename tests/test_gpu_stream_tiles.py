@@ -1,0 +1,33 @@
+"""The bf16 convolutions that stream their weights: every tile the launch can choose (the choice follows the size of the call
+only), remainders of columns at every tile, both operand formats, one- and two-plane operands, and kernel sizes that take
+the LDS kernel.  Every tile adds in the same order, so a handle restricted to the largest tile gives the same bits."""
+import numpy as np
+import pytest
+
+import demon_inputs as di
+import oracle
+from gpu_util import assert_close, make, to_device
+from paper_2605_28657_amd import DemonVAE
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("spec,T,kw", [
+    (di.DecoderSpec(64, (2,), (512,), (1, 3, 9)), 1, {}),                            # one frame: two columns
+    (di.DecoderSpec(64, (2,), (512,), (1, 3, 9)), 257, {}),                          # 32-row tiles, half operands
+    (di.DecoderSpec(64, (2, 2), (512, 256), (3, 9)), 501, dict(flags=1)),            # 64 x 64 / 80 / 96, unfused 256 channels
+    (di.DecoderSpec(64, (2, 2), (512, 128), (1, 9)), 3001, dict(flags=1)),           # up to the 128 x 128 tile in one call
+    (di.DecoderSpec(64, (2, 2), (512, 128), (9,)), 129, dict(wide_operands=2)),      # hi + lo operand planes
+    (di.DecoderSpec(64, (2, 2), (512, 128), (1, 3), res_kernel=5), 130, dict(flags=1)),      # five taps: the LDS kernel
+])
+def test_stream_tiles(spec, T, kw):
+    vae, w, z = make(spec, "bf16", T, max_extended_frames=T, **kw)
+    large = DemonVAE(spec, w, dtype="bf16", max_frames=T, max_extended_frames=T, small_tile_wgs=-1, **kw)
+    zt = to_device(z, "bf16")
+    full = vae.decode(zt).cpu().numpy()
+    assert np.array_equal(large.decode(zt).cpu().numpy(), full)
+    n = min(T, 300)
+    halo = max(oracle.receptive_field(spec))
+    ref = oracle.decode_windowed(spec, w, z[0], window=n, halo=halo, frame_begin=0, frame_end=n)
+    assert_close(full[0][:, :n * spec.total_stride], ref[:, :n * spec.total_stride], "bf16", str(spec))
+    vae.close(); large.close()
