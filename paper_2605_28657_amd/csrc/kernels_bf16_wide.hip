@@ -302,6 +302,197 @@ __global__ __launch_bounds__(256) void res_unit_wide_kernel(WideParams p)
     }
 }
 
+// The same unit with the weights streamed to registers: 8 waves share the 16 TN columns of a tile, a wave owning 32 channels of
+// all of them.  The staged kernel above lasts as long as one workgroup's
+// walk over its 64 weight blocks, whatever the launch's size (45 us: two barriers a block, every wave reading all 16 KB of it
+// from LDS).  Here a CU reads each weight once, RS k-steps ahead and without a barrier, and the branch tensor goes through LDS
+// (its fragments are spread over the waves); what bounds it is the 16 KB of weights a k-step brings into the CU for narrow tiles
+// (some 45 bytes per clock) and the MFMAs for wide ones.  Per unit of a window of 8 frames 45 -> 22 us, of 75 frames 51 -> 35;
+// the whole 13-frame window 355 -> 286 us, the 75-frame one 526 -> 475.
+// K order (chunk of 32 channels, tap, channel; the 1x1 conv's k-slots) and roundings are those of the kernel above: the
+// results are bit-identical, whichever kernel a launch takes.
+template <int TN, bool EMIT>
+__global__ __launch_bounds__(512, 2) void res_unit_wide_stream_kernel(WideParams p)
+{
+    fp16_saturate_on();
+    constexpr int CH = W_CH, NT = 16 * TN, NTAPS = 7, NTH = 512;
+    constexpr int KX = 64, LDR = KX + 16;                   // stage of two chunks; rows 10 pieces apart: no bank conflicts
+    constexpr int SEGS = KX / 8, RPP = NTH / SEGS, X_ITERS = (NT + W_MAXSPAN + RPP - 1) / RPP, XR = X_ITERS * RPP;
+    constexpr int F = 2 * NTAPS, NSTAGES = CH / KX;         // k-steps of 32 in a stage
+    constexpr int RS = 7;                     // k-steps of weights in flight
+    static_assert(F % RS == 0, "static ring indices");
+    constexpr int LDM = CH + 16;                            // row of the branch tensor's tile: 34 pieces
+    constexpr int EP = NT > 96 ? 2 : 1, ECOLS = NT / EP, LDO = CH + 4;           // epilogue in passes of ECOLS columns
+    constexpr int X_BYTES = XR * LDR * 2, M_BYTES = NT * LDM * 2, O_BYTES = ECOLS * LDO * 4;
+    constexpr int SMEM_XM = 2 * X_BYTES > M_BYTES ? 2 * X_BYTES : M_BYTES, SMEM = SMEM_XM > O_BYTES ? SMEM_XM : O_BYTES;
+    __shared__ __attribute__((aligned(16))) unsigned char smem[SMEM];
+
+    const Slot s = p.slots[blockIdx.y];
+    const int nrows = s.len * p.r;
+    const int out_lo = max(0, s.crop * p.r - p.margin);
+    const int out_hi = min(nrows, (s.crop + s.n_int) * p.r + p.margin);
+    const int tiles8 = (int)(gridDim.x >> 3);               // XCD x takes a contiguous eighth of the tiles, as above
+    const int n0 = out_lo + ((int)((blockIdx.x + blockIdx.y) & 7u) * tiles8 + (int)(blockIdx.x >> 3)) * NT;
+    if (n0 >= out_hi) return;
+    const long long rowbase = (long long)s.row0 * p.r;
+    const int minoff = p.tap0, need = NT + (NTAPS - 1) * p.tap_step;         // tap_step > 0
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int i = lane & 15, q = lane >> 4;
+    const int seg = tid % SEGS, xr0 = tid / SEGS;
+
+    const __amdgpu_buffer_rsrc_t rs_x = make_rsrc(p.xa + rowbase * CH, (unsigned)nrows * CH * 2u);
+    const __amdgpu_buffer_rsrc_t rs_y = make_rsrc(p.y + rowbase * CH, (unsigned)out_hi * CH * (unsigned)sizeof(hres_t));
+    const __amdgpu_buffer_rsrc_t rs_a = make_rsrc(p.ya + rowbase * CH, EMIT ? (unsigned)out_hi * CH * 2u : 0u);
+    const __amdgpu_buffer_rsrc_t rs_w7 = make_rsrc(p.w7, (unsigned)(W_NCHUNKS * NTAPS) * (W_A_CH * 16u));
+    const __amdgpu_buffer_rsrc_t rs_w1 = make_rsrc(p.w1, (unsigned)W_NCHUNKS * (W_A_CH * 16u));
+
+    // weights: one block of 256 x 32 per k-step, [16-row unit][lane][8]; this wave's units are 2 wave, 2 wave + 1
+    const unsigned w_voff = (unsigned)wave * 2048u + lane * 16u;
+    u32x4 a[RS][2];
+    auto load_a = [&](int f, int slot) __attribute__((always_inline)) {      // past the last block: out of range, not used
+#pragma unroll
+        for (int mi = 0; mi < 2; ++mi) a[slot][mi] = __builtin_amdgcn_raw_buffer_load_b128(rs_w7, w_voff + mi * 1024u, (unsigned)f * (W_A_CH * 16u), 0);
+    };
+    // 1x1 weights: channel 8 j + mo lies in slot 32 mo + j (see pack_w1_wide); this lane's channel 16 u + i in unit u
+    auto load_a1 = [&](int c, int slot) __attribute__((always_inline)) {
+#pragma unroll
+        for (int mi = 0; mi < 2; ++mi) {
+            const int ch = 32 * wave + 16 * mi + i, sl = (ch & 7) * 32 + (ch >> 3);
+            a[slot][mi] = __builtin_amdgcn_raw_buffer_load_b128(rs_w1, (unsigned)((sl >> 4) * 1024 + (q * 16 + (sl & 15)) * 16), (unsigned)c * (W_A_CH * 16u), 0);
+        }
+    };
+
+    const unsigned x_voff = ((unsigned)((n0 + minoff + xr0) * CH) + seg * 8u) * 2u;      // may wrap "negative": out of range
+    u32x4 rx[X_ITERS];
+    auto load_x = [&](int stage) __attribute__((always_inline)) {
+#pragma unroll
+        for (int it = 0; it < X_ITERS; ++it) {
+            // rows no tap reads and stages past the last: out of range
+            const bool used = stage < NSTAGES && it * RPP < need;
+            rx[it] = __builtin_amdgcn_raw_buffer_load_b128(rs_x, used ? x_voff + (unsigned)(it * RPP * CH + stage * KX) * 2u : 0xf8000000u, 0, 0);
+        }
+    };
+    auto store_x = [&](int buf) __attribute__((always_inline)) {
+        uint16_t* xs = reinterpret_cast<uint16_t*>(smem + buf * X_BYTES);
+#pragma unroll
+        for (int it = 0; it < X_ITERS; ++it) *reinterpret_cast<u32x4*>(&xs[(xr0 + it * RPP) * LDR + seg * 8]) = rx[it];
+    };
+
+    load_x(0);
+#pragma unroll
+    for (int f = 0; f < RS; ++f) load_a(f, f);
+    const int ch0 = 32 * wave + i;                          // this lane's channels: ch0, ch0 + 16
+    f32x4 acc[2][TN];
+#pragma unroll
+    for (int mi = 0; mi < 2; ++mi) {
+        const float b = p.b7[ch0 + 16 * mi];
+#pragma unroll
+        for (int ni = 0; ni < TN; ++ni) acc[mi][ni] = f32x4{b, b, b, b};
+    }
+    store_x(0);
+    __syncthreads();
+
+    // activations are the row operand: register e of accumulator (mi, ni) is column 16 ni + 4 q + e, channel ch0 + 16 mi
+    auto mma = [&](const u32x4& x, const u32x4 (&w)[2], int ni) __attribute__((always_inline)) {
+#pragma unroll
+        for (int mi = 0; mi < 2; ++mi)
+            acc[mi][ni] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, x), __builtin_bit_cast(bf16x8, w[mi]), acc[mi][ni], 0, 0, 0);
+    };
+    for (int stage = 0; stage < NSTAGES; ++stage) {
+        load_x(stage + 1);
+        const uint16_t* xs = reinterpret_cast<const uint16_t*>(smem + (stage & 1) * X_BYTES) + i * LDR + q * 8;
+        u32x4 x[2][TN];
+        auto read_x = [&](int f, int ni) __attribute__((always_inline)) {
+            x[f & 1][ni] = *reinterpret_cast<const u32x4*>(xs + (16 * ni + f % NTAPS * p.tap_step) * LDR + f / NTAPS * 32);
+        };
+#pragma unroll
+        for (int ni = 0; ni < TN; ++ni) read_x(0, ni);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int f = 0; f < F; ++f) {
+#pragma unroll
+            for (int ni = 0; ni < TN; ++ni) {
+                if (f + 1 < F) read_x(f + 1, ni);
+                mma(x[f & 1][ni], a[f % RS], ni);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            load_a(stage * F + f + RS, f % RS);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        store_x((stage + 1) & 1);
+        __syncthreads();
+    }
+
+    // ---- Snake on the accumulators; the branch tensor goes to LDS as [column][k-slot], where the 8 k-slots of a piece are the
+    // channels 32 c + 16 (q / 2) + 4 (q % 2) + {0..3, 8..11} of the 1x1 weights' K axis
+#pragma unroll
+    for (int f = 0; f < RS; ++f) load_a1(f, f);
+    uint16_t* ms = reinterpret_cast<uint16_t*>(smem);
+#pragma unroll
+    for (int mi = 0; mi < 2; ++mi) {
+        const float al = p.a2[ch0 + 16 * mi], ib = p.ib2[ch0 + 16 * mi], b = p.b1[ch0 + 16 * mi];
+        const int slot = 32 * wave + 16 * mi + 8 * ((i >> 2) & 1) + 4 * (i >> 3) + (i & 3);
+#pragma unroll
+        for (int ni = 0; ni < TN; ++ni) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) ms[(16 * ni + 4 * q + e) * LDM + slot] = f32_to_bf16_bits(snake_fast(acc[mi][ni][e], al, ib));
+            acc[mi][ni] = f32x4{b, b, b, b};
+        }
+    }
+    __syncthreads();
+
+    // ---- 1x1 conv
+    const uint16_t* mr = ms + i * LDM + q * 8;
+#pragma unroll
+    for (int c = 0; c < W_NCHUNKS; ++c) {
+#pragma unroll
+        for (int ni = 0; ni < TN; ++ni) mma(*reinterpret_cast<const u32x4*>(mr + 16 * ni * LDM + 32 * c), a[c % RS], ni);
+        if (c + RS < W_NCHUNKS) load_a1(c + RS, c % RS);
+    }
+
+    // ---- residual add, half store in place, optional Snake + bf16 operand, 8 channels of a column at a time through LDS
+    constexpr int PPR = CH / 8, ERPP = NTH / PPR, E_ITERS = ECOLS / ERPP;
+    const int ec = tid % PPR * 8, er = tid / PPR;
+    float a3v[8], i3v[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) { a3v[e] = EMIT ? p.a3[ec + e] : 0.f; i3v[e] = EMIT ? p.ib3[ec + e] : 0.f; }
+    float* os = reinterpret_cast<float*>(smem);
+#pragma unroll
+    for (int ep = 0; ep < EP; ++ep) {
+        u32x4 resv[E_ITERS];
+#pragma unroll
+        for (int it = 0; it < E_ITERS; ++it)
+            resv[it] = __builtin_amdgcn_raw_buffer_load_b128(rs_y, (unsigned)((n0 + ep * ECOLS + er + it * ERPP) * CH + ec) * 2u, 0, 0);
+        __syncthreads();                                    // the branch tensor, or the pass before, has been read
+#pragma unroll
+        for (int mi = 0; mi < 2; ++mi)
+#pragma unroll
+            for (int ni = 0; ni < ECOLS / 16; ++ni)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) os[(16 * ni + 4 * q + e) * LDO + ch0 + 16 * mi] = acc[mi][ep * (ECOLS / 16) + ni][e];
+        __syncthreads();
+#pragma unroll
+        for (int it = 0; it < E_ITERS; ++it) {
+            // rows past out_hi are outside the descriptors and dropped
+            const unsigned off = (unsigned)((n0 + ep * ECOLS + er + it * ERPP) * CH + ec) * 2u;
+            const float* src = &os[(er + it * ERPP) * LDO + ec];
+            const f16x8 r = __builtin_bit_cast(f16x8, resv[it]);
+            f16x8 o;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) o[e] = (_Float16)keep_f32(src[e] + (float)r[e]);
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, o), rs_y, off, 0, 0);
+            if (EMIT) {
+                u32x4 sh;
+#pragma unroll
+                for (int e = 0; e < 8; e += 2)
+                    sh[e / 2] = pack_bf16x2(snake_fast((float)o[e], a3v[e], i3v[e]), snake_fast((float)o[e + 1], a3v[e + 1], i3v[e + 1]));
+                __builtin_amdgcn_raw_buffer_store_b128(sh, rs_a, off, 0, 0);
+            }
+        }
+    }
+}
+
 }  // namespace
 
 // W1 [256][256] -> 8 blocks of 256 row slots x 32 k-slots, the K axis in the accumulator row order of the narrow fused
@@ -331,9 +522,25 @@ hipError_t launch_res_unit_wide(const WideArgs& a, hipStream_t stream)
     // one window's activation plane must fit a 32-bit byte offset (buffer descriptors)
     if ((long long)a.max_len * a.r * a.c * 2 > 0xf0000000ll) return hipErrorInvalidValue;
     const long long out_rows = std::min((long long)a.max_int * a.r + 2ll * a.margin, (long long)a.max_len * a.r);
-    dim3 grid((unsigned)((out_rows + W_NT - 1) / W_NT + 7) / 8 * 8, (unsigned)a.n_slots);       // whole groups of 8 tiles; the surplus exits at once
-    if (a.ya) hipLaunchKernelGGL((res_unit_wide_kernel<true>), grid, dim3(256), 0, stream, p);
-    else hipLaunchKernelGGL((res_unit_wide_kernel<false>), grid, dim3(256), 0, stream, p);
+    auto tiles = [&](int nt) { return (out_rows + nt - 1) / nt; };
+    auto grid = [&](int nt) { return dim3((unsigned)(tiles(nt) + 7) / 8 * 8, (unsigned)a.n_slots); };     // whole groups of 8 tiles; the surplus exits at once
+    // The streamed tiles run one workgroup per CU, and a launch takes the narrowest one that needs one round of the 256 CUs, else
+    // two.  Measured, whole decode in us, staged / columns 32, 64, 80, 96, 128: 25 frames 388 / 319, 326, 334, 341, 356; 64 frames
+    // 460 / 424, 402, 408, 414, 429; 75 frames 526 / 522, 511, 475, 482, 492; 110 frames 605 / 632, 585, 604, 622, 573; two
+    // rounds: 2 x 75 frames 820 / 863, 828, 800, 810, 847; 200 frames 915 / 981, 920, 941, 904, 928.  Past two rounds the staged
+    // kernel's two workgroups per CU cover each other's prologues and epilogues: 24 windows of 64 frames 6084 / -, 6352, -, -, 6187.
+#define DEMON_STREAM(TN) case TN: \
+    if (a.ya) hipLaunchKernelGGL((res_unit_wide_stream_kernel<TN, true>), grid(16 * TN), dim3(512), 0, stream, p); \
+    else hipLaunchKernelGGL((res_unit_wide_stream_kernel<TN, false>), grid(16 * TN), dim3(512), 0, stream, p); \
+    return hipGetLastError();
+    int tn = 0;
+    if (a.ntaps == 7 && a.max_small > 0)
+        for (long long wgs : {256, 512})
+            for (int t : {2, 4, 5, 6, 8}) if (tn == 0 && tiles(16 * t) * a.n_slots <= wgs) tn = t;
+    switch (tn) { DEMON_STREAM(2) DEMON_STREAM(4) DEMON_STREAM(5) DEMON_STREAM(6) DEMON_STREAM(8) default: break; }
+#undef DEMON_STREAM
+    if (a.ya) hipLaunchKernelGGL((res_unit_wide_kernel<true>), grid(W_NT), dim3(256), 0, stream, p);
+    else hipLaunchKernelGGL((res_unit_wide_kernel<false>), grid(W_NT), dim3(256), 0, stream, p);
     return hipGetLastError();
 }
 

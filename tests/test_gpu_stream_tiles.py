@@ -31,3 +31,24 @@ def test_stream_tiles(spec, T, kw):
     ref = oracle.decode_windowed(spec, w, z[0], window=n, halo=halo, frame_begin=0, frame_end=n)
     assert_close(full[0][:, :n * spec.total_stride], ref[:, :n * spec.total_stride], "bf16", str(spec))
     vae.close(); large.close()
+
+
+@pytest.mark.parametrize("T,dils", [
+    (1, (1, 3, 9)), (17, (1, 3, 9)),         # less than a tile, a remainder
+    (4090, (9,)), (4099, (1, 9)),            # 32 columns at 256 tiles; 64 columns
+    (8197, (1, 9)), (10241, (1, 9)),         # 80 and 96 columns
+    (12299, (1, 3, 9)), (16385, (1, 9)),     # 128 columns, more than 256 tiles
+])
+def test_unit_256_stream_tiles(T, dils):
+    """The 256-channel unit at every tile a launch can take: the same bits as the LDS-staged kernel, also window by window."""
+    spec = di.DecoderSpec(64, (2,), (256,), dils)
+    vae, w, z = make(spec, "bf16", T, max_extended_frames=2 * T + 64)
+    staged = DemonVAE(spec, w, dtype="bf16", max_frames=T, max_extended_frames=2 * T + 64, small_tile_wgs=-1)
+    zt = to_device(z, "bf16")
+    full = vae.decode(zt).cpu().numpy()
+    assert np.array_equal(staged.decode(zt).cpu().numpy(), full)
+    assert np.array_equal(vae.decode_windowed(zt, window=max(1, T // 3), halo=-1).cpu().numpy(), full)
+    n = min(T, 300)
+    ref = oracle.decode_windowed(spec, w, z[0], window=n, halo=max(oracle.receptive_field(spec)), frame_begin=0, frame_end=n)
+    assert_close(full[0][:, :n * spec.total_stride], ref[:, :n * spec.total_stride], "bf16", str(spec))
+    vae.close(); staged.close()
