@@ -54,6 +54,11 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base, un
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, (int)bytes, 0x00020000);
 }
 
+// Index of a weight block to request ahead, held inside the layer's n blocks: past the end the last block is requested again and
+// not used.  Block indices go into a load's scalar offset, which the range check does not cover -- it compares the per-lane
+// offset with (bytes - scalar offset) -- so a request past the end may not be left to the descriptor.
+__device__ __forceinline__ int block_in(int i, int n) { return min(i, n - 1); }
+
 // Residual stream h of the bf16 path in HBM: IEEE half.  bf16 storage of h (one rounding of 2^-9 per layer, at
 // full strength on the main path) would by itself exceed the error budget; half has 3 more mantissa bits, its
 // roundings are an order of magnitude below those of the bf16 MFMA operands, and it halves the traffic of the

@@ -261,7 +261,7 @@ __global__ __launch_bounds__(64 * WM * WN) void conv_mfma_kernel(MfmaParams p)
     u32x4 rx[X_ITERS][NP];
 
     auto load_a = [&](int stage) __attribute__((always_inline)) {
-        const unsigned base = w_tile0 + (unsigned)stage * (A_CH * 16u);
+        const unsigned base = w_tile0 + (unsigned)block_in(stage, nstages) * (A_CH * 16u);
 #pragma unroll
         for (int it = 0; it < A_ITERS; ++it)
             if (A_CH % NTH == 0 || tid + it * NTH < A_CH)
@@ -392,8 +392,8 @@ __global__ __launch_bounds__(64 * WM * WN) void conv_mfma_kernel(MfmaParams p)
         __builtin_amdgcn_s_setprio(0);
     };
     // One weight block in flight is enough where three workgroups share the CU and cover each other's loads (two blocks: the
-    // same step time, 16 more registers).  The request is unconditional -- past the last stage it reads another row tile's
-    // block or nothing -- because behind a branch the compiler cannot count it.
+    // same step time, 16 more registers).  The request is unconditional -- past the last stage it reads the last block
+    // again -- because behind a branch the compiler cannot count it.
     for (int stage = 0; stage < nstages; ++stage) {
         int ntap = tap + 1, nchunk = chunk;
         if (ntap == p.ntaps) { ntap = 0; ++nchunk; }

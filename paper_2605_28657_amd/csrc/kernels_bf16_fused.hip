@@ -148,7 +148,7 @@ __global__ __launch_bounds__(256, (CH == 128 && TN == 2) ? 2 : 3) void res_unit_
     float al[8], ib[8];
 
     auto load_a = [&](int stage) __attribute__((always_inline)) {
-        const unsigned base = (unsigned)stage * (A_CH * 16u);
+        const unsigned base = (unsigned)block_in(stage, nstages) * (A_CH * 16u);
 #pragma unroll
         for (int it = 0; it < A_ITERS; ++it) ra[it] = __builtin_amdgcn_raw_buffer_load_b128(rs_w, a_voff, base + it * 4096u, 0);
     };

@@ -96,8 +96,7 @@ __global__ __launch_bounds__(64 * WM * WN) void conv_stream_kernel(MfmaParams p,
     const unsigned w_tile = (unsigned)panel * (unsigned)nblocks * 16384u;
     u32x4 a[RS][TM];
     auto load_a = [&](int stage, int f) __attribute__((always_inline)) {     // f may run past the stage
-        // past the last stage: another panel's block or out of range; not used
-        const unsigned blk = w_tile + (unsigned)(stage * (F / 2) + f / 2) * 16384u;
+        const unsigned blk = w_tile + (unsigned)block_in(stage * (F / 2) + f / 2, nblocks) * 16384u;
 #pragma unroll
         for (int mi = 0; mi < TM; ++mi) a[f % RS][mi] = __builtin_amdgcn_raw_buffer_load_b128(rs_w, w_voff + ((mi & 1) * 2 + (mi >> 1)) * 2048u + (f & 1) * 1024u, blk, 0);
     };

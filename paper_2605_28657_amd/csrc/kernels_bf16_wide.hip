@@ -97,8 +97,8 @@ __global__ __launch_bounds__(256) void res_unit_wide_kernel(WideParams p)
 
     u32x4 ra[A_ITERS], rb[A_ITERS];     // rb: second set, only for the blocks of the 1x1 weights (requested two ahead)
     u32x4 rx[X_ITERS];
-    auto load_set = [&](u32x4 (&r)[A_ITERS], __amdgpu_buffer_rsrc_t rs, int block) __attribute__((always_inline)) {
-        const unsigned base = (unsigned)block * (W_A_CH * 16u);
+    auto load_set = [&](u32x4 (&r)[A_ITERS], __amdgpu_buffer_rsrc_t rs, int block, int nblocks) __attribute__((always_inline)) {
+        const unsigned base = (unsigned)block_in(block, nblocks) * (W_A_CH * 16u);
 #pragma unroll
         for (int it = 0; it < A_ITERS; ++it) r[it] = __builtin_amdgcn_raw_buffer_load_b128(rs, a_voff, base + it * 4096u, 0);
     };
@@ -107,7 +107,6 @@ __global__ __launch_bounds__(256) void res_unit_wide_kernel(WideParams p)
         for (int it = 0; it < A_ITERS; ++it)
             *reinterpret_cast<u32x4*>(&As[buf * CH * LDK + frag_row<KC>(tid + it * 256) * LDK + frag_piece<KC>(tid + it * 256) * 8]) = r[it];
     };
-    auto load_a = [&](__amdgpu_buffer_rsrc_t rs, int block) __attribute__((always_inline)) { load_set(ra, rs, block); };
     auto store_a = [&](int buf) __attribute__((always_inline)) { store_set(ra, buf); };
     auto load_x = [&](int chunk) __attribute__((always_inline)) {
         const unsigned coff = x_voff + (unsigned)(chunk * KC) * 2u;
@@ -128,7 +127,7 @@ __global__ __launch_bounds__(256) void res_unit_wide_kernel(WideParams p)
     };
 
     // every request of the prologue is issued before the first result is waited for, in the order of use
-    load_a(rs_w7, 0);
+    load_set(ra, rs_w7, 0, nstages);
     load_x(0);
     constexpr int PRM_ITERS = 4 * CH / 256;
     float pv[PRM_ITERS];
@@ -192,13 +191,13 @@ __global__ __launch_bounds__(256) void res_unit_wide_kernel(WideParams p)
     // Weight blocks are requested two stages ahead, alternating between the two register sets (the second set is otherwise
     // only used by the 1x1 convolution): with one workgroup per CU (a single playback window) nothing else hides the
     // latency of a block's load, and one stage of MFMAs is shorter than it.  The request is unconditional (past the last
-    // block it is out of the descriptor's range and reads nothing): behind a branch the compiler could not count it, and the
-    // wait for the older block would wait for it as well.
+    // block it reads that block again): behind a branch the compiler could not count it, and the wait for the older block
+    // would wait for it as well.
     auto iter = [&](int stage, u32x4 (&rload)[A_ITERS], const u32x4 (&rstore)[A_ITERS]) __attribute__((always_inline)) {
         int ntap = tap + 1, nchunk = chunk;
         if (ntap == p.ntaps) { ntap = 0; ++nchunk; }
         const bool new_chunk = nchunk != chunk;
-        load_set(rload, rs_w7, stage + 2);
+        load_set(rload, rs_w7, stage + 2, nstages);
         if (new_chunk) load_x(nchunk);
         mma_stage(stage);
         if (new_chunk) {
@@ -209,12 +208,12 @@ __global__ __launch_bounds__(256) void res_unit_wide_kernel(WideParams p)
         __syncthreads();
         tap = ntap; chunk = nchunk;
     };
-    load_set(rb, rs_w7, 1);
+    load_set(rb, rs_w7, 1, nstages);
     for (int stage = 0; stage + 1 < nstages; stage += 2) {
         iter(stage, ra, rb);
         if (stage + 2 < nstages) iter(stage + 1, rb, ra);
     }
-    load_a(rs_w1, 0);
+    load_set(ra, rs_w1, 0, W_NCHUNKS);
     mma_stage(nstages - 1);
 
     // ---- Snake on the accumulators; repack them as the B fragments of the 1x1 conv (k step kk = 2 mi + g/2)
@@ -236,8 +235,8 @@ __global__ __launch_bounds__(256) void res_unit_wide_kernel(WideParams p)
     // the epilogue are requested in the second half of the loop, where the fragments already used have freed registers.
     __syncthreads();                                   // all waves are done with the last stage's operands
     store_a(0);
-    load_set(ra, rs_w1, 1);
-    load_set(rb, rs_w1, 2);
+    load_set(ra, rs_w1, 1, W_NCHUNKS);
+    load_set(rb, rs_w1, 2, W_NCHUNKS);
     // accumulator tile mo of the 1x1 conv: [time row 8g + 4h + q][channel slot j] = channel 8 j + mo; starts at its bias
 #pragma unroll
     for (int mo = 0; mo < TM; ++mo) {
@@ -263,7 +262,7 @@ __global__ __launch_bounds__(256) void res_unit_wide_kernel(WideParams p)
         if (c + 1 < W_NCHUNKS) {
             if ((c + 1) & 1) store_set(ra, (c + 1) & 1); else store_set(rb, (c + 1) & 1);
             __syncthreads();
-            if (c + 3 < W_NCHUNKS) { if ((c + 3) & 1) load_set(ra, rs_w1, c + 3); else load_set(rb, rs_w1, c + 3); }
+            if (c + 3 < W_NCHUNKS) { if ((c + 3) & 1) load_set(ra, rs_w1, c + 3, W_NCHUNKS); else load_set(rb, rs_w1, c + 3, W_NCHUNKS); }
         }
         if (c >= W_NCHUNKS / 2) {                      // chunks 4..7 request four time rows each
 #pragma unroll
@@ -350,16 +349,18 @@ __global__ __launch_bounds__(512, 2) void res_unit_wide_stream_kernel(WideParams
     // weights: one block of 256 x 32 per k-step, [16-row unit][lane][8]; this wave's units are 2 wave, 2 wave + 1
     const unsigned w_voff = (unsigned)wave * 2048u + lane * 16u;
     u32x4 a[RS][2];
-    auto load_a = [&](int f, int slot) __attribute__((always_inline)) {      // past the last block: out of range, not used
+    auto load_a = [&](int f, int slot) __attribute__((always_inline)) {
+        const unsigned blk = (unsigned)block_in(f, W_NCHUNKS * NTAPS) * (W_A_CH * 16u);
 #pragma unroll
-        for (int mi = 0; mi < 2; ++mi) a[slot][mi] = __builtin_amdgcn_raw_buffer_load_b128(rs_w7, w_voff + mi * 1024u, (unsigned)f * (W_A_CH * 16u), 0);
+        for (int mi = 0; mi < 2; ++mi) a[slot][mi] = __builtin_amdgcn_raw_buffer_load_b128(rs_w7, w_voff + mi * 1024u, blk, 0);
     };
     // 1x1 weights: channel 8 j + mo lies in slot 32 mo + j (see pack_w1_wide); this lane's channel 16 u + i in unit u
     auto load_a1 = [&](int c, int slot) __attribute__((always_inline)) {
+        const unsigned blk = (unsigned)block_in(c, W_NCHUNKS) * (W_A_CH * 16u);
 #pragma unroll
         for (int mi = 0; mi < 2; ++mi) {
             const int ch = 32 * wave + 16 * mi + i, sl = (ch & 7) * 32 + (ch >> 3);
-            a[slot][mi] = __builtin_amdgcn_raw_buffer_load_b128(rs_w1, (unsigned)((sl >> 4) * 1024 + (q * 16 + (sl & 15)) * 16), (unsigned)c * (W_A_CH * 16u), 0);
+            a[slot][mi] = __builtin_amdgcn_raw_buffer_load_b128(rs_w1, (unsigned)((sl >> 4) * 1024 + (q * 16 + (sl & 15)) * 16), blk, 0);
         }
     };
 

@@ -112,11 +112,11 @@ __global__ __launch_bounds__(256) void conv_f32_mfma_kernel(ConvArgs a, int nchu
 
     u32x4 wr[PF][TM][2];
     auto load_w = [&](u32x4 (&r)[TM][2], int stage) __attribute__((always_inline)) {
-        // past the last stage another tile's block (or nothing) is read and not used
+        const unsigned blk = (unsigned)block_in(stage, nstages) * 2048u;
 #pragma unroll
         for (int mi = 0; mi < TM; ++mi)
 #pragma unroll
-            for (int g = 0; g < 2; ++g) r[mi][g] = __builtin_amdgcn_raw_buffer_load_b128(rs_w, w_off[mi], (unsigned)stage * 2048u + g * 1024u, 0);
+            for (int g = 0; g < 2; ++g) r[mi][g] = __builtin_amdgcn_raw_buffer_load_b128(rs_w, w_off[mi], blk + g * 1024u, 0);
     };
     auto fetch = [&](int chunk, int row) __attribute__((always_inline)) -> float4 {
         const long long n = row0 + row;
