@@ -20,10 +20,10 @@
  * used by one host thread at a time, and its decode calls must go to one
  * stream (or be ordered by the caller): they share the handle's workspace.
  * Decode calls are asynchronous on the given HIP stream and allocate nothing.
- * With two or more windows the bf16 path runs half of the windows on a second,
- * internal stream that it forks from and joins back into the given stream
- * within the call, so the call is ordered on the given stream like any other
- * work and can be captured into a graph.
+ * Calls of two or more windows and some hundred frames run, on the bf16 path,
+ * half of the windows on a second, internal stream that is forked from and
+ * joined back into the given stream within the call, so the call is ordered on
+ * the given stream like any other work and can be captured into a graph.
  * A window grid (clips, frames, range, window, halo) seen for the first time has its table written by a small
  * kernel on the same stream; the 16 most recent grids are kept.  A call recorded into a HIP graph pins its grid's
  * entry for the life of the handle (the graph holds the table's address), so at most 16 different grids can be
@@ -34,6 +34,7 @@
  * process (read once when the library is loaded):
  *   DEMON_VAE_WIDE_OPERANDS=bf16x2  default of wide_operands becomes 2
  *   DEMON_VAE_NO_FUSED=1            as if DEMON_VAE_FLAG_NO_FUSED were set in every config
+ *   DEMON_VAE_ONE_STREAM=1          as if DEMON_VAE_FLAG_ONE_STREAM were set in every config
  *   DEMON_VAE_SMALL_TILE_WGS=n      default of small_tile_wgs becomes n (0 = never)
  */
 #ifndef DEMON_VAE_H
@@ -73,7 +74,7 @@ typedef enum {
 
 /* demon_vae_config.flags */
 #define DEMON_VAE_FLAG_NO_FUSED   1   /* every residual unit as two kernels (no fused units)          */
-#define DEMON_VAE_FLAG_ONE_STREAM 2   /* accepted, without effect: all launches are on the given stream */
+#define DEMON_VAE_FLAG_ONE_STREAM 2   /* no internal second stream: all launches on the given stream  */
 #define DEMON_VAE_FLAG_NO_WIDE_TILE 4 /* accepted, without effect: the 128 x 256 tile it switched off is gone */
 #define DEMON_VAE_FLAG_NO_HEAD_FUSION 8 /* the head always runs as its own kernel (bit-identical results) */
 

@@ -33,6 +33,7 @@ const int g_env_wide_fmt = [] {
     return (e && strcmp(e, "bf16x2") == 0) ? (int)OP_BF16X2 : (int)OP_F16;
 }();
 const bool g_env_no_fused = getenv("DEMON_VAE_NO_FUSED") != nullptr;
+const bool g_env_one_stream = getenv("DEMON_VAE_ONE_STREAM") != nullptr;
 const long long g_env_small_tile_wgs = [] {
     const char* e = getenv("DEMON_VAE_SMALL_TILE_WGS");
     return e ? atoll(e) : 1024ll;
@@ -64,6 +65,9 @@ struct Plan {
     int n_clips = 0, n_frames = 0, frame_begin = 0, frame_end = 0, window = 0, halo = 0;
     int n_slots = 0, max_len = 0, max_int = 0;
     long long total_frames = 0;
+    // where a call that runs as two groups of windows is cut: the window whose first extended frame is nearest to half of all
+    int split = 0;
+    long long split_frame0 = 0;
     Slot* d_slots = nullptr;
     unsigned long long last_use = 0;
     // A call on this grid was recorded into a HIP graph: the graph holds the address of this entry's table (and the
@@ -118,6 +122,7 @@ struct demon_vae {
     long long per_frame = 0;           // largest rate x width of a layer: elements of one latent frame at its widest
     int rf_left = 0, rf_right = 0;
     int device = 0;
+    bool has_staged_convs = false;     // bf16 path: some convolution outside the fused units takes an LDS-staged tile
     bool has_split_operands = false;   // bf16 path: some layer carries its operand as hi + lo planes
     long long small_tile_wgs = 1024;   // bf16 path: launches of more 128 x 128 tiles than this take that tile
     bool head_fusable = false;         // bf16 path: the last layer is a fused 64-channel unit that can run the head in its kernel
@@ -142,6 +147,8 @@ struct demon_vae {
     Workspace ws;
     unsigned char* scratch = nullptr;              // this device's copy of the static scratch array
     Slot* d_slot_arena = nullptr;
+    hipStream_t stream2 = nullptr;                 // second lane of the bf16 layer sequence (default priority, non-blocking)
+    hipEvent_t ev_fork = nullptr, ev_join = nullptr;
     Plan plans[kPlanCache];
     unsigned long long use_counter = 0;
 
@@ -244,6 +251,22 @@ demon_status check_plane(const demon_vae* v, int max_len)
     return DEMON_OK;
 }
 
+// Whether the layer sequence of a call runs as two groups of windows on two streams: the ramp and tail of one group's launches
+// (a last round of workgroups that fills a fraction of the CUs, prologues, epilogues) overlap with the other's.  Both take the
+// tiles that the whole call would take.  One / two groups in us on the x1920 stack, windows of 64 frames: 250 frames (286
+// extended) 1180 / 1191, 310 frames 1483 / 1462, 600 frames 2603 / 2438, 1500 frames 6102 / 5994, four clips of 1500 frames
+// 23.83 / 23.72 ms.  Calls that fit one or two rounds of the chip lose by the split, hence the bound: five windows of 50 frames
+// (298 extended) 1182 / 1305, three of 75 frames 1117 / 1228, two of 32 frames 429 / 489.  LDS-staged convolutions have longer
+// tails (a stack of 960 to 64 channels): two windows of 40 frames (104 extended) 1046 / 1080, two of 60 (144) 1245 / 1222, 220 frames
+// 1935 / 1782.
+// One group for a gated call, which may turn out to be launches only, and where a mode wants one ordered launch sequence
+// (per-launch timing, debug tap).
+bool two_groups(const demon_vae* v, const Plan* p, bool gated)
+{
+    return p->split > 0 && p->total_frames >= (v->has_staged_convs ? 150 : 320) && !gated && v->stream2 && v->timing < 2 &&
+           !(v->tap_layer >= 0 && v->tap_dst);
+}
+
 // Looks the window grid up in the plan cache; on a miss the table of the least recently used entry that no graph holds is
 // rewritten by a small kernel on the decode stream, so the call stays asynchronous (kernels of earlier calls that still
 // read the replaced table precede that kernel on the stream) and can itself be recorded into a graph.
@@ -293,6 +316,15 @@ demon_status get_plan(demon_vae* v, int n_clips, int n_frames, int fb, int fe, i
     victim->window = window; victim->halo = halo;
     victim->n_slots = (int)n_slots; victim->max_len = gc.max_len; victim->max_int = gc.max_int;
     victim->total_frames = total; victim->d_slots = d; victim->last_use = v->use_counter;
+    victim->split = 0; victim->split_frame0 = 0;
+    long long best = -1, row = 0, i = 0;
+    for (int c = 0; c < n_clips; ++c)
+        for (long long b = fb; b < fe; b += window, ++i) {
+            const long long e = std::min<long long>(b + window, fe);
+            const long long d = std::abs(total - 2 * row);
+            if (i >= 1 && (best < 0 || d < best)) { best = d; victim->split = (int)i; victim->split_frame0 = row; }
+            row += std::min<long long>(n_frames, e + halo) - std::max<long long>(0, b - halo);
+        }
     *out = victim;
     return DEMON_OK;
 }
@@ -325,10 +357,31 @@ demon_status run_pass(demon_vae* v, const Workspace& ws, const Plan* plan, const
         slots = ws.slot_gated;
     }
 
+    // the launches address a group of windows (gs, gn) on a stream gst: all windows on the caller's stream, or two
+    // groups of consecutive windows on two streams (see the bf16 path below)
+    const int n_groups = two_groups(v, plan, io.d_skip != nullptr) ? 2 : 1;
+    const Slot* gs = slots;
+    int gn = ns;
+    long long frame0 = 0;
+    hipStream_t gst = stream;
+    bool marks_on = true;
+    auto select_group = [&](int which, hipStream_t on) {
+        gs = slots + (which ? plan->split : 0);
+        gn = n_groups == 1 ? ns : which ? ns - plan->split : plan->split;
+        frame0 = which ? plan->split_frame0 : 0;
+        gst = on;
+    };
+    // The groups can be at different layers at the same time, and the bytes a window occupies depend on the layer's rate x
+    // width: in every activation buffer of the bf16 path the second group owns what lies from frame0 x (largest rate x width)
+    // on.  `at` is the base from which the rows of the window table, which count from the first window, fall into it.
+    auto at = [&](const void* buf, int rate, int width) -> uint16_t* {
+        return buf ? (uint16_t*)const_cast<void*>(buf) + (size_t)frame0 * (size_t)(v->per_frame - (long long)rate * width) : nullptr;
+    };
+
     v->n_marks = 0;
     const int ring_base = (v->timed_calls % kTimingRing) * v->marks_per_call;
     auto mark = [&](int level) -> hipError_t {
-        if (v->timing < level || v->n_marks >= v->marks_per_call) return hipSuccess;
+        if (!marks_on || v->timing < level || v->n_marks >= v->marks_per_call) return hipSuccess;
         return hipEventRecord(v->events[ring_base + v->n_marks++], stream);
     };
     // level 1 marks: start, after gather (stem), after the last convolution, after head (sampling step), after stitch.
@@ -347,19 +400,20 @@ demon_status run_pass(demon_vae* v, const Workspace& ws, const Plan* plan, const
         const size_t want = (size_t)plan->total_frames * r * c;
         return launch_to_f32(x, v->tap_dst, std::min(want, v->tap_cap), bf ? 2 : 0, stream);
     };
+    // samples per frame after a layer
+    auto resampled = [](int rate, const ConvLayer& L) { return L.down > 0 ? rate / L.down : L.stride > 0 ? rate * L.stride : rate; };
     auto conv_args = [&](const ConvLayer& L, const void* x, void* y, const void* res) {
         ConvArgs a;
-        a.x = x; a.y = y; a.res = res; a.w = L.w; a.bias = L.bias;
+        const int ro = resampled(r, L);
+        a.x = at(x, r, L.cin); a.y = at(y, ro, L.cout); a.res = at(res, ro, L.cout); a.w = L.w; a.bias = L.bias;
         a.out_alpha = L.out_alpha; a.out_inv_beta = L.out_inv_beta;
-        a.slots = slots; a.n_slots = ns; a.max_len = ml; a.max_int = plan->max_int; a.margin = L.margin; a.r_in = r;
+        a.slots = gs; a.n_slots = gn; a.call_slots = ns; a.max_len = ml; a.max_int = plan->max_int; a.margin = L.margin; a.r_in = r;
         a.cin = L.cin; a.cout = L.cout; a.ntaps = L.ntaps; a.dil = L.dil; a.stride = L.stride; a.down = L.down;
         a.in_fmt = L.in_fmt;
         a.in_lo_off = a.out_lo_off = lo_off;
         a.small_tile_wgs = v->small_tile_wgs;
         return a;
     };
-    // samples per frame after a resampling layer
-    auto resampled = [](int rate, const ConvLayer& L) { return L.down > 0 ? rate / L.down : rate * L.stride; };
 
     if (!bf) {
         // ---- fp32 path.  Three buffers in rotation: `cur` holds the residual stream h, `act` the activated operand of the
@@ -409,17 +463,25 @@ demon_status run_pass(demon_vae* v, const Workspace& ws, const Plan* plan, const
         uint16_t* acur = (uint16_t*)ws.buf[3];
         uint16_t* aoth = (uint16_t*)ws.buf[4];
         uint16_t* mid = (uint16_t*)ws.buf[2];
-        if (enc) {
-            const ConvLayer* C = v->first_consumer;
-            HIP_TRY(launch_stem(io.d_wave, ws.buf[0], true, C ? ws.buf[3] : nullptr, C ? C->in_fmt : 0, v->stem_w, v->stem_bias,
-                                C ? C->in_alpha : nullptr, C ? C->in_inv_beta : nullptr, v->st.out_channels, v->stem_cout,
-                                v->st.head_kernel, S, n_frames, v->stem_margin, slots, ns, ml, plan->max_int, stream), "stem");
-        } else {
-            const ConvLayer& U0 = *v->first_consumer;
-            HIP_TRY(launch_gather(io.d_latent, nullptr, v->st.c0, n_frames, true, slots, ns, ml, stream, (uint16_t*)ws.buf[3],
-                                  U0.in_fmt, lo_off, U0.in_alpha, U0.in_inv_beta), "gather");
+        for (int gi = 0; gi < n_groups; ++gi) {
+            select_group(gi, stream);
+            if (enc) {
+                const ConvLayer* C = v->first_consumer;
+                HIP_TRY(launch_stem(io.d_wave, at(ws.buf[0], S, v->stem_cout), true, C ? at(ws.buf[3], S, v->stem_cout) : nullptr,
+                                    C ? C->in_fmt : 0, v->stem_w, v->stem_bias, C ? C->in_alpha : nullptr, C ? C->in_inv_beta : nullptr,
+                                    v->st.out_channels, v->stem_cout, v->st.head_kernel, S, n_frames, v->stem_margin, gs, gn, ml,
+                                    plan->max_int, stream), "stem");
+            } else {
+                const ConvLayer& U0 = *v->first_consumer;
+                HIP_TRY(launch_gather(io.d_latent, nullptr, v->st.c0, n_frames, true, gs, gn, ml, stream, at(ws.buf[3], 1, v->st.c0),
+                                      U0.in_fmt, lo_off, U0.in_alpha, U0.in_inv_beta), "gather");
+            }
         }
         HIP_TRY(mark(1), "event");
+        auto layers = [&]() -> demon_status {
+        cur = ws.buf[0]; other = ws.buf[1];
+        acur = (uint16_t*)ws.buf[3]; aoth = (uint16_t*)ws.buf[4];
+        r = enc ? S : 1; layer_id = 0;
         for (size_t si = 0; si < n_steps; ++si) {
             const Step& T = v->steps[si];
             const bool last = si + 1 == n_steps;
@@ -428,8 +490,8 @@ demon_status run_pass(demon_vae* v, const Workspace& ws, const Plan* plan, const
             const ConvLayer* C = T.consumer;
             if (T.conv) {
                 ConvArgs a = conv_args(*T.conv, acur, other, nullptr);
-                if (C) { a.ya = aoth; a.out_alpha = C->in_alpha; a.out_inv_beta = C->in_inv_beta; a.out_fmt = C->in_fmt; }
-                HIP_TRY(launch_conv_bf16(a, T.conv->variant, stream), "resampling convolution");
+                if (C) { a.ya = at(aoth, resampled(r, *T.conv), T.conv->cout); a.out_alpha = C->in_alpha; a.out_inv_beta = C->in_inv_beta; a.out_fmt = C->in_fmt; }
+                HIP_TRY(launch_conv_bf16(a, T.conv->variant, gst), "resampling convolution");
                 if (C) std::swap(acur, aoth);
                 HIP_TRY(mark(last ? 1 : 2), "event");
                 std::swap(cur, other);
@@ -440,13 +502,13 @@ demon_status run_pass(demon_vae* v, const Workspace& ws, const Plan* plan, const
             const ResUnit& U = *T.unit;
             if (U.fused) {
                 FusedArgs f;
-                f.x = cur; f.y = other;
-                if (C) { f.ya = acur; f.a3 = C->in_alpha; f.ib3 = C->in_inv_beta; }
+                f.x = at(cur, r, U.dilated.cin); f.y = at(other, r, U.dilated.cin);
+                if (C) { f.ya = at(acur, r, U.dilated.cin); f.a3 = C->in_alpha; f.ib3 = C->in_inv_beta; }
                 f.w7 = (const uint16_t*)U.dilated.w; f.w1 = U.w1_fused;
                 f.b7 = U.dilated.bias; f.b1 = U.pointwise.bias;
                 f.a1 = U.dilated.in_alpha; f.ib1 = U.dilated.in_inv_beta;
                 f.a2 = U.dilated.out_alpha; f.ib2 = U.dilated.out_inv_beta;
-                f.slots = slots; f.n_slots = ns; f.max_len = ml; f.max_int = plan->max_int; f.margin = U.pointwise.margin;
+                f.slots = gs; f.n_slots = gn; f.max_len = ml; f.max_int = plan->max_int; f.margin = U.pointwise.margin;
                 f.r = r; f.c = U.dilated.cin; f.ntaps = U.dilated.ntaps; f.dil = U.dilated.dil;
                 if (C && C->in_fmt != OP_BF16) return fail(DEMON_ERR_UNSUPPORTED, "a fused unit cannot feed a layer with wide operands");
                 if (last && head_in_unit) {
@@ -454,52 +516,80 @@ demon_status run_pass(demon_vae* v, const Workspace& ws, const Plan* plan, const
                     f.hy = ws.head_out; f.total_rows = plan->total_frames * r;
                     f.oc = v->st.out_channels; f.hk = v->st.head_kernel;
                 }
-                HIP_TRY(launch_res_unit_fused(f, stream), "fused residual unit");
+                HIP_TRY(launch_res_unit_fused(f, gst), "fused residual unit");
                 std::swap(cur, other);
                 HIP_TRY(mark(2), "event");
             } else if (U.wide) {
                 WideArgs f;
-                f.xa = acur; f.y = cur;
-                if (C) { f.ya = aoth; f.a3 = C->in_alpha; f.ib3 = C->in_inv_beta; }
+                f.xa = at(acur, r, U.dilated.cin); f.y = at(cur, r, U.dilated.cin);
+                if (C) { f.ya = at(aoth, r, U.dilated.cin); f.a3 = C->in_alpha; f.ib3 = C->in_inv_beta; }
                 f.w7 = (const uint16_t*)U.dilated.w; f.w1 = U.w1_fused;
                 f.b7 = U.dilated.bias; f.b1 = U.pointwise.bias;
                 f.a2 = U.dilated.out_alpha; f.ib2 = U.dilated.out_inv_beta;
-                f.slots = slots; f.n_slots = ns; f.max_len = ml; f.max_int = plan->max_int; f.margin = U.pointwise.margin;
+                f.slots = gs; f.n_slots = gn; f.call_slots = ns; f.max_len = ml; f.max_int = plan->max_int; f.margin = U.pointwise.margin;
                 f.r = r; f.c = U.dilated.cin; f.ntaps = U.dilated.ntaps; f.dil = U.dilated.dil;
                 if (C && C->in_fmt != OP_BF16) return fail(DEMON_ERR_UNSUPPORTED, "a fused unit cannot feed a layer with wide operands");
                 f.max_small = v->small_tile_wgs;
-                HIP_TRY(launch_res_unit_wide(f, stream), "fused residual unit (256 channels)");
+                HIP_TRY(launch_res_unit_wide(f, gst), "fused residual unit (256 channels)");
                 if (C) std::swap(acur, aoth);
                 HIP_TRY(mark(2), "event");
             } else {
                 ConvArgs d = conv_args(U.dilated, acur, nullptr, nullptr);
-                d.ya = mid; d.out_fmt = U.pointwise.in_fmt;   // Snake between the convolutions: the layer's own out_alpha
-                HIP_TRY(launch_conv_bf16(d, U.dilated.variant, stream), "dilated convolution");
+                d.ya = at(mid, r, U.dilated.cout); d.out_fmt = U.pointwise.in_fmt;   // Snake between the convolutions: the layer's own out_alpha
+                HIP_TRY(launch_conv_bf16(d, U.dilated.variant, gst), "dilated convolution");
                 HIP_TRY(mark(2), "event");
                 ConvArgs q = conv_args(U.pointwise, mid, cur, cur);   // in place on the residual stream
-                if (C) { q.ya = acur; q.out_alpha = C->in_alpha; q.out_inv_beta = C->in_inv_beta; q.out_fmt = C->in_fmt; }
-                HIP_TRY(launch_conv_bf16(q, U.pointwise.variant, stream), "pointwise convolution");
+                if (C) { q.ya = at(acur, r, U.pointwise.cout); q.out_alpha = C->in_alpha; q.out_inv_beta = C->in_inv_beta; q.out_fmt = C->in_fmt; }
+                HIP_TRY(launch_conv_bf16(q, U.pointwise.variant, gst), "pointwise convolution");
             }
             HIP_TRY(mark(last ? 1 : 2), "event");
             HIP_TRY(tap(cur, U.pointwise.cout), "debug tap");
         }
+        return DEMON_OK;
+        };
+        if (n_groups == 2) {
+            marks_on = false;
+            HIP_TRY(hipEventRecord(v->ev_fork, stream), "event");
+            HIP_TRY(hipStreamWaitEvent(v->stream2, v->ev_fork, 0), "hipStreamWaitEvent");
+        }
+        demon_status lrc = DEMON_OK;
+        for (int gi = 0; gi < n_groups && lrc == DEMON_OK; ++gi) {
+            select_group(gi, gi == 1 ? v->stream2 : stream);
+            lrc = layers();
+        }
+        if (n_groups == 2) {
+            // also after a failed launch: the second stream joins the caller's again (an open capture stays well-formed)
+            const hipError_t e1 = hipEventRecord(v->ev_join, v->stream2);
+            const hipError_t e2 = e1 == hipSuccess ? hipStreamWaitEvent(stream, v->ev_join, 0) : e1;
+            if (lrc != DEMON_OK) return lrc;
+            HIP_TRY(e2, "joining the second stream");
+            marks_on = true;
+            HIP_TRY(mark(1), "event");                       // after the last convolution
+        }
+        if (lrc != DEMON_OK) return lrc;
     }
     if (enc) {
         // sampling step on the moments, trim and scatter into the caller's [clip, channel, frame] arrays
-        HIP_TRY(launch_sample(cur, bf, io.d_eps, io.d_moments, io.d_zout, bf, v->st.c0, n_frames, slots, ns, plan->max_int, stream), "sampling step");
+        for (int gi = 0; gi < n_groups; ++gi) {
+            select_group(gi, stream);
+            HIP_TRY(launch_sample(at(cur, r, 2 * v->st.c0), bf, io.d_eps, io.d_moments, io.d_zout, bf, v->st.c0, n_frames, gs, gn,
+                                  plan->max_int, stream), "sampling step");
+        }
         HIP_TRY(mark(1), "event");
         if (v->timing > 0) ++v->timed_calls;
         return DEMON_OK;
     }
-    // head and stitch; the window waveforms are planar [channel][all rows]
+    // head (group by group on the caller's stream) and stitch; the window waveforms are planar [channel][all rows]
     const long long total_rows = plan->total_frames * r;
-    if (!head_in_unit) {
+    for (int gi = 0; gi < n_groups && !head_in_unit; ++gi) {
+        select_group(gi, stream);
+        const void* x = at(cur, r, v->head_cin);
         if (v->head_wfrag)
-            HIP_TRY(launch_head_mfma(cur, ws.head_out, v->head_wfrag, v->head_bias, v->head_alpha, v->head_inv_beta, v->head_cin,
-                                     v->st.out_channels, v->st.head_kernel, r, total_rows, slots, ns, ml, plan->max_int, stream), "head");
+            HIP_TRY(launch_head_mfma(x, ws.head_out, v->head_wfrag, v->head_bias, v->head_alpha, v->head_inv_beta, v->head_cin,
+                                     v->st.out_channels, v->st.head_kernel, r, total_rows, gs, gn, ml, plan->max_int, stream), "head");
         else
-            HIP_TRY(launch_head(cur, bf, ws.head_out, v->head_w, v->head_bias, v->head_alpha, v->head_inv_beta, v->head_cin,
-                                v->st.out_channels, v->st.head_kernel, r, total_rows, bf, slots, ns, plan->max_int, stream), "head");
+            HIP_TRY(launch_head(x, bf, ws.head_out, v->head_w, v->head_bias, v->head_alpha, v->head_inv_beta, v->head_cin,
+                                v->st.out_channels, v->st.head_kernel, r, total_rows, bf, gs, gn, plan->max_int, stream), "head");
     }
     HIP_TRY(mark(1), "event");
     if (io.d_pcm)
@@ -531,6 +621,7 @@ demon_status create_impl(const demon_vae_config* cfg, const float* host_weights,
     // 0 in a field = the default, which the environment may have changed (see the header)
     const int g_wide_fmt = cfg->wide_operands == 1 ? (int)OP_F16 : cfg->wide_operands == 2 ? (int)OP_BF16X2 : g_env_wide_fmt;
     const bool g_allow_fused = !((cfg->flags & DEMON_VAE_FLAG_NO_FUSED) || g_env_no_fused);
+    const bool g_dual_stream = !((cfg->flags & DEMON_VAE_FLAG_ONE_STREAM) || g_env_one_stream);
     if (bf) {
         if (st.c0 % 16) return fail(DEMON_ERR_UNSUPPORTED, "bf16 path: latent_channels %d is not a multiple of 16", st.c0);
         for (int c : st.widths)
@@ -772,6 +863,9 @@ demon_status create_impl(const demon_vae_config* cfg, const float* host_weights,
         if (v->ws.head_out) (void)hipFree(v->ws.head_out);
         if (v->d_slot_arena) (void)hipFree(v->d_slot_arena);
         if (v->ws.slot_gated) (void)hipFree(v->ws.slot_gated);
+        if (v->ev_fork) (void)hipEventDestroy(v->ev_fork);
+        if (v->ev_join) (void)hipEventDestroy(v->ev_join);
+        if (v->stream2) (void)hipStreamDestroy(v->stream2);
     };
     hipError_t e = hipMalloc(&v->d_params, ar.bytes.size());
     // fp32 path: 4 bytes per element; bf16 path: half residual stream (2 bytes), bf16 operand buffers with hi and lo planes (4)
@@ -779,6 +873,11 @@ demon_status create_impl(const demon_vae_config* cfg, const float* host_weights,
     if (e == hipSuccess) e = hipMalloc((void**)&v->ws.head_out, head_bytes);
     if (e == hipSuccess) e = hipMalloc((void**)&v->d_slot_arena, sizeof(Slot) * kMaxSlots * kPlanCache);
     if (e == hipSuccess) e = hipMalloc((void**)&v->ws.slot_gated, sizeof(Slot) * kMaxSlots);
+    if (e == hipSuccess && bf && g_dual_stream) {
+        e = hipStreamCreateWithFlags(&v->stream2, hipStreamNonBlocking);
+        if (e == hipSuccess) e = hipEventCreateWithFlags(&v->ev_fork, hipEventDisableTiming);
+        if (e == hipSuccess) e = hipEventCreateWithFlags(&v->ev_join, hipEventDisableTiming);
+    }
     if (e == hipSuccess) e = hipMemcpy(v->d_params, ar.bytes.data(), ar.bytes.size(), hipMemcpyHostToDevice);
     if (e != hipSuccess) { cleanup(); return hip_fail(e, "allocating device memory"); }
 
@@ -814,6 +913,10 @@ demon_status create_impl(const demon_vae_config* cfg, const float* host_weights,
     };
     for (size_t i = 0; i + 1 < v->steps.size(); ++i) v->steps[i].consumer = operand_layer(v->steps[i + 1]);
     v->first_consumer = operand_layer(v->steps[0]);
+    for (const Step& s : v->steps) {
+        const ConvLayer& L = s.conv ? *s.conv : s.unit->dilated;
+        if (bf && L.generic && (L.variant != 0 || (s.unit && L.ntaps != 7))) v->has_staged_convs = true;
+    }
     // the head can run inside the last residual unit's kernel when that unit is the fused 64-channel form
     if (!encoder && head_mfma && !(cfg->flags & DEMON_VAE_FLAG_NO_HEAD_FUSION) && !v->steps.empty()) {
         const Step& last = v->steps.back();
@@ -848,6 +951,9 @@ void demon_vae_destroy(demon_vae* v)
     (void)hipFree(v->d_slot_arena);
     (void)hipFree(v->ws.slot_gated);
     for (hipEvent_t e : v->events) (void)hipEventDestroy(e);
+    if (v->ev_fork) (void)hipEventDestroy(v->ev_fork);
+    if (v->ev_join) (void)hipEventDestroy(v->ev_join);
+    if (v->stream2) (void)hipStreamDestroy(v->stream2);
     delete v;
 }
 

@@ -35,7 +35,7 @@ struct MfmaParams {
 // other kernels; launches of more than `max_small` 128 x 128 tiles do not look for a smaller tile.
 // stream_conv_ok: whether it has a kernel for the call.
 bool stream_conv_ok(const MfmaParams& p, int mode, int in_fmt);
-hipError_t launch_conv_stream(MfmaParams p, int mode, int in_fmt, int emit, int rows, long long ncols, int n_slots, long long max_small,
+hipError_t launch_conv_stream(MfmaParams p, int mode, int in_fmt, int emit, int rows, long long ncols, int n_slots, int call_slots, long long max_small,
                               hipStream_t stream);
 
 }  // namespace demon

@@ -65,6 +65,7 @@ struct ConvArgs {
     const float* out_alpha;  const float* out_inv_beta;   // Snake applied before writing ya, or nullptr
     const Slot* slots;    // device
     int n_slots;
+    int call_slots;       // windows of the whole call: its launches run beside those of the other group, see two_groups in api.hip
     int max_len;          // longest slot (frames)
     int max_int;          // longest interior (frames)
     int margin;           // rows of the OUTPUT level beyond each window's interior that later layers still
@@ -132,7 +133,7 @@ struct WideArgs {
     const uint16_t* w7;      // packed as pack_bf16 does for variant 3 (MT = 256, KC = 32)
     const uint16_t* w1;      // packed by pack_w1_wide
     const float* b7; const float* b1; const float* a2; const float* ib2;
-    const Slot* slots; int n_slots, max_len, max_int, margin;
+    const Slot* slots; int n_slots, call_slots, max_len, max_int, margin;
     int r, c, ntaps, dil;
     long long max_small = 0;           // 0: the LDS-staged kernel always (small_tile_wgs of the config)
 };

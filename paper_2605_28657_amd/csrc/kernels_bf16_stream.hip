@@ -335,7 +335,7 @@ bool stream_conv_ok(const MfmaParams& p, int mode, int in_fmt)
     }
 }
 
-hipError_t launch_conv_stream(MfmaParams p, int mode, int in_fmt, int emit, int rows, long long ncols, int n_slots, long long max_small, hipStream_t stream)
+hipError_t launch_conv_stream(MfmaParams p, int mode, int in_fmt, int emit, int rows, long long ncols, int n_slots, int call_slots, long long max_small, hipStream_t stream)
 {
     if (rows % 128 != 0 || ncols < 1 || !stream_conv_ok(p, mode, in_fmt)) return hipErrorInvalidValue;
     // Tile of a launch: the cheapest by (workgroups on the busiest of 256 CUs) x (time of one K step of 32, in ns, with one
@@ -345,10 +345,10 @@ hipError_t launch_conv_stream(MfmaParams p, int mode, int in_fmt, int emit, int 
     struct Tile { int mt, nt; double alone, shared; };
     static const Tile kTiles[6] = {{32, 32, 25, 26}, {64, 64, 57, 70}, {64, 80, 65, 85}, {64, 96, 73, 97}, {128, 64, 90, 122}, {128, 128, 185, 212}};
     int best = 5;
-    if ((ncols + 127) / 128 * (rows / 128) * n_slots <= max_small) {
+    if ((ncols + 127) / 128 * (rows / 128) * call_slots <= max_small) {
         double least = 0;
         for (int t = 0; t < 6; ++t) {
-            const long long wgs = (ncols + kTiles[t].nt - 1) / kTiles[t].nt * (rows / kTiles[t].mt) * n_slots;
+            const long long wgs = (ncols + kTiles[t].nt - 1) / kTiles[t].nt * (rows / kTiles[t].mt) * call_slots;
             const double cost = wgs <= 256 ? kTiles[t].alone : wgs <= 1024 ? (double)((wgs + 255) / 256) * kTiles[t].shared : (wgs / 256.0 + 0.5) * kTiles[t].shared;
             if (t == 0 || cost < least) { least = cost; best = t; }
         }
