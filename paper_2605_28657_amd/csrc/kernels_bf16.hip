@@ -552,11 +552,7 @@ hipError_t launch_conv_bf16(const ConvArgs& a, int variant, hipStream_t stream)
     //  * W larger, more than 8 row tiles: ids run over row tiles first, so XCD x owns the row tiles = x mod 8 (an
     //    eighth of W, resident) and reads all activations: about 8 X + W.
     //  * else column tiles fastest (blockIdx.x): workgroups in flight share one row tile of the weights: mtiles X + W.
-    // Two operand planes cost the 16 x 16 x 32 form of the streamed kernel twice the MFMAs (half its K slots are zero), which shows
-    // once a launch fills the chip: streamed against staged, whole decodes in us, 60 s clip 7749 / 6635, 130 frames 751 / 869.
-    // Such launches of more than one 128 x 128 tile per CU take the staged tile.
-    const bool staged = a.in_fmt == OP_BF16X2 && (ncols + 127) / 128 * (M / 128) * a.call_slots > 256;
-    if (variant == 0 && !staged && stream_conv_ok(p, mode, a.in_fmt))
+    if (variant == 0 && stream_conv_ok(p, mode, a.in_fmt))
         return launch_conv_stream(p, mode, a.in_fmt, emit, M, ncols, a.n_slots, a.call_slots, a.small_tile_wgs, stream);
     const long long ntiles = (ncols + v.NT - 1) / v.NT;
     const int mtiles = M / v.MT;

@@ -191,24 +191,18 @@ __global__ __launch_bounds__(64 * WM * WN) void conv_stream_kernel(MfmaParams p,
 #pragma unroll
         for (int f = 0; f < F; ++f) {
 #pragma unroll
-            for (int ni = 0; ni < TN; ++ni) {
-                if (f + AHEAD < F) read_x(f + AHEAD, ni);
-                // activations are the row operand: the accumulator tile is [time][GEMM row].  Two operand planes alternate per 16
-                // K values (hi, then lo: the order of the 32 x 32 x 16 form): the other half of the step's K slots are zero.
+            for (int t = 0; t < NP * TN; ++t) {
+                const int pl = t / TN, ni = t % TN;
+                if (pl == 0 && f + AHEAD < F) read_x(f + AHEAD, ni);
+                // activations are the row operand: the accumulator tile is [time][GEMM row].  Two operand planes: the step's hi
+                // values of every column tile, then its lo values, against the same weights.
 #pragma unroll
                 for (int mi = 0; mi < TM; ++mi) {
                     const u32x4 w = a[f % RS][mi];
-                    if constexpr (NP == 2) {
-                        const u32x4 z = {0, 0, 0, 0};
-#pragma unroll
-                        for (int k = 0; k < 4; ++k) {
-                            const u32x4 xv = (q >> 1) == (k >> 1) ? x[f % XD][ni][k & 1] : z;
-                            acc[mi][ni] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, xv), __builtin_bit_cast(bf16x8, w), acc[mi][ni], 0, 0, 0);
-                        }
-                    } else if (IN == OP_F16)
-                        acc[mi][ni] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, x[f % XD][ni][0]), __builtin_bit_cast(f16x8, w), acc[mi][ni], 0, 0, 0);
+                    if (IN == OP_F16)
+                        acc[mi][ni] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, x[f % XD][ni][pl]), __builtin_bit_cast(f16x8, w), acc[mi][ni], 0, 0, 0);
                     else
-                        acc[mi][ni] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, x[f % XD][ni][0]), __builtin_bit_cast(bf16x8, w), acc[mi][ni], 0, 0, 0);
+                        acc[mi][ni] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, x[f % XD][ni][pl]), __builtin_bit_cast(bf16x8, w), acc[mi][ni], 0, 0, 0);
                 }
                 __builtin_amdgcn_sched_barrier(0);
             }
@@ -290,6 +284,10 @@ __global__ __launch_bounds__(64 * WM * WN) void conv_stream_kernel(MfmaParams p,
 template <int TM, int TN, int WM, int WN>
 hipError_t launch_tile(const MfmaParams& p, const StreamGrid& sg, int mode, int in_fmt, int emit, dim3 grid, hipStream_t stream)
 {
+    // Two operand planes (hi + lo) are two MFMAs per k-step against one set of weights, as in the LDS-staged kernel, and twice the
+    // LDS per stage.  Whole decodes in us, before (planes alternating per 16 K values, half of every MFMA's K slots zero, with
+    // the LDS-staged tile from 256 tiles on) and after: 75 frames 566 -> 511, 250 frames 1231 -> 1204, 750 frames 3249 -> 3225, 1500
+    // frames 6410 -> 6439.
     // SC: the more k-steps a stage holds, the deeper the weight ring of the small tiles and the fewer barriers; the chunk
     // count of the layer must be a multiple
     constexpr bool small = TM == 1;
@@ -307,7 +305,9 @@ hipError_t launch_tile(const MfmaParams& p, const StreamGrid& sg, int mode, int 
     } else if (mode == MODE_RES) {
         if (p.nchunks % SR == 0) { DEMON_CASE(1, SR, 0, MODE_RES, OP_BF16, 2) DEMON_CASE(1, SR, 0, MODE_RES, OP_F16, 2) }
         else { DEMON_CASE(1, 2, 0, MODE_RES, OP_BF16, 2) DEMON_CASE(1, 2, 0, MODE_RES, OP_F16, 2) }
-        DEMON_CASE(1, 2, 0, MODE_RES, OP_BF16X2, 2)
+        constexpr int SX = SR >= 4 ? SR / 2 : 1;            // two planes: half the chunks in the same LDS
+        if (p.nchunks % SX == 0) { DEMON_CASE(1, SX, 0, MODE_RES, OP_BF16X2, 2) }
+        DEMON_CASE(1, 1, 0, MODE_RES, OP_BF16X2, 2)
     } else if (mode == MODE_DOWN) {
         if (p.nchunks == 1) { DEMON_CASE(4, 1, 3, MODE_DOWN, OP_BF16, 1) DEMON_CASE(4, 1, 3, MODE_DOWN, OP_F16, 1) }
         else if (p.nchunks % SD == 0) { DEMON_CASE(4, SD, 3, MODE_DOWN, OP_BF16, 2) DEMON_CASE(4, SD, 3, MODE_DOWN, OP_F16, 2) }
@@ -316,6 +316,7 @@ hipError_t launch_tile(const MfmaParams& p, const StreamGrid& sg, int mode, int 
         if (p.nchunks == 1) { DEMON_CASE(2, 1, 1, MODE_UP, OP_BF16, 1) DEMON_CASE(2, 1, 1, MODE_UP, OP_F16, 1) }
         else if (p.nchunks % SU == 0) { DEMON_CASE(2, SU, 1, MODE_UP, OP_BF16, 2) DEMON_CASE(2, SU, 1, MODE_UP, OP_F16, 2) }
         else { DEMON_CASE(2, 1, 1, MODE_UP, OP_BF16, 2) DEMON_CASE(2, 1, 1, MODE_UP, OP_F16, 2) }
+        if (p.nchunks % 2 == 0) { DEMON_CASE(2, small ? 2 : 1, 1, MODE_UP, OP_BF16X2, 2) }
         DEMON_CASE(2, 1, 1, MODE_UP, OP_BF16X2, 2)
     }
 #undef DEMON_CASE

@@ -3,6 +3,7 @@ only), remainders of columns at every tile, both operand formats, one- and two-p
 the LDS kernel.  Every tile adds in the same order, so a handle restricted to the largest tile gives the same bits."""
 import numpy as np
 import pytest
+import torch
 
 import demon_inputs as di
 import oracle
@@ -52,3 +53,17 @@ def test_unit_256_stream_tiles(T, dils):
     ref = oracle.decode_windowed(spec, w, z[0], window=n, halo=max(oracle.receptive_field(spec)), frame_begin=0, frame_end=n)
     assert_close(full[0][:, :n * spec.total_stride], ref[:, :n * spec.total_stride], "bf16", str(spec))
     vae.close(); staged.close()
+
+
+def test_two_planes_give_the_same_bits_at_every_size_of_call():
+    """Two operand planes: a clip whose 1x1 and transposed convolutions take the largest tile, and windows of it that take the
+    smallest; a value may not depend on which."""
+    spec, T = di.DecoderSpec(64, (2, 2), (512, 512), (9,)), 4300
+    vae, w, z = make(spec, "bf16", T, max_extended_frames=T + 200, wide_operands=2)
+    zt = to_device(z, "bf16")
+    full = vae.decode(zt)
+    S = spec.total_stride
+    for begin, n in ((0, 7), (2000, 61), (3900, 400)):
+        out = vae.decode_windowed(zt, window=n, halo=-1, frame_begin=begin, frame_end=begin + n)
+        assert torch.equal(out[:, :, begin * S:(begin + n) * S], full[:, :, begin * S:(begin + n) * S]), (begin, n)
+    vae.close()
