@@ -915,7 +915,7 @@ demon_status create_impl(const demon_vae_config* cfg, const float* host_weights,
     v->first_consumer = operand_layer(v->steps[0]);
     for (const Step& s : v->steps) {
         const ConvLayer& L = s.conv ? *s.conv : s.unit->dilated;
-        if (bf && L.generic && (L.variant != 0 || (s.unit && L.ntaps != 7))) v->has_staged_convs = true;
+        if (bf && L.generic && L.variant != 0) v->has_staged_convs = true;
     }
     // the head can run inside the last residual unit's kernel when that unit is the fused 64-channel form
     if (!encoder && head_mfma && !(cfg->flags & DEMON_VAE_FLAG_NO_HEAD_FUSION) && !v->steps.empty()) {

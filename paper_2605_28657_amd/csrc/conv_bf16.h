@@ -1,5 +1,6 @@
-// Parameters and modes shared by the implicit-GEMM convolution kernels of the bf16 path (kernels_bf16.hip: tiles staged
-// through LDS for shapes that kernels_bf16_stream.hip, which streams the weights to registers, turns away).
+// Parameters and modes shared by the implicit-GEMM convolution kernels of the bf16 path: kernels_bf16_stream.hip, which streams
+// the weights to registers, for layers of whole 128-row panels and 64-channel chunks (variant 0), kernels_bf16.hip, which stages
+// them through LDS, for the others.
 #pragma once
 
 #include "device_common.h"
@@ -32,9 +33,8 @@ struct MfmaParams {
 
 // kernels_bf16_stream.hip: weights streamed to registers, on weights packed for the 128 x 128 tile (variant 0).  `rows` is the
 // GEMM's M, `ncols` the most columns a window needs, `mode`, `in_fmt` and `emit` as the template arguments of the
-// other kernels; launches of more than `max_small` 128 x 128 tiles do not look for a smaller tile.
-// stream_conv_ok: whether it has a kernel for the call.
-bool stream_conv_ok(const MfmaParams& p, int mode, int in_fmt);
+// other kernels; `call_slots` the windows of the whole call, `n_slots` those of this launch; launches of more than `max_small`
+// 128 x 128 tiles do not look for a smaller tile.
 hipError_t launch_conv_stream(MfmaParams p, int mode, int in_fmt, int emit, int rows, long long ncols, int n_slots, int call_slots, long long max_small,
                               hipStream_t stream);
 

@@ -192,13 +192,7 @@ __global__ __launch_bounds__(64 * WM * WN) void conv_mfma_kernel(MfmaParams p)
     static_assert(MODE != MODE_ACT || EMIT > 0, "the dilated conv only has the activated output");
     static_assert(MODE != MODE_DOWN || IN != OP_BF16X2, "the strided conv takes one operand plane");
 
-    // Three workgroups per CU hide each other's barriers and load latencies markedly better than two (-10 to -28 % per
-    // launch), and the 128 x 128 tile gets there with one weight buffer in LDS instead of two (46 KB with the dilated
-    // conv's activation tile; the next blocks wait in registers and are stored between two barriers) and with the
-    // residual values requested after the K loop instead of before it.
-    constexpr int NBUF = (MT == 128) ? 1 : 2;
-    constexpr bool LATE_RES = MT == 128;
-    constexpr int AS_BYTES = NBUF * MT * LDK * 2, XS_BYTES = NP * XR_MAX * LDK * 2;
+    constexpr int AS_BYTES = 2 * MT * LDK * 2, XS_BYTES = NP * XR_MAX * LDK * 2;
     constexpr int SMEM_BYTES = AS_BYTES + XS_BYTES;
     __shared__ __attribute__((aligned(16))) unsigned char smem[SMEM_BYTES];
     uint16_t (*As)[MT * LDK] = reinterpret_cast<uint16_t (*)[MT * LDK]>(smem);
@@ -326,9 +320,9 @@ __global__ __launch_bounds__(64 * WM * WN) void conv_mfma_kernel(MfmaParams p)
     const unsigned out_rows = (unsigned)out_hi;
     const __amdgpu_buffer_rsrc_t rs_y = make_rsrc(MODE == MODE_ACT ? nullptr : p.y + rowbase_o * p.cout,
                                                   MODE == MODE_ACT ? 0u : out_rows * p.cout * (unsigned)sizeof(hres_t));
-    // The residual values this lane will add are requested in one go, before the K loop or (LATE_RES) right after it:
-    // issued in the epilogue where they are used, each of the loads would be waited for in turn (they cannot move
-    // above the in-place stores), a chain of memory latencies per tile.
+    // The residual values this lane will add are requested in one go, before the K loop: issued in the epilogue where they
+    // are used, each of the loads would be waited for in turn (they cannot move above the in-place stores), a chain of
+    // memory latencies per tile.
     using pack_t = std::conditional_t<PW == 2, uint32_t, uint16_t>;     // PW 16-bit values
     pack_t resv[MODE == MODE_RES ? TN : 1][16];
     auto load_res = [&]() __attribute__((always_inline)) {
@@ -340,7 +334,7 @@ __global__ __launch_bounds__(64 * WM * WN) void conv_mfma_kernel(MfmaParams p)
                 else resv[ni][gq] = __builtin_amdgcn_raw_buffer_load_b16(rs_y, elem(ni, gq) * 2u, 0, 0);
             }
     };
-    if (MODE == MODE_RES && !LATE_RES) load_res();
+    if (MODE == MODE_RES) load_res();
 
     load_a(0);
     load_x(0);
@@ -352,7 +346,7 @@ __global__ __launch_bounds__(64 * WM * WN) void conv_mfma_kernel(MfmaParams p)
     auto mma = [&](int stage) __attribute__((always_inline)) {
         __builtin_amdgcn_s_setprio(1);
         const int off = p.tap0 + tap * p.tap_step - minoff;
-        const uint16_t* abase = &As[NBUF == 2 ? (stage & 1) : 0][(wm * WTM + j) * LDK + h * 8];
+        const uint16_t* abase = &As[stage & 1][(wm * WTM + j) * LDK + h * 8];
         const int xoff = ((wn * WTN + j) * XS + off) * LDK + h * 8;
 #pragma unroll
         for (int ks = 0; ks < KC / 16; ++ks) {
@@ -391,8 +385,7 @@ __global__ __launch_bounds__(64 * WM * WN) void conv_mfma_kernel(MfmaParams p)
         __builtin_amdgcn_sched_group_barrier(0x008, M - PAIRS, 0);
         __builtin_amdgcn_s_setprio(0);
     };
-    // One weight block in flight is enough where three workgroups share the CU and cover each other's loads (two blocks: the
-    // same step time, 16 more registers).  The request is unconditional -- past the last stage it reads the last block
+    // One weight block in flight and two in LDS.  The request is unconditional -- past the last stage it reads the last block
     // again -- because behind a branch the compiler cannot count it.
     for (int stage = 0; stage < nstages; ++stage) {
         int ntap = tap + 1, nchunk = chunk;
@@ -403,17 +396,15 @@ __global__ __launch_bounds__(64 * WM * WN) void conv_mfma_kernel(MfmaParams p)
         if (new_chunk) load_x(nchunk);
         mma(stage);
         if (more) {
-            if (new_chunk || NBUF == 1) {
-                __syncthreads();              // every wave is done with the old X tile (and the single weight buffer)
-                if (new_chunk) store_x();
+            if (new_chunk) {
+                __syncthreads();              // every wave is done with the old X tile
+                store_x();
             }
-            store_a(NBUF == 2 ? ((stage + 1) & 1) : 0);
+            store_a((stage + 1) & 1);
             __syncthreads();
         }
         tap = ntap; chunk = nchunk;
     }
-
-    if (MODE == MODE_RES && LATE_RES) load_res();
 
     // ---- epilogue, straight from the accumulators: register gq of tile (mi, ni) is time row 8g + 4h + q of time tile
     // ni and GEMM row mu0 + mi.  Rows past out_hi (and, for the transposed conv, before row 0) are out of range of the
@@ -546,14 +537,14 @@ hipError_t launch_conv_bf16(const ConvArgs& a, int variant, hipStream_t stream)
     // most columns any window needs: interior plus margins, never more than the longest window
     long long out_rows = std::min((long long)a.max_int * r_out + 2ll * a.margin, (long long)a.max_len * r_out);
     const long long ncols = a.stride > 0 ? out_rows / a.stride + 2 : out_rows;
+    if (variant == 0)
+        return launch_conv_stream(p, mode, a.in_fmt, emit, M, ncols, a.n_slots, a.call_slots, a.small_tile_wgs, stream);
     // Grid order (L2 miss traffic; X = activation bytes, W = weight bytes, 8 XCDs with 4 MB of L2 each).
     //  * W fits one L2: the row tiles of a column tile go to the same XCD, adjacent in dispatch order; they share
     //    its activation rows in that L2 and the weights stay resident: about X + 8 W.
     //  * W larger, more than 8 row tiles: ids run over row tiles first, so XCD x owns the row tiles = x mod 8 (an
     //    eighth of W, resident) and reads all activations: about 8 X + W.
     //  * else column tiles fastest (blockIdx.x): workgroups in flight share one row tile of the weights: mtiles X + W.
-    if (variant == 0 && stream_conv_ok(p, mode, a.in_fmt))
-        return launch_conv_stream(p, mode, a.in_fmt, emit, M, ncols, a.n_slots, a.call_slots, a.small_tile_wgs, stream);
     const long long ntiles = (ncols + v.NT - 1) / v.NT;
     const int mtiles = M / v.MT;
     const long long ntiles8 = (ntiles + 7) / 8 * 8;           // whole groups of 8 column tiles; the surplus exits at once
@@ -563,7 +554,6 @@ hipError_t launch_conv_bf16(const ConvArgs& a, int variant, hipStream_t stream)
     p.xcd_group = w_fits_l2 ? 1 : 0;
     dim3 grid(m_fastest ? (unsigned)(ntiles8 * mtiles) : (unsigned)ntiles, (unsigned)a.n_slots, m_fastest ? 1u : (unsigned)mtiles);
     switch (variant) {
-        case 0: return launch_variant<128, 128, 64, 2, 2>(p, mode, a.in_fmt, emit, grid, stream);
         case 1: return launch_variant<64, 256, 64, 1, 4>(p, mode, a.in_fmt, emit, grid, stream);
         default: return launch_variant<32, 128, 16, 1, 4>(p, mode, a.in_fmt, emit, grid, stream);
     }

@@ -15,8 +15,7 @@
 // Measured, LDS-staged tile -> here: 1024-channel dilated conv 46 -> 9.6 us (200 columns), 47 -> 17 (830), 258 -> 214 (17000);
 // 512 channels 34 -> 21 (4700), 333 -> 298 (100000: 1.23 PFLOP/s); 1x1 conv of 1024 channels 13 -> 5 (200), 14 -> 7.6 (830);
 // strided conv 1024 -> 128, stride 10: 146 -> 25 (75 columns).
-// Both MFMA forms add the products of 8 consecutive K values at a time, in K order, so with the K order (chunk, tap, channel)
-// of kernels_bf16.hip the results are bit-identical.
+// Every tile adds in the same order (chunk, tap, k-step, for two operand planes hi before lo), so a value does not depend on the tile.
 #include <algorithm>
 
 #include "conv_bf16.h"
@@ -32,6 +31,7 @@ struct StreamGrid {
 
 // Tile: WM x WN waves of TM x TN accumulator tiles of 16 rows x 16 columns.
 // NB: activation buffers, 2, or 1 for layers of a single stage.
+// NTAPS: the taps, unrolled, or 0: any number, counted at run time (dilated convs of kernel sizes other than 7).
 template <int TM, int TN, int WM, int WN, int NTAPS, int SC, int SPAN, int MODE, int IN, int NB>
 __global__ __launch_bounds__(64 * WM * WN) void conv_stream_kernel(MfmaParams p, StreamGrid sg, int emit)
 {
@@ -45,10 +45,12 @@ __global__ __launch_bounds__(64 * WM * WN) void conv_stream_kernel(MfmaParams p,
     constexpr int NP = IN == OP_BF16X2 ? 2 : 1;
     constexpr int SEGS = KX / 8, RPP = NTH / SEGS, X_ITERS = (XROWS + RPP - 1) / RPP;
     constexpr int XR = X_ITERS * RPP;                      // rows held (whole passes)
+    constexpr bool ANY = NTAPS == 0;
     constexpr int F = SC * NTAPS * 2;                      // k-steps of a stage
     // k-steps in flight: a step lasts TM x TN MFMAs of 8 ns, an L2 hit some 400 ns
-    constexpr int RS = TM >= 4 ? 2 : TM * F <= 32 ? F : F / 2;
-    static_assert(F % RS == 0, "static ring indices");
+    constexpr int RS = ANY ? (TM == 1 ? 12 : 8) : TM * F <= 32 ? F : F / 2;
+    static_assert(F % RS == 0 && RS % 2 == 0, "static ring indices");
+    const int ntaps = ANY ? p.ntaps : NTAPS;
     constexpr int LDO = MT + 4;                            // padded row of the fp32 output tile
     constexpr int X_BYTES = NP * XR * LDR * 2;
     constexpr int EP = NT * LDO * 4 > NB * X_BYTES && TN % 2 == 0 ? 2 : 1;      // passes of the epilogue
@@ -76,7 +78,7 @@ __global__ __launch_bounds__(64 * WM * WN) void conv_stream_kernel(MfmaParams p,
     if (n0 >= ncols) return;
     const int sub = mi8 % SUB, m0 = panel * 128 + sub * MT;
     const long long rowbase = (long long)s.row0 * p.r_in, rowbase_o = (long long)s.row0 * r_out;
-    const int minoff = min(p.tap0, p.tap0 + (NTAPS - 1) * p.tap_step);
+    const int minoff = min(p.tap0, p.tap0 + (ntaps - 1) * p.tap_step);
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave / WN, wn = wave % WN;
@@ -88,15 +90,15 @@ __global__ __launch_bounds__(64 * WM * WN) void conv_stream_kernel(MfmaParams p,
     const __amdgpu_buffer_rsrc_t rs_xl = make_rsrc(p.xa + p.in_lo_off + rowbase * p.cin, NP == 2 ? (unsigned)nrows * p.cin * 2u : 0u);
 
     // ---- weights: blocks of 128 x 64 (16 KB) in fragment order, [16-slot tile][2 k-steps][lane][8].  Slot 32 k + l of a group of
-    // 64 is row 2 l + k (the lane order of the 128 x 128 tile): slot tiles 0, 2 hold rows 0..31 of the group (even, odd), 1, 3
+    // 64 is row 2 l + k (see slot_to_row): slot tiles 0, 2 hold rows 0..31 of the group (even, odd), 1, 3
     // rows 32..63.  Unit u of a panel takes them in the order 0, 2, 1, 3; its lane i is row 32 (u / 2) + 2 i + u % 2.
-    const int nblocks = p.nchunks * NTAPS;
+    const int nblocks = p.nchunks * ntaps;
     const int unit0 = sub * (MT / 16) + wm * TM;                             // first unit of this wave in the panel
     const unsigned w_voff = (unsigned)((unit0 & ~3) + (unit0 & 1) * 2 + (unit0 >> 1 & 1)) * 2048u + lane * 16u;
     const unsigned w_tile = (unsigned)panel * (unsigned)nblocks * 16384u;
     u32x4 a[RS][TM];
-    auto load_a = [&](int stage, int f) __attribute__((always_inline)) {     // f may run past the stage
-        const unsigned blk = w_tile + (unsigned)block_in(stage * (F / 2) + f / 2, nblocks) * 16384u;
+    auto load_a = [&](int block0, int f) __attribute__((always_inline)) {    // k-step f from block0 on
+        const unsigned blk = w_tile + (unsigned)block_in(block0 + f / 2, nblocks) * 16384u;
 #pragma unroll
         for (int mi = 0; mi < TM; ++mi) a[f % RS][mi] = __builtin_amdgcn_raw_buffer_load_b128(rs_w, w_voff + ((mi & 1) * 2 + (mi >> 1)) * 2048u + (f & 1) * 1024u, blk, 0);
     };
@@ -111,11 +113,13 @@ __global__ __launch_bounds__(64 * WM * WN) void conv_stream_kernel(MfmaParams p,
     const int nstages = p.nchunks / SC;
     u32x4 rx[X_ITERS][NP];
     auto load_x = [&](int stage) __attribute__((always_inline)) {
-        const unsigned off = stage < nstages ? x_voff + (unsigned)(stage * KX) * 2u : 0xf8000000u;      // past the last stage: out of range
+        const unsigned base = stage < nstages ? x_voff + (unsigned)(stage * KX) * 2u : 0xf8000000u;      // past the last stage: out of range
 #pragma unroll
         for (int it = 0; it < X_ITERS; ++it) {
-            rx[it][0] = __builtin_amdgcn_raw_buffer_load_b128(rs_x, off + it * x_row_step, 0, 0);
-            if (NP == 2) rx[it][NP - 1] = __builtin_amdgcn_raw_buffer_load_b128(rs_xl, off + it * x_row_step, 0, 0);
+            // any number of taps: rows that no tap reads are out of range too
+            const unsigned off = ANY && it * RPP >= XS * (NT - 1) + 1 + (ntaps - 1) * p.tap_step ? 0xf8000000u : base + it * x_row_step;
+            rx[it][0] = __builtin_amdgcn_raw_buffer_load_b128(rs_x, off, 0, 0);
+            if (NP == 2) rx[it][NP - 1] = __builtin_amdgcn_raw_buffer_load_b128(rs_xl, off, 0, 0);
         }
     };
     auto store_x = [&](int buf) __attribute__((always_inline)) {
@@ -173,6 +177,70 @@ __global__ __launch_bounds__(64 * WM * WN) void conv_stream_kernel(MfmaParams p,
     // MFMAs, the step's weight registers refilled right after them.  (Left to itself the compiler runs one accumulator's whole
     // chain, then the next, waiting out the LDS latency of every fragment.)
     constexpr int AHEAD = TM * TN <= 2 ? 6 : TM * TN <= 4 ? 3 : 1, XD = AHEAD + 1;
+    if constexpr (ANY) {
+        // One walk over all blocks of K, unrolled by the ring: a block is a tap of a 64-channel chunk, two k-steps.  Fragments are
+        // read AH k-steps ahead, past the end of a stage from the same buffer again (in bounds, not used); at the switch to the
+        // next stage they are read once more.  1024-channel dilated conv of 9 taps, LDS-staged 128 x 128 tile -> here:
+        // 83 -> 26 us (13 frames), 84 -> 32 (75 frames), 199 -> 169 (1000), 306 -> 266 (1500).
+        constexpr int RB = RS / 2, AH = TM * TN <= 2 ? 4 : TM * TN <= 6 ? 2 : 1, D = (AH + 1) / 2, XR3 = AH + (AH > 1 ? 2 : 1) - (AH == 2 ? 1 : 0);
+        static_assert(RS % XR3 == 0 && NP == 1, "static indices; one operand plane");
+        const int nb = SC * ntaps;                                           // blocks of a stage
+        const uint16_t* xs = nullptr;
+        int off[D + 1], rt = 0, rc = 0, next = 0;                            // LDS offsets of this block and the D after it
+        auto push = [&]() __attribute__((always_inline)) {
+#pragma unroll
+            for (int d = 0; d < D; ++d) off[d] = off[d + 1];
+            off[D] = next;
+            next += p.tap_step * LDR;
+            if (++rt == ntaps) { rt = 0; if (++rc == SC) rc = 0; next = rc * 64; }
+        };
+        u32x4 x[XR3][TN];
+        auto read_x = [&](int slot, int at, int ni) __attribute__((always_inline)) {
+            x[slot][ni] = *reinterpret_cast<const u32x4*>(xs + at + ni * 16 * LDR);
+        };
+        int stage = -1, b = nb;
+        for (int g0 = 0; g0 < nblocks; g0 += RB) {
+#pragma unroll
+            for (int u = 0; u < RB; ++u) {
+                if (g0 + u >= nblocks) break;
+                if (b == nb) {
+                    if (stage >= 0) { store_x((stage + 1) & 1); __syncthreads(); }
+                    ++stage;
+                    load_x(stage + 1);
+                    xs = reinterpret_cast<const uint16_t*>(smem + (stage & 1) * X_BYTES) + (wn * (16 * TN) + i) * LDR + q * 8;
+                    b = rt = rc = next = 0;
+#pragma unroll
+                    for (int d = 0; d <= D; ++d) push();
+#pragma unroll
+                    for (int s = 0; s < AH; ++s)
+#pragma unroll
+                        for (int ni = 0; ni < TN; ++ni) read_x((2 * u + s) % XR3, off[s / 2] + s % 2 * 32, ni);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int ks = 0; ks < 2; ++ks) {
+                    const int f = 2 * u + ks;
+#pragma unroll
+                    for (int ni = 0; ni < TN; ++ni) {
+                        read_x((f + AH) % XR3, off[(ks + AH) / 2] + (ks + AH) % 2 * 32, ni);
+#pragma unroll
+                        for (int mi = 0; mi < TM; ++mi) {
+                            if (IN == OP_F16)
+                                acc[mi][ni] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, x[f % XR3][ni]), __builtin_bit_cast(f16x8, a[f][mi]), acc[mi][ni], 0, 0, 0);
+                            else
+                                acc[mi][ni] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, x[f % XR3][ni]), __builtin_bit_cast(bf16x8, a[f][mi]), acc[mi][ni], 0, 0, 0);
+                        }
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                    load_a(g0, f + RS);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                push();
+                ++b;
+            }
+        }
+        __syncthreads();
+    } else
     for (int stage = 0; stage < nstages; ++stage) {
         if (NB == 2) load_x(stage + 1);
         const uint16_t* xs = reinterpret_cast<const uint16_t*>(smem + (NB == 2 ? (stage & 1) * X_BYTES : 0)) + (wn * (16 * TN) + i) * XS * LDR + q * 8;
@@ -206,7 +274,7 @@ __global__ __launch_bounds__(64 * WM * WN) void conv_stream_kernel(MfmaParams p,
                 }
                 __builtin_amdgcn_sched_barrier(0);
             }
-            load_a(stage, f + RS);
+            load_a(stage * (F / 2), f + RS);
             __builtin_amdgcn_sched_barrier(0);
         }
         if (NB == 2) store_x((stage + 1) & 1);
@@ -299,7 +367,11 @@ hipError_t launch_tile(const MfmaParams& p, const StreamGrid& sg, int mode, int 
     }
     if (mode == MODE_ACT) {
         const int span = (p.ntaps - 1) * p.tap_step;
-        if (span <= 6) { DEMON_CASE(7, SA, 6, MODE_ACT, OP_BF16, 2) DEMON_CASE(7, SA, 6, MODE_ACT, OP_F16, 2) }
+        if (p.ntaps == 1) {                                 // no rows beyond the columns
+            if (p.nchunks % SR == 0) { DEMON_CASE(1, SR, 0, MODE_ACT, OP_BF16, 2) DEMON_CASE(1, SR, 0, MODE_ACT, OP_F16, 2) }
+            else { DEMON_CASE(1, 2, 0, MODE_ACT, OP_BF16, 2) DEMON_CASE(1, 2, 0, MODE_ACT, OP_F16, 2) }
+        } else if (p.ntaps != 7) { DEMON_CASE(0, SA, MAXSPAN, MODE_ACT, OP_BF16, 2) DEMON_CASE(0, SA, MAXSPAN, MODE_ACT, OP_F16, 2) }
+        else if (span <= 6) { DEMON_CASE(7, SA, 6, MODE_ACT, OP_BF16, 2) DEMON_CASE(7, SA, 6, MODE_ACT, OP_F16, 2) }
         else if (span <= 18) { DEMON_CASE(7, SA, 18, MODE_ACT, OP_BF16, 2) DEMON_CASE(7, SA, 18, MODE_ACT, OP_F16, 2) }
         else { DEMON_CASE(7, SA, MAXSPAN, MODE_ACT, OP_BF16, 2) DEMON_CASE(7, SA, MAXSPAN, MODE_ACT, OP_F16, 2) }
     } else if (mode == MODE_RES) {
@@ -323,18 +395,19 @@ hipError_t launch_tile(const MfmaParams& p, const StreamGrid& sg, int mode, int 
     return hipErrorInvalidValue;
 }
 
-}  // namespace
-
+// what the kernels' instances assume of a layer
 bool stream_conv_ok(const MfmaParams& p, int mode, int in_fmt)
 {
     if (p.cout % 8 != 0) return false;
     switch (mode) {
-        case MODE_ACT: return p.ntaps == 7 && p.nchunks % 2 == 0 && in_fmt != OP_BF16X2;
+        case MODE_ACT: return (p.ntaps - 1) * p.tap_step <= MAXSPAN && p.nchunks % 2 == 0 && in_fmt != OP_BF16X2;
         case MODE_RES: return p.ntaps == 1 && p.nchunks % 2 == 0;
         case MODE_DOWN: return p.ntaps == 4 && in_fmt != OP_BF16X2;
         default: return p.ntaps == 2;
     }
 }
+
+}  // namespace
 
 hipError_t launch_conv_stream(MfmaParams p, int mode, int in_fmt, int emit, int rows, long long ncols, int n_slots, int call_slots, long long max_small, hipStream_t stream)
 {
@@ -344,7 +417,12 @@ hipError_t launch_conv_stream(MfmaParams p, int mode, int in_fmt, int emit, int 
     // columns.  A CU takes weights in at some 45 bytes per clock, so small tiles are bound by that and large ones by their
     // MFMAs.  Launches of more than `max_small` 128 x 128 tiles take that tile without further ado.
     struct Tile { int mt, nt; double alone, shared; };
-    static const Tile kTiles[6] = {{32, 32, 25, 26}, {64, 64, 57, 70}, {64, 80, 65, 85}, {64, 96, 73, 97}, {128, 64, 90, 122}, {128, 128, 185, 212}};
+    static const Tile kFixed[6] = {{32, 32, 25, 26}, {64, 64, 57, 70}, {64, 80, 65, 85}, {64, 96, 73, 97}, {128, 64, 90, 122}, {128, 128, 185, 212}};
+    // Any number of taps: the small tiles have fewer k-steps in flight and the LDS of the largest span.  Measured with 3 to 15 taps
+    // (1024-channel dilated conv of 9 taps in us, tiles in this order: 75 frames 49, 32, 34, 37, 40, 56; 250 frames 149, 72, 97, 75, 63,
+    // 64; 750 frames 430, 198, 258, 227, 168, 161; 1500 frames 847, 388, 488, 435, 297, 270).
+    static const Tile kAny[6] = {{32, 32, 75, 45}, {64, 64, 90, 78}, {64, 80, 100, 115}, {64, 96, 105, 132}, {128, 64, 120, 118}, {128, 128, 177, 190}};
+    const Tile* kTiles = mode == MODE_ACT && p.ntaps != 7 && p.ntaps != 1 ? kAny : kFixed;
     int best = 5;
     if ((ncols + 127) / 128 * (rows / 128) * call_slots <= max_small) {
         double least = 0;
