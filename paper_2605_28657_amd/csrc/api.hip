@@ -261,9 +261,11 @@ demon_status check_plane(const demon_vae* v, int max_len)
 // 1935 / 1782.
 // One group for a gated call, which may turn out to be launches only, and where a mode wants one ordered launch sequence
 // (per-launch timing, debug tap).
+long long two_group_frames(const demon_vae* v) { return v->has_staged_convs ? 150 : 320; }
+
 bool two_groups(const demon_vae* v, const Plan* p, bool gated)
 {
-    return p->split > 0 && p->total_frames >= (v->has_staged_convs ? 150 : 320) && !gated && v->stream2 && v->timing < 2 &&
+    return p->split > 0 && p->total_frames >= two_group_frames(v) && !gated && v->stream2 && v->timing < 2 &&
            !(v->tap_layer >= 0 && v->tap_dst);
 }
 
@@ -852,6 +854,13 @@ demon_status create_impl(const demon_vae_config* cfg, const float* host_weights,
         rate = 1;                              // no window waveforms to hold
     }
 
+    for (const Block& B : v->blocks) {
+        auto staged = [&](const ConvLayer& L) { return bf && L.generic && L.variant != 0; };
+        if (staged(B.up)) v->has_staged_convs = true;
+        for (const ResUnit& U : B.res)
+            if (staged(U.dilated)) v->has_staged_convs = true;
+    }
+
     // ---- device memory
     const size_t act_elems = (size_t)v->cap_frames * (size_t)per_frame;
     v->ws.act_elems = act_elems;
@@ -867,13 +876,14 @@ demon_status create_impl(const demon_vae_config* cfg, const float* host_weights,
         if (v->ev_join) (void)hipEventDestroy(v->ev_join);
         if (v->stream2) (void)hipStreamDestroy(v->stream2);
     };
+    ar.reserve(kWeightSlack);
     hipError_t e = hipMalloc(&v->d_params, ar.bytes.size());
     // fp32 path: 4 bytes per element; bf16 path: half residual stream (2 bytes), bf16 operand buffers with hi and lo planes (4)
     for (int i = 0; e == hipSuccess && i < (bf ? 5 : 3); ++i) e = hipMalloc(&v->ws.buf[i], act_elems * ((bf && i < 2) ? 2 : 4));
     if (e == hipSuccess) e = hipMalloc((void**)&v->ws.head_out, head_bytes);
     if (e == hipSuccess) e = hipMalloc((void**)&v->d_slot_arena, sizeof(Slot) * kMaxSlots * kPlanCache);
     if (e == hipSuccess) e = hipMalloc((void**)&v->ws.slot_gated, sizeof(Slot) * kMaxSlots);
-    if (e == hipSuccess && bf && g_dual_stream) {
+    if (e == hipSuccess && bf && g_dual_stream && v->cap_frames >= two_group_frames(v.get())) {      // else no call can use it
         e = hipStreamCreateWithFlags(&v->stream2, hipStreamNonBlocking);
         if (e == hipSuccess) e = hipEventCreateWithFlags(&v->ev_fork, hipEventDisableTiming);
         if (e == hipSuccess) e = hipEventCreateWithFlags(&v->ev_join, hipEventDisableTiming);
@@ -913,10 +923,6 @@ demon_status create_impl(const demon_vae_config* cfg, const float* host_weights,
     };
     for (size_t i = 0; i + 1 < v->steps.size(); ++i) v->steps[i].consumer = operand_layer(v->steps[i + 1]);
     v->first_consumer = operand_layer(v->steps[0]);
-    for (const Step& s : v->steps) {
-        const ConvLayer& L = s.conv ? *s.conv : s.unit->dilated;
-        if (bf && L.generic && L.variant != 0) v->has_staged_convs = true;
-    }
     // the head can run inside the last residual unit's kernel when that unit is the fused 64-channel form
     if (!encoder && head_mfma && !(cfg->flags & DEMON_VAE_FLAG_NO_HEAD_FUSION) && !v->steps.empty()) {
         const Step& last = v->steps.back();

@@ -55,6 +55,11 @@ enum OperandFmt { OP_BF16 = 0,     // one bf16 plane
                   OP_BF16X2 = 1,   // hi + lo bf16 planes, two MFMAs per k-step
                   OP_F16 = 2 };    // one IEEE half plane, f16 MFMA
 
+// bytes past a layer's packed weights that its kernel may request (and not use), see weight_rsrc; the parameter allocation ends
+// with as many, and a layer's weights are smaller than 4 GB by as many
+constexpr unsigned kWeightSlack = 256 * 1024;
+constexpr unsigned long long kMaxWeightBytes = 0xffffffffull - kWeightSlack;
+
 struct ConvArgs {
     const void* x;        // activated input [rows_in, cin] (fp32 path: fp32; bf16 path: 16-bit operand)
     void* y;              // output activation [rows_out, cout] (fp32 path: fp32; bf16 path: half); bf16 dilated conv: unused

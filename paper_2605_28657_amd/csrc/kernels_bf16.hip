@@ -241,7 +241,8 @@ __global__ __launch_bounds__(64 * WM * WN) void conv_mfma_kernel(MfmaParams p)
     const int seg = tid % SEGS, xr0 = tid / SEGS;
 
     // ---- descriptors (uniform)
-    const __amdgpu_buffer_rsrc_t rs_w = make_rsrc(p.w, p.w_bytes);
+    const __amdgpu_buffer_rsrc_t rs_w = weight_rsrc(p.w, p.w_bytes);
+    static_assert(A_CH * 16u <= kWeightSlack, "one block ahead");
     const __amdgpu_buffer_rsrc_t rs_x = make_rsrc(p.xa + rowbase * p.cin, (unsigned)nrows * p.cin * 2u);
     const __amdgpu_buffer_rsrc_t rs_xl = make_rsrc(p.xa + p.in_lo_off + rowbase * p.cin, SPLIT_IN ? (unsigned)nrows * p.cin * 2u : 0u);
 
@@ -255,7 +256,7 @@ __global__ __launch_bounds__(64 * WM * WN) void conv_mfma_kernel(MfmaParams p)
     u32x4 rx[X_ITERS][NP];
 
     auto load_a = [&](int stage) __attribute__((always_inline)) {
-        const unsigned base = w_tile0 + (unsigned)block_in(stage, nstages) * (A_CH * 16u);
+        const unsigned base = w_tile0 + (unsigned)stage * (A_CH * 16u);
 #pragma unroll
         for (int it = 0; it < A_ITERS; ++it)
             if (A_CH % NTH == 0 || tid + it * NTH < A_CH)
@@ -385,8 +386,8 @@ __global__ __launch_bounds__(64 * WM * WN) void conv_mfma_kernel(MfmaParams p)
         __builtin_amdgcn_sched_group_barrier(0x008, M - PAIRS, 0);
         __builtin_amdgcn_s_setprio(0);
     };
-    // One weight block in flight and two in LDS.  The request is unconditional -- past the last stage it reads the last block
-    // again -- because behind a branch the compiler cannot count it.
+    // One weight block in flight and two in LDS.  The request is unconditional -- past the last stage it reads another row tile's
+    // block or the slack -- because behind a branch the compiler cannot count it.
     for (int stage = 0; stage < nstages; ++stage) {
         int ntap = tap + 1, nchunk = chunk;
         if (ntap == p.ntaps) { ntap = 0; ++nchunk; }
@@ -514,7 +515,7 @@ hipError_t launch_conv_bf16(const ConvArgs& a, int variant, hipStream_t stream)
     p.nchunks = cin / v.KC; p.margin = a.margin;
     p.in_lo_off = a.in_lo_off; p.out_lo_off = a.out_lo_off;
     const size_t wb = (size_t)M * ntaps * cin * 2;
-    if (wb > 0xffffffffull) return hipErrorInvalidValue;
+    if (wb > kMaxWeightBytes) return hipErrorInvalidValue;
     p.w_bytes = (unsigned)wb;
     int mode;
     if (a.down > 0) { p.tap0 = -1; p.tap_step = 1; mode = MODE_DOWN; }

@@ -136,7 +136,7 @@ __global__ __launch_bounds__(256, (CH == 128 && TN == 2) ? 2 : 3) void res_unit_
     const __amdgpu_buffer_rsrc_t rs_x = make_rsrc(p.x + rowbase * CH, (unsigned)nrows * CH * (unsigned)sizeof(hres_t));
     const __amdgpu_buffer_rsrc_t rs_y = make_rsrc(p.y + rowbase * CH, (unsigned)out_hi * CH * (unsigned)sizeof(hres_t));
     const __amdgpu_buffer_rsrc_t rs_a = make_rsrc(p.ya + rowbase * CH, EMIT ? (unsigned)out_hi * CH * 2u : 0u);
-    const __amdgpu_buffer_rsrc_t rs_w = make_rsrc(p.w7, (unsigned)(p.nchunks * p.ntaps) * (A_CH * 16u));
+    const __amdgpu_buffer_rsrc_t rs_w = weight_rsrc(p.w7, (unsigned)(p.nchunks * p.ntaps) * (A_CH * 16u));
 
     const int nstages = p.nchunks * p.ntaps;
     const unsigned a_voff = tid * 16u;
@@ -148,7 +148,7 @@ __global__ __launch_bounds__(256, (CH == 128 && TN == 2) ? 2 : 3) void res_unit_
     float al[8], ib[8];
 
     auto load_a = [&](int stage) __attribute__((always_inline)) {
-        const unsigned base = (unsigned)block_in(stage, nstages) * (A_CH * 16u);
+        const unsigned base = (unsigned)stage * (A_CH * 16u);
 #pragma unroll
         for (int it = 0; it < A_ITERS; ++it) ra[it] = __builtin_amdgcn_raw_buffer_load_b128(rs_w, a_voff, base + it * 4096u, 0);
     };

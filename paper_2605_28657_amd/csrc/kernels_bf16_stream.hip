@@ -49,7 +49,7 @@ __global__ __launch_bounds__(64 * WM * WN) void conv_stream_kernel(MfmaParams p,
     constexpr int F = SC * NTAPS * 2;                      // k-steps of a stage
     // k-steps in flight: a step lasts TM x TN MFMAs of 8 ns, an L2 hit some 400 ns
     constexpr int RS = ANY ? (TM == 1 ? 12 : 8) : TM * F <= 32 ? F : F / 2;
-    static_assert(F % RS == 0 && RS % 2 == 0, "static ring indices");
+    static_assert(F % RS == 0 && RS % 2 == 0 && RS / 2 * 16384 <= kWeightSlack, "static ring indices");
     const int ntaps = ANY ? p.ntaps : NTAPS;
     constexpr int LDO = MT + 4;                            // padded row of the fp32 output tile
     constexpr int X_BYTES = NP * XR * LDR * 2;
@@ -85,7 +85,7 @@ __global__ __launch_bounds__(64 * WM * WN) void conv_stream_kernel(MfmaParams p,
     const int i = lane & 15, q = lane >> 4;
     const int seg = tid % SEGS, xr0 = tid / SEGS;
 
-    const __amdgpu_buffer_rsrc_t rs_w = make_rsrc(p.w, p.w_bytes);
+    const __amdgpu_buffer_rsrc_t rs_w = weight_rsrc(p.w, p.w_bytes);
     const __amdgpu_buffer_rsrc_t rs_x = make_rsrc(p.xa + rowbase * p.cin, (unsigned)nrows * p.cin * 2u);
     const __amdgpu_buffer_rsrc_t rs_xl = make_rsrc(p.xa + p.in_lo_off + rowbase * p.cin, NP == 2 ? (unsigned)nrows * p.cin * 2u : 0u);
 
@@ -96,11 +96,13 @@ __global__ __launch_bounds__(64 * WM * WN) void conv_stream_kernel(MfmaParams p,
     const int unit0 = sub * (MT / 16) + wm * TM;                             // first unit of this wave in the panel
     const unsigned w_voff = (unsigned)((unit0 & ~3) + (unit0 & 1) * 2 + (unit0 >> 1 & 1)) * 2048u + lane * 16u;
     const unsigned w_tile = (unsigned)panel * (unsigned)nblocks * 16384u;
+    // requests past the panel's last block read the next panel's (nobody's after the last panel) and are not used
+    const bool more_panels = w_tile + (unsigned)nblocks * 16384u < p.w_bytes;
     u32x4 a[RS][TM];
-    auto load_a = [&](int block0, int f) __attribute__((always_inline)) {    // k-step f from block0 on
-        const unsigned blk = w_tile + (unsigned)block_in(block0 + f / 2, nblocks) * 16384u;
+    auto load_a = [&](int block0, int f, unsigned voff) __attribute__((always_inline)) {     // k-step f from block0 on
+        const unsigned blk = w_tile + (unsigned)(block0 + f / 2) * 16384u;
 #pragma unroll
-        for (int mi = 0; mi < TM; ++mi) a[f % RS][mi] = __builtin_amdgcn_raw_buffer_load_b128(rs_w, w_voff + ((mi & 1) * 2 + (mi >> 1)) * 2048u + (f & 1) * 1024u, blk, 0);
+        for (int mi = 0; mi < TM; ++mi) a[f % RS][mi] = __builtin_amdgcn_raw_buffer_load_b128(rs_w, voff + ((mi & 1) * 2 + (mi >> 1)) * 2048u + (f & 1) * 1024u, blk, 0);
     };
     auto lane_row = [&](int mi) __attribute__((always_inline)) -> int {      // GEMM row of this lane in the tile
         const int u = unit0 + mi;
@@ -134,7 +136,7 @@ __global__ __launch_bounds__(64 * WM * WN) void conv_stream_kernel(MfmaParams p,
     // every request of the prologue in the order of use
     load_x(0);
 #pragma unroll
-    for (int f = 0; f < RS; ++f) load_a(0, f);
+    for (int f = 0; f < RS; ++f) load_a(0, f, ANY ? ahead_voff(w_voff, more_panels || f / 2 < nblocks) : w_voff);
     float bv[TM];
 #pragma unroll
     for (int mi = 0; mi < TM; ++mi) bv[mi] = p.bias[(MODE == MODE_UP) ? (m0 + lane_row(mi)) % p.cout : m0 + lane_row(mi)];
@@ -216,6 +218,7 @@ __global__ __launch_bounds__(64 * WM * WN) void conv_stream_kernel(MfmaParams p,
 #pragma unroll
                         for (int ni = 0; ni < TN; ++ni) read_x((2 * u + s) % XR3, off[s / 2] + s % 2 * 32, ni);
                 }
+                const unsigned voff = ahead_voff(w_voff, more_panels || g0 + u + RB < nblocks);
                 __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                 for (int ks = 0; ks < 2; ++ks) {
@@ -232,7 +235,7 @@ __global__ __launch_bounds__(64 * WM * WN) void conv_stream_kernel(MfmaParams p,
                         }
                         __builtin_amdgcn_sched_barrier(0);
                     }
-                    load_a(g0, f + RS);
+                    load_a(g0, f + RS, voff);
                     __builtin_amdgcn_sched_barrier(0);
                 }
                 push();
@@ -243,6 +246,7 @@ __global__ __launch_bounds__(64 * WM * WN) void conv_stream_kernel(MfmaParams p,
     } else
     for (int stage = 0; stage < nstages; ++stage) {
         if (NB == 2) load_x(stage + 1);
+        const unsigned voff_next = ahead_voff(w_voff, more_panels || stage + 1 < nstages);
         const uint16_t* xs = reinterpret_cast<const uint16_t*>(smem + (NB == 2 ? (stage & 1) * X_BYTES : 0)) + (wn * (16 * TN) + i) * XS * LDR + q * 8;
         u32x4 x[XD][TN][NP];
         auto read_x = [&](int f, int ni) __attribute__((always_inline)) {
@@ -274,7 +278,7 @@ __global__ __launch_bounds__(64 * WM * WN) void conv_stream_kernel(MfmaParams p,
                 }
                 __builtin_amdgcn_sched_barrier(0);
             }
-            load_a(stage * (F / 2), f + RS);
+            load_a(stage * (F / 2), f + RS, f + RS < F ? w_voff : voff_next);
             __builtin_amdgcn_sched_barrier(0);
         }
         if (NB == 2) store_x((stage + 1) & 1);

@@ -83,8 +83,8 @@ __global__ __launch_bounds__(256) void res_unit_wide_kernel(WideParams p)
     const __amdgpu_buffer_rsrc_t rs_y = make_rsrc(p.y + rowbase * CH, (unsigned)out_hi * CH * (unsigned)sizeof(hres_t));
     const __amdgpu_buffer_rsrc_t rs_a = make_rsrc(p.ya + rowbase * CH, EMIT ? (unsigned)out_hi * CH * 2u : 0u);
     const int nstages = W_NCHUNKS * p.ntaps;
-    const __amdgpu_buffer_rsrc_t rs_w7 = make_rsrc(p.w7, (unsigned)nstages * (W_A_CH * 16u));
-    const __amdgpu_buffer_rsrc_t rs_w1 = make_rsrc(p.w1, (unsigned)W_NCHUNKS * (W_A_CH * 16u));
+    const __amdgpu_buffer_rsrc_t rs_w7 = weight_rsrc(p.w7, (unsigned)nstages * (W_A_CH * 16u));
+    const __amdgpu_buffer_rsrc_t rs_w1 = weight_rsrc(p.w1, (unsigned)W_NCHUNKS * (W_A_CH * 16u));
 
     // Staging pattern of the activations.  An LDS row is 80 bytes (20 banks), so the 8 lanes that one cycle of a 16-byte LDS write serves
     // must not hold two neighbouring rows (rows r and r + 1 overlap in 4 banks): lanes 0..3 of each group of 8 take the
@@ -97,10 +97,10 @@ __global__ __launch_bounds__(256) void res_unit_wide_kernel(WideParams p)
 
     u32x4 ra[A_ITERS], rb[A_ITERS];     // rb: second set, only for the blocks of the 1x1 weights (requested two ahead)
     u32x4 rx[X_ITERS];
-    auto load_set = [&](u32x4 (&r)[A_ITERS], __amdgpu_buffer_rsrc_t rs, int block, int nblocks) __attribute__((always_inline)) {
-        const unsigned base = (unsigned)block_in(block, nblocks) * (W_A_CH * 16u);
+    auto load_set = [&](u32x4 (&r)[A_ITERS], __amdgpu_buffer_rsrc_t rs, int block) __attribute__((always_inline)) {
+        const unsigned base = (unsigned)block * (W_A_CH * 16u), voff = ahead_voff(a_voff, block < nstages);
 #pragma unroll
-        for (int it = 0; it < A_ITERS; ++it) r[it] = __builtin_amdgcn_raw_buffer_load_b128(rs, a_voff, base + it * 4096u, 0);
+        for (int it = 0; it < A_ITERS; ++it) r[it] = __builtin_amdgcn_raw_buffer_load_b128(rs, voff, base + it * 4096u, 0);
     };
     auto store_set = [&](const u32x4 (&r)[A_ITERS], int buf) __attribute__((always_inline)) {
 #pragma unroll
@@ -127,7 +127,7 @@ __global__ __launch_bounds__(256) void res_unit_wide_kernel(WideParams p)
     };
 
     // every request of the prologue is issued before the first result is waited for, in the order of use
-    load_set(ra, rs_w7, 0, nstages);
+    load_set(ra, rs_w7, 0);
     load_x(0);
     constexpr int PRM_ITERS = 4 * CH / 256;
     float pv[PRM_ITERS];
@@ -191,13 +191,13 @@ __global__ __launch_bounds__(256) void res_unit_wide_kernel(WideParams p)
     // Weight blocks are requested two stages ahead, alternating between the two register sets (the second set is otherwise
     // only used by the 1x1 convolution): with one workgroup per CU (a single playback window) nothing else hides the
     // latency of a block's load, and one stage of MFMAs is shorter than it.  The request is unconditional (past the last
-    // block it reads that block again): behind a branch the compiler could not count it, and the wait for the older block
+    // block nothing is read): behind a branch the compiler could not count it, and the wait for the older block
     // would wait for it as well.
     auto iter = [&](int stage, u32x4 (&rload)[A_ITERS], const u32x4 (&rstore)[A_ITERS]) __attribute__((always_inline)) {
         int ntap = tap + 1, nchunk = chunk;
         if (ntap == p.ntaps) { ntap = 0; ++nchunk; }
         const bool new_chunk = nchunk != chunk;
-        load_set(rload, rs_w7, stage + 2, nstages);
+        load_set(rload, rs_w7, stage + 2);
         if (new_chunk) load_x(nchunk);
         mma_stage(stage);
         if (new_chunk) {
@@ -208,12 +208,12 @@ __global__ __launch_bounds__(256) void res_unit_wide_kernel(WideParams p)
         __syncthreads();
         tap = ntap; chunk = nchunk;
     };
-    load_set(rb, rs_w7, 1, nstages);
+    load_set(rb, rs_w7, 1);
     for (int stage = 0; stage + 1 < nstages; stage += 2) {
         iter(stage, ra, rb);
         if (stage + 2 < nstages) iter(stage + 1, rb, ra);
     }
-    load_set(ra, rs_w1, 0, W_NCHUNKS);
+    load_set(ra, rs_w1, 0);
     mma_stage(nstages - 1);
 
     // ---- Snake on the accumulators; repack them as the B fragments of the 1x1 conv (k step kk = 2 mi + g/2)
@@ -235,8 +235,8 @@ __global__ __launch_bounds__(256) void res_unit_wide_kernel(WideParams p)
     // the epilogue are requested in the second half of the loop, where the fragments already used have freed registers.
     __syncthreads();                                   // all waves are done with the last stage's operands
     store_a(0);
-    load_set(ra, rs_w1, 1, W_NCHUNKS);
-    load_set(rb, rs_w1, 2, W_NCHUNKS);
+    load_set(ra, rs_w1, 1);
+    load_set(rb, rs_w1, 2);
     // accumulator tile mo of the 1x1 conv: [time row 8g + 4h + q][channel slot j] = channel 8 j + mo; starts at its bias
 #pragma unroll
     for (int mo = 0; mo < TM; ++mo) {
@@ -262,7 +262,7 @@ __global__ __launch_bounds__(256) void res_unit_wide_kernel(WideParams p)
         if (c + 1 < W_NCHUNKS) {
             if ((c + 1) & 1) store_set(ra, (c + 1) & 1); else store_set(rb, (c + 1) & 1);
             __syncthreads();
-            if (c + 3 < W_NCHUNKS) { if ((c + 3) & 1) load_set(ra, rs_w1, c + 3, W_NCHUNKS); else load_set(rb, rs_w1, c + 3, W_NCHUNKS); }
+            if (c + 3 < W_NCHUNKS) { if ((c + 3) & 1) load_set(ra, rs_w1, c + 3); else load_set(rb, rs_w1, c + 3); }
         }
         if (c >= W_NCHUNKS / 2) {                      // chunks 4..7 request four time rows each
 #pragma unroll
@@ -319,7 +319,7 @@ __global__ __launch_bounds__(512, 2) void res_unit_wide_stream_kernel(WideParams
     constexpr int SEGS = KX / 8, RPP = NTH / SEGS, X_ITERS = (NT + W_MAXSPAN + RPP - 1) / RPP, XR = X_ITERS * RPP;
     constexpr int F = 2 * NTAPS, NSTAGES = CH / KX;         // k-steps of 32 in a stage
     constexpr int RS = 7;                     // k-steps of weights in flight
-    static_assert(F % RS == 0, "static ring indices");
+    static_assert(F % RS == 0 && RS * (W_A_CH * 16u) <= kWeightSlack, "static ring indices");
     constexpr int LDM = CH + 16;                            // row of the branch tensor's tile: 34 pieces
     constexpr int EP = NT > 96 ? 2 : 1, ECOLS = NT / EP, LDO = CH + 4;           // epilogue in passes of ECOLS columns
     constexpr int X_BYTES = XR * LDR * 2, M_BYTES = NT * LDM * 2, O_BYTES = ECOLS * LDO * 4;
@@ -343,20 +343,20 @@ __global__ __launch_bounds__(512, 2) void res_unit_wide_stream_kernel(WideParams
     const __amdgpu_buffer_rsrc_t rs_x = make_rsrc(p.xa + rowbase * CH, (unsigned)nrows * CH * 2u);
     const __amdgpu_buffer_rsrc_t rs_y = make_rsrc(p.y + rowbase * CH, (unsigned)out_hi * CH * (unsigned)sizeof(hres_t));
     const __amdgpu_buffer_rsrc_t rs_a = make_rsrc(p.ya + rowbase * CH, EMIT ? (unsigned)out_hi * CH * 2u : 0u);
-    const __amdgpu_buffer_rsrc_t rs_w7 = make_rsrc(p.w7, (unsigned)(W_NCHUNKS * NTAPS) * (W_A_CH * 16u));
-    const __amdgpu_buffer_rsrc_t rs_w1 = make_rsrc(p.w1, (unsigned)W_NCHUNKS * (W_A_CH * 16u));
+    const __amdgpu_buffer_rsrc_t rs_w7 = weight_rsrc(p.w7, (unsigned)(W_NCHUNKS * NTAPS) * (W_A_CH * 16u));
+    const __amdgpu_buffer_rsrc_t rs_w1 = weight_rsrc(p.w1, (unsigned)W_NCHUNKS * (W_A_CH * 16u));
 
     // weights: one block of 256 x 32 per k-step, [16-row unit][lane][8]; this wave's units are 2 wave, 2 wave + 1
     const unsigned w_voff = (unsigned)wave * 2048u + lane * 16u;
     u32x4 a[RS][2];
-    auto load_a = [&](int f, int slot) __attribute__((always_inline)) {
-        const unsigned blk = (unsigned)block_in(f, W_NCHUNKS * NTAPS) * (W_A_CH * 16u);
+    auto load_a = [&](int f, int slot, unsigned voff) __attribute__((always_inline)) {
+        const unsigned blk = (unsigned)f * (W_A_CH * 16u);
 #pragma unroll
-        for (int mi = 0; mi < 2; ++mi) a[slot][mi] = __builtin_amdgcn_raw_buffer_load_b128(rs_w7, w_voff + mi * 1024u, blk, 0);
+        for (int mi = 0; mi < 2; ++mi) a[slot][mi] = __builtin_amdgcn_raw_buffer_load_b128(rs_w7, voff + mi * 1024u, blk, 0);
     };
     // 1x1 weights: channel 8 j + mo lies in slot 32 mo + j (see pack_w1_wide); this lane's channel 16 u + i in unit u
     auto load_a1 = [&](int c, int slot) __attribute__((always_inline)) {
-        const unsigned blk = (unsigned)block_in(c, W_NCHUNKS) * (W_A_CH * 16u);
+        const unsigned blk = (unsigned)c * (W_A_CH * 16u);
 #pragma unroll
         for (int mi = 0; mi < 2; ++mi) {
             const int ch = 32 * wave + 16 * mi + i, sl = (ch & 7) * 32 + (ch >> 3);
@@ -382,7 +382,7 @@ __global__ __launch_bounds__(512, 2) void res_unit_wide_stream_kernel(WideParams
 
     load_x(0);
 #pragma unroll
-    for (int f = 0; f < RS; ++f) load_a(f, f);
+    for (int f = 0; f < RS; ++f) load_a(f, f, w_voff);
     const int ch0 = 32 * wave + i;                          // this lane's channels: ch0, ch0 + 16
     f32x4 acc[2][TN];
 #pragma unroll
@@ -402,6 +402,7 @@ __global__ __launch_bounds__(512, 2) void res_unit_wide_stream_kernel(WideParams
     };
     for (int stage = 0; stage < NSTAGES; ++stage) {
         load_x(stage + 1);
+        const unsigned voff_next = ahead_voff(w_voff, stage + 1 < NSTAGES);
         const uint16_t* xs = reinterpret_cast<const uint16_t*>(smem + (stage & 1) * X_BYTES) + i * LDR + q * 8;
         u32x4 x[2][TN];
         auto read_x = [&](int f, int ni) __attribute__((always_inline)) {
@@ -418,7 +419,7 @@ __global__ __launch_bounds__(512, 2) void res_unit_wide_stream_kernel(WideParams
                 mma(x[f & 1][ni], a[f % RS], ni);
                 __builtin_amdgcn_sched_barrier(0);
             }
-            load_a(stage * F + f + RS, f % RS);
+            load_a(stage * F + f + RS, f % RS, f + RS < F ? w_voff : voff_next);
             __builtin_amdgcn_sched_barrier(0);
         }
         store_x((stage + 1) & 1);

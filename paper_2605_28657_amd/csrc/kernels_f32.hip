@@ -104,15 +104,16 @@ __global__ __launch_bounds__(256) void conv_f32_mfma_kernel(ConvArgs a, int nchu
     const float* __restrict__ x = (const float*)a.x + ((long long)s.row0 * a.r_in + row0) * a.cin + piece * 4;
 
     const int nstages = nchunks * a.ntaps;
-    const __amdgpu_buffer_rsrc_t rs_w = make_rsrc(a.w, (unsigned)M * (unsigned)nstages * (KC * 4u));
+    const __amdgpu_buffer_rsrc_t rs_w = weight_rsrc(a.w, (unsigned)M * (unsigned)nstages * (KC * 4u));
+    static_assert(PF * 2048u <= kWeightSlack, "stages ahead");
     const unsigned tile_bytes = (unsigned)nstages * 2048u;
     unsigned w_off[TM];
 #pragma unroll
-    for (int mi = 0; mi < TM; ++mi) w_off[mi] = (unsigned)(m0 / 16 + wm * TM + mi) * tile_bytes + lane * 16u;   // past M: out of range, zero
+    for (int mi = 0; mi < TM; ++mi) w_off[mi] = (unsigned)(m0 / 16 + wm * TM + mi) * tile_bytes + lane * 16u;   // past M: the slack or out of range, not used
 
     u32x4 wr[PF][TM][2];
     auto load_w = [&](u32x4 (&r)[TM][2], int stage) __attribute__((always_inline)) {
-        const unsigned blk = (unsigned)block_in(stage, nstages) * 2048u;
+        const unsigned blk = (unsigned)stage * 2048u;
 #pragma unroll
         for (int mi = 0; mi < TM; ++mi)
 #pragma unroll

@@ -11,7 +11,7 @@ KERNELS = [s for s in b.SOURCES if s.startswith("kernels_")]
 
 def _calls(text, name):
     """(position, arguments) of every call of `name` in the text."""
-    for m in re.finditer(re.escape(name) + r"\w*\(", text):
+    for m in re.finditer(re.escape(name.rstrip("(")) + r"\w*\(", text):
         depth, args, cur = 1, [], ""
         for ch in text[m.end():]:
             depth += (ch in "([{") - (ch in ")]}")
@@ -28,12 +28,29 @@ def _calls(text, name):
 @pytest.mark.parametrize("src", KERNELS)
 def test_scalar_offsets_stay_inside_the_descriptor(src):
     """A buffer load's range check covers the per-lane offset only: it is compared with (size - scalar offset), which means
-    nothing once the scalar offset is past the size.  Prefetches run past a layer's last weight block, so wherever a
-    load has a scalar offset, the block it is computed from must be held inside the layer (block_in)."""
+    nothing once the scalar offset is past the size.  Prefetches run past a layer's last weight block, so every load
+    with a scalar offset must go through a descriptor that reaches over the slack (weight_rsrc)."""
     text = open(os.path.join(b.CSRC, src)).read()
+    kernels = [m.start() for m in re.finditer(r"__global__", text)] + [len(text)]
+    loads = 0
     for pos, args in _calls(text, "__builtin_amdgcn_raw_buffer_load"):
         assert len(args) == 4, (src, args)
         if args[2] == "0":
             continue
-        body = text[text.rfind("auto ", 0, pos):pos] + args[2]        # the lambda that issues the load
-        assert "block_in(" in body, f"{src}: scalar offset {args[2]!r} is not held inside the layer"
+        kernel = text[max(k for k in kernels if k < pos):min(k for k in kernels if k > pos)]
+        # the descriptor itself, or a parameter of the lambda that every caller fills with one
+        if args[0] == "rs":
+            made = [a[1] for _, a in _calls(kernel, "load_set(") if a[1].startswith("rs_")]
+            assert made
+        else:
+            made = [args[0]]
+        for rs in made:
+            assert re.search(rf"\b{rs} = weight_rsrc\(", kernel), f"{src}: {rs} takes a scalar offset {args[2]!r} but covers no slack"
+        loads += 1
+    if loads:
+        assert "kWeightSlack" in text or "if (more) load_a(stage + 1);" in text, f"{src}: how far its prefetch runs is not checked"
+
+
+def test_the_parameter_allocation_ends_with_the_slack():
+    text = open(os.path.join(b.CSRC, "api.hip")).read()
+    assert re.search(r"ar\.reserve\(kWeightSlack\);\s*hipError_t e = hipMalloc\(&v->d_params, ar\.bytes\.size\(\)\)", text)
