@@ -7,7 +7,6 @@
 // x is the already activated input: every producer writes, beside the residual stream h, the operand of the layer that
 // consumes it (Snake with that layer's parameters), so no layer needs a pass of its own for its Snake.
 #include <algorithm>
-#include <type_traits>
 
 #include "device_common.h"
 
@@ -68,14 +67,22 @@ void pack_f32(const float* w, int cin, int cout, int ntaps, int stride, float* d
 // is staged, once per 32-channel chunk for all taps.  Four waves of TM x TN accumulator tiles of 16 rows x 16 columns.
 // The tile is chosen per launch for the number of CUs it fills (see launch_conv_f32); every tile shape adds in the same
 // order -- chunk, tap, 16-channel group, MFMA -- so results do not depend on the choice, nor on the place in a tile.
+// All requests are unconditional and through descriptors (out of range where there is nothing to read), so that the compiler
+// can count them: a wait for one block of weights leaves the later ones in flight, but for the first stage of a round of PF
+// (the compiler leads a round's early end through the loop's own test; a round without one, with the remainder after the loop,
+// takes 210 registers instead of 130 and is 4 % slower).  The epilogue takes the accumulators from LDS: sinf is too long to
+// unroll, and a dynamic index into registers had put those of the 128 x 128 tile in scratch memory, written back every stage.
+// 3 s window of the x1920 stack 3297 -> 2974 us, 2 s clip of the x32 one 153 -> 142.
+constexpr int f32_rows_in_registers(int nt) { return nt <= 32 ? 96 : nt <= 64 ? 128 : 192; }      // rows of the next chunk held
+
 template <int TM, int TN, int WM, int WN>
 __global__ __launch_bounds__(256) void conv_f32_mfma_kernel(ConvArgs a, int nchunks, int xrows)
 {
     static_assert(WM * WN == 4, "four waves");
     constexpr int MT = 16 * TM * WM, NT = 16 * TN * WN, KC = F_KC;
     constexpr int PF = TM * TN >= 16 ? 2 : 4;      // weight stages in flight: a small tile's stage is shorter than an L2 access
-    constexpr int XI = TN * WN <= 2 ? 3 : TN * WN <= 4 ? 4 : 6;      // rows prefetched in registers: 32 per pass
-    extern __shared__ __attribute__((aligned(16))) float xs[];          // [xrows][32], 16-byte pieces XOR-swizzled by the row
+    constexpr int XI = f32_rows_in_registers(NT) / 32;      // 32 rows per pass
+    extern __shared__ __attribute__((aligned(16))) float xs[];          // [rows][32], 16-byte pieces XOR-swizzled by the row
 
     const Slot s = a.slots[blockIdx.y];
     const int M = a.stride > 0 ? a.stride * a.cout : a.cout;
@@ -101,7 +108,11 @@ __global__ __launch_bounds__(256) void conv_f32_mfma_kernel(ConvArgs a, int nchu
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave / WN, wn = wave % WN, j = lane & 15, q = lane >> 4;
     const int piece = tid & 7, xr0 = tid >> 3;
-    const float* __restrict__ x = (const float*)a.x + ((long long)s.row0 * a.r_in + row0) * a.cin + piece * 4;
+    // the tile's rows inside the window: rows outside read as zero
+    const long long row_lo = max(0ll, row0), row_hi = max(row_lo, min(nrows_in, row0 + xrows));
+    const __amdgpu_buffer_rsrc_t rs_x = make_rsrc((const float*)a.x + ((long long)s.row0 * a.r_in + row_lo) * a.cin,
+                                                  (unsigned)(row_hi - row_lo) * (unsigned)a.cin * 4u);
+    const int before = (int)(row_lo - row0);             // staged rows before the window; their offsets wrap: out of range
 
     const int nstages = nchunks * a.ntaps;
     const __amdgpu_buffer_rsrc_t rs_w = weight_rsrc(a.w, (unsigned)M * (unsigned)nstages * (KC * 4u));
@@ -119,21 +130,16 @@ __global__ __launch_bounds__(256) void conv_f32_mfma_kernel(ConvArgs a, int nchu
 #pragma unroll
             for (int g = 0; g < 2; ++g) r[mi][g] = __builtin_amdgcn_raw_buffer_load_b128(rs_w, w_off[mi], blk + g * 1024u, 0);
     };
-    auto fetch = [&](int chunk, int row) __attribute__((always_inline)) -> float4 {
-        const long long n = row0 + row;
-        float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (row < xrows && n >= 0 && n < nrows_in && chunk * KC + piece * 4 < a.cin)
-            v = *reinterpret_cast<const float4*>(x + (long long)row * a.cin + chunk * KC);
-        return v;
+    auto fetch = [&](int chunk, int row) __attribute__((always_inline)) -> u32x4 {
+        const int c = chunk * KC + piece * 4;            // past the last channel: out of range
+        return __builtin_amdgcn_raw_buffer_load_b128(rs_x, c < a.cin ? (unsigned)((row - before) * a.cin + c) * 4u : 0xf8000000u, 0, 0);
     };
-    float4 rx[XI];
+    u32x4 rx[XI];
     auto load_x = [&](int chunk) __attribute__((always_inline)) {
 #pragma unroll
         for (int it = 0; it < XI; ++it) rx[it] = fetch(chunk, xr0 + it * 32);
     };
-    auto put = [&](int row, float4 v) __attribute__((always_inline)) {
-        if (row < xrows) *reinterpret_cast<float4*>(&xs[row * KC + ((piece ^ (row & 7)) * 4)]) = v;
-    };
+    auto put = [&](int row, u32x4 v) __attribute__((always_inline)) { *reinterpret_cast<u32x4*>(&xs[row * KC + ((piece ^ (row & 7)) * 4)]) = v; };
     auto store_x = [&](int chunk) __attribute__((always_inline)) {
 #pragma unroll
         for (int it = 0; it < XI; ++it) put(xr0 + it * 32, rx[it]);
@@ -156,10 +162,17 @@ __global__ __launch_bounds__(256) void conv_f32_mfma_kernel(ConvArgs a, int nchu
     store_x(0);
     __syncthreads();
 
+    load_x(1);
     int tap = 0, chunk = 0;
-    auto body = [&](int stage, auto U) __attribute__((always_inline)) {
-        constexpr int u = decltype(U)::value;
-        if (tap == 0 && chunk + 1 < nchunks) load_x(chunk + 1);
+    auto body = [&](int stage, int u) __attribute__((always_inline)) {
+        if (tap == a.ntaps) {
+            tap = 0;
+            ++chunk;
+            __syncthreads();
+            store_x(chunk);
+            __syncthreads();
+            load_x(chunk + 1);
+        }
         const int off = base + tap * step - minoff;
         int row[TN];
 #pragma unroll
@@ -178,48 +191,40 @@ __global__ __launch_bounds__(256) void conv_f32_mfma_kernel(ConvArgs a, int nchu
                         acc[mi][ni] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(wr[u][mi][g][e]), xv[ni][e], acc[mi][ni], 0, 0, 0);
         }
         load_w(wr[u], stage + PF);
-        if (++tap == a.ntaps) {
-            tap = 0;
-            if (++chunk < nchunks) {
-                __syncthreads();
-                store_x(chunk);
-                __syncthreads();
-            }
-        }
+        ++tap;
     };
-    for (int stage = 0; stage < nstages; stage += PF) {
-        body(stage, std::integral_constant<int, 0>{});
-        if (stage + 1 < nstages) body(stage + 1, std::integral_constant<int, 1>{});
-        if constexpr (PF == 4) {
-            if (stage + 2 < nstages) body(stage + 2, std::integral_constant<int, 2>{});
-            if (stage + 3 < nstages) body(stage + 3, std::integral_constant<int, 3>{});
+    for (int stage = 0; stage < nstages; stage += PF)
+#pragma unroll
+        for (int u = 0; u < PF; ++u) {
+            if (stage + u >= nstages) break;
+            body(stage + u, u);
         }
-    }
 
     // ---- epilogue: lane (j, q) holds rows 4 q + {0..3} of column j of every accumulator tile
+    __syncthreads();                                     // the activation tile has been read
+    f32x4* own = reinterpret_cast<f32x4*>(xs) + wave * (TM * TN * 64) + lane;
+#pragma unroll
+    for (int mi = 0; mi < TM; ++mi)
+#pragma unroll
+        for (int ni = 0; ni < TN; ++ni) own[(mi * TN + ni) * 64] = acc[mi][ni];
     const long long rowbase_o = (long long)s.row0 * r_out;
     const float* res = (const float*)a.res;
-#pragma unroll
-    for (int mi = 0; mi < TM; ++mi) {
-        const int mu = m0 + (wm * TM + mi) * 16 + 4 * q;
-        if (mu >= M) continue;
+#pragma unroll 1
+    for (int i = 0; i < TM * TN; ++i) {
+        const int mu = m0 + (wm * TM + i / TN) * 16 + 4 * q;
         const int phi = a.stride > 0 ? mu / a.cout : 0, o = mu - phi * a.cout;
-        f32x4 al = {0.f, 0.f, 0.f, 0.f}, ib = al;
-        if (a.out_alpha) { al = *reinterpret_cast<const f32x4*>(a.out_alpha + o); ib = *reinterpret_cast<const f32x4*>(a.out_inv_beta + o); }
+        const long long col = n0 + (wn * TN + i % TN) * 16 + j;
+        const long long n = a.stride > 0 ? col * a.stride - a.stride / 2 + phi : col;
+        if (mu >= M || n < 0 || n >= out_hi) continue;
+        const size_t idx = (size_t)(rowbase_o + n) * a.cout + o;
+        f32x4 v = own[i * 64];
+        if (res) v += *reinterpret_cast<const f32x4*>(res + idx);
+        if (a.y) *reinterpret_cast<f32x4*>((float*)a.y + idx) = v;
+        if (a.ya) {
+            const f32x4 al = *reinterpret_cast<const f32x4*>(a.out_alpha + o), ib = *reinterpret_cast<const f32x4*>(a.out_inv_beta + o);
 #pragma unroll
-        for (int ni = 0; ni < TN; ++ni) {
-            const long long col = n0 + (wn * TN + ni) * 16 + j;
-            const long long n = a.stride > 0 ? col * a.stride - a.stride / 2 + phi : col;
-            if (n < 0 || n >= out_hi) continue;
-            const size_t idx = (size_t)(rowbase_o + n) * a.cout + o;
-            f32x4 v = acc[mi][ni];
-            if (res) v += *reinterpret_cast<const f32x4*>(res + idx);
-            if (a.y) *reinterpret_cast<f32x4*>((float*)a.y + idx) = v;
-            if (a.ya) {
-#pragma unroll
-                for (int e = 0; e < 4; ++e) v[e] = snake_precise(v[e], al[e], ib[e]);
-                *reinterpret_cast<f32x4*>((float*)a.ya + idx) = v;
-            }
+            for (int e = 0; e < 4; ++e) v[e] = snake_precise(v[e], al[e], ib[e]);
+            *reinterpret_cast<f32x4*>((float*)a.ya + idx) = v;
         }
     }
 }
@@ -319,7 +324,12 @@ hipError_t launch_conv_f32(const ConvArgs& a, hipStream_t stream)
                 grid = dim3((unsigned)gx, (unsigned)a.n_slots, (unsigned)gz);
             }
         }
-        const size_t lds = (size_t)xrows * F_KC * 4;
+        // the activation tile, then the accumulators
+        size_t lds = 0;
+        if (best >= 0) {
+            const Tile& t = kTiles[best];
+            lds = std::max((size_t)std::max(xrows, f32_rows_in_registers(16 * t.tn * t.wn)) * F_KC * 4, (size_t)(4 * t.tm * t.tn) * 1024);
+        }
         switch (best) {
             case 0: hipLaunchKernelGGL((conv_f32_mfma_kernel<4, 4, 2, 2>), grid, dim3(256), lds, stream, a, nchunks, xrows); return hipGetLastError();
             case 1: hipLaunchKernelGGL((conv_f32_mfma_kernel<2, 2, 2, 2>), grid, dim3(256), lds, stream, a, nchunks, xrows); return hipGetLastError();

@@ -54,3 +54,34 @@ def test_scalar_offsets_stay_inside_the_descriptor(src):
 def test_the_parameter_allocation_ends_with_the_slack():
     text = open(os.path.join(b.CSRC, "api.hip")).read()
     assert re.search(r"ar\.reserve\(kWeightSlack\);\s*hipError_t e = hipMalloc\(&v->d_params, ar\.bytes\.size\(\)\)", text)
+
+
+def _resources():
+    """{kernel: (bytes of scratch memory, spilled registers)} of the gfx950 code in the built library."""
+    import subprocess
+    import tempfile
+    llvm = "/opt/rocm/llvm/bin"
+    if not (os.path.exists(b.LIB) and os.path.exists(os.path.join(llvm, "llvm-readelf"))):
+        pytest.skip("no built library or no LLVM tools")
+    out = {}
+    with tempfile.TemporaryDirectory() as d:
+        fat, one, elf = (os.path.join(d, n) for n in ("fat", "one", "elf"))
+        subprocess.run([f"{llvm}/llvm-objcopy", f"--dump-section=.hip_fatbin={fat}", b.LIB, os.path.join(d, "copy")], check=True)
+        data = open(fat, "rb").read()
+        starts = [m.start() for m in re.finditer(b"__CLANG_OFFLOAD_BUNDLE__", data)] + [len(data)]
+        for lo, hi in zip(starts, starts[1:]):
+            open(one, "wb").write(data[lo:hi])
+            subprocess.run([f"{llvm}/clang-offload-bundler", "--unbundle", "--type=o", f"--input={one}", f"--output={elf}",
+                            "--targets=hipv4-amdgcn-amd-amdhsa--gfx950"], check=True)
+            notes = subprocess.run([f"{llvm}/llvm-readelf", "--notes", elf], capture_output=True, text=True, check=True).stdout
+            for k in notes.split("- .agpr_count:")[1:]:
+                field = lambda f: re.search(rf"\.{f}:\s+(\S+)", k).group(1)
+                out[field("name")] = int(field("private_segment_fixed_size")), int(field("vgpr_spill_count"))
+    return out
+
+
+def test_convolution_kernels_keep_their_accumulators_in_registers():
+    """A dynamic index into the accumulators puts them in scratch memory, a round trip per stage of the K loop."""
+    res = {n: r for n, r in _resources().items() if "conv_" in n or "res_unit_wide" in n}
+    assert len(res) > 100
+    assert {n: r for n, r in res.items() if r != (0, 0)} == {}
