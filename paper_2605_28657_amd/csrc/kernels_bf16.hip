@@ -429,7 +429,7 @@ __global__ __launch_bounds__(64 * WM * WN) void conv_mfma_kernel(MfmaParams p)
             if (MODE == MODE_RES) {
 #pragma unroll
                 for (int k = 0; k < PW; ++k)
-                    v[k] += (float)__builtin_bit_cast(_Float16, (uint16_t)(resv[ni][gq] >> (16 * k)));
+                    v[k] = keep_f32(v[k] + (float)__builtin_bit_cast(_Float16, (uint16_t)(resv[ni][gq] >> (16 * k))));
             }
             if (MODE != MODE_ACT) {
                 // half store of h; the next layer's operand is Snake of the STORED value

@@ -288,7 +288,7 @@ __global__ __launch_bounds__(256) void res_unit_wide_kernel(WideParams p)
         const f16x8 r = __builtin_bit_cast(f16x8, resv[gq]);
         f16x8 o;
 #pragma unroll
-        for (int mo = 0; mo < TM; ++mo) o[mo] = (_Float16)(acc[mo][gq] + (float)r[mo]);     // round to nearest even
+        for (int mo = 0; mo < TM; ++mo) o[mo] = (_Float16)keep_f32(acc[mo][gq] + (float)r[mo]);     // fp32 sum, then one rounding
         __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, o), rs_y, off, 0, 0);
         if (EMIT) {
             // the next layer's operand is Snake of the STORED value
