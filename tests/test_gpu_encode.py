@@ -218,8 +218,8 @@ def test_every_layer_against_oracle_primitives(dtype, spec):
 
 
 def test_four_clips_in_one_call_and_graph_replay():
-    """A batch of clips equals clip-by-clip encodes bit for bit; an encode recorded into a HIP graph (two window groups on
-    two streams, a grid never seen before the capture) replays to the eager result, also after the waveform changed in place."""
+    """A batch of clips equals clip-by-clip encodes bit for bit; an encode recorded into a HIP graph (a grid never seen
+    before the capture) replays to the eager result, also after the waveform changed in place."""
     spec, T = di.DecoderSpec(64, (4, 2), (128, 64), (1, 3, 9)), 40
     enc, w, x, eps = make(spec, "bf16", T, n_clips=4, max_extended_frames=4 * 5 * T)
     xt, et = dev(x), dev(eps)

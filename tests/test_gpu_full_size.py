@@ -60,7 +60,8 @@ def test_single_clip_windowed_full_and_oracle_samples(name, starts):
 def test_10s_clip_whole_against_the_oracle_with_every_kernel_variant():
     """configs[1] element by element over the whole clip (the f64 oracle decodes 10 s in seconds), for the default
     kernels and for each alternative the config selects: hi + lo bf16 operands on the wide levels, unfused residual
-    units, one stream, no small tiles.  Each variant also reproduces its own full decode bit for bit."""
+    units, one stream, no small tiles.  Each variant also reproduces its own full decode bit for bit, in windows of 64 frames
+    and in windows of 32, which are enough frames for two groups of windows on two streams (but with the one-stream flag)."""
     wl = di.WORKLOADS["full_10s_bf16"]
     weights, lat = di.workload_inputs(wl)
     ref = oracle.decode(SPEC, weights, lat[0])
@@ -69,10 +70,11 @@ def test_10s_clip_whole_against_the_oracle_with_every_kernel_variant():
     base = None
     for name, kw in [("default", {}), ("bf16x2", dict(wide_operands=2)), ("unfused", dict(flags=DEMON_VAE_FLAG_NO_FUSED)),
                      ("one stream", dict(flags=DEMON_VAE_FLAG_ONE_STREAM)), ("large tiles only", dict(small_tile_wgs=-1))]:
-        vae = DemonVAE(SPEC, weights, dtype="bf16", max_frames=wl.n_frames, max_extended_frames=n_windows * (wl.window + 2 * H), **kw)
+        vae = DemonVAE(SPEC, weights, dtype="bf16", max_frames=wl.n_frames, max_extended_frames=2 * n_windows * (wl.window // 2 + 2 * H), **kw)
         win = vae.decode_windowed(zt, window=wl.window, halo=-1)
         full = vae.decode(zt)
         assert torch.equal(win, full), name
+        assert torch.equal(vae.decode_windowed(zt, window=wl.window // 2, halo=-1), full), name
         g = win[0].cpu().numpy()
         ma, rl = assert_close(g, ref, "bf16", name)
         print(f"10 s clip, {name}: max-abs {ma:.3e} rel-L2 {rl:.3e} over {g.size} samples")

@@ -314,9 +314,9 @@ print("ok")
 
 
 def test_small_grid_tile_is_bit_identical_to_the_large_tile(tmp_path):
-    """Launches with few workgroups use a 64 x 64 tile on the same packed weights (here: every generic launch, the
-    inputs are short); DEMON_VAE_SMALL_TILE_WGS=0 in a subprocess keeps the 128 x 128 tile.  Same K order, so the two
-    decodes must agree bit for bit."""
+    """Launches with few workgroups use smaller tiles on the same packed weights (here: every generic launch, the inputs
+    are short); DEMON_VAE_SMALL_TILE_WGS=0 in a subprocess keeps the 128 x 128 tile (and the LDS-staged 256-channel unit).
+    Same K order, so the two decodes must agree bit for bit."""
     import os
     import subprocess
     import sys
@@ -350,9 +350,10 @@ print("ok")
     assert np.all(np.isfinite(got["small"])) and np.abs(got["small"]).max() > 1e-3
 
 
-def test_wide_column_tile_is_bit_identical_to_the_square_tile():
-    """Dilated convs with many columns run a 128 x 256 tile on the same packed weights, in the same K order: a long clip
-    on a stack with a 512-channel level selects it (one window: 2 x 17000 rows, 4 row tiles), the flag switches it off."""
+def test_one_window_of_a_long_clip_equals_its_small_windows():
+    """One window of 17000 frames takes the 128 x 128 tile without further ado (2 x 17000 rows, 4 row tiles at the 512-channel
+    level: more of them than small_tile_wgs), windows of a few frames the smallest tiles.  NO_WIDE_TILE is still accepted and
+    changes nothing."""
     spec = di.DecoderSpec(64, (2, 2), (512, 64), (1, 9))
     T = 17000
     vae, w, z = make(spec, "bf16", T, max_extended_frames=T)
@@ -362,6 +363,10 @@ def test_wide_column_tile_is_bit_identical_to_the_square_tile():
     b = ref_vae.decode(zt)
     torch.cuda.synchronize()
     assert torch.equal(a, b)
+    S = spec.total_stride
+    for begin, n in ((0, 5), (8190, 31), (16900, 100)):
+        win = vae.decode_windowed(zt, window=n, halo=-1, frame_begin=begin, frame_end=begin + n)
+        assert torch.equal(win[:, :, begin * S:(begin + n) * S], a[:, :, begin * S:(begin + n) * S]), (begin, n)
     # and against the oracle on the first frames (a clip edge and the interior of the first tiles)
     ref = oracle.decode_windowed(spec, w, z[0], window=24, halo=max(oracle.receptive_field(spec)), frame_begin=0, frame_end=24)
     assert_close(a[0, :, :24 * spec.total_stride].cpu().numpy(), ref, "bf16", "first frames")
@@ -565,7 +570,7 @@ def test_playback_window_decode_replays_from_a_hip_graph():
     zt = to_device(z, "bf16")
     out_eager = torch.zeros((1, spec.out_channels, T * S), device="cuda:0")
     out_graph = torch.zeros_like(out_eager)
-    # two windows: the two halves of the layer sequence run on two streams, forked from and joined into the captured one
+    # two windows in one launch sequence (calls that run as two groups on two streams: test_gpu_groups.py)
     args = dict(window=13, halo=-1, frame_begin=30, frame_end=55)
     vae.decode_windowed(zt, out=out_eager, **args)              # also caches the plan (its slot table is uploaded here)
     torch.cuda.synchronize()

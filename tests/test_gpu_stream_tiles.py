@@ -1,6 +1,6 @@
 """The bf16 convolutions that stream their weights: every tile the launch can choose (the choice follows the size of the call
-only), remainders of columns at every tile, both operand formats, one- and two-plane operands, and kernel sizes that take
-the LDS kernel.  Every tile adds in the same order, so a handle restricted to the largest tile gives the same bits."""
+only), remainders of columns at every tile, both operand formats, one- and two-plane operands, taps unrolled and counted at
+run time.  Every tile adds in the same order, so a handle restricted to the largest tile gives the same bits."""
 import numpy as np
 import pytest
 import torch
@@ -19,7 +19,7 @@ pytestmark = pytest.mark.gpu
     (di.DecoderSpec(64, (2, 2), (512, 256), (3, 9)), 501, dict(flags=1)),            # 64 x 64 / 80 / 96, unfused 256 channels
     (di.DecoderSpec(64, (2, 2), (512, 128), (1, 9)), 3001, dict(flags=1)),           # up to the 128 x 128 tile in one call
     (di.DecoderSpec(64, (2, 2), (512, 128), (9,)), 129, dict(wide_operands=2)),      # hi + lo operand planes
-    (di.DecoderSpec(64, (2, 2), (512, 128), (1, 3), res_kernel=5), 130, dict(flags=1)),      # five taps: the LDS kernel
+    (di.DecoderSpec(64, (2, 2), (512, 128), (1, 3), res_kernel=5), 130, dict(flags=1)),      # five taps
 ])
 def test_stream_tiles(spec, T, kw):
     vae, w, z = make(spec, "bf16", T, max_extended_frames=T, **kw)
