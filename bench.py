@@ -22,18 +22,34 @@ PEAK_BF16_TFLOPS = 2500.0      # MI355X dense bf16 MFMA
 PEAK_HBM_GBS = 8000.0
 
 
+def kernel_sources_digest():
+    """Digest of the library's device code, without comments and white space: what a counter profile was taken of."""
+    import glob
+    import hashlib
+    import re
+    h = hashlib.sha256()
+    for path in sorted(glob.glob(os.path.join(ROOT, "paper_2605_28657_amd", "csrc", "*"))):
+        if path.endswith((".hip", ".h", ".cpp")) and not path.endswith("mfma_probe.hip"):
+            text = re.sub(r"//[^\n]*|/\*.*?\*/", "", open(path).read(), flags=re.S)
+            h.update(os.path.basename(path).encode() + re.sub(r"\s+", "", text).encode())
+    return h.hexdigest()[:16]
+
+
 def measured_traffic(workload):
     """HBM bytes per step of the convolution kernels from the committed rocprofv3 counter summary of this workload
-    (FETCH_SIZE + WRITE_SIZE, scaled by a plain copy; not collectable inside this process), or None.  The summary
-    names the source revision it was measured on; a kernel change makes it stale until the profile is taken again."""
+    (FETCH_SIZE + WRITE_SIZE, scaled by a plain copy; not collectable inside this process), or None: where there is no
+    summary, or it was taken of other kernels than these (it names the digest of their sources)."""
     path = os.path.join(ROOT, "profiles", f"{workload}_hbm_traffic.txt")
+    traffic = digest = None
     try:
         for line in open(path):
             if line.startswith("MFMA convolution kernels, bytes per step:"):
-                return int(line.split(":")[1].split()[0])
+                traffic = int(line.split(":")[1].split()[0])
+            elif line.startswith("Kernel sources:"):
+                digest = line.split(":")[1].split()[0]
     except (OSError, ValueError):
-        pass
-    return None
+        return None
+    return traffic if digest == kernel_sources_digest() else None
 
 
 def mfma_probe_rates(seconds=1.0):
@@ -237,12 +253,13 @@ def main():
                                 "channels on (f16 MFMA); fp32 accumulation; residual stream stored as IEEE half")
                    if wl.bf16 else "fp32"},
         "roofline": {
-            "kernel": "MFMA convolution kernels (conv_mfma_kernel, res_unit_wide_kernel, res_unit_fused_kernel): all %d "
+            "kernel": "MFMA convolution kernels (conv_stream_kernel, res_unit_wide_kernel, res_unit_wide_stream_kernel, "
+                      "res_unit_fused_kernel; conv_mfma_kernel for widths that are no multiple of 128): all %d "
                       "convolution layers of a step" % n_conv_launches,
             "bound": "mfma", "achieved": achieved, "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
             "frac": achieved / PEAK_BF16_TFLOPS,
             # L2 miss traffic of these kernels per step from rocprofv3 FETCH_SIZE + WRITE_SIZE (bytes, scaled by a plain
-            # copy), read from profiles/<workload>_hbm_traffic.txt; null where no such profile is committed
+            # copy), read from profiles/<workload>_hbm_traffic.txt; null where no such profile of these kernels is committed
             "traffic": measured_traffic(args.workload),
             "algorithmic_flop": conv_f * frames,
             "time_ms": conv_ms,

@@ -99,8 +99,10 @@ typedef struct {
                              2 = hi + lo bf16 pairs on the bf16 MFMA (two MFMAs per k-step in the transposed and 1x1
                              convolutions) for stacks whose wide-level activations may leave the half range */
     int flags;            /* DEMON_VAE_FLAG_* */
-    int small_tile_wgs;   /* launches of at most this many 128 x 128 tiles may use smaller tiles instead (bit-identical
-                             results, more workgroups for a single playback window); default 1024, negative = never */
+    int small_tile_wgs;   /* convolutions outside the fused units: launches of at most this many 128 x 128 tiles may use
+                             smaller tiles instead (bit-identical results, more workgroups for a single playback
+                             window); default 1024, negative = never, and then the 256-channel unit keeps its
+                             LDS-staged kernel too (any other value leaves that unit its own choice) */
 } demon_vae_config;
 
 /* One window of the grid: interior latent frames [begin, end) of clip `clip`, decoded from the

@@ -531,7 +531,7 @@ demon_status run_pass(demon_vae* v, const Workspace& ws, const Plan* plan, const
                 f.slots = gs; f.n_slots = gn; f.call_slots = ns; f.max_len = ml; f.max_int = plan->max_int; f.margin = U.pointwise.margin;
                 f.r = r; f.c = U.dilated.cin; f.ntaps = U.dilated.ntaps; f.dil = U.dilated.dil;
                 if (C && C->in_fmt != OP_BF16) return fail(DEMON_ERR_UNSUPPORTED, "a fused unit cannot feed a layer with wide operands");
-                f.max_small = v->small_tile_wgs;
+                f.staged_only = v->small_tile_wgs == 0;
                 HIP_TRY(launch_res_unit_wide(f, gst), "fused residual unit (256 channels)");
                 if (C) std::swap(acur, aoth);
                 HIP_TRY(mark(2), "event");

@@ -140,7 +140,7 @@ struct WideArgs {
     const float* b7; const float* b1; const float* a2; const float* ib2;
     const Slot* slots; int n_slots, call_slots, max_len, max_int, margin;
     int r, c, ntaps, dil;
-    long long max_small = 0;           // 0: the LDS-staged kernel always (small_tile_wgs of the config)
+    bool staged_only = false;          // the LDS-staged kernel also in launches of few tiles (small_tile_wgs < 0 in the config)
 };
 hipError_t launch_res_unit_wide(const WideArgs& a, hipStream_t stream);
 void pack_w1_wide(const float* w /*[256][256]*/, uint16_t* dst);

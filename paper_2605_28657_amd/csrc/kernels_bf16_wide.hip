@@ -536,7 +536,7 @@ hipError_t launch_res_unit_wide(const WideArgs& a, hipStream_t stream)
     else hipLaunchKernelGGL((res_unit_wide_stream_kernel<TN, false>), grid(16 * TN), dim3(512), 0, stream, p); \
     return hipGetLastError();
     int tn = 0;
-    if (a.ntaps == 7 && a.max_small > 0)
+    if (a.ntaps == 7 && !a.staged_only)
         for (long long wgs : {256, 512})
             for (int t : {2, 4, 5, 6, 8}) if (tn == 0 && tiles(16 * t) * a.call_slots <= wgs) tn = t;
     switch (tn) { DEMON_STREAM(2) DEMON_STREAM(4) DEMON_STREAM(5) DEMON_STREAM(6) DEMON_STREAM(8) default: break; }
