@@ -13,7 +13,7 @@
 // A CU takes some 45 bytes of weights per clock in, whether they hit its L1 or not, and reads 190 bytes per clock from LDS: the
 // large tile gives every wave 32 rows x 128 columns (8 KB of weights and 32 KB of LDS reads per 288 cycles of MFMAs).
 // Measured, LDS-staged tile -> here: 1024-channel dilated conv 46 -> 9.6 us (200 columns), 47 -> 17 (830), 258 -> 214 (17000);
-// 512 channels 34 -> 21 (4700), 333 -> 298 (100000: 1.23 PFLOP/s); 1x1 conv of 1024 channels 13 -> 5 (200), 14 -> 7.6 (830);
+// 512 channels 34 -> 21 (4700), 60 s clip 297 (a 128 x 256 tile) -> 266 (1.24 PFLOP/s); 1x1 conv of 1024 channels 13 -> 5 (200), 14 -> 7.6 (830);
 // strided conv 1024 -> 128, stride 10: 146 -> 25 (75 columns).
 // Every tile adds in the same order (chunk, tap, k-step, for two operand planes hi before lo), so a value does not depend on the tile.
 #include <algorithm>

@@ -18,6 +18,7 @@ pytestmark = pytest.mark.gpu
     (di.DecoderSpec(256, (2,), (64,), (1, 9)), 400, 150, 2, {}),                # widest at the latent; the cut inside a clip
     (di.DecoderSpec(64, (2, 2), (512, 128), (1,)), 161, 40, 3, dict(wide_operands=2)),
     (di.DecoderSpec(32, (4, 2), (96, 32)), 200, 37, 1, {}),                     # LDS-staged tiles
+    (di.DecoderSpec(64, (4, 2), (96, 64), (1, 3)), 170, 60, 1, {}),             # LDS-staged tiles, the head inside the last unit
 ])
 def test_two_groups_equal_one_stream(spec, T, window, clips, kw):
     vae, w, z = make(spec, "bf16", T, n_clips=clips, max_extended_frames=8 * T * clips, **kw)
