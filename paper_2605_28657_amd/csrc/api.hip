@@ -481,73 +481,73 @@ demon_status run_pass(demon_vae* v, const Workspace& ws, const Plan* plan, const
         }
         HIP_TRY(mark(1), "event");
         auto layers = [&]() -> demon_status {
-        cur = ws.buf[0]; other = ws.buf[1];
-        acur = (uint16_t*)ws.buf[3]; aoth = (uint16_t*)ws.buf[4];
-        r = enc ? S : 1; layer_id = 0;
-        for (size_t si = 0; si < n_steps; ++si) {
-            const Step& T = v->steps[si];
-            const bool last = si + 1 == n_steps;
-            // the layer that consumes this step's output through an activated operand; nullptr when that layer reads the
-            // residual stream itself (narrow fused unit, head, sampling step)
-            const ConvLayer* C = T.consumer;
-            if (T.conv) {
-                ConvArgs a = conv_args(*T.conv, acur, other, nullptr);
-                if (C) { a.ya = at(aoth, resampled(r, *T.conv), T.conv->cout); a.out_alpha = C->in_alpha; a.out_inv_beta = C->in_inv_beta; a.out_fmt = C->in_fmt; }
-                HIP_TRY(launch_conv_bf16(a, T.conv->variant, gst), "resampling convolution");
-                if (C) std::swap(acur, aoth);
-                HIP_TRY(mark(last ? 1 : 2), "event");
-                std::swap(cur, other);
-                r = resampled(r, *T.conv);
-                HIP_TRY(tap(cur, T.conv->cout), "debug tap");
-                continue;
-            }
-            const ResUnit& U = *T.unit;
-            if (U.fused) {
-                FusedArgs f;
-                f.x = at(cur, r, U.dilated.cin); f.y = at(other, r, U.dilated.cin);
-                if (C) { f.ya = at(acur, r, U.dilated.cin); f.a3 = C->in_alpha; f.ib3 = C->in_inv_beta; }
-                f.w7 = (const uint16_t*)U.dilated.w; f.w1 = U.w1_fused;
-                f.b7 = U.dilated.bias; f.b1 = U.pointwise.bias;
-                f.a1 = U.dilated.in_alpha; f.ib1 = U.dilated.in_inv_beta;
-                f.a2 = U.dilated.out_alpha; f.ib2 = U.dilated.out_inv_beta;
-                f.slots = gs; f.n_slots = gn; f.max_len = ml; f.max_int = plan->max_int; f.margin = U.pointwise.margin;
-                f.r = r; f.c = U.dilated.cin; f.ntaps = U.dilated.ntaps; f.dil = U.dilated.dil;
-                if (C && C->in_fmt != OP_BF16) return fail(DEMON_ERR_UNSUPPORTED, "a fused unit cannot feed a layer with wide operands");
-                if (last && head_in_unit) {
-                    f.hw = v->head_wfrag; f.hb = v->head_bias; f.ha = v->head_alpha; f.hib = v->head_inv_beta;
-                    f.hy = ws.head_out; f.total_rows = plan->total_frames * r;
-                    f.oc = v->st.out_channels; f.hk = v->st.head_kernel;
+            cur = ws.buf[0]; other = ws.buf[1];
+            acur = (uint16_t*)ws.buf[3]; aoth = (uint16_t*)ws.buf[4];
+            r = enc ? S : 1; layer_id = 0;
+            for (size_t si = 0; si < n_steps; ++si) {
+                const Step& T = v->steps[si];
+                const bool last = si + 1 == n_steps;
+                // the layer that consumes this step's output through an activated operand; nullptr when that layer reads the
+                // residual stream itself (narrow fused unit, head, sampling step)
+                const ConvLayer* C = T.consumer;
+                if (T.conv) {
+                    ConvArgs a = conv_args(*T.conv, acur, other, nullptr);
+                    if (C) { a.ya = at(aoth, resampled(r, *T.conv), T.conv->cout); a.out_alpha = C->in_alpha; a.out_inv_beta = C->in_inv_beta; a.out_fmt = C->in_fmt; }
+                    HIP_TRY(launch_conv_bf16(a, T.conv->variant, gst), "resampling convolution");
+                    if (C) std::swap(acur, aoth);
+                    HIP_TRY(mark(last ? 1 : 2), "event");
+                    std::swap(cur, other);
+                    r = resampled(r, *T.conv);
+                    HIP_TRY(tap(cur, T.conv->cout), "debug tap");
+                    continue;
                 }
-                HIP_TRY(launch_res_unit_fused(f, gst), "fused residual unit");
-                std::swap(cur, other);
-                HIP_TRY(mark(2), "event");
-            } else if (U.wide) {
-                WideArgs f;
-                f.xa = at(acur, r, U.dilated.cin); f.y = at(cur, r, U.dilated.cin);
-                if (C) { f.ya = at(aoth, r, U.dilated.cin); f.a3 = C->in_alpha; f.ib3 = C->in_inv_beta; }
-                f.w7 = (const uint16_t*)U.dilated.w; f.w1 = U.w1_fused;
-                f.b7 = U.dilated.bias; f.b1 = U.pointwise.bias;
-                f.a2 = U.dilated.out_alpha; f.ib2 = U.dilated.out_inv_beta;
-                f.slots = gs; f.n_slots = gn; f.call_slots = ns; f.max_len = ml; f.max_int = plan->max_int; f.margin = U.pointwise.margin;
-                f.r = r; f.c = U.dilated.cin; f.ntaps = U.dilated.ntaps; f.dil = U.dilated.dil;
-                if (C && C->in_fmt != OP_BF16) return fail(DEMON_ERR_UNSUPPORTED, "a fused unit cannot feed a layer with wide operands");
-                f.staged_only = v->small_tile_wgs == 0;
-                HIP_TRY(launch_res_unit_wide(f, gst), "fused residual unit (256 channels)");
-                if (C) std::swap(acur, aoth);
-                HIP_TRY(mark(2), "event");
-            } else {
-                ConvArgs d = conv_args(U.dilated, acur, nullptr, nullptr);
-                d.ya = at(mid, r, U.dilated.cout); d.out_fmt = U.pointwise.in_fmt;   // Snake between the convolutions: the layer's own out_alpha
-                HIP_TRY(launch_conv_bf16(d, U.dilated.variant, gst), "dilated convolution");
-                HIP_TRY(mark(2), "event");
-                ConvArgs q = conv_args(U.pointwise, mid, cur, cur);   // in place on the residual stream
-                if (C) { q.ya = at(acur, r, U.pointwise.cout); q.out_alpha = C->in_alpha; q.out_inv_beta = C->in_inv_beta; q.out_fmt = C->in_fmt; }
-                HIP_TRY(launch_conv_bf16(q, U.pointwise.variant, gst), "pointwise convolution");
+                const ResUnit& U = *T.unit;
+                if (U.fused) {
+                    FusedArgs f;
+                    f.x = at(cur, r, U.dilated.cin); f.y = at(other, r, U.dilated.cin);
+                    if (C) { f.ya = at(acur, r, U.dilated.cin); f.a3 = C->in_alpha; f.ib3 = C->in_inv_beta; }
+                    f.w7 = (const uint16_t*)U.dilated.w; f.w1 = U.w1_fused;
+                    f.b7 = U.dilated.bias; f.b1 = U.pointwise.bias;
+                    f.a1 = U.dilated.in_alpha; f.ib1 = U.dilated.in_inv_beta;
+                    f.a2 = U.dilated.out_alpha; f.ib2 = U.dilated.out_inv_beta;
+                    f.slots = gs; f.n_slots = gn; f.max_len = ml; f.max_int = plan->max_int; f.margin = U.pointwise.margin;
+                    f.r = r; f.c = U.dilated.cin; f.ntaps = U.dilated.ntaps; f.dil = U.dilated.dil;
+                    if (C && C->in_fmt != OP_BF16) return fail(DEMON_ERR_UNSUPPORTED, "a fused unit cannot feed a layer with wide operands");
+                    if (last && head_in_unit) {
+                        f.hw = v->head_wfrag; f.hb = v->head_bias; f.ha = v->head_alpha; f.hib = v->head_inv_beta;
+                        f.hy = ws.head_out; f.total_rows = plan->total_frames * r;
+                        f.oc = v->st.out_channels; f.hk = v->st.head_kernel;
+                    }
+                    HIP_TRY(launch_res_unit_fused(f, gst), "fused residual unit");
+                    std::swap(cur, other);
+                    HIP_TRY(mark(2), "event");
+                } else if (U.wide) {
+                    WideArgs f;
+                    f.xa = at(acur, r, U.dilated.cin); f.y = at(cur, r, U.dilated.cin);
+                    if (C) { f.ya = at(aoth, r, U.dilated.cin); f.a3 = C->in_alpha; f.ib3 = C->in_inv_beta; }
+                    f.w7 = (const uint16_t*)U.dilated.w; f.w1 = U.w1_fused;
+                    f.b7 = U.dilated.bias; f.b1 = U.pointwise.bias;
+                    f.a2 = U.dilated.out_alpha; f.ib2 = U.dilated.out_inv_beta;
+                    f.slots = gs; f.n_slots = gn; f.call_slots = ns; f.max_len = ml; f.max_int = plan->max_int; f.margin = U.pointwise.margin;
+                    f.r = r; f.c = U.dilated.cin; f.ntaps = U.dilated.ntaps; f.dil = U.dilated.dil;
+                    if (C && C->in_fmt != OP_BF16) return fail(DEMON_ERR_UNSUPPORTED, "a fused unit cannot feed a layer with wide operands");
+                    f.staged_only = v->small_tile_wgs == 0;
+                    HIP_TRY(launch_res_unit_wide(f, gst), "fused residual unit (256 channels)");
+                    if (C) std::swap(acur, aoth);
+                    HIP_TRY(mark(2), "event");
+                } else {
+                    ConvArgs d = conv_args(U.dilated, acur, nullptr, nullptr);
+                    d.ya = at(mid, r, U.dilated.cout); d.out_fmt = U.pointwise.in_fmt;   // Snake between the convolutions: the layer's own out_alpha
+                    HIP_TRY(launch_conv_bf16(d, U.dilated.variant, gst), "dilated convolution");
+                    HIP_TRY(mark(2), "event");
+                    ConvArgs q = conv_args(U.pointwise, mid, cur, cur);   // in place on the residual stream
+                    if (C) { q.ya = at(acur, r, U.pointwise.cout); q.out_alpha = C->in_alpha; q.out_inv_beta = C->in_inv_beta; q.out_fmt = C->in_fmt; }
+                    HIP_TRY(launch_conv_bf16(q, U.pointwise.variant, gst), "pointwise convolution");
+                }
+                HIP_TRY(mark(last ? 1 : 2), "event");
+                HIP_TRY(tap(cur, U.pointwise.cout), "debug tap");
             }
-            HIP_TRY(mark(last ? 1 : 2), "event");
-            HIP_TRY(tap(cur, U.pointwise.cout), "debug tap");
-        }
-        return DEMON_OK;
+            return DEMON_OK;
         };
         if (n_groups == 2) {
             marks_on = false;

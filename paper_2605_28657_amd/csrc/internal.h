@@ -56,9 +56,8 @@ enum OperandFmt { OP_BF16 = 0,     // one bf16 plane
                   OP_F16 = 2 };    // one IEEE half plane, f16 MFMA
 
 // bytes past a layer's packed weights that its kernel may request (and not use), see weight_rsrc; the parameter allocation ends
-// with as many, and a layer's weights are smaller than 4 GB by as many
+// with as many
 constexpr unsigned kWeightSlack = 256 * 1024;
-constexpr unsigned long long kMaxWeightBytes = 0xffffffffull - kWeightSlack;
 
 struct ConvArgs {
     const void* x;        // activated input [rows_in, cin] (fp32 path: fp32; bf16 path: 16-bit operand)

@@ -515,7 +515,7 @@ hipError_t launch_conv_bf16(const ConvArgs& a, int variant, hipStream_t stream)
     p.nchunks = cin / v.KC; p.margin = a.margin;
     p.in_lo_off = a.in_lo_off; p.out_lo_off = a.out_lo_off;
     const size_t wb = (size_t)M * ntaps * cin * 2;
-    if (wb > kMaxWeightBytes) return hipErrorInvalidValue;
+    if (wb > 0xffffffffull) return hipErrorInvalidValue;
     p.w_bytes = (unsigned)wb;
     int mode;
     if (a.down > 0) { p.tap0 = -1; p.tap_step = 1; mode = MODE_DOWN; }

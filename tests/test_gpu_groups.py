@@ -46,6 +46,7 @@ def test_two_groups_equal_one_stream(spec, T, window, clips, kw):
         g.replay()
         torch.cuda.synchronize()
         assert torch.equal(out, ref)
+        assert torch.equal(vae.decode_windowed(zt, window=window, halo=-1), ref)         # eager work between the replays
     vae.close(); one.close()
 
 
