@@ -58,8 +58,9 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base, un
 // layer's last one, and a block index is a load's scalar offset, which the range check does not cover: it compares the per-lane
 // offset with (bytes - scalar offset).  So such a request may not be left to the descriptor: the descriptor reaches over the slack,
 // and the parameter allocation ends with as many bytes (another layer's weights or zeros are read and not used).  Clamping the
-// block index instead costs 1.4 % of a 3 s window (473 -> 480 us).
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t weight_rsrc(const void* base, unsigned bytes) { return make_rsrc(base, bytes > 0xffffffffu - kWeightSlack ? 0xffffffffu : bytes + kWeightSlack); }
+// block index instead costs 1.4 % of a 3 s window (473 -> 480 us).  `bytes` must be scalar and the sum not saturate: a saturated
+// sum is a vector instruction, and with a descriptor in vector registers every load is a loop over its lanes.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t weight_rsrc(const void* base, unsigned bytes) { return make_rsrc(base, bytes + kWeightSlack); }
 
 // Per-lane offset of a request ahead: out of range, so that nothing is read, where the block lies past the layer's last one.
 __device__ __forceinline__ unsigned ahead_voff(unsigned voff, bool in_layer) { return in_layer ? voff : 0xf8000000u; }

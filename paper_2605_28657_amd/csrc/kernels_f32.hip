@@ -72,7 +72,15 @@ void pack_f32(const float* w, int cin, int cout, int ntaps, int stride, float* d
 // (the compiler leads a round's early end through the loop's own test; a round without one, with the remainder after the loop,
 // takes 210 registers instead of 130 and is 4 % slower).  The epilogue takes the accumulators from LDS: sinf is too long to
 // unroll, and a dynamic index into registers had put those of the 128 x 128 tile in scratch memory, written back every stage.
-// 3 s window of the x1920 stack 3297 -> 2974 us, 2 s clip of the x32 one 153 -> 142.
+// 3 s window of the x1920 stack 3297 -> 2974 us, 2 s clip of the x32 one 153 -> 138.
+// A value that every lane holds, in scalar registers: comparisons of 64-bit values are vector instructions, and a descriptor made of
+// their results is not scalar (see weight_rsrc).
+static __device__ __forceinline__ long long uniform64(long long v)
+{
+    return (long long)((unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane((int)v) |
+                       (unsigned long long)(unsigned)__builtin_amdgcn_readfirstlane((int)(v >> 32)) << 32);
+}
+
 constexpr int f32_rows_in_registers(int nt) { return nt <= 32 ? 96 : nt <= 64 ? 128 : 192; }      // rows of the next chunk held
 
 template <int TM, int TN, int WM, int WN>
@@ -94,7 +102,7 @@ __global__ __launch_bounds__(256) void conv_f32_mfma_kernel(ConvArgs a, int nchu
     if (out_hi <= out_lo) return;                        // an empty window (a gated clip)
     const long long col_lo = a.stride > 0 ? (out_lo + a.stride / 2) / a.stride : out_lo;
     const long long col_hi = a.stride > 0 ? (out_hi - 1 + a.stride / 2) / a.stride + 1 : out_hi;
-    const long long n0 = col_lo + (long long)blockIdx.x * NT;
+    const long long n0 = uniform64(col_lo + (long long)blockIdx.x * NT);
     if (n0 >= col_hi) return;
     const int m0 = blockIdx.z * MT;
 
@@ -109,7 +117,7 @@ __global__ __launch_bounds__(256) void conv_f32_mfma_kernel(ConvArgs a, int nchu
     const int wm = wave / WN, wn = wave % WN, j = lane & 15, q = lane >> 4;
     const int piece = tid & 7, xr0 = tid >> 3;
     // the tile's rows inside the window: rows outside read as zero
-    const long long row_lo = max(0ll, row0), row_hi = max(row_lo, min(nrows_in, row0 + xrows));
+    const long long row_lo = uniform64(max(0ll, row0)), row_hi = uniform64(max(row_lo, min(nrows_in, row0 + xrows)));
     const __amdgpu_buffer_rsrc_t rs_x = make_rsrc((const float*)a.x + ((long long)s.row0 * a.r_in + row_lo) * a.cin,
                                                   (unsigned)(row_hi - row_lo) * (unsigned)a.cin * 4u);
     const int before = (int)(row_lo - row0);             // staged rows before the window; their offsets wrap: out of range

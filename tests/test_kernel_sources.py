@@ -85,3 +85,29 @@ def test_convolution_kernels_keep_their_accumulators_in_registers():
     res = {n: r for n, r in _resources().items() if "conv_" in n or "res_unit_wide" in n}
     assert len(res) > 100
     assert {n: r for n, r in res.items() if r != (0, 0)} == {}
+
+
+def test_descriptors_are_scalar():
+    """A buffer descriptor held in vector registers turns every load through it into a loop over the lanes' values
+    (v_readfirstlane of all four words, a compare, a branch back)."""
+    import shutil
+    import subprocess
+    import tempfile
+    from concurrent.futures import ThreadPoolExecutor
+    if shutil.which("hipcc") is None:
+        pytest.skip("hipcc not available")
+    flags = [f for f in b.FLAGS if f != "-fPIC"]
+
+    def asm_of(src):
+        with tempfile.TemporaryDirectory() as d:
+            out = os.path.join(d, "k.s")
+            subprocess.run(["hipcc"] + flags + ["-S", "--cuda-device-only", "-o", out, os.path.join(b.CSRC, src)], check=True, capture_output=True)
+            return open(out).read()
+
+    # (the narrow fused unit that runs the head as well reads its window table into vector registers and does loop: not in the list)
+    srcs = ["kernels_bf16_stream.hip", "kernels_bf16.hip", "kernels_bf16_wide.hip", "kernels_f32.hip"]
+    with ThreadPoolExecutor(max_workers=len(srcs)) as ex:
+        for src, text in zip(srcs, ex.map(asm_of, srcs)):
+            # the loop's mark: descriptor words compared with the lanes' own, then the lanes that agree masked in
+            loops = re.findall(r"v_cmp_eq_u64_e\w+ [^\n]*\n(?:[^\n]*\n){0,8}?[^\n]*s_and_saveexec_b64", text)
+            assert not loops, f"{src}: {len(loops)} loops over a descriptor's lanes"
