@@ -98,9 +98,9 @@ __global__ __launch_bounds__(256) void res_unit_wide_kernel(WideParams p)
     u32x4 ra[A_ITERS], rb[A_ITERS];     // rb: second set, only for the blocks of the 1x1 weights (requested two ahead)
     u32x4 rx[X_ITERS];
     auto load_set = [&](u32x4 (&r)[A_ITERS], __amdgpu_buffer_rsrc_t rs, int block) __attribute__((always_inline)) {
-        const unsigned base = (unsigned)block * (W_A_CH * 16u), voff = ahead_voff(a_voff, block < nstages);
+        const unsigned base = (unsigned)block * (W_A_CH * 16u);
 #pragma unroll
-        for (int it = 0; it < A_ITERS; ++it) r[it] = __builtin_amdgcn_raw_buffer_load_b128(rs, voff, base + it * 4096u, 0);
+        for (int it = 0; it < A_ITERS; ++it) r[it] = __builtin_amdgcn_raw_buffer_load_b128(rs, a_voff, base + it * 4096u, 0);
     };
     auto store_set = [&](const u32x4 (&r)[A_ITERS], int buf) __attribute__((always_inline)) {
 #pragma unroll
@@ -190,14 +190,14 @@ __global__ __launch_bounds__(256) void res_unit_wide_kernel(WideParams p)
     };
     // Weight blocks are requested two stages ahead, alternating between the two register sets (the second set is otherwise
     // only used by the 1x1 convolution): with one workgroup per CU (a single playback window) nothing else hides the
-    // latency of a block's load, and one stage of MFMAs is shorter than it.  The request is unconditional (past the last
-    // block nothing is read): behind a branch the compiler could not count it, and the wait for the older block
-    // would wait for it as well.
-    auto iter = [&](int stage, u32x4 (&rload)[A_ITERS], const u32x4 (&rstore)[A_ITERS]) __attribute__((always_inline)) {
+    // latency of a block's load, and one stage of MFMAs is shorter than it.  The request is unconditional: behind a
+    // branch the compiler could not count it, and the wait for the older block would wait for it as well.  In place of the block
+    // past the last one the first block of the 1x1 weights is requested.
+    auto iter = [&](int stage, u32x4 (&rload)[A_ITERS], const u32x4 (&rstore)[A_ITERS], __amdgpu_buffer_rsrc_t rs, int block) __attribute__((always_inline)) {
         int ntap = tap + 1, nchunk = chunk;
         if (ntap == p.ntaps) { ntap = 0; ++nchunk; }
         const bool new_chunk = nchunk != chunk;
-        load_set(rload, rs_w7, stage + 2);
+        load_set(rload, rs, block);
         if (new_chunk) load_x(nchunk);
         mma_stage(stage);
         if (new_chunk) {
@@ -209,11 +209,12 @@ __global__ __launch_bounds__(256) void res_unit_wide_kernel(WideParams p)
         tap = ntap; chunk = nchunk;
     };
     load_set(rb, rs_w7, 1);
-    for (int stage = 0; stage + 1 < nstages; stage += 2) {
-        iter(stage, ra, rb);
-        if (stage + 2 < nstages) iter(stage + 1, rb, ra);
+    static_assert(W_NCHUNKS % 2 == 0, "an even number of stages");
+    for (int stage = 0; stage + 2 < nstages; stage += 2) {
+        iter(stage, ra, rb, rs_w7, stage + 2);
+        iter(stage + 1, rb, ra, rs_w7, stage + 3);
     }
-    load_set(ra, rs_w1, 0);
+    iter(nstages - 2, ra, rb, rs_w1, 0);
     mma_stage(nstages - 1);
 
     // ---- Snake on the accumulators; repack them as the B fragments of the 1x1 conv (k step kk = 2 mi + g/2)
