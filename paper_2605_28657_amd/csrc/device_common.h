@@ -54,8 +54,8 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base, un
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, (int)bytes, 0x00020000);
 }
 
-// Descriptor of a layer's packed weights.  The kernels request blocks ahead, unconditionally, up to kWeightSlack bytes past the
-// layer's last one, and a block index is a load's scalar offset, which the range check does not cover: it compares the per-lane
+// Descriptor of a layer's packed weights.  Kernels whose last stage is not on its own request blocks ahead, unconditionally, up to
+// kWeightSlack bytes past the layer's last one, and a block index is a load's scalar offset, which the range check does not cover: it compares the per-lane
 // offset with (bytes - scalar offset).  So such a request may not be left to the descriptor: the descriptor reaches over the slack,
 // and the parameter allocation ends with as many bytes (another layer's weights or zeros are read and not used).  Clamping the
 // block index instead costs 1.4 % of a 3 s window (473 -> 480 us).  `bytes` must be scalar and the sum not saturate: a saturated

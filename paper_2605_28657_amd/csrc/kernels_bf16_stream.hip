@@ -17,6 +17,7 @@
 // strided conv 1024 -> 128, stride 10: 146 -> 25 (75 columns).
 // Every tile adds in the same order (chunk, tap, k-step, for two operand planes hi before lo), so a value does not depend on the tile.
 #include <algorithm>
+#include <type_traits>
 
 #include "conv_bf16.h"
 
@@ -32,8 +33,9 @@ struct StreamGrid {
 // Tile: WM x WN waves of TM x TN accumulator tiles of 16 rows x 16 columns.
 // NB: activation buffers, 2, or 1 for layers of a single stage.
 // NTAPS: the taps, unrolled, or 0: any number, counted at run time (dilated convs of kernel sizes other than 7).
+// The transposed conv's largest tile keeps to the 168 registers of three workgroups per CU (170: +5 %).
 template <int TM, int TN, int WM, int WN, int NTAPS, int SC, int SPAN, int MODE, int IN, int NB>
-__global__ __launch_bounds__(64 * WM * WN) void conv_stream_kernel(MfmaParams p, StreamGrid sg, int emit)
+__global__ __launch_bounds__(64 * WM * WN, MODE == MODE_UP && TM * TN == 16 && IN != OP_BF16X2 ? 3 : 1) void conv_stream_kernel(MfmaParams p, StreamGrid sg, int emit)
 {
     fp16_saturate_on();
     constexpr int NTH = 64 * WM * WN, MT = 16 * TM * WM, NT = 16 * TN * WN;
@@ -96,7 +98,7 @@ __global__ __launch_bounds__(64 * WM * WN) void conv_stream_kernel(MfmaParams p,
     const int unit0 = sub * (MT / 16) + wm * TM;                             // first unit of this wave in the panel
     const unsigned w_voff = (unsigned)((unit0 & ~3) + (unit0 & 1) * 2 + (unit0 >> 1 & 1)) * 2048u + lane * 16u;
     const unsigned w_tile = (unsigned)panel * (unsigned)nblocks * 16384u;
-    // requests past the panel's last block read the next panel's (nobody's after the last panel) and are not used
+    // any number of taps: requests past the panel's last block read the next panel's (nobody's after the last panel) and are not used
     const bool more_panels = w_tile + (unsigned)nblocks * 16384u < p.w_bytes;
     u32x4 a[RS][TM];
     auto load_a = [&](int block0, int f, unsigned voff) __attribute__((always_inline)) {     // k-step f from block0 on
@@ -243,47 +245,52 @@ __global__ __launch_bounds__(64 * WM * WN) void conv_stream_kernel(MfmaParams p,
             }
         }
         __syncthreads();
-    } else
-    for (int stage = 0; stage < nstages; ++stage) {
-        if (NB == 2) load_x(stage + 1);
-        const unsigned voff_next = ahead_voff(w_voff, more_panels || stage + 1 < nstages);
-        const uint16_t* xs = reinterpret_cast<const uint16_t*>(smem + (NB == 2 ? (stage & 1) * X_BYTES : 0)) + (wn * (16 * TN) + i) * XS * LDR + q * 8;
-        u32x4 x[XD][TN][NP];
-        auto read_x = [&](int f, int ni) __attribute__((always_inline)) {
-            const int ks = f & 1, tap = (f / 2) % NTAPS, c = f / (2 * NTAPS);
-            const uint16_t* xt = xs + (p.tap0 + tap * p.tap_step - minoff) * LDR + c * 64 + ks * 32 + ni * 16 * XS * LDR;
+    } else {
+        // the last stage on its own: nothing is requested past the layer's end
+        auto run_stage = [&](int stage, auto last) __attribute__((always_inline)) {
+            constexpr bool LAST = decltype(last)::value;
+            if (!LAST) load_x(stage + 1);
+            const uint16_t* xs = reinterpret_cast<const uint16_t*>(smem + (NB == 2 ? (stage & 1) * X_BYTES : 0)) + (wn * (16 * TN) + i) * XS * LDR + q * 8;
+            u32x4 x[XD][TN][NP];
+            auto read_x = [&](int f, int ni) __attribute__((always_inline)) {
+                const int ks = f & 1, tap = (f / 2) % NTAPS, c = f / (2 * NTAPS);
+                const uint16_t* xt = xs + (p.tap0 + tap * p.tap_step - minoff) * LDR + c * 64 + ks * 32 + ni * 16 * XS * LDR;
 #pragma unroll
-            for (int pl = 0; pl < NP; ++pl) x[f % XD][ni][pl] = *reinterpret_cast<const u32x4*>(xt + pl * XR * LDR);
-        };
+                for (int pl = 0; pl < NP; ++pl) x[f % XD][ni][pl] = *reinterpret_cast<const u32x4*>(xt + pl * XR * LDR);
+            };
 #pragma unroll
-        for (int f = 0; f < AHEAD && f < F; ++f)
+            for (int f = 0; f < AHEAD && f < F; ++f)
 #pragma unroll
-            for (int ni = 0; ni < TN; ++ni) read_x(f, ni);
-        __builtin_amdgcn_sched_barrier(0);
+                for (int ni = 0; ni < TN; ++ni) read_x(f, ni);
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int f = 0; f < F; ++f) {
+            for (int f = 0; f < F; ++f) {
 #pragma unroll
-            for (int t = 0; t < NP * TN; ++t) {
-                const int pl = t / TN, ni = t % TN;
-                if (pl == 0 && f + AHEAD < F) read_x(f + AHEAD, ni);
-                // activations are the row operand: the accumulator tile is [time][GEMM row].  Two operand planes: the step's hi
-                // values of every column tile, then its lo values, against the same weights.
+                for (int t = 0; t < NP * TN; ++t) {
+                    const int pl = t / TN, ni = t % TN;
+                    if (pl == 0 && f + AHEAD < F) read_x(f + AHEAD, ni);
+                    // activations are the row operand: the accumulator tile is [time][GEMM row].  Two operand planes: the step's hi
+                    // values of every column tile, then its lo values, against the same weights.
 #pragma unroll
-                for (int mi = 0; mi < TM; ++mi) {
-                    const u32x4 w = a[f % RS][mi];
-                    if (IN == OP_F16)
-                        acc[mi][ni] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, x[f % XD][ni][pl]), __builtin_bit_cast(f16x8, w), acc[mi][ni], 0, 0, 0);
-                    else
-                        acc[mi][ni] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, x[f % XD][ni][pl]), __builtin_bit_cast(bf16x8, w), acc[mi][ni], 0, 0, 0);
+                    for (int mi = 0; mi < TM; ++mi) {
+                        const u32x4 w = a[f % RS][mi];
+                        if (IN == OP_F16)
+                            acc[mi][ni] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, x[f % XD][ni][pl]), __builtin_bit_cast(f16x8, w), acc[mi][ni], 0, 0, 0);
+                        else
+                            acc[mi][ni] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, x[f % XD][ni][pl]), __builtin_bit_cast(bf16x8, w), acc[mi][ni], 0, 0, 0);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
                 }
+                if (!LAST || f + RS < F) load_a(stage * (F / 2), f + RS, w_voff);
                 __builtin_amdgcn_sched_barrier(0);
             }
-            load_a(stage * (F / 2), f + RS, f + RS < F ? w_voff : voff_next);
-            __builtin_amdgcn_sched_barrier(0);
-        }
-        if (NB == 2) store_x((stage + 1) & 1);
-        __syncthreads();
-        if (NB == 1) break;
+            if (!LAST) store_x((stage + 1) & 1);
+            __syncthreads();
+        };
+        int stage = 0;
+        if constexpr (NB == 2)
+            for (; stage + 1 < nstages; ++stage) run_stage(stage, std::false_type{});
+        run_stage(stage, std::true_type{});
     }
 
     // ---- epilogue: register e of lane (i, q) is time row 4 q + e, GEMM row lane_row(mi)
