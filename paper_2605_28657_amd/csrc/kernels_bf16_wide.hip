@@ -2,9 +2,10 @@
 //     h += W1 * snake2(W7 (*) a + b7) + b1,      a = bf16(snake1(h)) written by the producer of h
 // in one kernel: the activated branch tensor between the two convolutions never goes to HBM, and the 1x1
 // convolution (a short reduction with a long epilogue, bound by HBM when it runs on its own) costs one more
-// K loop instead of a launch.
+// K loop instead of a launch.  Three kernels with the same results: weights streamed to registers for seven taps (narrow tiles for
+// launches of few of them, tall ones else), and the LDS-staged one, first below, for any number of taps.
 //
-// Workgroup = 4 waves, tile = all 256 channels x 128 time columns, every wave all 256 rows of its 32 columns
+// LDS-staged: workgroup = 4 waves, tile = all 256 channels x 128 time columns, every wave all 256 rows of its 32 columns
 // (8 accumulator tiles of 32 x 32).  The dilated convolution runs as in kernels_bf16.hip on the pre-activated
 // bf16 operand, with K stages of 32 channels so that two workgroups fit the LDS of a CU.  As in the narrow fused
 // unit, a lane of an accumulator tile holds column j and rows 8g + 4h + {0..3}, which after bias + Snake are the
@@ -17,6 +18,7 @@
 // The residual stream is updated in place (only this tile reads or writes its elements); the emitted operand of
 // the next layer goes to a second buffer because neighbouring tiles still read this tile's input rows.
 #include <algorithm>
+#include <type_traits>
 
 #include "device_common.h"
 
@@ -302,13 +304,12 @@ __global__ __launch_bounds__(256) void res_unit_wide_kernel(WideParams p)
     }
 }
 
-// The same unit with the weights streamed to registers: 8 waves share the 16 TN columns of a tile, a wave owning 32 channels of
-// all of them.  The staged kernel above lasts as long as one workgroup's
+// The same unit with the weights streamed to registers, for launches of few tiles: 8 waves share the 16 TN columns of a tile, a wave
+// owning 32 channels of all of them.  The staged kernel above lasts as long as one workgroup's
 // walk over its 64 weight blocks, whatever the launch's size (45 us: two barriers a block, every wave reading all 16 KB of it
 // from LDS).  Here a CU reads each weight once, RS k-steps ahead and without a barrier, and the branch tensor goes through LDS
 // (its fragments are spread over the waves); what bounds it is the 16 KB of weights a k-step brings into the CU for narrow tiles
-// (some 45 bytes per clock) and the MFMAs for wide ones.  Per unit of a window of 8 frames 45 -> 22 us, of 75 frames 51 -> 35;
-// the whole 13-frame window 355 -> 286 us, the 75-frame one 526 -> 475.
+// (some 45 bytes per clock) and the MFMAs for wide ones.  Per unit of a window of 8 frames 45 -> 22 us, of 75 frames 51 -> 27.
 // K order (chunk of 32 channels, tap, channel; the 1x1 conv's k-slots) and roundings are those of the kernel above: the
 // results are bit-identical, whichever kernel a launch takes.
 template <int TN, bool EMIT>
@@ -322,8 +323,8 @@ __global__ __launch_bounds__(512, 2) void res_unit_wide_stream_kernel(WideParams
     constexpr int RS = 7;                     // k-steps of weights in flight
     static_assert(F % RS == 0 && RS * (W_A_CH * 16u) <= kWeightSlack, "static ring indices");
     constexpr int LDM = CH + 16;                            // row of the branch tensor's tile: 34 pieces
-    constexpr int EP = NT > 96 ? 2 : 1, ECOLS = NT / EP, LDO = CH + 4;           // epilogue in passes of ECOLS columns
-    constexpr int X_BYTES = XR * LDR * 2, M_BYTES = NT * LDM * 2, O_BYTES = ECOLS * LDO * 4;
+    constexpr int LDO = CH + 4;                             // row of the fp32 output tile
+    constexpr int X_BYTES = XR * LDR * 2, M_BYTES = NT * LDM * 2, O_BYTES = NT * LDO * 4;
     constexpr int SMEM_XM = 2 * X_BYTES > M_BYTES ? 2 * X_BYTES : M_BYTES, SMEM = SMEM_XM > O_BYTES ? SMEM_XM : O_BYTES;
     __shared__ __attribute__((aligned(16))) unsigned char smem[SMEM];
 
@@ -455,42 +456,260 @@ __global__ __launch_bounds__(512, 2) void res_unit_wide_stream_kernel(WideParams
     }
 
     // ---- residual add, half store in place, optional Snake + bf16 operand, 8 channels of a column at a time through LDS
-    constexpr int PPR = CH / 8, ERPP = NTH / PPR, E_ITERS = ECOLS / ERPP;
+    constexpr int PPR = CH / 8, ERPP = NTH / PPR, E_ITERS = NT / ERPP;
     const int ec = tid % PPR * 8, er = tid / PPR;
     float a3v[8], i3v[8];
 #pragma unroll
     for (int e = 0; e < 8; ++e) { a3v[e] = EMIT ? p.a3[ec + e] : 0.f; i3v[e] = EMIT ? p.ib3[ec + e] : 0.f; }
     float* os = reinterpret_cast<float*>(smem);
+    u32x4 resv[E_ITERS];
 #pragma unroll
-    for (int ep = 0; ep < EP; ++ep) {
-        u32x4 resv[E_ITERS];
+    for (int it = 0; it < E_ITERS; ++it) resv[it] = __builtin_amdgcn_raw_buffer_load_b128(rs_y, (unsigned)((n0 + er + it * ERPP) * CH + ec) * 2u, 0, 0);
+    __syncthreads();                                        // the branch tensor has been read
 #pragma unroll
-        for (int it = 0; it < E_ITERS; ++it)
-            resv[it] = __builtin_amdgcn_raw_buffer_load_b128(rs_y, (unsigned)((n0 + ep * ECOLS + er + it * ERPP) * CH + ec) * 2u, 0, 0);
-        __syncthreads();                                    // the branch tensor, or the pass before, has been read
+    for (int mi = 0; mi < 2; ++mi)
 #pragma unroll
-        for (int mi = 0; mi < 2; ++mi)
+        for (int ni = 0; ni < TN; ++ni)
 #pragma unroll
-            for (int ni = 0; ni < ECOLS / 16; ++ni)
+            for (int e = 0; e < 4; ++e) os[(16 * ni + 4 * q + e) * LDO + ch0 + 16 * mi] = acc[mi][ni][e];
+    __syncthreads();
 #pragma unroll
-                for (int e = 0; e < 4; ++e) os[(16 * ni + 4 * q + e) * LDO + ch0 + 16 * mi] = acc[mi][ep * (ECOLS / 16) + ni][e];
+    for (int it = 0; it < E_ITERS; ++it) {
+        // rows past out_hi are outside the descriptors and dropped
+        const unsigned off = (unsigned)((n0 + er + it * ERPP) * CH + ec) * 2u;
+        const float* src = &os[(er + it * ERPP) * LDO + ec];
+        const f16x8 r = __builtin_bit_cast(f16x8, resv[it]);
+        f16x8 o;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) o[e] = (_Float16)keep_f32(src[e] + (float)r[e]);
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, o), rs_y, off, 0, 0);
+        if (EMIT) {
+            u32x4 sh;
+#pragma unroll
+            for (int e = 0; e < 8; e += 2)
+                sh[e / 2] = pack_bf16x2(snake_fast((float)o[e], a3v[e], i3v[e]), snake_fast((float)o[e + 1], a3v[e + 1], i3v[e + 1]));
+            __builtin_amdgcn_raw_buffer_store_b128(sh, rs_a, off, 0, 0);
+        }
+    }
+}
+
+// The same unit for launches that fill the chip: 4 waves share a tile of 128 columns, a wave owning 64 channels of all of them, two
+// workgroups on a CU (256 registers, 70 KB of LDS).  What bound the staged kernel is LDS reads: a wave of 256 channels x 32 columns
+// reads 9 KB per 256 cycles of MFMAs, four of them more than the LDS delivers, with two barriers per weight block on top.  64 channels x 128
+// columns need 4 KB of streamed weights and 8 KB of LDS reads per 512 cycles of MFMAs, a third of what either path delivers, and
+// one barrier per 14 k-steps; the next stage's activations travel two rows of a thread at a time, so that
+// accumulators (128 registers), four k-steps of weights (64) and the fragments read ahead fit without spills.
+// The dilated conv has the weights as the row operand (a lane ends with four consecutive channels of a column: 8-byte LDS writes of
+// the branch tensor), the 1x1 conv the activations (a lane ends with four channels of a row, 16 lanes with 128 bytes: the
+// epilogue goes straight to memory).  60 s clip 388 -> 313 us per unit (1.2 PFLOP/s; HBM traffic and Snake included), 375 frames
+// 111 -> 80, encode of 60 s 438 -> 353.  Bit-identical to the kernels above.
+template <bool EMIT>
+__global__ __launch_bounds__(256, 2) void res_unit_wide_tall_kernel(WideParams p)
+{
+    fp16_saturate_on();
+    constexpr int CH = W_CH, TM = 4, TN = 8, NT = 16 * TN, NTAPS = 7, NTH = 256;
+    constexpr int KX = 64, LDR = KX + 16;                   // stage of two chunks; rows 10 pieces apart: no bank conflicts
+    constexpr int SEGS = KX / 8, RPP = NTH / SEGS, X_ITERS = (NT + W_MAXSPAN) / RPP, XR = X_ITERS * RPP;
+    constexpr int F = 2 * NTAPS, NSTAGES = CH / KX;         // k-steps of 32 in a stage
+    constexpr int RS = 4;                                   // k-steps of weights in flight
+    constexpr int XA = 5, XQ = XA + 1;                      // activation fragments read ahead of their MFMAs
+    constexpr int LDM = CH + 16;                            // row of the branch tensor's tile: 34 pieces
+    constexpr int X_BYTES = XR * LDR * 2, M_BYTES = NT * LDM * 2;
+    constexpr int SMEM = 2 * X_BYTES > M_BYTES ? 2 * X_BYTES : M_BYTES;
+    static_assert(XR == NT + W_MAXSPAN && X_ITERS == 6 && NSTAGES % 2 == 0 && 2 * F % RS == 0 && W_NCHUNKS % RS == 0, "static indices");
+    __shared__ __attribute__((aligned(16))) unsigned char smem[SMEM];
+
+    const Slot s = p.slots[blockIdx.y];
+    const int nrows = s.len * p.r;
+    const int out_lo = max(0, s.crop * p.r - p.margin);
+    const int out_hi = min(nrows, (s.crop + s.n_int) * p.r + p.margin);
+    const int tiles8 = (int)(gridDim.x >> 3);               // XCD x takes a contiguous eighth of the tiles, as above
+    const int n0 = out_lo + ((int)((blockIdx.x + blockIdx.y) & 7u) * tiles8 + (int)(blockIdx.x >> 3)) * NT;
+    if (n0 >= out_hi) return;
+    const long long rowbase = (long long)s.row0 * p.r;
+    const int minoff = p.tap0;                              // tap_step > 0
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int i = lane & 15, q = lane >> 4;
+    const int seg = tid % SEGS, xr0 = tid / SEGS;
+
+    const __amdgpu_buffer_rsrc_t rs_x = make_rsrc(p.xa + rowbase * CH, (unsigned)nrows * CH * 2u);
+    const __amdgpu_buffer_rsrc_t rs_y = make_rsrc(p.y + rowbase * CH, (unsigned)out_hi * CH * (unsigned)sizeof(hres_t));
+    const __amdgpu_buffer_rsrc_t rs_a = make_rsrc(p.ya + rowbase * CH, EMIT ? (unsigned)out_hi * CH * 2u : 0u);
+    const __amdgpu_buffer_rsrc_t rs_w7 = weight_rsrc(p.w7, (unsigned)(W_NCHUNKS * NTAPS) * (W_A_CH * 16u));
+    const __amdgpu_buffer_rsrc_t rs_w1 = weight_rsrc(p.w1, (unsigned)W_NCHUNKS * (W_A_CH * 16u));
+
+    // weights: one block of 256 x 32 per k-step, [16-row unit][lane][8]; this wave's units are 4 wave .. 4 wave + 3
+    const unsigned w_voff = (unsigned)wave * (TM * 1024u) + lane * 16u;
+    u32x4 a[RS][TM];
+    auto load_a = [&](int f) __attribute__((always_inline)) {
+#pragma unroll
+        for (int mi = 0; mi < TM; ++mi) a[f % RS][mi] = __builtin_amdgcn_raw_buffer_load_b128(rs_w7, w_voff + mi * 1024u, (unsigned)f * (W_A_CH * 16u), 0);
+    };
+    // 1x1 weights: lane i of unit mi is channel 64 wave + 4 i + mi, which lies in slot 32 (channel % 8) + channel / 8 (pack_w1_wide)
+    const unsigned w1_voff = (unsigned)((8 * (i & 1) + (wave >> 1)) * 1024 + (8 * (wave & 1) + (i >> 1)) * 16 + q * 256);
+    auto load_a1 = [&](int c) __attribute__((always_inline)) {
+#pragma unroll
+        for (int mi = 0; mi < TM; ++mi) a[c % RS][mi] = __builtin_amdgcn_raw_buffer_load_b128(rs_w1, w1_voff, (unsigned)c * (W_A_CH * 16u) + mi * 2048u, 0);
+    };
+
+    const unsigned x_voff = ((unsigned)((n0 + minoff + xr0) * CH) + seg * 8u) * 2u;      // may wrap "negative": out of range
+    u32x4 rx[X_ITERS];
+    auto load_x = [&](int stage, int it) __attribute__((always_inline)) {
+        rx[it] = __builtin_amdgcn_raw_buffer_load_b128(rs_x, x_voff + (unsigned)(it * RPP * CH + stage * KX) * 2u, 0, 0);
+    };
+    auto store_x = [&](int buf, int it) __attribute__((always_inline)) {
+        *reinterpret_cast<u32x4*>(smem + buf * X_BYTES + ((xr0 + it * RPP) * LDR + seg * 8) * 2) = rx[it];
+    };
+
+#pragma unroll
+    for (int it = 0; it < X_ITERS; ++it) load_x(0, it);
+#pragma unroll
+    for (int f = 0; f < RS; ++f) load_a(f);
+    f32x4 acc[TM][TN];
+    const int ch0 = 64 * wave + 4 * q;                      // dilated conv: register e of (mi, ni) is channel ch0 + 16 mi + e, column 16 ni + i
+#pragma unroll
+    for (int mi = 0; mi < TM; ++mi) {
+        const f32x4 b = *reinterpret_cast<const f32x4*>(p.b7 + ch0 + 16 * mi);
+#pragma unroll
+        for (int ni = 0; ni < TN; ++ni) acc[mi][ni] = b;
+    }
+#pragma unroll
+    for (int it = 0; it < X_ITERS; ++it) store_x(0, it);
+    __syncthreads();
+
+    const int tap_bytes = p.tap_step * (LDR * 2);
+    auto run_stage = [&](int stage, int half, auto last) __attribute__((always_inline)) {
+        constexpr bool LAST = decltype(last)::value;
+        // LDS offset of the tap that is read, kept as one running register (left to itself the compiler holds one for every tap)
+        unsigned at = half * X_BYTES + (i * LDR + q * 8) * 2;
+        u32x4 x[XQ];
+        auto read_x = [&](int t) __attribute__((always_inline)) {
+            const int f = t / TN, ni = t % TN;
+            if (t > 0 && ni == 0) {
+                at = f % NTAPS == 0 ? at - (NTAPS - 1) * tap_bytes + 64 : at + tap_bytes;
+                asm volatile("" : "+v"(at));
+            }
+            x[t % XQ] = *reinterpret_cast<const u32x4*>(smem + at + 16 * ni * LDR * 2);
+        };
+#pragma unroll
+        for (int t = 0; t < XA; ++t) read_x(t);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int f = 0; f < F; ++f) {
+            // the next stage's activations, two rows of a thread at a time
+            if (!LAST || half == 0) {
+                if (f >= 4 && f % 4 == 0) { store_x(half ^ 1, f / 2 - 2); store_x(half ^ 1, f / 2 - 1); }
+                if (f % 4 == 0 && f < 12) { load_x(stage + 1, f / 2); load_x(stage + 1, f / 2 + 1); }
+            }
+#pragma unroll
+            for (int ni = 0; ni < TN; ++ni) {
+                const int t = f * TN + ni;
+                if (t + XA < F * TN) read_x(t + XA);
+#pragma unroll
+                for (int mi = 0; mi < TM; ++mi)
+                    acc[mi][ni] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a[(half * F + f) % RS][mi]), __builtin_bit_cast(bf16x8, x[t % XQ]), acc[mi][ni], 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            // k-steps past the last are the first ones of the 1x1 conv
+            if (LAST && half == 1 && f + RS >= F) load_a1(f + RS - F);
+            else {
+                const unsigned blk = (unsigned)(stage * F + f + RS) * (W_A_CH * 16u);
+#pragma unroll
+                for (int mi = 0; mi < TM; ++mi) a[(half * F + f) % RS][mi] = __builtin_amdgcn_raw_buffer_load_b128(rs_w7, w_voff + mi * 1024u, blk, 0);
+            }
+            __builtin_amdgcn_sched_barrier(0);
+        }
         __syncthreads();
+    };
+    for (int stage = 0; stage + 2 < NSTAGES; stage += 2) {
+        run_stage(stage, 0, std::false_type{});
+        run_stage(stage + 1, 1, std::false_type{});
+    }
+    run_stage(NSTAGES - 2, 0, std::true_type{});
+    run_stage(NSTAGES - 1, 1, std::true_type{});
+
+    // ---- Snake on the accumulators; the branch tensor goes to LDS as [column][k-slot]: channel 16 m + 4 q + e of a group of 32 is
+    // k-slot 16 m + 8 (q % 2) + 4 (q / 2) + e of the 1x1 weights' K axis
+    uint16_t* ms = reinterpret_cast<uint16_t*>(smem);
 #pragma unroll
-        for (int it = 0; it < E_ITERS; ++it) {
-            // rows past out_hi are outside the descriptors and dropped
-            const unsigned off = (unsigned)((n0 + ep * ECOLS + er + it * ERPP) * CH + ec) * 2u;
-            const float* src = &os[(er + it * ERPP) * LDO + ec];
-            const f16x8 r = __builtin_bit_cast(f16x8, resv[it]);
-            f16x8 o;
+    for (int mi = 0; mi < TM; ++mi) {
+        const f32x4 al = *reinterpret_cast<const f32x4*>(p.a2 + ch0 + 16 * mi), ib = *reinterpret_cast<const f32x4*>(p.ib2 + ch0 + 16 * mi);
 #pragma unroll
-            for (int e = 0; e < 8; ++e) o[e] = (_Float16)keep_f32(src[e] + (float)r[e]);
-            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, o), rs_y, off, 0, 0);
+        for (int ni = 0; ni < TN; ++ni) {
+            const f32x4 v = acc[mi][ni];
+            u32x2 o;
+            o[0] = pack_bf16x2(snake_fast(v[0], al[0], ib[0]), snake_fast(v[1], al[1], ib[1]));
+            o[1] = pack_bf16x2(snake_fast(v[2], al[2], ib[2]), snake_fast(v[3], al[3], ib[3]));
+            *reinterpret_cast<u32x2*>(&ms[(16 * ni + i) * LDM + 64 * wave + 16 * mi + 8 * (q & 1) + 4 * (q >> 1)]) = o;
+        }
+    }
+    // ---- 1x1 conv, activations as the row operand: register e of (mi, ni) is column 16 ni + 4 q + e, channel 64 wave + 4 i + mi, so
+    // that a lane holds four consecutive channels of a column and 16 lanes 128 bytes of it
+    const int ec = 64 * wave + 4 * i;
+    const f32x4 b1v = *reinterpret_cast<const f32x4*>(p.b1 + ec);
+#pragma unroll
+    for (int mi = 0; mi < TM; ++mi)
+#pragma unroll
+        for (int ni = 0; ni < TN; ++ni) acc[mi][ni] = f32x4{b1v[mi], b1v[mi], b1v[mi], b1v[mi]};
+    __syncthreads();
+
+    u32x2 resv[TN][4];
+    unsigned e_voff = (unsigned)((n0 + 4 * q) * CH + ec) * 2u;
+    // residual values, requested into the registers that the weights of the 1x1 conv's last k-steps free
+    auto load_res = [&](int ni) __attribute__((always_inline)) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) resv[ni][e] = __builtin_amdgcn_raw_buffer_load_b64(rs_y, e_voff + (unsigned)((16 * ni + e) * CH * 2), 0, 0);
+    };
+    {
+        const uint16_t* mr = ms + i * LDM + q * 8;
+        constexpr int XA = 3, XQ = XA + 1;
+        u32x4 x[XQ];
+        auto read_x = [&](int t) __attribute__((always_inline)) { x[t % XQ] = *reinterpret_cast<const u32x4*>(mr + (t % TN) * 16 * LDM + (t / TN) * 32); };
+#pragma unroll
+        for (int t = 0; t < XA; ++t) read_x(t);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int c = 0; c < W_NCHUNKS; ++c) {
+#pragma unroll
+            for (int ni = 0; ni < TN; ++ni) {
+                const int t = c * TN + ni;
+                if (t + XA < W_NCHUNKS * TN) read_x(t + XA);
+#pragma unroll
+                for (int mi = 0; mi < TM; ++mi)
+                    acc[mi][ni] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, x[t % XQ]), __builtin_bit_cast(bf16x8, a[c % RS][mi]), acc[mi][ni], 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            if (c + RS < W_NCHUNKS) load_a1(c + RS);
+            else if (c + RS > W_NCHUNKS) { load_res(2 * (c + RS - W_NCHUNKS) - 2); load_res(2 * (c + RS - W_NCHUNKS) - 1); }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+    load_res(TN - 2);
+    load_res(TN - 1);
+    asm volatile("" : "+v"(e_voff));                        // the 32 offsets are formed again, not kept
+
+    // ---- residual add, half store in place, optional Snake + bf16 operand for the next layer.  Rows past out_hi are outside the
+    // descriptors and dropped.
+    f32x4 a3v = {0.f, 0.f, 0.f, 0.f}, i3v = {0.f, 0.f, 0.f, 0.f};
+    if (EMIT) { a3v = *reinterpret_cast<const f32x4*>(p.a3 + ec); i3v = *reinterpret_cast<const f32x4*>(p.ib3 + ec); }
+#pragma unroll
+    for (int ni = 0; ni < TN; ++ni) {
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const unsigned off = e_voff + (unsigned)((16 * ni + e) * CH * 2);
+            const f16x4 r = __builtin_bit_cast(f16x4, resv[ni][e]);
+            f16x4 o;
+#pragma unroll
+            for (int mi = 0; mi < TM; ++mi) o[mi] = (_Float16)keep_f32(acc[mi][ni][e] + (float)r[mi]);     // fp32 sum, then one rounding
+            __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, o), rs_y, off, 0, 0);
             if (EMIT) {
-                u32x4 sh;
-#pragma unroll
-                for (int e = 0; e < 8; e += 2)
-                    sh[e / 2] = pack_bf16x2(snake_fast((float)o[e], a3v[e], i3v[e]), snake_fast((float)o[e + 1], a3v[e + 1], i3v[e + 1]));
-                __builtin_amdgcn_raw_buffer_store_b128(sh, rs_a, off, 0, 0);
+                // the next layer's operand is Snake of the STORED value
+                u32x2 sh;
+                sh[0] = pack_bf16x2(snake_fast((float)o[0], a3v[0], i3v[0]), snake_fast((float)o[1], a3v[1], i3v[1]));
+                sh[1] = pack_bf16x2(snake_fast((float)o[2], a3v[2], i3v[2]), snake_fast((float)o[3], a3v[3], i3v[3]));
+                __builtin_amdgcn_raw_buffer_store_b64(sh, rs_a, off, 0, 0);
             }
         }
     }
@@ -527,21 +746,25 @@ hipError_t launch_res_unit_wide(const WideArgs& a, hipStream_t stream)
     const long long out_rows = std::min((long long)a.max_int * a.r + 2ll * a.margin, (long long)a.max_len * a.r);
     auto tiles = [&](int nt) { return (out_rows + nt - 1) / nt; };
     auto grid = [&](int nt) { return dim3((unsigned)(tiles(nt) + 7) / 8 * 8, (unsigned)a.n_slots); };     // whole groups of 8 tiles; the surplus exits at once
-    // The streamed tiles run one workgroup per CU, and a launch takes the narrowest one that needs one round of the 256 CUs, else
-    // two.  Measured, whole decode in us, staged / columns 32, 64, 80, 96, 128: 25 frames 388 / 319, 326, 334, 341, 356; 64 frames
-    // 460 / 424, 402, 408, 414, 429; 75 frames 526 / 522, 511, 475, 482, 492; 110 frames 605 / 632, 585, 604, 622, 573; two
-    // rounds: 2 x 75 frames 820 / 863, 828, 800, 810, 847; 200 frames 915 / 981, 920, 941, 904, 928.  Past two rounds the staged
-    // kernel's two workgroups per CU cover each other's prologues and epilogues: 24 windows of 64 frames 6084 / -, 6352, -, -, 6187.
-#define DEMON_STREAM(TN) case TN: \
-    if (a.ya) hipLaunchKernelGGL((res_unit_wide_stream_kernel<TN, true>), grid(16 * TN), dim3(512), 0, stream, p); \
-    else hipLaunchKernelGGL((res_unit_wide_stream_kernel<TN, false>), grid(16 * TN), dim3(512), 0, stream, p); \
-    return hipGetLastError();
-    int tn = 0;
-    if (a.ntaps == 7 && !a.staged_only)
-        for (long long wgs : {256, 512})
-            for (int t : {2, 4, 5, 6, 8}) if (tn == 0 && tiles(16 * t) * a.call_slots <= wgs) tn = t;
-    switch (tn) { DEMON_STREAM(2) DEMON_STREAM(4) DEMON_STREAM(5) DEMON_STREAM(6) DEMON_STREAM(8) default: break; }
+    // Seven taps: the narrow streamed tiles run one workgroup of 8 waves per CU, and a launch takes the narrowest one that fits the 256
+    // CUs; larger launches take the tall kernel, two workgroups of 4 waves per CU.  Per unit in us, columns 32, 64, 80, 96 in one round (two
+    // rounds in brackets) / tall: 13 frames 18, 21, 23, 26 / 28; 40 frames (30), 22, 24, 27 / 29; 75 frames (44), (39), 28, 29 / 31; 110 frames
+    // (55), (40), (46), (52) / 33; 150 frames (70), (59), (50), (55) / 49; four windows of 64 frames 3 rounds and more: 109, 81, 94, 82 / 58.
+    // Against the LDS-staged kernel: 375 frames 111 -> 80, 60 s clip 388 -> 313 (1.2 PFLOP/s).
+    const bool streamed = a.ntaps == 7 && !a.staged_only;
+#define DEMON_STREAM(TN) \
+    if (streamed && tiles(16 * TN) * a.call_slots <= 256) { \
+        if (a.ya) hipLaunchKernelGGL((res_unit_wide_stream_kernel<TN, true>), grid(16 * TN), dim3(512), 0, stream, p); \
+        else hipLaunchKernelGGL((res_unit_wide_stream_kernel<TN, false>), grid(16 * TN), dim3(512), 0, stream, p); \
+        return hipGetLastError(); \
+    }
+    DEMON_STREAM(2) DEMON_STREAM(4) DEMON_STREAM(5) DEMON_STREAM(6)
 #undef DEMON_STREAM
+    if (streamed) {
+        if (a.ya) hipLaunchKernelGGL((res_unit_wide_tall_kernel<true>), grid(W_NT), dim3(256), 0, stream, p);
+        else hipLaunchKernelGGL((res_unit_wide_tall_kernel<false>), grid(W_NT), dim3(256), 0, stream, p);
+        return hipGetLastError();
+    }
     if (a.ya) hipLaunchKernelGGL((res_unit_wide_kernel<true>), grid(W_NT), dim3(256), 0, stream, p);
     else hipLaunchKernelGGL((res_unit_wide_kernel<false>), grid(W_NT), dim3(256), 0, stream, p);
     return hipGetLastError();

@@ -55,6 +55,26 @@ def test_unit_256_stream_tiles(T, dils):
     vae.close(); staged.close()
 
 
+@pytest.mark.parametrize("c,T,window", [
+    (256, 4200, 37), (256, 13000, 6001),     # many ragged windows, two long ones: more tiles than the narrow kernel takes
+])
+def test_units_of_large_calls_window_by_window(c, T, window):
+    """The fused units' kernels for launches that fill the chip, on windows whose ends fall inside a tile: the same bits as the whole clip,
+    and as a window short enough for the kernel of few tiles."""
+    spec = di.DecoderSpec(64, (2,), (c,), (1, 3, 9))
+    halo = max(oracle.receptive_field(spec))
+    vae, w, z = make(spec, "bf16", T, max_extended_frames=T + (T // window + 1) * 2 * halo)
+    zt = to_device(z, "bf16")
+    full = vae.decode_windowed(zt, window=T, halo=-1)
+    assert torch.equal(vae.decode_windowed(zt, window=window, halo=-1), full)
+    out = vae.decode_windowed(zt, window=15, halo=-1, frame_begin=T // 2, frame_end=T // 2 + 15)
+    S = spec.total_stride
+    assert torch.equal(out[:, :, T // 2 * S:(T // 2 + 15) * S], full[:, :, T // 2 * S:(T // 2 + 15) * S])
+    ref = oracle.decode_windowed(spec, w, z[0], window=60, halo=halo, frame_begin=T - 60, frame_end=T)
+    assert_close(full[0].cpu().numpy()[:, (T - 60) * S:], ref[:, (T - 60) * S:], "bf16", f"{c} channels")
+    vae.close()
+
+
 def test_two_planes_give_the_same_bits_at_every_size_of_call():
     """Two operand planes: a clip whose 1x1 and transposed convolutions take the largest tile, and windows of it that take the
     smallest; a value may not depend on which."""
