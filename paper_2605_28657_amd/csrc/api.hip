@@ -510,7 +510,7 @@ demon_status run_pass(demon_vae* v, const Workspace& ws, const Plan* plan, const
                     f.b7 = U.dilated.bias; f.b1 = U.pointwise.bias;
                     f.a1 = U.dilated.in_alpha; f.ib1 = U.dilated.in_inv_beta;
                     f.a2 = U.dilated.out_alpha; f.ib2 = U.dilated.out_inv_beta;
-                    f.slots = gs; f.n_slots = gn; f.max_len = ml; f.max_int = plan->max_int; f.margin = U.pointwise.margin;
+                    f.slots = gs; f.n_slots = gn; f.call_slots = ns; f.max_len = ml; f.max_int = plan->max_int; f.margin = U.pointwise.margin;
                     f.r = r; f.c = U.dilated.cin; f.ntaps = U.dilated.ntaps; f.dil = U.dilated.dil;
                     if (C && C->in_fmt != OP_BF16) return fail(DEMON_ERR_UNSUPPORTED, "a fused unit cannot feed a layer with wide operands");
                     if (last && head_in_unit) {

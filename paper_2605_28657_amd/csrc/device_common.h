@@ -47,6 +47,14 @@ __device__ __forceinline__ float snake_fast(float x, float alpha_rev, float inv_
     return fmaf(s * s, inv_beta, x);
 }
 
+// The same on a half: the product is written as a fused multiply-add with +0 (same value), which takes the half as it is, one
+// conversion less.
+__device__ __forceinline__ float snake_fast_half(_Float16 x, float alpha_rev, float inv_beta)
+{
+    const float s = __builtin_amdgcn_sinf(fmaf(alpha_rev, (float)x, 0.f));
+    return fmaf(s * s, inv_beta, (float)x);
+}
+
 // Raw buffer descriptor over [base, base + bytes): loads outside return zero, stores outside are dropped.
 // Dword 3 selects 32-bit raw addressing on gfx9-family parts.
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base, unsigned bytes)
@@ -81,6 +89,11 @@ __device__ __forceinline__ float keep_f32(float v)
     asm("" : "+v"(v));
     return v;
 }
+
+// acc + r for a half r, in one instruction that takes the half as it is: `one` is 1.0f behind opaque_one(), so that the compiler does
+// not turn the fused multiply-add (same value) back into a conversion and an addition.
+__device__ __forceinline__ float opaque_one() { float one = 1.f; asm("" : "+v"(one)); return one; }
+__device__ __forceinline__ float add_half(float acc, _Float16 r, float one) { return fmaf((float)r, one, acc); }
 
 // Conversions to half saturate instead of overflowing: with the FP16_OVFL bit of the wave's MODE register set, a
 // result beyond the half range is clamped to +-65504 (true infinities stay).  The residual stream and the operands of

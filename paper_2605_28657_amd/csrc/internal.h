@@ -117,7 +117,7 @@ struct FusedArgs {
     const uint16_t* w1;      // packed by pack_w1_fused
     const float* b7; const float* b1;
     const float* a1; const float* ib1; const float* a2; const float* ib2;
-    const Slot* slots; int n_slots, max_len, max_int, margin;
+    const Slot* slots; int n_slots, call_slots, max_len, max_int, margin;
     int r, c, ntaps, dil;
     // optional: the decoder's head in the same kernel (64 channels, the unit feeds nothing else; y is then not written).
     // hw: half-precision MFMA fragments (pack_head_mfma), hb bias, ha / hib the head's Snake, hy planar window waveforms

@@ -1,8 +1,9 @@
 // Fused residual unit for the narrow, high-rate levels (C = 64 or 128 channels):
 //     h_out = h + W1 * snake2(W7 (*) snake1(h) + b7) + b1
-// in one kernel, so that the activated branch tensor never goes to HBM.
+// in one kernel, so that the activated branch tensor never goes to HBM.  Two kernels: the LDS-staged one, first below, for kernel
+// sizes other than 7 and for 64 channels in calls whose tensors exceed the last-level cache, and the streamed one.
 //
-// The dilated conv runs as in kernels_bf16.hip (implicit GEMM, rows = output channels, columns = time,
+// LDS-staged: the dilated conv runs as in kernels_bf16.hip (implicit GEMM, rows = output channels, columns = time,
 // one weight block in LDS, the next waiting in registers), except that the kernel reads the half-precision residual stream itself and
 // applies Snake while staging (cheaper in HBM traffic than a separate bf16 operand at these rates),
 // and that every wave owns ALL C rows of its 32*TN columns.  A lane of a 32x32 MFMA accumulator tile
@@ -479,6 +480,378 @@ __global__ __launch_bounds__(256, (CH == 128 && TN == 2) ? 2 : 3) void res_unit_
     }
 }
 
+// The same unit with the weights streamed to registers (seven taps): WM x WN waves, a wave owning 16 TM channels x 16 TN columns, the
+// branch tensor through LDS.  What bound the kernel above: two barriers per 8 or 16 KB weight block (a launch of few tiles lasts as long as
+// one workgroup's 14 of them), and at 128 channels LDS reads (6 KB per wave and 256 cycles of MFMAs).  Here a stage of KX channels has all its taps
+// between two barriers and the next stage's Snake runs in the shadow of its MFMAs, a quarter row every other group of TM MFMAs.
+//  * 128 channels, large calls: 64 x 128 per wave, 2 x 2 waves, two workgroups per CU (256 registers, 77 KB): a third of the LDS reads.
+//    What bounds it now is the two waves of a SIMD: matrix cores busy 50 %, other VALU work (Snake of 1.25 + 1 values per output) 30 %,
+//    which overlap in part.  Waves in the K loop go first (s_setprio: 390 -> 368 us).  60 s clip 425 -> 360 us per unit, 375 frames 111 -> 91.
+//  * 128 channels, few tiles: 32 x 64 per wave, 4 x 1 waves: window of 13 frames 25 -> 10 us, 75 frames 37 -> 27.
+//  * 64 channels: one stage, two by two waves of 32 channels: 13 frames 13 -> 9 us (with the head 19 -> 11), 75 frames 20 -> 17 (28 -> 23),
+//    375 frames 62 -> 55.
+// K order: 128 channels (32 channels, tap), 64 channels (tap, channel) as above, where the results are bit-identical to the kernel above's.
+template <int KX, int TM, int TN, int WM, int WN, int OCC, bool EMIT, bool HEAD>
+__global__ __launch_bounds__(64 * WM * WN, OCC) void res_unit_narrow_stream_kernel(FusedParams p)
+{
+    fp16_saturate_on();
+    constexpr int CH = 16 * TM * WM, NT = 16 * TN * WN, NTAPS = 7, NTH = 64 * WM * WN;
+    constexpr int LDR = KX + 16;                            // stage of KX channels; rows 6 or 10 pieces apart: no bank conflicts
+    constexpr int SEGS = KX / 8, RPP = NTH / SEGS, X_ITERS = (NT + FUSED_MAXSPAN + RPP - 1) / RPP, XR = X_ITERS * RPP;
+    constexpr int NSTAGES = CH / KX, SX = KX / 32, F = NTAPS * SX, NSTEPS = NSTAGES * F, KS1 = CH / 32;
+    constexpr bool TIGHT = TM * TN > 24;                    // accumulators take half of the registers
+    constexpr int RS = TIGHT ? 4 : 7;                       // k-steps of weights in flight
+    constexpr int XA = TIGHT ? 3 : 5, XQ = XA + 1;          // activation fragments read ahead of their MFMAs
+    constexpr int RX = TIGHT ? 2 : X_ITERS;                 // rows of a thread requested ahead
+    constexpr int G = F * TN;                               // groups of TM MFMAs in a stage
+    constexpr int LDM = CH + 16;
+    constexpr int X_BYTES = XR * LDR * 2, M_BYTES = NT * LDM * 2;
+    constexpr int XS_BYTES = (NSTAGES > 1 ? 2 : 1) * X_BYTES, SMEM = XS_BYTES > M_BYTES ? XS_BYTES : M_BYTES;
+    constexpr unsigned BLOCK = CH * 128u;                   // bytes of a weight block: CH rows x 64 channels
+    constexpr int PW = G / X_ITERS, PD = PW >= 8 ? 2 : 1;   // groups a staged row lasts, groups between its quarters
+    constexpr int AUX = TIGHT ? 2 : 0;                      // stores of large calls pass the caches by
+    // HEAD: weight fragments, then the tile of operands, in the activation tile's space
+    constexpr int LDH = CH + 8, HW_BYTES = FUSED_HEAD_MAXK * CH * 16, HW_ITERS = HEAD ? (HW_BYTES / 16 + NTH - 1) / NTH : 1;
+    static_assert(!HEAD || (CH == 64 && !EMIT && NT % (32 * WM * WN) == 0 && HW_BYTES + (NT + FUSED_HEAD_MAXK - 1) * LDH * 2 <= SMEM), "the head follows a 64-channel unit that feeds nothing else");
+    static_assert(KS1 <= RS && KS1 % TM == 0 && PW >= 4 && (NSTAGES == 1 || NSTAGES == 4), "static indices; a quarter row per group");
+    __shared__ __attribute__((aligned(16))) unsigned char smem[SMEM];
+    __shared__ __attribute__((aligned(16))) float prm[(EMIT || HEAD ? 8 : 6) * CH];     // (a1, ib1) pairs | b7 | a2 | ib2 | b1 | a3 | ib3 (of the head)
+
+    const Slot s = p.slots[blockIdx.y];
+    const int nrows = s.len * p.r;
+    const int out_lo = max(0, s.crop * p.r - p.margin);
+    const int out_hi = min(nrows, (s.crop + s.n_int) * p.r + p.margin);
+    const int tiles8 = (int)(gridDim.x >> 3);               // XCD x takes a contiguous eighth of the tiles, as above
+    const int tile = (int)((blockIdx.x + blockIdx.y) & 7u) * tiles8 + (int)(blockIdx.x >> 3);
+    const int hhalf = HEAD ? (p.hk - 1) / 2 : 0;
+    const int h_lo = s.crop * p.r, h_hi = (s.crop + s.n_int) * p.r;     // HEAD: the interior rows the head produces
+    const int n0 = HEAD ? h_lo - hhalf + tile * (NT - 2 * hhalf) : out_lo + tile * NT;
+    if (HEAD ? n0 + hhalf >= h_hi : n0 >= out_hi) return;
+    const long long rowbase = (long long)s.row0 * p.r;
+
+    int tid = threadIdx.x;
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave / WN, wn = wave % WN;
+    int i = lane & 15, q = lane >> 4;
+    const int seg = tid % SEGS, xr0 = tid / SEGS;
+
+    const __amdgpu_buffer_rsrc_t rs_x = make_rsrc(p.x + rowbase * CH, (unsigned)nrows * CH * (unsigned)sizeof(hres_t));
+    const __amdgpu_buffer_rsrc_t rs_y = make_rsrc(p.y + rowbase * CH, (unsigned)out_hi * CH * (unsigned)sizeof(hres_t));
+    const __amdgpu_buffer_rsrc_t rs_a = make_rsrc(p.ya + rowbase * CH, EMIT ? (unsigned)out_hi * CH * 2u : 0u);
+    const __amdgpu_buffer_rsrc_t rs_w = weight_rsrc(p.w7, (unsigned)(CH / 64 * NTAPS) * BLOCK);
+    const __amdgpu_buffer_rsrc_t rs_w1 = weight_rsrc(p.w1, CH * CH * 2u);
+
+    // weights: blocks of CH x 64 in fragment order, [16-row unit][2 k-steps][lane][8]; this wave's units are TM wm .. TM wm + TM - 1
+    const unsigned w_voff = (unsigned)wm * (TM * 2048u) + lane * 16u;
+    u32x4 a[RS][TM];
+    auto load_a = [&](int g) __attribute__((always_inline)) {              // k-step g: stage, tap, 32 channels of the stage
+        const int c32 = g / F * SX + g % SX, tap = g % F / SX;
+#pragma unroll
+        for (int mi = 0; mi < TM; ++mi)
+            a[g % RS][mi] = __builtin_amdgcn_raw_buffer_load_b128(rs_w, w_voff, (unsigned)((c32 >> 1) * NTAPS + tap) * BLOCK + (c32 & 1) * 1024u + mi * 2048u, 0);
+    };
+    // 1x1 weights: lane i of unit mi is channel 16 TM wm + TM i + mi, which lies in slot 32 (channel % (CH / 32)) + channel / (CH / 32)
+    auto load_a1 = [&](int c) __attribute__((always_inline)) {
+#pragma unroll
+        for (int mi = 0; mi < TM; ++mi) {
+            // the slot of unit mi lies 32 mi after that of unit 0 (TM i and the wave's first channel are multiples of TM <= CH / 32)
+            const int ch = 16 * TM * wm + TM * i, sl = ch % KS1 * 32 + ch / KS1;
+            a[(NSTEPS + c) % RS][mi] = __builtin_amdgcn_raw_buffer_load_b128(rs_w1, (unsigned)((sl >> 4) * (KS1 * 1024) + q * 256 + (sl & 15) * 16), c * 1024u + mi * (2 * KS1 * 1024u), 0);
+        }
+    };
+
+    // activations: row j of the staging (j = stage x X_ITERS + pass), 8 channels a thread
+    const unsigned x_voff = ((unsigned)((n0 + p.tap0 + xr0) * CH) + seg * 8u) * 2u;      // may wrap "negative": out of range
+    auto load_x = [&](int j) __attribute__((always_inline)) -> u32x4 {
+        return __builtin_amdgcn_raw_buffer_load_b128(rs_x, x_voff + (unsigned)(j % X_ITERS * RPP * CH + j / X_ITERS * KX) * 2u, 0, 0);
+    };
+    auto x_slot = [&](int j) __attribute__((always_inline)) -> u32x4* {
+        return reinterpret_cast<u32x4*>(smem + (j / X_ITERS & 1) * X_BYTES + ((xr0 + j % X_ITERS * RPP) * LDR + seg * 8) * 2);
+    };
+    auto read_prm = [&](int j, int k) __attribute__((always_inline)) -> f32x4 {          // Snake parameters of channels 2 k, 2 k + 1 of the thread's 8
+        return *reinterpret_cast<const f32x4*>(&prm[(j / X_ITERS * KX + seg * 8 + 2 * k) * 2]);
+    };
+    auto snake2 = [&](uint32_t v, f32x4 pr) __attribute__((always_inline)) -> uint32_t {
+        const f16x2 hv = __builtin_bit_cast(f16x2, v);
+        return pack_bf16x2(snake_fast_half(hv[0], pr[0], pr[1]), snake_fast_half(hv[1], pr[2], pr[3]));
+    };
+
+    // every request of the prologue in the order of use
+    u32x4 px[X_ITERS], rx[NSTAGES > 1 ? RX : 1];
+#pragma unroll
+    for (int j = 0; j < X_ITERS; ++j) px[j] = load_x(j);
+    f32x4 pal[2], pib[2];                                    // Snake of the first stage's rows
+#pragma unroll
+    for (int k = 0; k < 2; ++k) { pal[k] = *reinterpret_cast<const f32x4*>(p.a1 + seg * 8 + 4 * k); pib[k] = *reinterpret_cast<const f32x4*>(p.ib1 + seg * 8 + 4 * k); }
+    // per-channel vectors: the first CH threads take half of them, the next CH the others
+    constexpr int NPV = EMIT || HEAD ? 4 : 3;
+    const int ph = __builtin_amdgcn_readfirstlane(tid / CH), pc = tid % CH;
+    const float* const psrc[4] = {ph ? p.a2 : p.a1, ph ? p.ib2 : p.ib1, ph ? p.b1 : p.b7, HEAD ? (ph ? p.hib : p.ha) : (ph ? p.ib3 : p.a3)};
+    float pv[NPV];
+#pragma unroll
+    for (int k = 0; k < NPV; ++k) pv[k] = psrc[k][pc];
+#pragma unroll
+    for (int g = 0; g < RS; ++g) load_a(g);
+    if constexpr (NSTAGES > 1) {
+#pragma unroll
+        for (int j = 0; j < RX; ++j) rx[(X_ITERS + j) % RX] = load_x(X_ITERS + j);
+    }
+#pragma unroll
+    for (int j = 0; j < X_ITERS; ++j) {
+        u32x4 v;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) v[k] = snake2(px[j][k], f32x4{pal[k / 2][k % 2 * 2], pib[k / 2][k % 2 * 2], pal[k / 2][k % 2 * 2 + 1], pib[k / 2][k % 2 * 2 + 1]});
+        *x_slot(j) = v;
+    }
+    if (ph == 0) { prm[2 * pc] = pv[0]; prm[2 * pc + 1] = pv[1]; prm[2 * CH + pc] = pv[2]; }
+    else if (ph == 1) { prm[3 * CH + pc] = pv[0]; prm[4 * CH + pc] = pv[1]; prm[5 * CH + pc] = pv[2]; }
+    if (NPV == 4 && ph < 2) prm[(6 + ph) * CH + pc] = pv[NPV - 1];
+    __syncthreads();
+    f32x4 acc[TM][TN];
+    int ch0 = 16 * TM * wm + 4 * q;                         // dilated conv: register e of (mi, ni) is channel ch0 + 16 mi + e, column 16 ni + i
+#pragma unroll
+    for (int mi = 0; mi < TM; ++mi) {
+        const f32x4 b = *reinterpret_cast<const f32x4*>(&prm[2 * CH + ch0 + 16 * mi]);
+#pragma unroll
+        for (int ni = 0; ni < TN; ++ni) acc[mi][ni] = b;
+    }
+
+    // waves in this loop go first: the matrix cores are what the workgroups of a CU share (-5 % per unit)
+    __builtin_amdgcn_s_setprio(1);
+    const int tap_bytes = p.tap_step * (LDR * 2);
+    auto run_stage = [&](auto stage) __attribute__((always_inline)) {
+        constexpr int st = decltype(stage)::value;
+        // LDS offset of the tap that is read, kept as one running register (left to itself the compiler holds one for every tap)
+        unsigned at = (st & 1) * X_BYTES + ((wn * (16 * TN) + i) * LDR + q * 8) * 2;
+        asm volatile("" : "+v"(at));
+        u32x4 x[XQ];
+        auto read_x = [&](int t) __attribute__((always_inline)) {
+            if (t > 0 && t % (SX * TN) == 0) { at += tap_bytes; asm volatile("" : "+v"(at)); }
+            x[t % XQ] = *reinterpret_cast<const u32x4*>(smem + at + (16 * (t % TN) * LDR + t / TN % SX * 32) * 2);
+        };
+        f32x4 pr = st + 1 < NSTAGES ? read_prm((st + 1) * X_ITERS, 0) : f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int t = 0; t < XA; ++t) read_x(t);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int t = 0; t < G; ++t) {
+            const int f = t / TN, ni = t % TN, g = st * F + f;
+            // the next stage's activations, in the shadow of the MFMAs: Snake on two values of a row, PD groups of MFMAs apart
+            if (st + 1 < NSTAGES && t < X_ITERS * PW && t % PW >= PW - 1 - 3 * PD && (PW - 1 - t % PW) % PD == 0) {
+                const int it = t / PW, k = 3 - (PW - 1 - t % PW) / PD, j = (st + 1) * X_ITERS + it;
+                rx[j % RX][k] = snake2(rx[j % RX][k], pr);
+                if (k < 3) pr = read_prm(j, k + 1);
+                else {
+                    *x_slot(j) = rx[j % RX];
+                    if (it + 1 < X_ITERS) pr = read_prm(j + 1, 0);
+                    if (j + RX < NSTAGES * X_ITERS) rx[j % RX] = load_x(j + RX);
+                }
+            }
+            if (t + XA < G) read_x(t + XA);
+#pragma unroll
+            for (int mi = 0; mi < TM; ++mi)
+                acc[mi][ni] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a[g % RS][mi]), __builtin_bit_cast(bf16x8, x[t % XQ]), acc[mi][ni], 0, 0, 0);
+            __builtin_amdgcn_sched_barrier(0);
+            if (ni == TN - 1) {                             // k-steps past the last are those of the 1x1 conv
+                if (g + RS < NSTEPS) load_a(g + RS);
+                else if (g + RS < NSTEPS + KS1) load_a1(g + RS - NSTEPS);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+        __syncthreads();
+    };
+    run_stage(std::integral_constant<int, 0>{});
+    if constexpr (NSTAGES == 4) {
+        run_stage(std::integral_constant<int, 1>{});
+        run_stage(std::integral_constant<int, 2>{});
+        run_stage(std::integral_constant<int, 3>{});
+    }
+
+    __builtin_amdgcn_s_setprio(0);
+    // what the lane's number decides is formed again: nothing of it is held through the loop
+    asm volatile("" : "+v"(tid));
+    i = tid & 15; q = (tid >> 4) & 3; ch0 = 16 * TM * wm + 4 * q;
+
+    // 1x1 conv, activations as the row operand: register e of (mi, ni) is column 16 ni + 4 q + e, channel 16 TM wm + TM i + mi, so that a
+    // lane holds TM consecutive channels of a column and 16 lanes 16 TM of it
+    const int ec = 16 * TM * wm + TM * i;
+    unsigned e_voff = (unsigned)((n0 + wn * (16 * TN) + 4 * q) * CH + ec) * 2u;
+    typedef _Float16 halfs_t __attribute__((ext_vector_type(TM)));
+    using res_t = std::conditional_t<TM == 2, uint32_t, u32x2>;
+    static_assert(sizeof(halfs_t) == sizeof(res_t), "TM halves");
+    res_t resv[TN][4];
+    auto load_res = [&](int ni) __attribute__((always_inline)) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const unsigned off = e_voff + (unsigned)((16 * ni + e) * CH * 2);
+            if constexpr (TM == 2) resv[ni][e] = __builtin_amdgcn_raw_buffer_load_b32(rs_x, off, 0, 0);
+            else resv[ni][e] = __builtin_amdgcn_raw_buffer_load_b64(rs_x, off, 0, 0);
+        }
+    };
+    if (!TIGHT) {
+#pragma unroll
+        for (int ni = 0; ni < TN; ++ni) load_res(ni);
+    }
+
+    // ---- Snake on the accumulators; the branch tensor goes to LDS as [column][k-slot]: channel 16 m + 4 q + e of a group of 32 is
+    // k-slot 16 m + 8 (q % 2) + 4 (q / 2) + e of the 1x1 weights' K axis
+    uint16_t* ms = reinterpret_cast<uint16_t*>(smem);
+#pragma unroll
+    for (int mi = 0; mi < TM; ++mi) {
+        const f32x4 al = *reinterpret_cast<const f32x4*>(&prm[3 * CH + ch0 + 16 * mi]), ib = *reinterpret_cast<const f32x4*>(&prm[4 * CH + ch0 + 16 * mi]);
+#pragma unroll
+        for (int ni = 0; ni < TN; ++ni) {
+            const f32x4 v = acc[mi][ni];
+            u32x2 o;
+            o[0] = pack_bf16x2(snake_fast(v[0], al[0], ib[0]), snake_fast(v[1], al[1], ib[1]));
+            o[1] = pack_bf16x2(snake_fast(v[2], al[2], ib[2]), snake_fast(v[3], al[3], ib[3]));
+            *reinterpret_cast<u32x2*>(&ms[(wn * (16 * TN) + 16 * ni + i) * LDM + 16 * TM * wm + 16 * mi + 8 * (q & 1) + 4 * (q >> 1)]) = o;
+        }
+    }
+#pragma unroll
+    for (int mi = 0; mi < TM; ++mi) {
+        const float b = prm[5 * CH + ec + mi];
+#pragma unroll
+        for (int ni = 0; ni < TN; ++ni) acc[mi][ni] = f32x4{b, b, b, b};
+    }
+    __syncthreads();
+    u32x4 rhw[HW_ITERS];                                    // HEAD: its weight fragments on their way to LDS, [fragment][h][channel < 8][8 halves]
+    const int n_hw = HEAD ? p.hk * (CH / 16) * 2 * 8 : 0;
+    if constexpr (HEAD) {
+        const u32x4* src = reinterpret_cast<const u32x4*>(p.hw);          // [fragment][lane = h * 32 + channel][8 halves]
+#pragma unroll
+        for (int it = 0; it < HW_ITERS; ++it) {
+            const int k = tid + it * NTH;
+            rhw[it] = k < n_hw ? src[(k / 8) * 32 + k % 8] : u32x4{0, 0, 0, 0};
+        }
+    }
+    {
+        const uint16_t* mr = ms + (wn * (16 * TN) + i) * LDM + q * 8;
+        constexpr int XA = 3, XQ = XA + 1;
+        u32x4 x[XQ];
+        auto read_x = [&](int t) __attribute__((always_inline)) { x[t % XQ] = *reinterpret_cast<const u32x4*>(mr + t % TN * 16 * LDM + t / TN * 32); };
+#pragma unroll
+        for (int t = 0; t < XA; ++t) read_x(t);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int c = 0; c < KS1; ++c) {
+#pragma unroll
+            for (int ni = 0; ni < TN; ++ni) {
+                const int t = c * TN + ni;
+                if (t + XA < KS1 * TN) read_x(t + XA);
+#pragma unroll
+                for (int mi = 0; mi < TM; ++mi)
+                    acc[mi][ni] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, x[t % XQ]), __builtin_bit_cast(bf16x8, a[(NSTEPS + c) % RS][mi]), acc[mi][ni], 0, 0, 0);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            // the registers of the weights hold the residual values now
+            if (TIGHT && c > 0) { load_res(2 * c - 2); load_res(2 * c - 1); }
+            __builtin_amdgcn_sched_barrier(0);
+        }
+    }
+    if (TIGHT) {
+#pragma unroll
+        for (int ni = 2 * (KS1 - 1); ni < TN; ++ni) load_res(ni);
+    }
+    asm volatile("" : "+v"(e_voff));                        // the offsets are formed again, not kept
+
+    const float one = opaque_one();
+    float a3v[TM], i3v[TM];                                 // Snake of the consumer: the layer that takes the operand, or the head
+#pragma unroll
+    for (int mi = 0; mi < TM; ++mi) {
+        a3v[mi] = NPV == 4 ? prm[(NPV == 4 ? 6 : 0) * CH + ec + mi] : 0.f;
+        i3v[mi] = NPV == 4 ? prm[(NPV == 4 ? 7 : 0) * CH + ec + mi] : 0.f;
+    }
+    // ---- residual add and half store to the other buffer.  Rows past out_hi are outside the descriptors and dropped.
+    // HEAD: Snake of the (half) value the unit would have stored, in fp32, rounded once to half, goes to an LDS tile, rows shifted by
+    // (k - 1) / 2 so that a tap is a row offset >= 0; rows outside the window are the head's zero padding
+    uint16_t* Ws = reinterpret_cast<uint16_t*>(smem);
+    _Float16* Hs = reinterpret_cast<_Float16*>(smem + HW_BYTES);
+    if constexpr (HEAD) {
+        __syncthreads();                                    // the branch tensor has been read
+#pragma unroll
+        for (int it = 0; it < HW_ITERS; ++it) {
+            const int k = tid + it * NTH;
+            if (k < n_hw) reinterpret_cast<u32x4*>(Ws)[k] = rhw[it];
+        }
+        // rows past the unit's columns (context of columns that are not produced): defined, unused
+        for (int k = tid; k < 2 * hhalf * (CH / 2); k += NTH) {
+            const int rr = k / (CH / 2), cc = k % (CH / 2);
+            *reinterpret_cast<uint32_t*>(&Hs[(rr < hhalf ? rr : NT + rr) * LDH + 2 * cc]) = 0u;
+        }
+    }
+#pragma unroll
+    for (int ni = 0; ni < TN; ++ni) {
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const unsigned off = e_voff + (unsigned)((16 * ni + e) * CH * 2);
+            const halfs_t r = __builtin_bit_cast(halfs_t, resv[ni][e]);
+            halfs_t o;
+#pragma unroll
+            for (int mi = 0; mi < TM; ++mi) o[mi] = (_Float16)keep_f32(add_half(acc[mi][ni][e], r[mi], one));     // fp32 sum, then one rounding
+            if constexpr (HEAD) {
+                const int col = wn * (16 * TN) + 16 * ni + 4 * q + e, n = n0 + col;
+                const bool inside = n >= 0 && n < nrows;
+#pragma unroll
+                for (int mi = 0; mi < TM; ++mi) {
+                    const _Float16 v = (_Float16)keep_f32(snake_fast_half(o[mi], a3v[mi], i3v[mi]));
+                    o[mi] = inside ? v : (_Float16)0.f;
+                }
+                *reinterpret_cast<halfs_t*>(&Hs[(col + hhalf) * LDH + ec]) = o;
+                continue;
+            }
+            if constexpr (TM == 2) __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, o), rs_y, off, 0, AUX);
+            else __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, o), rs_y, off, 0, AUX);
+            if (EMIT) {
+                // the next layer's operand is Snake of the STORED value
+                uint32_t sh[TM / 2];
+#pragma unroll
+                for (int mi = 0; mi < TM; mi += 2)
+                    sh[mi / 2] = pack_bf16x2(snake_fast_half(o[mi], a3v[mi], i3v[mi]), snake_fast_half(o[mi + 1], a3v[mi + 1], i3v[mi + 1]));
+                if constexpr (TM == 2) __builtin_amdgcn_raw_buffer_store_b32(sh[0], rs_a, off, 0, AUX);
+                else { const u32x2 s2 = {sh[0], sh[1]}; __builtin_amdgcn_raw_buffer_store_b64(s2, rs_a, off, 0, AUX); }
+            }
+        }
+    }
+    if constexpr (HEAD) {
+        // ---- the head on this tile, as in the kernel above: per wave NT / 128 tiles of 32 columns x k taps x 4 k-steps
+        __syncthreads();
+        constexpr int HT = NT / 32 / (WM * WN), KS = CH / 16;
+        const int j = lane & 31, hh = lane >> 5;
+        f32x16 hacc[HT];
+#pragma unroll
+        for (int k = 0; k < 16; ++k) {
+            const float hb = k < 4 && 4 * hh + k < p.oc ? p.hb[4 * hh + k] : 0.f;
+#pragma unroll
+            for (int mi = 0; mi < HT; ++mi) hacc[mi][k] = hb;
+        }
+        for (int t = 0; t < p.hk; ++t) {
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) {
+                f16x8 bw = {0, 0, 0, 0, 0, 0, 0, 0};
+                if (j < 8) bw = *reinterpret_cast<const f16x8*>(&Ws[(((t * KS + ks) * 2 + hh) * 8 + j) * 8]);
+#pragma unroll
+                for (int mi = 0; mi < HT; ++mi) {
+                    const f16x8 av = *reinterpret_cast<const f16x8*>(&Hs[((wave * HT + mi) * 32 + j + t) * LDH + ks * 16 + hh * 8]);
+                    hacc[mi] = __builtin_amdgcn_mfma_f32_32x32x16_f16(bw, av, hacc[mi], 0, 0, 0);
+                }
+            }
+        }
+        // lane (j, hh) holds time column j and output channels 4 hh + {0..3} in its first four registers
+#pragma unroll
+        for (int mi = 0; mi < HT; ++mi) {
+            const int col = (wave * HT + mi) * 32 + j, n = n0 + col;
+            if (col < hhalf || col >= NT - hhalf || n < h_lo || n >= h_hi) continue;
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const int c = 4 * hh + k;
+                if (c < p.oc) p.hy[(size_t)c * p.total_rows + rowbase + n] = tanhf(hacc[mi][k]);
+            }
+        }
+    }
+}
+
 hipError_t launch_res_unit_fused(const FusedArgs& a, hipStream_t stream)
 {
     FusedParams p;
@@ -493,19 +866,44 @@ hipError_t launch_res_unit_fused(const FusedArgs& a, hipStream_t stream)
     if ((long long)a.max_len * a.r * a.c * (long long)sizeof(hres_t) > 0xf0000000ll) return hipErrorInvalidValue;
     const long long out_rows = std::min((long long)a.max_int * a.r + 2ll * a.margin, (long long)a.max_len * a.r);
     const bool emit = a.ya != nullptr;
+    p.hw = nullptr; p.hb = p.ha = p.hib = nullptr; p.hy = nullptr; p.total_rows = 0; p.oc = p.hk = 0;
     if (a.hw) {
         // the unit before the head, with the head in the same kernel: tiles advance by NT - (k - 1) interior columns
         if (a.c != 64 || a.ya || !a.hy || !a.hb || !a.ha || !a.hib || a.hk < 1 || (a.hk & 1) == 0 || a.hk > FUSED_HEAD_MAXK ||
             a.oc < 1 || a.oc > 8 || a.margin < (a.hk - 1) / 2) return hipErrorInvalidValue;
         p.hw = a.hw; p.hb = a.hb; p.ha = a.ha; p.hib = a.hib; p.hy = a.hy; p.total_rows = a.total_rows; p.oc = a.oc; p.hk = a.hk;
-        constexpr int NT = 4 * 32 * 2;
-        const long long interior = (long long)a.max_int * a.r;
-        const long long per_tile = NT - (a.hk - 1);
-        dim3 grid((unsigned)((interior + per_tile - 1) / per_tile + 7) / 8 * 8, (unsigned)a.n_slots);
-        hipLaunchKernelGGL((res_unit_fused_kernel<64, 2, false, true>), grid, dim3(256), 0, stream, p);
+    }
+    auto tiles = [&](int nt) { return a.hw ? ((long long)a.max_int * a.r + nt - a.hk) / (nt - (a.hk - 1)) : (out_rows + nt - 1) / nt; };
+    auto grid = [&](int nt) { return dim3((unsigned)(tiles(nt) + 7) / 8 * 8, (unsigned)a.n_slots); };       // whole groups of 8 tiles; the surplus exits at once
+#define DEMON_NARROW(KX, TM, TN, WM, WN, OCC) { \
+        if (emit) hipLaunchKernelGGL((res_unit_narrow_stream_kernel<KX, TM, TN, WM, WN, OCC, true, false>), grid(16 * TN * WN), dim3(64 * WM * WN), 0, stream, p); \
+        else hipLaunchKernelGGL((res_unit_narrow_stream_kernel<KX, TM, TN, WM, WN, OCC, false, false>), grid(16 * TN * WN), dim3(64 * WM * WN), 0, stream, p); \
+        return hipGetLastError(); \
+    }
+    if (a.ntaps == 7 && a.c == 128) {
+        // 64 columns a workgroup up to five of them per CU, else 256.  Per unit (dilation 1, 3, 9 with emitted operand) in us, 64 / 256 columns:
+        // 13 frames 10, 10, 11 / 20, 20, 21; 40 frames 17, 18, 17 / 21, 20, 21; 75 frames (1133 tiles) 26, 28, 28 / 29, 30, 32; 110 frames (1656)
+        // 35, 40, 45 / 32, 32, 35; 375 frames 102, 112, 132 / 90, 92, 107; 60 s clip 457, 445, 533 / 364, 359, 404.
+        if (tiles(64) * a.call_slots <= 1280) DEMON_NARROW(32, 2, 4, 4, 1, 3)
+        DEMON_NARROW(32, 4, 8, 2, 2, 2)
+    }
+    if (a.ntaps == 7 && a.hw) {
+        hipLaunchKernelGGL((res_unit_narrow_stream_kernel<64, 2, 4, 2, 2, 3, false, true>), grid(128), dim3(256), 0, stream, p);
         return hipGetLastError();
     }
-    p.hw = nullptr; p.hb = p.ha = p.hib = nullptr; p.hy = nullptr; p.total_rows = 0; p.oc = p.hk = 0;
+    // 64 channels: streamed while the tensors read and written fit the 256 MB last-level cache (then its stores go there as well), else
+    // the LDS-staged kernel, whose stores of whole rows suit the memory better.  Per unit in us, staged / 128 columns / 256 columns: 13
+    // frames 13, 12 / 9, 8 / 10, 10; 75 frames 19 / 17 / 17; 150 frames 30 / 27 / 27; 200 frames 35 / 34 / 32; 500 frames 79 / - / 71; 600 frames
+    // 97 / - / 102; 1000 frames 163 / - / 175.
+    if (a.ntaps == 7 && a.c == 64 && out_rows * a.call_slots * 64 * 2 * 2 <= 256ll << 20) {
+        if (tiles(128) * a.call_slots <= 2304) DEMON_NARROW(64, 2, 4, 2, 2, 3)
+        DEMON_NARROW(64, 2, 8, 2, 2, 3)
+    }
+#undef DEMON_NARROW
+    if (a.hw) {
+        hipLaunchKernelGGL((res_unit_fused_kernel<64, 2, false, true>), grid(256), dim3(256), 0, stream, p);
+        return hipGetLastError();
+    }
     if (a.c == 64) {
         constexpr int NT = 4 * 32 * 2;
         dim3 grid((unsigned)((out_rows + NT - 1) / NT + 7) / 8 * 8, (unsigned)a.n_slots);       // whole groups of 8 tiles; the surplus exits at once

@@ -82,7 +82,7 @@ def _resources():
 
 def test_convolution_kernels_keep_their_accumulators_in_registers():
     """A dynamic index into the accumulators puts them in scratch memory, a round trip per stage of the K loop."""
-    res = {n: r for n, r in _resources().items() if "conv_" in n or "res_unit_wide" in n}
+    res = {n: r for n, r in _resources().items() if "conv_" in n or "res_unit_wide" in n or "res_unit_narrow" in n}
     assert len(res) > 100
     assert {n: r for n, r in res.items() if r != (0, 0)} == {}
 
