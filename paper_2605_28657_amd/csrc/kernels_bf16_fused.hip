@@ -109,7 +109,7 @@ __global__ __launch_bounds__(256, (CH == 128 && TN == 2) ? 2 : 3) void res_unit_
     uint16_t* Xs = reinterpret_cast<uint16_t*>(smem + AS_BYTES);
 
     const Slot s = p.slots[blockIdx.y];
-    const int nrows = s.len * p.r;
+    const int nrows = __builtin_amdgcn_readfirstlane(s.len * p.r);        // (the descriptors must be scalar)
     const int out_lo = max(0, s.crop * p.r - p.margin);
     const int out_hi = min(nrows, (s.crop + s.n_int) * p.r + p.margin);
     // Workgroups are dealt to the 8 XCDs round-robin by linear id, and each XCD has its own L2: XCD x takes a contiguous
@@ -122,7 +122,7 @@ __global__ __launch_bounds__(256, (CH == 128 && TN == 2) ? 2 : 3) void res_unit_
     const int n0 = HEAD ? s.crop * p.r - hhalf + tile * (NT - 2 * hhalf) : out_lo + tile * NT;
     const int h_lo = s.crop * p.r, h_hi = (s.crop + s.n_int) * p.r;     // HEAD: the interior rows the head produces
     if (HEAD ? (n0 + hhalf >= h_hi) : (n0 >= out_hi)) return;
-    const long long rowbase = (long long)s.row0 * p.r;
+    const long long rowbase = (long long)__builtin_amdgcn_readfirstlane(s.row0) * p.r;
 
     const int last_off = p.tap0 + (p.ntaps - 1) * p.tap_step;
     const int minoff = min(p.tap0, last_off);
@@ -518,7 +518,7 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) void res_unit_narrow_stream_kern
     __shared__ __attribute__((aligned(16))) float prm[(EMIT || HEAD ? 8 : 6) * CH];     // (a1, ib1) pairs | b7 | a2 | ib2 | b1 | a3 | ib3 (of the head)
 
     const Slot s = p.slots[blockIdx.y];
-    const int nrows = s.len * p.r;
+    const int nrows = __builtin_amdgcn_readfirstlane(s.len * p.r);        // (the descriptors must be scalar)
     const int out_lo = max(0, s.crop * p.r - p.margin);
     const int out_hi = min(nrows, (s.crop + s.n_int) * p.r + p.margin);
     const int tiles8 = (int)(gridDim.x >> 3);               // XCD x takes a contiguous eighth of the tiles, as above
@@ -527,7 +527,7 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) void res_unit_narrow_stream_kern
     const int h_lo = s.crop * p.r, h_hi = (s.crop + s.n_int) * p.r;     // HEAD: the interior rows the head produces
     const int n0 = HEAD ? h_lo - hhalf + tile * (NT - 2 * hhalf) : out_lo + tile * NT;
     if (HEAD ? n0 + hhalf >= h_hi : n0 >= out_hi) return;
-    const long long rowbase = (long long)s.row0 * p.r;
+    const long long rowbase = (long long)__builtin_amdgcn_readfirstlane(s.row0) * p.r;
 
     int tid = threadIdx.x;
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);

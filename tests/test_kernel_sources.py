@@ -104,8 +104,7 @@ def test_descriptors_are_scalar():
             subprocess.run(["hipcc"] + flags + ["-S", "--cuda-device-only", "-o", out, os.path.join(b.CSRC, src)], check=True, capture_output=True)
             return open(out).read()
 
-    # (the narrow fused unit that runs the head as well reads its window table into vector registers and does loop: not in the list)
-    srcs = ["kernels_bf16_stream.hip", "kernels_bf16.hip", "kernels_bf16_wide.hip", "kernels_f32.hip"]
+    srcs = ["kernels_bf16_stream.hip", "kernels_bf16.hip", "kernels_bf16_wide.hip", "kernels_bf16_fused.hip", "kernels_f32.hip"]
     with ThreadPoolExecutor(max_workers=len(srcs)) as ex:
         for src, text in zip(srcs, ex.map(asm_of, srcs)):
             # the loop's mark: descriptor words compared with the lanes' own, then the lanes that agree masked in
