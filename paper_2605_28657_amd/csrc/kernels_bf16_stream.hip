@@ -17,6 +17,7 @@
 // strided conv 1024 -> 128, stride 10: 146 -> 25 (75 columns).
 // Every tile adds in the same order (chunk, tap, k-step, for two operand planes hi before lo), so a value does not depend on the tile.
 #include <algorithm>
+
 #include <type_traits>
 
 #include "conv_bf16.h"
@@ -360,6 +361,178 @@ __global__ __launch_bounds__(64 * WM * WN, MODE == MODE_UP && TM * TN == 16 && I
     }
 }
 
+// Dilated convs of seven taps in launches of many tiles: 256 rows x 128 columns, a wave owning 64 rows of all columns (256 registers, two
+// workgroups per CU).  The 128 x 128 tile above reads 8 KB of LDS per wave and 256 cycles of MFMAs, the most a CU delivers; here it is 8 KB per
+// 512, with 4 KB of weights.  Weights are the row operand, so that a lane ends with 8 consecutive channels of a column and the
+// epilogue needs no LDS.  512 channels, 60 s clip 261 -> 242 us (1.36 PFLOP/s, what the stage loop alone sustains under the power
+// limit); the call 5551 -> 5500.  The same shape for the transposed convs (few k-steps, long epilogues: two workgroups per CU cover them
+// less well than three) is slower: 231 -> 242 us, 205 -> 244.
+template <int SPAN, int IN>
+__global__ __launch_bounds__(256, 2) void conv_tall_kernel(MfmaParams p, StreamGrid sg, bool half_out)
+{
+    fp16_saturate_on();
+    constexpr int NTAPS = 7, TM = 4, TN = 8, MT = 256, NT = 16 * TN;
+    constexpr int KX = 64, LDR = KX + 16;                   // stage of a chunk; rows 10 pieces apart: no bank conflicts
+    constexpr int SEGS = KX / 8, RPP = 256 / SEGS, X_ITERS = (NT + SPAN + RPP - 1) / RPP, XR = X_ITERS * RPP;
+    constexpr int F = 2 * NTAPS, G = F * TN;                // k-steps of 32 in a stage, groups of TM MFMAs
+    constexpr int RS = 4;                                   // k-steps of weights in flight
+    constexpr int XA = 3, XQ = XA + 1;                      // activation fragments read ahead of their MFMAs
+    constexpr int X_BYTES = XR * LDR * 2;
+    static_assert(2 * F % RS == 0 && X_ITERS <= 6 && RS / 2 * 16384 <= kWeightSlack, "static ring indices");
+    __shared__ __attribute__((aligned(16))) unsigned char smem[2 * X_BYTES];
+
+    const Slot s = p.slots[blockIdx.y];
+    const int nrows = __builtin_amdgcn_readfirstlane(s.len * p.r_in);     // (the descriptors must be scalar)
+    const int out_lo = max(0, s.crop * p.r_in - p.margin);
+    const int out_hi = min(nrows, (s.crop + s.n_int) * p.r_in + p.margin);
+    // XCD (x % xm, x / xm) takes every xm-th row tile and every xn-th column tile, as above
+    const int xcd = (int)((blockIdx.x + blockIdx.y) & 7u), q8 = (int)(blockIdx.x >> 3);
+    const int mtile = xcd % sg.xm + sg.xm * (q8 % sg.mper), ntile = xcd / sg.xm + sg.xn * (q8 / sg.mper);
+    const int n0 = out_lo + ntile * NT, m0 = mtile * MT;
+    if (n0 >= out_hi) return;                               // (also an empty window: a gated clip)
+    const long long rowbase = (long long)__builtin_amdgcn_readfirstlane(s.row0) * p.r_in;
+
+    int tid = threadIdx.x;
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    int i = lane & 15, q = lane >> 4;
+    const int seg = tid % SEGS, xr0 = tid / SEGS;
+
+    const __amdgpu_buffer_rsrc_t rs_w = weight_rsrc(p.w, p.w_bytes);
+    const __amdgpu_buffer_rsrc_t rs_x = make_rsrc(p.xa + rowbase * p.cin, (unsigned)nrows * p.cin * 2u);
+
+    // weights as above: this wave's four units are half of a panel of 128 rows, unit u (order 0, 2, 1, 3 in the block) slot l is
+    // row 32 (u / 2) + 2 l + u % 2 of the wave's 64
+    const int nblocks = p.nchunks * NTAPS;
+    const unsigned w_voff = (unsigned)lane * 16u;
+    const unsigned w_tile = (unsigned)(2 * mtile + (wave >> 1)) * (unsigned)nblocks * 16384u + (wave & 1) * 8192u;
+    u32x4 a[RS][TM];
+    auto load_a = [&](int block0, int f, int slot) __attribute__((always_inline)) {          // k-step f from block0 on
+#pragma unroll
+        for (int mi = 0; mi < TM; ++mi)
+            a[slot][mi] = __builtin_amdgcn_raw_buffer_load_b128(rs_w, w_voff, w_tile + (unsigned)(block0 + f / 2) * 16384u + ((mi & 1) * 2 + (mi >> 1)) * 2048u + (f & 1) * 1024u, 0);
+    };
+
+    const unsigned x_voff = ((unsigned)((n0 + p.tap0 + xr0) * p.cin) + seg * 8u) * 2u;      // may wrap "negative": out of range
+    const unsigned x_row_step = (unsigned)(RPP * p.cin) * 2u;
+    const int nstages = p.nchunks;                          // even
+    u32x4 rx[X_ITERS];
+    auto load_x = [&](int stage, int it) __attribute__((always_inline)) {
+        rx[it] = __builtin_amdgcn_raw_buffer_load_b128(rs_x, x_voff + (unsigned)(stage * KX) * 2u + it * x_row_step, 0, 0);
+    };
+    auto store_x = [&](int buf, int it) __attribute__((always_inline)) {
+        *reinterpret_cast<u32x4*>(smem + buf * X_BYTES + ((xr0 + it * RPP) * LDR + seg * 8) * 2) = rx[it];
+    };
+#pragma unroll
+    for (int it = 0; it < X_ITERS; ++it) load_x(0, it);
+#pragma unroll
+    for (int f = 0; f < RS; ++f) load_a(0, f, f);
+    // weights are the row operand: registers e of units 2 pr, 2 pr + 1 are rows rb + 32 pr + {0..7} (2 e + unit) of column 16 ni + i
+    const int rb = m0 + 64 * wave + 8 * q;
+    f32x4 acc[TM][TN];
+#pragma unroll
+    for (int pr = 0; pr < 2; ++pr) {
+        const f32x4 b0 = *reinterpret_cast<const f32x4*>(p.bias + rb + 32 * pr), b1 = *reinterpret_cast<const f32x4*>(p.bias + rb + 32 * pr + 4);
+#pragma unroll
+        for (int ni = 0; ni < TN; ++ni) {
+            acc[2 * pr][ni] = f32x4{b0[0], b0[2], b1[0], b1[2]};
+            acc[2 * pr + 1][ni] = f32x4{b0[1], b0[3], b1[1], b1[3]};
+        }
+    }
+#pragma unroll
+    for (int it = 0; it < X_ITERS; ++it) store_x(0, it);
+    __syncthreads();
+
+    __builtin_amdgcn_s_setprio(1);                          // waves in this loop go first
+    const int tap_bytes = p.tap_step * (LDR * 2);
+    auto run_stage = [&](int stage_, auto half_, auto last) __attribute__((always_inline)) {
+        const int stage = __builtin_amdgcn_readfirstlane(stage_);
+        constexpr int half = decltype(half_)::value;
+        constexpr bool NEXT = half == 0 || !decltype(last)::value;          // another stage follows
+        unsigned at = half * X_BYTES + (i * LDR + q * 8) * 2;
+        u32x4 x[XQ];
+        auto read_x = [&](int t) __attribute__((always_inline)) {
+            const int f = t / TN, ni = t % TN;              // k-step (chunk half ks, tap): the taps of a half are 32 channels apart
+            if (t > 0 && t % (2 * TN) == 0) { at += tap_bytes; asm volatile("" : "+v"(at)); }
+            x[t % XQ] = *reinterpret_cast<const u32x4*>(smem + at + (16 * ni * LDR + f % 2 * 32) * 2);
+        };
+#pragma unroll
+        for (int t = 0; t < XA; ++t) read_x(t);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int f = 0; f < F; ++f) {
+            if constexpr (NEXT) {
+                // the next stage's activations, two rows of a thread at a time
+                if (f >= 4 && f % 4 == 0) {
+#pragma unroll
+                    for (int it = f / 2 - 2; it < f / 2 && it < X_ITERS; ++it) store_x(half ^ 1, it);
+                }
+                if (f % 4 == 0) {
+#pragma unroll
+                    for (int it = f / 2; it < f / 2 + 2 && it < X_ITERS; ++it) load_x(stage + 1, it);
+                }
+            }
+#pragma unroll
+            for (int ni = 0; ni < TN; ++ni) {
+                const int t = f * TN + ni;
+                if (t + XA < G) read_x(t + XA);
+#pragma unroll
+                for (int mi = 0; mi < TM; ++mi) {
+                    const u32x4 w = a[(half * F + f) % RS][mi];
+                    if (IN == OP_F16)
+                        acc[mi][ni] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, w), __builtin_bit_cast(f16x8, x[t % XQ]), acc[mi][ni], 0, 0, 0);
+                    else
+                        acc[mi][ni] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, w), __builtin_bit_cast(bf16x8, x[t % XQ]), acc[mi][ni], 0, 0, 0);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            if (NEXT || f + RS < F) load_a(stage * NTAPS, f + RS, (half * F + f) % RS);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+        if (NEXT) __syncthreads();
+    };
+    int stage = 0;
+    for (; stage + 2 < nstages; stage += 2) {
+        run_stage(stage, std::integral_constant<int, 0>{}, std::false_type{});
+        run_stage(stage + 1, std::integral_constant<int, 1>{}, std::false_type{});
+    }
+    run_stage(stage, std::integral_constant<int, 0>{}, std::true_type{});
+    run_stage(stage + 1, std::integral_constant<int, 1>{}, std::true_type{});
+    __builtin_amdgcn_s_setprio(0);
+    __builtin_amdgcn_sched_barrier(0);
+
+    // ---- epilogue: 8 rows (channels) of a column a lane, 64 bytes in four lanes
+    asm volatile("" : "+v"(tid));                           // what the lane's number decides is formed again: nothing of it is held through the loop
+    i = tid & 15; q = (tid >> 4) & 3;
+    const __amdgpu_buffer_rsrc_t rs_a = make_rsrc(p.ya + rowbase * p.cout, (unsigned)out_hi * p.cout * 2u);
+#pragma unroll
+    for (int pr = 0; pr < 2; ++pr) {
+        const int row = m0 + 64 * wave + 32 * pr + 8 * q;
+        float oa[8], ob[8];
+#pragma unroll
+        for (int e = 0; e < 8; e += 4) {
+            const f32x4 va = *reinterpret_cast<const f32x4*>(p.out_alpha + row + e), vb = *reinterpret_cast<const f32x4*>(p.out_inv_beta + row + e);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) { oa[e + k] = va[k]; ob[e + k] = vb[k]; }
+        }
+#pragma unroll
+        for (int ni = 0; ni < TN; ++ni) {
+            __builtin_amdgcn_sched_barrier(0);
+            float v[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) v[e] = keep_f32(snake_fast(acc[2 * pr + (e & 1)][ni][e >> 1], oa[e], ob[e]));       // fp32 Snake, then one rounding
+            u32x4 o;
+            if (half_out) {
+#pragma unroll
+                for (int k = 0; k < 4; ++k) o[k] = pack_f16x2(v[2 * k], v[2 * k + 1]);
+            } else {
+#pragma unroll
+                for (int k = 0; k < 4; ++k) o[k] = pack_bf16x2(v[2 * k], v[2 * k + 1]);
+            }
+            __builtin_amdgcn_raw_buffer_store_b128(o, rs_a, (unsigned)((n0 + 16 * ni + i) * p.cout + row) * 2u, 0, 0);
+        }
+    }
+}
+
 template <int TM, int TN, int WM, int WN>
 hipError_t launch_tile(const MfmaParams& p, const StreamGrid& sg, int mode, int in_fmt, int emit, dim3 grid, hipStream_t stream)
 {
@@ -428,24 +601,30 @@ hipError_t launch_conv_stream(MfmaParams p, int mode, int in_fmt, int emit, int 
     // columns.  A CU takes weights in at some 45 bytes per clock, so small tiles are bound by that and large ones by their
     // MFMAs.  Launches of more than `max_small` 128 x 128 tiles take that tile without further ado.
     struct Tile { int mt, nt; double alone, shared; };
-    static const Tile kFixed[6] = {{32, 32, 25, 26}, {64, 64, 57, 70}, {64, 80, 65, 85}, {64, 96, 73, 97}, {128, 64, 90, 122}, {128, 128, 185, 212}};
+    static const Tile kFixed[7] = {{32, 32, 25, 26}, {64, 64, 57, 70}, {64, 80, 65, 85}, {64, 96, 73, 97}, {128, 64, 90, 122}, {128, 128, 185, 212}, {256, 128, 335, 368}};
     // Any number of taps: the small tiles have fewer k-steps in flight and the LDS of the largest span.  Measured with 3 to 15 taps
     // (1024-channel dilated conv of 9 taps in us, tiles in this order: 75 frames 49, 32, 34, 37, 40, 56; 250 frames 149, 72, 97, 75, 63,
     // 64; 750 frames 430, 198, 258, 227, 168, 161; 1500 frames 847, 388, 488, 435, 297, 270).
     static const Tile kAny[6] = {{32, 32, 75, 45}, {64, 64, 90, 78}, {64, 80, 100, 115}, {64, 96, 105, 132}, {128, 64, 120, 118}, {128, 128, 177, 190}};
-    const Tile* kTiles = mode == MODE_ACT && p.ntaps != 7 && p.ntaps != 1 ? kAny : kFixed;
+    const bool any = mode == MODE_ACT && p.ntaps != 7 && p.ntaps != 1;
+    // Seven taps: the tall tile (conv_tall_kernel) where there is more than one round of its two workgroups per CU: below, it is faster by
+    // itself (8 windows of 64 frames, 512 channels: 93 -> 87 us) but not beside the other group's launches (1899 -> 1925 us a call).  Calls
+    // in us, without / with: 700 frames in one window 2622 / 2597, 750 frames 2843 / 2817, 1000 3676 / 3657, 1500 5573 / 5505.
+    const bool tall_ok = mode == MODE_ACT && p.ntaps == 7 && rows % 256 == 0 && in_fmt != OP_BF16X2 && (emit == 1 || emit == 3);
+    const Tile* kTiles = any ? kAny : kFixed;
+    const bool large = (ncols + 127) / 128 * (rows / 128) * call_slots > max_small;
     int best = 5;
-    if ((ncols + 127) / 128 * (rows / 128) * call_slots <= max_small) {
-        double least = 0;
-        for (int t = 0; t < 6; ++t) {
-            const long long wgs = (ncols + kTiles[t].nt - 1) / kTiles[t].nt * (rows / kTiles[t].mt) * call_slots;
-            const double cost = wgs <= 256 ? kTiles[t].alone : wgs <= 1024 ? (double)((wgs + 255) / 256) * kTiles[t].shared : (wgs / 256.0 + 0.5) * kTiles[t].shared;
-            if (t == 0 || cost < least) { least = cost; best = t; }
-        }
+    double cheapest = 0;
+    for (int t = large ? 5 : 0; t < (tall_ok ? 7 : 6); ++t) {
+        const long long wgs = (ncols + kTiles[t].nt - 1) / kTiles[t].nt * (rows / kTiles[t].mt) * call_slots;
+        if (t == 6 && wgs <= 512) continue;
+        const double cost = wgs <= 256 ? kTiles[t].alone : wgs <= 1024 ? (double)((wgs + 255) / 256) * kTiles[t].shared : (wgs / 256.0 + 0.5) * kTiles[t].shared;
+        if (cheapest == 0 || cost < cheapest) { cheapest = cost; best = t; }
     }
+    const bool tall = best == 6;
     const int mt = kTiles[best].mt, nt = kTiles[best].nt;
     StreamGrid sg;
-    const int panels = rows / 128;
+    const int panels = rows / std::max(128, mt);
     // split of the 8 XCDs over panels and column tiles with the least to read per XCD
     const double w = (double)p.w_bytes, x = (double)ncols * n_slots * (mode == MODE_DOWN ? 2 : 1) * p.cin * 2.0;
     double least = 0;
@@ -456,10 +635,19 @@ hipError_t launch_conv_stream(MfmaParams p, int mode, int in_fmt, int emit, int 
         if (sg.xm == 0 || cost < least) { sg.xm = xm; least = cost; }
     }
     sg.xn = 8 / sg.xm;
-    sg.mper = panels / sg.xm * (128 / mt);
+    sg.mper = panels / sg.xm * std::max(1, 128 / mt);
     const long long ntiles = ((ncols + nt - 1) / nt + sg.xn - 1) / sg.xn * sg.xn;
     if (ntiles * (rows / mt) > 0x7fffffffll) return hipErrorInvalidValue;
     const dim3 grid((unsigned)(ntiles * (rows / mt)), (unsigned)n_slots);
+    if (tall) {
+#define DEMON_TALL(SPAN_, IN_) if (in_fmt == IN_ && 6 * p.tap_step <= SPAN_) { \
+        hipLaunchKernelGGL((conv_tall_kernel<SPAN_, IN_>), grid, dim3(256), 0, stream, p, sg, emit == 3); \
+        return hipGetLastError(); \
+    }
+        DEMON_TALL(32, OP_BF16) DEMON_TALL(32, OP_F16) DEMON_TALL(MAXSPAN, OP_BF16) DEMON_TALL(MAXSPAN, OP_F16)
+#undef DEMON_TALL
+        return hipErrorInvalidValue;
+    }
     switch (best) {
         case 0: return launch_tile<1, 2, 2, 1>(p, sg, mode, in_fmt, emit, grid, stream);
         case 1: return launch_tile<1, 4, 4, 1>(p, sg, mode, in_fmt, emit, grid, stream);
