@@ -124,6 +124,7 @@ struct demon_vae {
     int device = 0;
     bool has_staged_convs = false;     // bf16 path: some convolution outside the fused units takes an LDS-staged tile
     bool has_split_operands = false;   // bf16 path: some layer carries its operand as hi + lo planes
+    bool fuse_f32 = false;             // fp32 path: residual units may run as one kernel
     long long small_tile_wgs = 1024;   // bf16 path: launches of more 128 x 128 tiles than this take that tile
     bool head_fusable = false;         // bf16 path: the last layer is a fused 64-channel unit that can run the head in its kernel
 
@@ -448,6 +449,16 @@ demon_status run_pass(demon_vae* v, const Workspace& ws, const Plan* plan, const
             } else {
                 const ResUnit& U = *T.unit;
                 ConvArgs d = conv_args(U.dilated, act, nullptr, nullptr);
+                ConvArgs fused = conv_args(U.pointwise, other, cur, cur);
+                emit_to(fused, other);                                 // (neighbouring tiles read `act`)
+                if (v->fuse_f32 && res_unit_f32_fuses(d, fused)) {
+                    HIP_TRY(launch_res_unit_f32(d, fused, stream), "residual unit");
+                    std::swap(act, other);
+                    HIP_TRY(mark(2), "event");
+                    HIP_TRY(mark(last ? 1 : 2), "event");
+                    HIP_TRY(tap(cur, U.pointwise.cout), "debug tap");
+                    continue;
+                }
                 d.ya = other;                                          // Snake between the convolutions: the layer's own out_alpha
                 HIP_TRY(launch_conv_f32(d, stream), "dilated convolution");
                 HIP_TRY(mark(2), "event");
@@ -645,6 +656,7 @@ demon_status create_impl(const demon_vae_config* cfg, const float* host_weights,
 
     v->st = st; v->dtype = cfg->dtype; v->max_frames = cfg->max_frames; v->max_clips = cfg->max_clips;
     v->encoder = encoder;
+    v->fuse_f32 = !bf && g_allow_fused;
     if (cfg->max_extended_frames < 0) return fail(DEMON_ERR_INVALID_ARG, "max_extended_frames must be >= 0");
     v->cap_frames = cfg->max_extended_frames > 0 ? cfg->max_extended_frames : 3ll * cfg->max_frames * cfg->max_clips;
     if (encoder) stack_encoder_receptive_field(st, &v->rf_left, &v->rf_right, nullptr, nullptr);

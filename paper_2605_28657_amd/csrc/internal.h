@@ -88,6 +88,9 @@ struct ConvArgs {
 
 // fp32 implicit GEMM on an activated input; y: the residual stream (or nullptr), ya: fp32 operand of the next layer (or nullptr)
 hipError_t launch_conv_f32(const ConvArgs& a, hipStream_t stream);
+// a residual unit (dilated conv, 1x1 conv) in one kernel, where res_unit_f32_fuses()
+bool res_unit_f32_fuses(const ConvArgs& d, const ConvArgs& p);
+hipError_t launch_res_unit_f32(const ConvArgs& d, const ConvArgs& p, hipStream_t stream);
 // bf16 MFMA implicit GEMM.  `variant` is the tile configuration chosen when the weights were packed.
 hipError_t launch_conv_bf16(const ConvArgs& a, int variant, hipStream_t stream);
 
