@@ -1,7 +1,7 @@
 #!/usr/bin/env python3
 """Benchmark of the windowed VAE decode on one MI355X.
 
-One step = one windowed decode (gather -> transposed/dilated/1x1 convolutions -> head -> stitch) of the
+One step = one windowed decode (gather -> transposed/dilated/1x1 convolutions -> head) of the
 60 s, 48 kHz stereo workload: a 64 x 1500 latent cut into 24 windows of 64 frames plus a 6-frame halo,
 all windows in one batch.  Inputs are synthetic (seeded) and resident in HBM before the timed region.
 Prints ONE JSON line.
@@ -253,7 +253,7 @@ def main():
                                 "channels on (f16 MFMA); fp32 accumulation; residual stream stored as IEEE half")
                    if wl.bf16 else "fp32"},
         "roofline": {
-            "kernel": "MFMA convolution kernels (conv_stream_kernel, res_unit_wide_kernel, res_unit_wide_stream_kernel, "
+            "kernel": "MFMA convolution kernels (conv_stream_kernel, conv_tall_kernel, res_unit_wide_*, res_unit_narrow_stream_kernel, "
                       "res_unit_fused_kernel; conv_mfma_kernel for widths that are no multiple of 128): all %d "
                       "convolution layers of a step" % n_conv_launches,
             "bound": "mfma", "achieved": achieved, "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
@@ -264,17 +264,13 @@ def main():
             "algorithmic_flop": conv_f * frames,
             "time_ms": conv_ms,
         },
-        "stage_ms": {"gather": float(groups[0]), "convolutions": conv_ms, "head": float(groups[2]),
-                     "stitch": float(groups[3])},
+        "stage_ms": {"gather": float(groups[0]), "convolutions": conv_ms, "head": float(groups[2])},
     }
     # HBM-bound kernels: algorithmic bytes = what must be read plus what must be written.  The head reads the
-    # interior rows of the last residual stream (half precision on the bf16 path) once and writes the window waveforms.
+    # interior rows of the last residual stream (half precision on the bf16 path) once and writes the caller's waveform (crop and stitch are in its addresses).
     rows = frames * S
     head_bytes = rows * spec.widths[-1] * (2 if wl.bf16 else 4) + rows * spec.out_channels * 4
-    stitch_bytes = 2 * rows * spec.out_channels * 4
-    result["hbm_kernels"] = {
-        "stitch": {"GB/s": stitch_bytes / (groups[3] * 1e-3) / 1e9, "frac": stitch_bytes / (groups[3] * 1e-3) / 1e9 / PEAK_HBM_GBS},
-    }
+    result["hbm_kernels"] = {}
     if groups[2] > 2e-2:
         result["hbm_kernels"]["head"] = {"GB/s": head_bytes / (groups[2] * 1e-3) / 1e9,
                                          "frac": head_bytes / (groups[2] * 1e-3) / 1e9 / PEAK_HBM_GBS}
@@ -292,7 +288,7 @@ def main():
             names.append(f"b{l}.up")
             for j in range(len(spec.dilations)):
                 names += [f"b{l}.r{j}.conv{spec.res_kernel}", f"b{l}.r{j}.conv1"]
-        names += ["head", "stitch"]
+        names += ["head"]
         result["launch_ms"] = dict(zip(names, [round(x, 4) for x in t]))
         result["layers"] = layer_table(spec, wl, result["launch_ms"])
     vae.set_timing(0)

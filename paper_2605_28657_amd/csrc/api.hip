@@ -342,7 +342,7 @@ struct Io {
 };
 
 // The launch sequence of one call over the windows of `plan`, in the memory of `ws`: the decoder's
-// gather | layers | head | stitch, or the encoder's stem | layers | sampling step.
+// gather | layers | head (| 16-bit render), or the encoder's stem | layers | sampling step.
 demon_status run_pass(demon_vae* v, const Workspace& ws, const Plan* plan, const Io& io, hipStream_t stream)
 {
     const bool bf = v->dtype == DEMON_BF16;
@@ -355,8 +355,7 @@ demon_status run_pass(demon_vae* v, const Workspace& ws, const Plan* plan, const
     const Slot* slots = plan->d_slots;
     const int ns = plan->n_slots, ml = plan->max_len;
     if (io.d_skip) {
-        // gated decode: every kernel reads a copy of the table in which the skipped clips' windows are empty
-        HIP_TRY(launch_gate_slots(plan->d_slots, ws.slot_gated, ns, io.d_skip, stream), "decode gate");
+        // gated decode: the gather writes a copy of the table in which the skipped clips' windows are empty, for all kernels after it
         slots = ws.slot_gated;
     }
 
@@ -387,11 +386,15 @@ demon_status run_pass(demon_vae* v, const Workspace& ws, const Plan* plan, const
         if (!marks_on || v->timing < level || v->n_marks >= v->marks_per_call) return hipSuccess;
         return hipEventRecord(v->events[ring_base + v->n_marks++], stream);
     };
-    // level 1 marks: start, after gather (stem), after the last convolution, after head (sampling step), after stitch.
+    // level 1 marks: start, after gather (stem), after the last convolution, after head (sampling step), after the 16-bit render.
     // level 2 adds a mark after every convolution launch.
     HIP_TRY(mark(1), "event");
 
     const int S = v->st.total_stride();
+    // the head writes the caller's waveform; the 16-bit render takes the windows' waveforms, planar [channel][all rows]
+    HeadOut head_out;
+    if (io.d_pcm) { head_out.y = ws.head_out; head_out.plane = plan->total_frames * S; }
+    else { head_out.y = io.d_out; head_out.plane = (long long)n_frames * S; head_out.n_frames = n_frames; }
     void* cur = ws.buf[0];
     void* other = ws.buf[1];
     int r = enc ? S : 1, layer_id = 0;
@@ -428,8 +431,8 @@ demon_status run_pass(demon_vae* v, const Workspace& ws, const Plan* plan, const
                                 v->stem_cout, v->st.head_kernel, S, n_frames, v->stem_margin, slots, ns, ml, plan->max_int, stream), "stem");
         } else {
             const ConvLayer& C = *v->first_consumer;
-            HIP_TRY(launch_gather(io.d_latent, (float*)act, v->st.c0, n_frames, false, slots, ns, ml, stream, nullptr, 0, 0,
-                                  C.in_alpha, C.in_inv_beta), "gather");
+            HIP_TRY(launch_gather(io.d_latent, (float*)act, v->st.c0, n_frames, false, plan->d_slots, ns, ml, stream, nullptr, 0, 0,
+                                  C.in_alpha, C.in_inv_beta, io.d_skip, ws.slot_gated), "gather");
         }
         HIP_TRY(mark(1), "event");
         for (size_t si = 0; si < n_steps; ++si) {
@@ -486,8 +489,8 @@ demon_status run_pass(demon_vae* v, const Workspace& ws, const Plan* plan, const
                                     plan->max_int, stream), "stem");
             } else {
                 const ConvLayer& U0 = *v->first_consumer;
-                HIP_TRY(launch_gather(io.d_latent, nullptr, v->st.c0, n_frames, true, gs, gn, ml, stream, at(ws.buf[3], 1, v->st.c0),
-                                      U0.in_fmt, lo_off, U0.in_alpha, U0.in_inv_beta), "gather");
+                HIP_TRY(launch_gather(io.d_latent, nullptr, v->st.c0, n_frames, true, io.d_skip ? plan->d_slots : gs, gn, ml, stream,
+                                      at(ws.buf[3], 1, v->st.c0), U0.in_fmt, lo_off, U0.in_alpha, U0.in_inv_beta, io.d_skip, ws.slot_gated), "gather");
             }
         }
         HIP_TRY(mark(1), "event");
@@ -526,7 +529,7 @@ demon_status run_pass(demon_vae* v, const Workspace& ws, const Plan* plan, const
                     if (C && C->in_fmt != OP_BF16) return fail(DEMON_ERR_UNSUPPORTED, "a fused unit cannot feed a layer with wide operands");
                     if (last && head_in_unit) {
                         f.hw = v->head_wfrag; f.hb = v->head_bias; f.ha = v->head_alpha; f.hib = v->head_inv_beta;
-                        f.hy = ws.head_out; f.total_rows = plan->total_frames * r;
+                        f.out = head_out;
                         f.oc = v->st.out_channels; f.hk = v->st.head_kernel;
                     }
                     HIP_TRY(launch_res_unit_fused(f, gst), "fused residual unit");
@@ -592,23 +595,20 @@ demon_status run_pass(demon_vae* v, const Workspace& ws, const Plan* plan, const
         if (v->timing > 0) ++v->timed_calls;
         return DEMON_OK;
     }
-    // head (group by group on the caller's stream) and stitch; the window waveforms are planar [channel][all rows]
-    const long long total_rows = plan->total_frames * r;
+    // head, group by group on the caller's stream
     for (int gi = 0; gi < n_groups && !head_in_unit; ++gi) {
         select_group(gi, stream);
         const void* x = at(cur, r, v->head_cin);
         if (v->head_wfrag)
-            HIP_TRY(launch_head_mfma(x, ws.head_out, v->head_wfrag, v->head_bias, v->head_alpha, v->head_inv_beta, v->head_cin,
-                                     v->st.out_channels, v->st.head_kernel, r, total_rows, gs, gn, ml, plan->max_int, stream), "head");
+            HIP_TRY(launch_head_mfma(x, head_out, v->head_wfrag, v->head_bias, v->head_alpha, v->head_inv_beta, v->head_cin,
+                                     v->st.out_channels, v->st.head_kernel, r, gs, gn, ml, plan->max_int, stream), "head");
         else
-            HIP_TRY(launch_head(x, bf, ws.head_out, v->head_w, v->head_bias, v->head_alpha, v->head_inv_beta, v->head_cin,
-                                v->st.out_channels, v->st.head_kernel, r, total_rows, bf, gs, gn, plan->max_int, stream), "head");
+            HIP_TRY(launch_head(x, bf, head_out, v->head_w, v->head_bias, v->head_alpha, v->head_inv_beta, v->head_cin,
+                                v->st.out_channels, v->st.head_kernel, r, bf, gs, gn, plan->max_int, stream), "head");
     }
     HIP_TRY(mark(1), "event");
     if (io.d_pcm)
-        HIP_TRY(launch_stitch_pcm16(ws.head_out, io.d_pcm, v->st.out_channels, r, n_frames, total_rows, slots, ns, plan->max_int, stream), "stitch");
-    else
-        HIP_TRY(launch_stitch(ws.head_out, io.d_out, v->st.out_channels, r, n_frames, total_rows, slots, ns, plan->max_int, stream), "stitch");
+        HIP_TRY(launch_stitch_pcm16(ws.head_out, io.d_pcm, v->st.out_channels, r, n_frames, head_out.plane, slots, ns, plan->max_int, stream), "stitch");
     HIP_TRY(mark(1), "event");
     if (v->timing > 0) ++v->timed_calls;
     return DEMON_OK;

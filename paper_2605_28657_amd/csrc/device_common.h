@@ -55,6 +55,12 @@ __device__ __forceinline__ float snake_fast_half(_Float16 x, float alpha_rev, fl
     return fmaf(s * s, inv_beta, (float)x);
 }
 
+// Element of HeadOut::y that channel 0 of a window's row 0 would fall on.
+__device__ __forceinline__ long long head_origin(const HeadOut& o, const Slot& s, int oc, int r)
+{
+    return o.n_frames > 0 ? ((long long)s.clip * oc * o.n_frames + s.begin - s.crop) * r : (long long)s.row0 * r;
+}
+
 // Raw buffer descriptor over [base, base + bytes): loads outside return zero, stores outside are dropped.
 // Dword 3 selects 32-bit raw addressing on gfx9-family parts.
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base, unsigned bytes)

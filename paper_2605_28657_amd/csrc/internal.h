@@ -112,6 +112,10 @@ uint16_t f32_to_bf16_rne(float v);
 uint16_t f32_to_f16_rne(float v);
 
 // Fused residual unit (bf16 path, C = 64 or 128): y = x + W1 snake2(W7 (*) snake1(x) + b7) + b1, x != y.
+// Where the head writes the interior rows of the windows: n_frames > 0: the caller's waveform, y[clip][channel][n_frames * r] (the
+// windows side by side: crop and stitch are in the address); 0: the window waveforms y[channel][plane], rows as in the workspace.
+struct HeadOut { float* y = nullptr; long long plane = 0; int n_frames = 0; };
+
 struct FusedArgs {
     const void* x; void* y;  // residual stream in its HBM storage type (half)
     uint16_t* ya = nullptr;  // optional: bf16(snake(y; a3, ib3)) for an unfused consumer
@@ -123,10 +127,9 @@ struct FusedArgs {
     const Slot* slots; int n_slots, call_slots, max_len, max_int, margin;
     int r, c, ntaps, dil;
     // optional: the decoder's head in the same kernel (64 channels, the unit feeds nothing else; y is then not written).
-    // hw: half-precision MFMA fragments (pack_head_mfma), hb bias, ha / hib the head's Snake, hy planar window waveforms
-    // [oc][total_rows] (rows counted like the unit's), hk the head's kernel size (odd, <= 7)
+    // hw: half-precision MFMA fragments (pack_head_mfma), hb bias, ha / hib the head's Snake, hk its kernel size (odd, <= 7)
     const uint16_t* hw = nullptr; const float* hb = nullptr; const float* ha = nullptr; const float* hib = nullptr;
-    float* hy = nullptr; long long total_rows = 0; int oc = 0, hk = 0;
+    HeadOut out; int oc = 0, hk = 0;
 };
 hipError_t launch_res_unit_fused(const FusedArgs& a, hipStream_t stream);
 void pack_w1_fused(const float* w, int C, uint16_t* dst);
@@ -151,11 +154,13 @@ struct IoArgs {
     const Slot* slots; int n_slots; int max_len;
 };
 // latent [n_clips, c0, n_frames] (fp32 or bf16) -> activated operand snake(x; alpha, inv_beta) of the first layer, [frames, c0]:
-// fp32 in x0 or, with `xa` (bf16 path), in operand format xa_fmt (lo plane at xa + xa_lo_off)
+// fp32 in x0 or, with `xa` (bf16 path), in operand format xa_fmt (lo plane at xa + xa_lo_off).  With `skip` (decode gate, one flag a
+// clip): nothing for the windows of flagged clips, and `gated` becomes the table with these windows empty, for the launches after it
 hipError_t launch_gather(const void* latent, float* x0, int c0, int n_frames, bool bf16,
                          const Slot* slots, int n_slots, int max_len, hipStream_t stream,
                          uint16_t* xa = nullptr, int xa_fmt = OP_BF16, long long xa_lo_off = 0,
-                         const float* alpha = nullptr, const float* inv_beta = nullptr);
+                         const float* alpha = nullptr, const float* inv_beta = nullptr,
+                         const int* skip = nullptr, Slot* gated = nullptr);
 // encoder stem: Conv1d(k, ch -> C) + bias from the planar fp32 waveform [n_clips, ch, n_frames * S] into the residual
 // stream y (half or fp32) of the rows each window needs (interior widened by `margin`); with ya also the activated
 // operand snake(y; alpha, inv_beta), fp32 or (half path) in format ya_fmt.  w: fp32 [k][ch][C].
@@ -169,27 +174,22 @@ hipError_t launch_sample(const void* m, bool m_half, const float* eps, float* mo
 // head: Snake -> Conv1d(k, cin -> oc) -> tanh; output planar fp32 [oc, total_rows]
 // `fast` selects the hardware-sine Snake (alpha given in revolutions) used by the bf16 path.
 // `x_half`: the input is the bf16 path's half-precision residual stream, else fp32.
-hipError_t launch_head(const void* x, bool x_half, float* y, const float* w /*[k][cin][oc]*/, const float* bias,
+hipError_t launch_head(const void* x, bool x_half, const HeadOut& out, const float* w /*[k][cin][oc]*/, const float* bias,
                        const float* alpha, const float* inv_beta, int cin, int oc, int k, int r,
-                       long long total_rows, bool fast, const Slot* slots, int n_slots, int max_int,
+                       bool fast, const Slot* slots, int n_slots, int max_int,
                        hipStream_t stream);
 // MFMA head of the bf16 path (cin 32 or 64, oc <= 32); weights packed by pack_head_mfma
 size_t head_mfma_frag_count(int cin, int k);          // 16-byte x 64-lane fragments
 void pack_head_mfma(const float* w /*[oc][cin][k]*/, int cin, int oc, int k, uint16_t* dst);
-hipError_t launch_head_mfma(const void* x, float* y, const uint16_t* wfrag, const float* bias, const float* alpha,
-                            const float* inv_beta, int cin, int oc, int k, int r, long long total_rows,
+hipError_t launch_head_mfma(const void* x, const HeadOut& out, const uint16_t* wfrag, const float* bias, const float* alpha,
+                            const float* inv_beta, int cin, int oc, int k, int r,
                             const Slot* slots, int n_slots, int max_len, int max_int, hipStream_t stream);
-// crop + stitch: planar slot waveform -> d_out [n_clips, oc, n_frames*S]
-hipError_t launch_stitch(const float* y, float* out, int oc, int S, int n_frames, long long total_rows,
-                         const Slot* slots, int n_slots, int max_int, hipStream_t stream);
 // crop + stitch + 16-bit render: planar slot waveform -> d_pcm [n_clips, n_frames*S, oc] interleaved int16
 hipError_t launch_stitch_pcm16(const float* y, int16_t* pcm, int oc, int S, int n_frames, long long total_rows,
                                const Slot* slots, int n_slots, int max_int, hipStream_t stream);
 // window table written on the device (no host copy); per_clip windows and clip_frames extended frames per clip.
 hipError_t launch_plan_slots(Slot* dst, int n_clips, int per_clip, int clip_frames, int n_frames, int frame_begin,
                              int frame_end, int window, int halo, hipStream_t stream);
-// decode gate: dst = src with the windows of clips whose skip flag is set emptied
-hipError_t launch_gate_slots(const Slot* src, Slot* dst, int n, const int* skip, hipStream_t stream);
 // latent similarity filter: per clip mse = mean((a-b)^2) over n elements and the gate mse < threshold
 hipError_t launch_latent_mse(const void* a, const void* b, int n_clips, long long n, bool bf16, float threshold,
                              float* mse, int* unchanged, hipStream_t stream);

@@ -41,8 +41,7 @@ struct FusedParams {
     // HEAD: the decoder's head (Snake -> Conv1d(hk) -> tanh) on this unit's output, in the same kernel
     const uint16_t* hw;          // half-precision MFMA fragments of the head weights (pack_head_mfma)
     const float* hb; const float* ha; const float* hib;
-    float* hy;                   // planar window waveforms [oc][total_rows]
-    long long total_rows;
+    HeadOut out;
     int oc, hk;
 };
 
@@ -466,6 +465,7 @@ __global__ __launch_bounds__(256, (CH == 128 && TN == 2) ? 2 : 3) void res_unit_
             }
         }
         // lane (j, h) holds time column j and output channels 4 h + {0..3} in its first four registers
+        const long long origin = head_origin(p.out, s, p.oc, p.r);
 #pragma unroll
         for (int mi = 0; mi < 2; ++mi) {
             const int col = wn * WTN + mi * 32 + j;
@@ -474,7 +474,7 @@ __global__ __launch_bounds__(256, (CH == 128 && TN == 2) ? 2 : 3) void res_unit_
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 const int c = 4 * h + q;
-                if (c < p.oc) p.hy[(size_t)c * p.total_rows + rowbase + n] = tanhf(hacc[mi][q]);
+                if (c < p.oc) p.out.y[c * p.out.plane + origin + n] = tanhf(hacc[mi][q]);
             }
         }
     }
@@ -839,6 +839,7 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) void res_unit_narrow_stream_kern
             }
         }
         // lane (j, hh) holds time column j and output channels 4 hh + {0..3} in its first four registers
+        const long long origin = head_origin(p.out, s, p.oc, p.r);
 #pragma unroll
         for (int mi = 0; mi < HT; ++mi) {
             const int col = (wave * HT + mi) * 32 + j, n = n0 + col;
@@ -846,7 +847,7 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) void res_unit_narrow_stream_kern
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
                 const int c = 4 * hh + k;
-                if (c < p.oc) p.hy[(size_t)c * p.total_rows + rowbase + n] = tanhf(hacc[mi][k]);
+                if (c < p.oc) p.out.y[c * p.out.plane + origin + n] = tanhf(hacc[mi][k]);
             }
         }
     }
@@ -866,12 +867,12 @@ hipError_t launch_res_unit_fused(const FusedArgs& a, hipStream_t stream)
     if ((long long)a.max_len * a.r * a.c * (long long)sizeof(hres_t) > 0xf0000000ll) return hipErrorInvalidValue;
     const long long out_rows = std::min((long long)a.max_int * a.r + 2ll * a.margin, (long long)a.max_len * a.r);
     const bool emit = a.ya != nullptr;
-    p.hw = nullptr; p.hb = p.ha = p.hib = nullptr; p.hy = nullptr; p.total_rows = 0; p.oc = p.hk = 0;
+    p.hw = nullptr; p.hb = p.ha = p.hib = nullptr; p.out = {}; p.oc = p.hk = 0;
     if (a.hw) {
         // the unit before the head, with the head in the same kernel: tiles advance by NT - (k - 1) interior columns
-        if (a.c != 64 || a.ya || !a.hy || !a.hb || !a.ha || !a.hib || a.hk < 1 || (a.hk & 1) == 0 || a.hk > FUSED_HEAD_MAXK ||
+        if (a.c != 64 || a.ya || !a.out.y || !a.hb || !a.ha || !a.hib || a.hk < 1 || (a.hk & 1) == 0 || a.hk > FUSED_HEAD_MAXK ||
             a.oc < 1 || a.oc > 8 || a.margin < (a.hk - 1) / 2) return hipErrorInvalidValue;
-        p.hw = a.hw; p.hb = a.hb; p.ha = a.ha; p.hib = a.hib; p.hy = a.hy; p.total_rows = a.total_rows; p.oc = a.oc; p.hk = a.hk;
+        p.hw = a.hw; p.hb = a.hb; p.ha = a.ha; p.hib = a.hib; p.out = a.out; p.oc = a.oc; p.hk = a.hk;
     }
     auto tiles = [&](int nt) { return a.hw ? ((long long)a.max_int * a.r + nt - a.hk) / (nt - (a.hk - 1)) : (out_rows + nt - 1) / nt; };
     auto grid = [&](int nt) { return dim3((unsigned)(tiles(nt) + 7) / 8 * 8, (unsigned)a.n_slots); };       // whole groups of 8 tiles; the surplus exits at once

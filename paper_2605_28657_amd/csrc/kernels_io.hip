@@ -1,10 +1,11 @@
-// Window gather, output head, crop/stitch and the debug tap (HBM-bound kernels).
+// Window gather, output head, 16-bit render and the debug tap (HBM-bound kernels).
 //
 // gather : step 1 of the windowed decode of paper section 3.6 (extend each window by its margins):
 //          copies latent frames [lo, hi) of every window into its slot, transposing to time-major.
 // head   : Snake -> Conv1d(k, C -> out_channels) -> tanh, the last layer of the decoder.
-// stitch : step 3 (trim the margins, keep the frame-aligned interior) plus the side-by-side write
-//          of the interiors into the clip's waveform.
+//          Step 3 (trim the margins, keep the frame-aligned interior, write the interiors side by side into the clip's
+//          waveform) is its store address; a kernel of its own for that cost 46 MB of traffic per 60 s clip and a launch (5 us of a
+//          0.5 s window).  Only the 16-bit render is a pass of its own.
 #include <algorithm>
 #include <type_traits>
 
@@ -28,11 +29,17 @@ template <typename T>
 __global__ __launch_bounds__(256) void gather_kernel(const T* __restrict__ latent, float* __restrict__ x0,
                                                      uint16_t* __restrict__ xa, int fmt, long long lo_off,
                                                      const float* __restrict__ alpha, const float* __restrict__ inv_beta,
-                                                     int c0, int n_frames, const Slot* __restrict__ slots)
+                                                     int c0, int n_frames, const Slot* __restrict__ slots,
+                                                     const int* __restrict__ skip, Slot* __restrict__ gated)
 {
     fp16_saturate_on();
     __shared__ float tile[GATHER_TILE][GATHER_TILE + 1];
-    const Slot s = slots[blockIdx.y];
+    Slot s = slots[blockIdx.y];
+    if (skip) {
+        // decode gate: the launches after this one read the table that the first workgroup of every window writes here
+        if (skip[s.clip] != 0) { s.len = 0; s.n_int = 0; s.crop = 0; }
+        if (blockIdx.x == 0 && blockIdx.z == 0 && threadIdx.x == 0) gated[blockIdx.y] = s;
+    }
     const int r0 = blockIdx.x * GATHER_TILE, cbase = blockIdx.z * GATHER_TILE;
     if (r0 >= s.len) return;
     const int lane = threadIdx.x % GATHER_TILE, sub = threadIdx.x / GATHER_TILE;      // 4 rows of 64 threads
@@ -63,14 +70,15 @@ __global__ __launch_bounds__(256) void gather_kernel(const T* __restrict__ laten
 
 hipError_t launch_gather(const void* latent, float* x0, int c0, int n_frames, bool bf16,
                          const Slot* slots, int n_slots, int max_len, hipStream_t stream,
-                         uint16_t* xa, int xa_fmt, long long xa_lo_off, const float* alpha, const float* inv_beta)
+                         uint16_t* xa, int xa_fmt, long long xa_lo_off, const float* alpha, const float* inv_beta,
+                         const int* skip, Slot* gated)
 {
-    if (!alpha || !inv_beta) return hipErrorInvalidValue;
+    if (!alpha || !inv_beta || (skip && !gated)) return hipErrorInvalidValue;
     dim3 grid((unsigned)((max_len + GATHER_TILE - 1) / GATHER_TILE), (unsigned)n_slots, (unsigned)((c0 + GATHER_TILE - 1) / GATHER_TILE));
     if (bf16)
-        hipLaunchKernelGGL(gather_kernel<uint16_t>, grid, dim3(256), 0, stream, (const uint16_t*)latent, x0, xa, xa_fmt, xa_lo_off, alpha, inv_beta, c0, n_frames, slots);
+        hipLaunchKernelGGL(gather_kernel<uint16_t>, grid, dim3(256), 0, stream, (const uint16_t*)latent, x0, xa, xa_fmt, xa_lo_off, alpha, inv_beta, c0, n_frames, slots, skip, gated);
     else
-        hipLaunchKernelGGL(gather_kernel<float>, grid, dim3(256), 0, stream, (const float*)latent, x0, xa, xa_fmt, xa_lo_off, alpha, inv_beta, c0, n_frames, slots);
+        hipLaunchKernelGGL(gather_kernel<float>, grid, dim3(256), 0, stream, (const float*)latent, x0, xa, xa_fmt, xa_lo_off, alpha, inv_beta, c0, n_frames, slots, skip, gated);
     return hipGetLastError();
 }
 
@@ -225,11 +233,10 @@ constexpr int HEAD_MAXK = 15;
 constexpr int HEAD_MAXOC = 8;
 
 template <typename TX, bool FAST, int OC, int K, int HEAD_SPT>
-__global__ __launch_bounds__(256) void head_fast_kernel(const TX* __restrict__ x, float* __restrict__ y,
+__global__ __launch_bounds__(256) void head_fast_kernel(const TX* __restrict__ x, HeadOut out, bool vec,
                                                         const float* __restrict__ w, const float* __restrict__ bias,
                                                         const float* __restrict__ alpha, const float* __restrict__ inv_beta,
-                                                        int cin, int r, long long total_rows,
-                                                        const Slot* __restrict__ slots)
+                                                        int cin, int r, const Slot* __restrict__ slots)
 {
     constexpr int HEAD_NT = 256 * HEAD_SPT;
     constexpr int HEAD_LDR = HEAD_NT + 20;                  // >= HEAD_NT + HEAD_MAXK - 1, = 4 (mod 16)
@@ -305,12 +312,12 @@ __global__ __launch_bounds__(256) void head_fast_kernel(const TX* __restrict__ x
                 }
         }
     }
-    const long long n = n0 + HEAD_SPT * tid;
+    const long long n = n0 + HEAD_SPT * tid, origin = head_origin(out, s, OC, r);
 #pragma unroll
     for (int o = 0; o < OC; ++o) {
         const float b = bias[o];
-        float* dst = y + (size_t)o * total_rows + rowbase + n;
-        if (HEAD_SPT == 4 && n + HEAD_SPT <= hi && (r % 4) == 0) {
+        float* dst = out.y + o * out.plane + origin + n;
+        if (HEAD_SPT == 4 && n + HEAD_SPT <= hi && vec) {
             *reinterpret_cast<float4*>(dst) = make_float4(tanhf(acc[0][o] + b), tanhf(acc[HEAD_SPT / 4][o] + b),
                                                           tanhf(acc[HEAD_SPT / 2][o] + b), tanhf(acc[HEAD_SPT - 1][o] + b));
         } else {
@@ -327,10 +334,10 @@ constexpr int HEADG_NT = 256;
 constexpr int HEADG_KC = 32;
 
 template <typename TX, bool FAST>
-__global__ __launch_bounds__(256) void head_generic_kernel(const TX* __restrict__ x, float* __restrict__ y,
+__global__ __launch_bounds__(256) void head_generic_kernel(const TX* __restrict__ x, HeadOut out,
                                                            const float* __restrict__ w, const float* __restrict__ bias,
                                                            const float* __restrict__ alpha, const float* __restrict__ inv_beta,
-                                                           int cin, int oc, int k, int r, long long total_rows,
+                                                           int cin, int oc, int k, int r,
                                                            const Slot* __restrict__ slots)
 {
     __shared__ float xs[(HEADG_NT + HEAD_MAXK - 1) * (HEADG_KC + 1)];
@@ -372,11 +379,11 @@ __global__ __launch_bounds__(256) void head_generic_kernel(const TX* __restrict_
             }
         }
     }
-    const long long n = n0 + threadIdx.x;
+    const long long n = n0 + threadIdx.x, origin = head_origin(out, s, oc, r);
     if (n < hi) {
 #pragma unroll
         for (int o = 0; o < HEAD_MAXOC; ++o)
-            if (o < oc) y[(size_t)o * total_rows + rowbase + n] = tanhf(acc[o] + bias[o]);
+            if (o < oc) out.y[o * out.plane + origin + n] = tanhf(acc[o] + bias[o]);
     }
 }
 
@@ -416,11 +423,10 @@ typedef _Float16 f16x8v __attribute__((ext_vector_type(8)));
 // zero padding and are not stored, which with the unpadded-weights tile leaves room for three workgroups per CU.
 template <int CIN, int OCP>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(OCP == 8 ? 3 : 2, OCP == 8 ? 3 : 2)))
-void head_mfma_kernel(const _Float16* __restrict__ x, float* __restrict__ y,
+void head_mfma_kernel(const _Float16* __restrict__ x, HeadOut out,
                                                         const uint16_t* __restrict__ wfrag, const float* __restrict__ bias,
                                                         const float* __restrict__ alpha, const float* __restrict__ inv_beta,
-                                                        int oc, int k, int r, long long total_rows,
-                                                        const Slot* __restrict__ slots)
+                                                        int oc, int k, int r, const Slot* __restrict__ slots)
 {
     fp16_saturate_on();
     constexpr int LDX = CIN + 8;                           // padded LDS row (halfs)
@@ -438,7 +444,7 @@ void head_mfma_kernel(const _Float16* __restrict__ x, float* __restrict__ y,
     const int XR = HM_NT + k - 1;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, j = lane & 31, h = lane >> 5;
     const int seg = tid % SEGS, xr0 = tid / SEGS;
-    const long long rowbase = (long long)s.row0 * r;
+    const long long rowbase = (long long)s.row0 * r, origin = head_origin(out, s, oc, r);
     const __amdgpu_buffer_rsrc_t rs_x = make_rsrc(x + rowbase * CIN, (unsigned)nrows * CIN * 2u);
     if (lo + (int)blockIdx.x * (HM_NT * HM_SUB) >= hi) return;
 
@@ -519,30 +525,30 @@ void head_mfma_kernel(const _Float16* __restrict__ x, float* __restrict__ y,
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
                     const int c = 8 * g + 4 * h + q;
-                    if (c < oc && n < hi) y[(size_t)c * total_rows + rowbase + n] = tanhf(acc[mi][4 * g + q]);
+                    if (c < oc && n < hi) out.y[c * out.plane + origin + n] = tanhf(acc[mi][4 * g + q]);
                 }
             }
         }
     }
 }
 
-hipError_t launch_head_mfma(const void* x, float* y, const uint16_t* wfrag, const float* bias, const float* alpha,
-                            const float* inv_beta, int cin, int oc, int k, int r, long long total_rows,
+hipError_t launch_head_mfma(const void* x, const HeadOut& out, const uint16_t* wfrag, const float* bias, const float* alpha,
+                            const float* inv_beta, int cin, int oc, int k, int r,
                             const Slot* slots, int n_slots, int max_len, int max_int, hipStream_t stream)
 {
     if (oc > 32 || k > HEAD_MAXK || (cin != 64 && cin != 32) || head_mfma_frag_count(cin, k) > HM_MAXFRAG) return hipErrorInvalidValue;
     if ((long long)max_len * r * cin * 2 > 0xf0000000ll) return hipErrorInvalidValue;
     const long long rows = (long long)max_int * r;
     dim3 grid((unsigned)((rows + HM_NT * HM_SUB - 1) / (HM_NT * HM_SUB)), (unsigned)n_slots);
-#define DEMON_HEAD(CIN_, OCP_) hipLaunchKernelGGL((head_mfma_kernel<CIN_, OCP_>), grid, dim3(256), 0, stream, (const _Float16*)x, y, wfrag, bias, alpha, inv_beta, oc, k, r, total_rows, slots)
+#define DEMON_HEAD(CIN_, OCP_) hipLaunchKernelGGL((head_mfma_kernel<CIN_, OCP_>), grid, dim3(256), 0, stream, (const _Float16*)x, out, wfrag, bias, alpha, inv_beta, oc, k, r, slots)
     if (cin == 64) { if (oc <= 8) DEMON_HEAD(64, 8); else DEMON_HEAD(64, 32); }
     else { if (oc <= 8) DEMON_HEAD(32, 8); else DEMON_HEAD(32, 32); }
 #undef DEMON_HEAD
     return hipGetLastError();
 }
 
-hipError_t launch_head(const void* x, bool x_half, float* y, const float* w, const float* bias, const float* alpha,
-                       const float* inv_beta, int cin, int oc, int k, int r, long long total_rows,
+hipError_t launch_head(const void* x, bool x_half, const HeadOut& out, const float* w, const float* bias, const float* alpha,
+                       const float* inv_beta, int cin, int oc, int k, int r,
                        bool fast, const Slot* slots, int n_slots, int max_int, hipStream_t stream)
 {
     if (k > HEAD_MAXK || oc > HEAD_MAXOC || (x_half && !fast)) return hipErrorInvalidValue;
@@ -550,8 +556,10 @@ hipError_t launch_head(const void* x, bool x_half, float* y, const float* w, con
     if (oc == 2 && k == 7 && cin % HEAD_KC == 0) {
         const bool few = (rows + 1023) / 1024 * n_slots < 512;        // two 1024-sample workgroups per CU
         const int nt = few ? 256 : 1024;
+        // 16-byte stores: rows of a window start at multiples of r in a plane, planes (and clips) are multiples of r apart
+        const bool vec = r % 4 == 0 && reinterpret_cast<uintptr_t>(out.y) % 16 == 0;
         dim3 grid((unsigned)((rows + nt - 1) / nt), (unsigned)n_slots);
-#define DEMON_HEADF(TX_, FAST_, SPT_) hipLaunchKernelGGL((head_fast_kernel<TX_, FAST_, 2, 7, SPT_>), grid, dim3(256), 0, stream, (const TX_*)x, y, w, bias, alpha, inv_beta, cin, r, total_rows, slots)
+#define DEMON_HEADF(TX_, FAST_, SPT_) hipLaunchKernelGGL((head_fast_kernel<TX_, FAST_, 2, 7, SPT_>), grid, dim3(256), 0, stream, (const TX_*)x, out, vec, w, bias, alpha, inv_beta, cin, r, slots)
         if (x_half) { if (few) DEMON_HEADF(_Float16, true, 1); else DEMON_HEADF(_Float16, true, 4); }
         else if (fast) { if (few) DEMON_HEADF(float, true, 1); else DEMON_HEADF(float, true, 4); }
         else { if (few) DEMON_HEADF(float, false, 1); else DEMON_HEADF(float, false, 4); }
@@ -560,49 +568,16 @@ hipError_t launch_head(const void* x, bool x_half, float* y, const float* w, con
     }
     dim3 grid((unsigned)((rows + HEADG_NT - 1) / HEADG_NT), (unsigned)n_slots);
     if (x_half)
-        hipLaunchKernelGGL((head_generic_kernel<_Float16, true>), grid, dim3(256), 0, stream, (const _Float16*)x, y, w, bias, alpha, inv_beta, cin, oc, k, r, total_rows, slots);
+        hipLaunchKernelGGL((head_generic_kernel<_Float16, true>), grid, dim3(256), 0, stream, (const _Float16*)x, out, w, bias, alpha, inv_beta, cin, oc, k, r, slots);
     else if (fast)
-        hipLaunchKernelGGL((head_generic_kernel<float, true>), grid, dim3(256), 0, stream, (const float*)x, y, w, bias, alpha, inv_beta, cin, oc, k, r, total_rows, slots);
+        hipLaunchKernelGGL((head_generic_kernel<float, true>), grid, dim3(256), 0, stream, (const float*)x, out, w, bias, alpha, inv_beta, cin, oc, k, r, slots);
     else
-        hipLaunchKernelGGL((head_generic_kernel<float, false>), grid, dim3(256), 0, stream, (const float*)x, y, w, bias, alpha, inv_beta, cin, oc, k, r, total_rows, slots);
+        hipLaunchKernelGGL((head_generic_kernel<float, false>), grid, dim3(256), 0, stream, (const float*)x, out, w, bias, alpha, inv_beta, cin, oc, k, r, slots);
     return hipGetLastError();
 }
 
-// ---------------------------------------------------------------------------------- stitch
-// grid (chunks of the interior, slots, output channels).  VEC = 4 when S % 4 == 0 (then every
-// interior starts on a 16-byte boundary in both buffers), else 1.
-template <int VEC>
-__global__ __launch_bounds__(256) void stitch_kernel(const float* __restrict__ y, float* __restrict__ out,
-                                                     int oc, int S, int n_frames, long long total_rows,
-                                                     const Slot* __restrict__ slots)
-{
-    const Slot s = slots[blockIdx.y];
-    const int c = blockIdx.z;
-    const long long n = (long long)s.n_int * S;
-    const long long i = ((long long)blockIdx.x * 256 + threadIdx.x) * VEC;
-    if (i >= n) return;
-    const float* src = y + (size_t)c * total_rows + ((long long)s.row0 + s.crop) * S + i;
-    float* dst = out + ((size_t)s.clip * oc + c) * ((size_t)n_frames * S) + (long long)s.begin * S + i;
-    if (VEC == 4) *reinterpret_cast<float4*>(dst) = *reinterpret_cast<const float4*>(src);
-    else *dst = *src;
-}
-
-hipError_t launch_stitch(const float* y, float* out, int oc, int S, int n_frames, long long total_rows,
-                         const Slot* slots, int n_slots, int max_int, hipStream_t stream)
-{
-    const bool vec = (S % 4 == 0) && ((reinterpret_cast<uintptr_t>(y) | reinterpret_cast<uintptr_t>(out)) % 16 == 0);
-    const long long per = (long long)max_int * S;
-    if (vec) {
-        dim3 grid((unsigned)((per / 4 + 255) / 256), (unsigned)n_slots, (unsigned)oc);
-        hipLaunchKernelGGL(stitch_kernel<4>, grid, dim3(256), 0, stream, y, out, oc, S, n_frames, total_rows, slots);
-    } else {
-        dim3 grid((unsigned)((per + 255) / 256), (unsigned)n_slots, (unsigned)oc);
-        hipLaunchKernelGGL(stitch_kernel<1>, grid, dim3(256), 0, stream, y, out, oc, S, n_frames, total_rows, slots);
-    }
-    return hipGetLastError();
-}
-
-// 16-bit render fused into the stitch: q = rint(32767 * clamp(y, -1, 1)) in fp32 (round half to even), channels
+// ---------------------------------------------------------------------------------- 16-bit render
+// Crop, stitch and 16-bit render of the window waveforms: q = rint(32767 * clamp(y, -1, 1)) in fp32 (round half to even), channels
 // interleaved per sample: pcm[clip][sample][channel].  One thread quantises VEC consecutive samples of all channels.
 template <int VEC, int OC>
 __global__ __launch_bounds__(256) void stitch_pcm16_kernel(const float* __restrict__ y, int16_t* __restrict__ pcm,
@@ -648,25 +623,6 @@ hipError_t launch_stitch_pcm16(const float* y, int16_t* pcm, int oc, int S, int 
         dim3 grid((unsigned)((per + 255) / 256), (unsigned)n_slots);
         hipLaunchKernelGGL((stitch_pcm16_kernel<1, 0>), grid, dim3(256), 0, stream, y, pcm, oc, S, n_frames, total_rows, slots);
     }
-    return hipGetLastError();
-}
-
-// ---------------------------------------------------------------------------------- decode gate
-// Copy of a window table in which the windows of skipped clips are empty (no rows, no interior): every kernel of the
-// decode derives its work from the table, so those clips cost (almost) nothing and their output is left untouched.
-__global__ __launch_bounds__(256) void gate_slots_kernel(const Slot* __restrict__ src, Slot* __restrict__ dst, int n,
-                                                         const int* __restrict__ skip)
-{
-    const int i = blockIdx.x * 256 + threadIdx.x;
-    if (i >= n) return;
-    Slot s = src[i];
-    if (skip[s.clip] != 0) { s.len = 0; s.n_int = 0; s.crop = 0; }
-    dst[i] = s;
-}
-
-hipError_t launch_gate_slots(const Slot* src, Slot* dst, int n, const int* skip, hipStream_t stream)
-{
-    hipLaunchKernelGGL(gate_slots_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, stream, src, dst, n, skip);
     return hipGetLastError();
 }
 

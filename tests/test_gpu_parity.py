@@ -750,3 +750,21 @@ def test_head_inside_the_last_unit_is_bit_identical_to_the_head_kernel(spec, T, 
     pcm_b = ref_vae.decode_windowed_pcm16(zt, window=window, halo=-1)
     assert torch.equal(pcm_a, pcm_b)
     vae.close(); ref_vae.close()
+
+
+@pytest.mark.parametrize("spec,dtype,T", [(di.TINY, "f32", 50), (di.TINY, "f32", 16400), (di.FULL, "bf16", 30), (di.FULL, "bf16", 270)])
+def test_waveform_at_any_address(spec, dtype, T):
+    """The head writes the caller's waveform: an address that is no multiple of 16 bytes, nothing before it or after it, and
+    outside the span that is decoded nothing either (one head kernel for each case)."""
+    vae, w, z = make(spec, dtype, T, n_clips=2, max_extended_frames=4 * (T + 4000))
+    zt = to_device(z, dtype)
+    kw = dict(window=64, halo=-1, frame_begin=1, frame_end=T - 1)
+    ref = vae.decode_windowed(zt, out=torch.full((2, spec.out_channels, T * spec.total_stride), 7.0, device="cuda:0"), **kw)
+    buf = torch.full((ref.numel() + 6,), 7.0, device="cuda:0")
+    vae.decode_windowed(zt, out=buf[3:-3].view(ref.shape), **kw)
+    assert torch.equal(buf[3:-3].view(ref.shape), ref)
+    S = spec.total_stride
+    assert (buf[:3] == 7.0).all() and (buf[-3:] == 7.0).all() and (ref[:, :, :S] == 7.0).all() and (ref[:, :, -S:] == 7.0).all()
+    full = vae.decode(zt)
+    assert torch.equal(full[:, :, S:-S], ref[:, :, S:-S])
+    vae.close()
