@@ -17,7 +17,6 @@
 // strided conv 1024 -> 128, stride 10: 146 -> 25 (75 columns).
 // Every tile adds in the same order (chunk, tap, k-step, for two operand planes hi before lo), so a value does not depend on the tile.
 #include <algorithm>
-
 #include <type_traits>
 
 #include "conv_bf16.h"
@@ -599,7 +598,7 @@ hipError_t launch_conv_stream(MfmaParams p, int mode, int in_fmt, int emit, int 
     // Tile of a launch: the cheapest by (workgroups on the busiest of 256 CUs) x (time of one K step of 32, in ns, with one
     // workgroup on a CU or with several), as measured on the dilated convs of 256 to 1024 channels with 200 to 100000
     // columns.  A CU takes weights in at some 45 bytes per clock, so small tiles are bound by that and large ones by their
-    // MFMAs.  Launches of more than `max_small` 128 x 128 tiles take that tile without further ado.
+    // MFMAs.  Launches of more than `max_small` 128 x 128 tiles take no smaller one (kDown: 128 x 64, unless `max_small` is 0).
     struct Tile { int mt, nt; double alone, shared; };
     static const Tile kFixed[7] = {{32, 32, 25, 26}, {64, 64, 57, 70}, {64, 80, 65, 85}, {64, 96, 73, 97}, {128, 64, 90, 122}, {128, 128, 185, 212}, {256, 128, 335, 368}};
     // Any number of taps: the small tiles have fewer k-steps in flight and the LDS of the largest span.  Measured with 3 to 15 taps
@@ -611,11 +610,24 @@ hipError_t launch_conv_stream(MfmaParams p, int mode, int in_fmt, int emit, int 
     // itself (8 windows of 64 frames, 512 channels: 93 -> 87 us) but not beside the other group's launches (1899 -> 1925 us a call).  Calls
     // in us, without / with: 700 frames in one window 2622 / 2597, 750 frames 2843 / 2817, 1000 3676 / 3657, 1500 5573 / 5505.
     const bool tall_ok = mode == MODE_ACT && p.ntaps == 7 && rows % 256 == 0 && in_fmt != OP_BF16X2 && (emit == 1 || emit == 3);
-    const Tile* kTiles = any ? kAny : kFixed;
+    // What a K step costs is not all: the 1x1 and transposed convs have few of them and long epilogues, which the 128 x 128 tile has nothing
+    // to cover with where a CU has one workgroup, and which 80 and 96 columns (no power of two) make longer; a transposed conv's
+    // 64-row tiles write half runs.  Fitted to the fastest tile of 498 1x1 and 280 transposed launches (13 to 1500 frames, windows of 13
+    // to 750): 9.89 -> 9.79 and 9.51 -> 9.39 ms in all (9.69 and 9.34 with the fastest each); transposed conv to 512 channels of a 10 s
+    // clip 63 -> 50 us, 1x1 conv of 1024 channels 20 -> 16.
+    static const Tile kRes[6] = {{32, 32, 25, 26}, {64, 64, 57, 70}, {64, 80, 65, 90}, {64, 96, 73, 100}, {128, 64, 90, 118}, {128, 128, 245, 190}};
+    static const Tile kUp[6] = {{32, 32, 25, 26}, {64, 64, 57, 80}, {64, 80, 65, 95}, {64, 96, 73, 120}, {128, 64, 90, 120}, {128, 128, 240, 190}};
+    // Strided convs of up to 512 merged channels: a column is two rows of the activation tile, so 128 columns leave room for two workgroups
+    // on a CU and 64 for three, which are faster at any size beyond one round (81 launches: 3.49 -> 3.15 ms; 128 -> 256 channels,
+    // 60 s clip by itself, 347 -> 297 us; the whole 60 s encode, two groups at the power limit, does not change).  Longer K loops (1536 merged channels) hide it: 128 columns 87 us where 64 take 106.  A single chunk
+    // (64 channels) is bound by its output: 97 us against 117.
+    static const Tile kDown[6] = {{32, 32, 25, 26}, {64, 64, 57, 70}, {64, 80, 65, 85}, {64, 96, 73, 97}, {128, 64, 90, 95}, {128, 128, 185, 212}};
+    const bool down = mode == MODE_DOWN && p.nchunks > 1 && p.cin <= 512;
+    const Tile* kTiles = any ? kAny : down ? kDown : mode == MODE_RES ? kRes : mode == MODE_UP ? kUp : kFixed;
     const bool large = (ncols + 127) / 128 * (rows / 128) * call_slots > max_small;
     int best = 5;
     double cheapest = 0;
-    for (int t = large ? 5 : 0; t < (tall_ok ? 7 : 6); ++t) {
+    for (int t = large ? (down && max_small > 0 ? 4 : 5) : 0; t < (tall_ok ? 7 : 6); ++t) {
         const long long wgs = (ncols + kTiles[t].nt - 1) / kTiles[t].nt * (rows / kTiles[t].mt) * call_slots;
         if (t == 6 && wgs <= 512) continue;
         const double cost = wgs <= 256 ? kTiles[t].alone : wgs <= 1024 ? (double)((wgs + 255) / 256) * kTiles[t].shared : (wgs / 256.0 + 0.5) * kTiles[t].shared;

@@ -8,7 +8,7 @@ import torch
 import demon_inputs as di
 import oracle
 from gpu_util import assert_close, make, to_device
-from paper_2605_28657_amd import DemonVAE
+from paper_2605_28657_amd import DemonVAE, DemonVAEEncoder
 
 pytestmark = pytest.mark.gpu
 
@@ -32,6 +32,23 @@ def test_stream_tiles(spec, T, kw):
     ref = oracle.decode_windowed(spec, w, z[0], window=n, halo=halo, frame_begin=0, frame_end=n)
     assert_close(full[0][:, :n * spec.total_stride], ref[:, :n * spec.total_stride], "bf16", str(spec))
     vae.close(); large.close()
+
+
+@pytest.mark.parametrize("widths,T", [((512, 256), 97), ((512, 256), 1601), ((512, 256), 9001),      # 64 x 64; 128 x 64; more than 1024 tiles
+                                      ((256, 128), 16401), ((256, 64), 3001)])                          # 256 merged channels; one chunk
+def test_strided_tiles(widths, T):
+    """The encoder's strided convolutions at their tiles: the same bits as on the 128 x 128 tile."""
+    spec = di.DecoderSpec(64, (4, 4 if widths[1] > 64 else 2), widths, (1,))
+    w = di.make_encoder_weights(spec, bf16=True)
+    g = torch.Generator(device="cuda:0")
+    g.manual_seed(T)
+    wave = (torch.randn(1, spec.out_channels, T * spec.total_stride, generator=g, device="cuda:0") * 0.25).clamp_(-1.0, 1.0)
+    got = []
+    for wgs in (0, -1):
+        enc = DemonVAEEncoder(spec, w, dtype="bf16", max_frames=T, max_extended_frames=T, small_tile_wgs=wgs)
+        got.append(enc.encode_windowed(wave, window=T)[0])
+        enc.close()
+    assert got[0].abs().max() > 0 and torch.equal(got[0], got[1])
 
 
 @pytest.mark.parametrize("T,dils", [
