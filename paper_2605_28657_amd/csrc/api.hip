@@ -1162,7 +1162,7 @@ demon_status demon_vae_set_timing(demon_vae* v, int level)
 {
     if (!v) return fail(DEMON_ERR_INVALID_ARG, "NULL handle");
     if (level < 0 || level > 2) return fail(DEMON_ERR_INVALID_ARG, "timing level must be 0, 1 or 2");
-    size_t launches = 3;                                    // gather, head, stitch
+    size_t launches = 3;                                    // gather, head, 16-bit render
     for (const Block& B : v->blocks) launches += 1 + 2 * B.res.size();
     v->marks_per_call = (int)launches + 1;
     while (level > 0 && v->events.size() < (size_t)v->marks_per_call * kTimingRing) {

@@ -111,11 +111,11 @@ void variant_block(int variant, int* rows, int* kc);
 uint16_t f32_to_bf16_rne(float v);
 uint16_t f32_to_f16_rne(float v);
 
-// Fused residual unit (bf16 path, C = 64 or 128): y = x + W1 snake2(W7 (*) snake1(x) + b7) + b1, x != y.
 // Where the head writes the interior rows of the windows: n_frames > 0: the caller's waveform, y[clip][channel][n_frames * r] (the
 // windows side by side: crop and stitch are in the address); 0: the window waveforms y[channel][plane], rows as in the workspace.
 struct HeadOut { float* y = nullptr; long long plane = 0; int n_frames = 0; };
 
+// Fused residual unit (bf16 path, C = 64 or 128): y = x + W1 snake2(W7 (*) snake1(x) + b7) + b1, x != y.
 struct FusedArgs {
     const void* x; void* y;  // residual stream in its HBM storage type (half)
     uint16_t* ya = nullptr;  // optional: bf16(snake(y; a3, ib3)) for an unfused consumer
