@@ -20,12 +20,14 @@
 // With EMIT the kernel also writes bf16(snake_next(h_out)), the operand of the next (unfused) layer.
 #include <algorithm>
 #include <type_traits>
+#include <utility>
 
 #include "device_common.h"
 
 namespace demon {
 
 constexpr int FUSED_MAXSPAN = 64;
+constexpr int FUSED_MAXSPAN7 = FUSED_MAXSPAN / 6 * 6;      // of seven taps
 
 struct FusedParams {
     const hres_t* x; hres_t* y;
@@ -480,42 +482,59 @@ __global__ __launch_bounds__(256, (CH == 128 && TN == 2) ? 2 : 3) void res_unit_
     }
 }
 
+// f(0), f(1), ... with the numbers as types: a loop of this many groups is past the compiler's limit for unrolling
+template <int... I, typename Fn>
+__device__ __forceinline__ void unrolled(std::integer_sequence<int, I...>, Fn&& f) { (f(std::integral_constant<int, I>{}), ...); }
+
 // The same unit with the weights streamed to registers (seven taps): WM x WN waves, a wave owning 16 TM channels x 16 TN columns, the
 // branch tensor through LDS.  What bound the kernel above: two barriers per 8 or 16 KB weight block (a launch of few tiles lasts as long as
-// one workgroup's 14 of them), and at 128 channels LDS reads (6 KB per wave and 256 cycles of MFMAs).  Here a stage of KX channels has all its taps
+// one workgroup's 14 of them), and at 128 channels LDS reads (6 KB per wave and 256 cycles of MFMAs).  Here a stage of 64 channels has all its taps
 // between two barriers and the next stage's Snake runs in the shadow of its MFMAs, a quarter row every other group of TM MFMAs.
-//  * 128 channels, large calls: 64 x 128 per wave, 2 x 2 waves, two workgroups per CU (256 registers, 77 KB): a third of the LDS reads.
+//  * 128 channels, large calls: 64 x 128 per wave, 2 x 2 waves, two workgroups per CU (256 registers, 80 KB): a third of the LDS reads.
 //    What bounds it now is the two waves of a SIMD: matrix cores busy 50 %, other VALU work (Snake of 1.25 + 1 values per output) 30 %,
 //    which overlap in part.  Waves in the K loop go first (s_setprio: 390 -> 368 us).  60 s clip 425 -> 360 us per unit, 375 frames 111 -> 91.
 //  * 128 channels, few tiles: 32 x 64 per wave, 4 x 1 waves: window of 13 frames 25 -> 10 us, 75 frames 37 -> 27.
 //  * 64 channels: one stage, two by two waves of 32 channels: 13 frames 13 -> 9 us (with the head 19 -> 11), 75 frames 20 -> 17 (28 -> 23),
 //    375 frames 62 -> 55.
-// K order: 128 channels (32 channels, tap), 64 channels (tap, channel) as above, where the results are bit-identical to the kernel above's.
-template <int KX, int TM, int TN, int WM, int WN, int OCC, bool EMIT, bool HEAD>
+// K order: (64 channels, tap, channel), as above: the results are the bits of the kernel above.  At 128 channels and 256 columns two stages
+// of 64 channels take all of the LDS that two workgroups per CU leave one (rows without padding, the late vectors in a tile that has been
+// read).  Stages of 32 channels with padded rows are 0.4 % faster (60 s clip 5401 us, 5424 with these), but another order of the sums:
+// another 4.5e-4 of every decode, 2.8e-3 of every encode.
+template <int TM, int TN, int WM, int WN, int OCC, bool EMIT, bool HEAD>
 __global__ __launch_bounds__(64 * WM * WN, OCC) void res_unit_narrow_stream_kernel(FusedParams p)
 {
     fp16_saturate_on();
-    constexpr int CH = 16 * TM * WM, NT = 16 * TN * WN, NTAPS = 7, NTH = 64 * WM * WN;
-    constexpr int LDR = KX + 16;                            // stage of KX channels; rows 6 or 10 pieces apart: no bank conflicts
-    constexpr int SEGS = KX / 8, RPP = NTH / SEGS, X_ITERS = (NT + FUSED_MAXSPAN + RPP - 1) / RPP, XR = X_ITERS * RPP;
+    constexpr int CH = 16 * TM * WM, NT = 16 * TN * WN, NTAPS = 7, NTH = 64 * WM * WN, KX = 64;
+    constexpr bool TIGHT = TM * TN > 24;                    // accumulators take half of the registers, activation tiles half of the LDS
+    // stage of KX channels.  Rows 10 pieces apart: no bank conflicts; TIGHT: rows of 8 pieces, piece sg of row r at sg ^ (r & 7)
+    constexpr int LDR = TIGHT ? KX : KX + 16;
+    constexpr int SEGS = KX / 8, RPP = NTH / SEGS, ROWS = NT + FUSED_MAXSPAN7, X_ITERS = (ROWS + RPP - 1) / RPP, XR = TIGHT ? ROWS : X_ITERS * RPP;
     constexpr int NSTAGES = CH / KX, SX = KX / 32, F = NTAPS * SX, NSTEPS = NSTAGES * F, KS1 = CH / 32;
-    constexpr bool TIGHT = TM * TN > 24;                    // accumulators take half of the registers
     constexpr int RS = TIGHT ? 4 : 7;                       // k-steps of weights in flight
     constexpr int XA = TIGHT ? 3 : 5, XQ = XA + 1;          // activation fragments read ahead of their MFMAs
     constexpr int RX = TIGHT ? 2 : X_ITERS;                 // rows of a thread requested ahead
     constexpr int G = F * TN;                               // groups of TM MFMAs in a stage
     constexpr int LDM = CH + 16;
-    constexpr int X_BYTES = XR * LDR * 2, M_BYTES = NT * LDM * 2;
-    constexpr int XS_BYTES = (NSTAGES > 1 ? 2 : 1) * X_BYTES, SMEM = XS_BYTES > M_BYTES ? XS_BYTES : M_BYTES;
+    // per-channel vectors in LDS: (a1, ib1) pairs | b7 | a2 | ib2 | b1 | a3 | ib3 (of the consumer or the head).  TIGHT: the pairs; the vectors
+    // from a2 on come in front of the branch tensor during the last stage, where nothing reads the first stage's tile any more
+    constexpr int PRM = TIGHT ? 2 * CH : (EMIT || HEAD ? 8 : 6) * CH, M_OFF = TIGHT ? (EMIT ? 5 : 3) * CH * 4 : 0;
+    constexpr int X_BYTES = XR * LDR * 2, M_BYTES = M_OFF + NT * LDM * 2;
+    constexpr int XS_BYTES = NSTAGES * X_BYTES, SMEM = XS_BYTES > M_BYTES ? XS_BYTES : M_BYTES;
     constexpr unsigned BLOCK = CH * 128u;                   // bytes of a weight block: CH rows x 64 channels
     constexpr int PW = G / X_ITERS, PD = PW >= 8 ? 2 : 1;   // groups a staged row lasts, groups between its quarters
     constexpr int AUX = TIGHT ? 2 : 0;                      // stores of large calls pass the caches by
     // HEAD: weight fragments, then the tile of operands, in the activation tile's space
     constexpr int LDH = CH + 8, HW_BYTES = FUSED_HEAD_MAXK * CH * 16, HW_ITERS = HEAD ? (HW_BYTES / 16 + NTH - 1) / NTH : 1;
     static_assert(!HEAD || (CH == 64 && !EMIT && NT % (32 * WM * WN) == 0 && HW_BYTES + (NT + FUSED_HEAD_MAXK - 1) * LDH * 2 <= SMEM), "the head follows a 64-channel unit that feeds nothing else");
-    static_assert(KS1 <= RS && KS1 % TM == 0 && PW >= 4 && (NSTAGES == 1 || NSTAGES == 4), "static indices; a quarter row per group");
-    __shared__ __attribute__((aligned(16))) unsigned char smem[SMEM];
-    __shared__ __attribute__((aligned(16))) float prm[(EMIT || HEAD ? 8 : 6) * CH];     // (a1, ib1) pairs | b7 | a2 | ib2 | b1 | a3 | ib3 (of the head)
+    static_assert(KS1 <= RS && KS1 % TM == 0 && PW >= 4 && (NSTAGES == 1 || NSTAGES == 2), "static indices; a quarter row per group");
+    static_assert(!TIGHT || (NSTAGES == 2 && NTH == 2 * CH && M_OFF <= X_BYTES), "vectors loaded by two threads a channel, over the first stage's tile");
+    // TIGHT: what the last pass stages past a tile's rows falls on rows of the second tile that are staged later, or on the first stage's pairs,
+    // which nothing reads (its Snake takes them from memory)
+    static_assert(!TIGHT || (SMEM == XS_BYTES && (X_ITERS * RPP - XR) * LDR * 2 <= 2 * KX * 4), "rows past the second tile");
+    static_assert(OCC * (SMEM + PRM * 4) <= 163840, "workgroups on a CU");
+    __shared__ __attribute__((aligned(16))) unsigned char smem[SMEM + PRM * 4];
+    float* const prm = reinterpret_cast<float*>(smem + SMEM);
+    float* const late = TIGHT ? reinterpret_cast<float*>(smem) : prm + 3 * CH;          // a2 | ib2 | b1 | a3 | ib3
 
     const Slot s = p.slots[blockIdx.y];
     const int nrows = __builtin_amdgcn_readfirstlane(s.len * p.r);        // (the descriptors must be scalar)
@@ -565,8 +584,9 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) void res_unit_narrow_stream_kern
     auto load_x = [&](int j) __attribute__((always_inline)) -> u32x4 {
         return __builtin_amdgcn_raw_buffer_load_b128(rs_x, x_voff + (unsigned)(j % X_ITERS * RPP * CH + j / X_ITERS * KX) * 2u, 0, 0);
     };
-    auto x_slot = [&](int j) __attribute__((always_inline)) -> u32x4* {
-        return reinterpret_cast<u32x4*>(smem + (j / X_ITERS & 1) * X_BYTES + ((xr0 + j % X_ITERS * RPP) * LDR + seg * 8) * 2);
+    auto put_x = [&](int j, u32x4 v) __attribute__((always_inline)) {
+        const int row = (j / X_ITERS) * XR + xr0 + j % X_ITERS * RPP;                    // counted through both tiles
+        *reinterpret_cast<u32x4*>(smem + (row * LDR + (TIGHT ? seg ^ (row & 7) : seg) * 8) * 2) = v;
     };
     auto read_prm = [&](int j, int k) __attribute__((always_inline)) -> f32x4 {          // Snake parameters of channels 2 k, 2 k + 1 of the thread's 8
         return *reinterpret_cast<const f32x4*>(&prm[(j / X_ITERS * KX + seg * 8 + 2 * k) * 2]);
@@ -588,8 +608,16 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) void res_unit_narrow_stream_kern
     const int ph = __builtin_amdgcn_readfirstlane(tid / CH), pc = tid % CH;
     const float* const psrc[4] = {ph ? p.a2 : p.a1, ph ? p.ib2 : p.ib1, ph ? p.b1 : p.b7, HEAD ? (ph ? p.hib : p.ha) : (ph ? p.ib3 : p.a3)};
     float pv[NPV];
+    f32x4 b7v[TIGHT ? TM : 1];
+    int ch0 = 16 * TM * wm + 4 * q;                         // dilated conv: register e of (mi, ni) is channel ch0 + 16 mi + e, column 16 ni + i
+    if constexpr (TIGHT) {
+        pv[0] = (ph ? p.ib1 : p.a1)[pc];
 #pragma unroll
-    for (int k = 0; k < NPV; ++k) pv[k] = psrc[k][pc];
+        for (int mi = 0; mi < TM; ++mi) b7v[mi] = *reinterpret_cast<const f32x4*>(p.b7 + ch0 + 16 * mi);
+    } else {
+#pragma unroll
+        for (int k = 0; k < NPV; ++k) pv[k] = psrc[k][pc];
+    }
 #pragma unroll
     for (int g = 0; g < RS; ++g) load_a(g);
     if constexpr (NSTAGES > 1) {
@@ -601,17 +629,19 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) void res_unit_narrow_stream_kern
         u32x4 v;
 #pragma unroll
         for (int k = 0; k < 4; ++k) v[k] = snake2(px[j][k], f32x4{pal[k / 2][k % 2 * 2], pib[k / 2][k % 2 * 2], pal[k / 2][k % 2 * 2 + 1], pib[k / 2][k % 2 * 2 + 1]});
-        *x_slot(j) = v;
+        put_x(j, v);
     }
-    if (ph == 0) { prm[2 * pc] = pv[0]; prm[2 * pc + 1] = pv[1]; prm[2 * CH + pc] = pv[2]; }
-    else if (ph == 1) { prm[3 * CH + pc] = pv[0]; prm[4 * CH + pc] = pv[1]; prm[5 * CH + pc] = pv[2]; }
-    if (NPV == 4 && ph < 2) prm[(6 + ph) * CH + pc] = pv[NPV - 1];
+    if constexpr (TIGHT) { if (pc >= KX) prm[2 * pc + ph] = pv[0]; }
+    else {
+        if (ph == 0) { prm[2 * pc] = pv[0]; prm[2 * pc + 1] = pv[1]; prm[2 * CH + pc] = pv[2]; }
+        else if (ph == 1) { late[pc] = pv[0]; late[CH + pc] = pv[1]; late[2 * CH + pc] = pv[2]; }
+        if (NPV == 4 && ph < 2) late[(3 + ph) * CH + pc] = pv[NPV - 1];
+    }
     __syncthreads();
     f32x4 acc[TM][TN];
-    int ch0 = 16 * TM * wm + 4 * q;                         // dilated conv: register e of (mi, ni) is channel ch0 + 16 mi + e, column 16 ni + i
 #pragma unroll
     for (int mi = 0; mi < TM; ++mi) {
-        const f32x4 b = *reinterpret_cast<const f32x4*>(&prm[2 * CH + ch0 + 16 * mi]);
+        const f32x4 b = TIGHT ? b7v[TIGHT ? mi : 0] : *reinterpret_cast<const f32x4*>(&prm[2 * CH + ch0 + 16 * mi]);
 #pragma unroll
         for (int ni = 0; ni < TN; ++ni) acc[mi][ni] = b;
     }
@@ -622,29 +652,45 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) void res_unit_narrow_stream_kern
     auto run_stage = [&](auto stage) __attribute__((always_inline)) {
         constexpr int st = decltype(stage)::value;
         // LDS offset of the tap that is read, kept as one running register (left to itself the compiler holds one for every tap)
-        unsigned at = (st & 1) * X_BYTES + ((wn * (16 * TN) + i) * LDR + q * 8) * 2;
+        unsigned at = st * X_BYTES + ((wn * (16 * TN) + i) * LDR + (TIGHT ? 0 : q * 8)) * 2;
         asm volatile("" : "+v"(at));
         u32x4 x[XQ];
+        unsigned pos = 0;                                   // TIGHT: of the k-step's piece
         auto read_x = [&](int t) __attribute__((always_inline)) {
             if (t > 0 && t % (SX * TN) == 0) { at += tap_bytes; asm volatile("" : "+v"(at)); }
-            x[t % XQ] = *reinterpret_cast<const u32x4*>(smem + at + (16 * (t % TN) * LDR + t / TN % SX * 32) * 2);
+            if constexpr (TIGHT) {
+                // piece q of the row (at / 128), its swizzle from the row's low bits; the k-step of the other 32 channels is 4 pieces on
+                if (t % TN == 0) { pos = t / TN % SX ? pos ^ 64u : at + ((q * 16u) ^ (at >> 3 & 0x70u)); asm volatile("" : "+v"(pos)); }
+                x[t % XQ] = *reinterpret_cast<const u32x4*>(smem + pos + 16 * (t % TN) * LDR * 2);
+            } else
+                x[t % XQ] = *reinterpret_cast<const u32x4*>(smem + at + (16 * (t % TN) * LDR + t / TN % SX * 32) * 2);
         };
         f32x4 pr = st + 1 < NSTAGES ? read_prm((st + 1) * X_ITERS, 0) : f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int t = 0; t < XA; ++t) read_x(t);
         __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int t = 0; t < G; ++t) {
-            const int f = t / TN, ni = t % TN, g = st * F + f;
+        unrolled(std::make_integer_sequence<int, G>{}, [&](auto group) __attribute__((always_inline)) {
+            constexpr int t = decltype(group)::value, ni = t % TN, g = st * F + t / TN;
             // the next stage's activations, in the shadow of the MFMAs: Snake on two values of a row, PD groups of MFMAs apart
-            if (st + 1 < NSTAGES && t < X_ITERS * PW && t % PW >= PW - 1 - 3 * PD && (PW - 1 - t % PW) % PD == 0) {
-                const int it = t / PW, k = 3 - (PW - 1 - t % PW) / PD, j = (st + 1) * X_ITERS + it;
+            if constexpr (st + 1 < NSTAGES && t < X_ITERS * PW && t % PW >= PW - 1 - 3 * PD && (PW - 1 - t % PW) % PD == 0) {
+                constexpr int it = t / PW, k = 3 - (PW - 1 - t % PW) / PD, j = (st + 1) * X_ITERS + it;
                 rx[j % RX][k] = snake2(rx[j % RX][k], pr);
-                if (k < 3) pr = read_prm(j, k + 1);
+                if constexpr (k < 3) pr = read_prm(j, k + 1);
                 else {
-                    *x_slot(j) = rx[j % RX];
-                    if (it + 1 < X_ITERS) pr = read_prm(j + 1, 0);
-                    if (j + RX < NSTAGES * X_ITERS) rx[j % RX] = load_x(j + RX);
+                    put_x(j, rx[j % RX]);
+                    if constexpr (it + 1 < X_ITERS) pr = read_prm(j + 1, 0);
+                    if constexpr (j + RX < NSTAGES * X_ITERS) rx[j % RX] = load_x(j + RX);
+                }
+            }
+            if constexpr (TIGHT && st + 1 == NSTAGES) {
+                // the vectors of the epilogue: requested here, stored two k-steps later (some twice: a branch would cut the schedule)
+                if constexpr (t == 0) {
+                    pv[0] = (ph ? p.ib2 : p.a2)[pc]; pv[1] = (ph ? EMIT ? p.ib3 : p.ib2 : p.b1)[pc];
+                    if (EMIT) pv[2] = (ph ? p.ib3 : p.a3)[pc];
+                }
+                if constexpr (t == 2 * TN) {
+                    late[ph * CH + pc] = pv[0]; late[(ph ? EMIT ? 4 : 1 : 2) * CH + pc] = pv[1];
+                    if (EMIT) late[(ph ? 4 : 3) * CH + pc] = pv[2];
                 }
             }
             if (t + XA < G) read_x(t + XA);
@@ -657,15 +703,11 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) void res_unit_narrow_stream_kern
                 else if (g + RS < NSTEPS + KS1) load_a1(g + RS - NSTEPS);
                 __builtin_amdgcn_sched_barrier(0);
             }
-        }
+        });
         __syncthreads();
     };
     run_stage(std::integral_constant<int, 0>{});
-    if constexpr (NSTAGES == 4) {
-        run_stage(std::integral_constant<int, 1>{});
-        run_stage(std::integral_constant<int, 2>{});
-        run_stage(std::integral_constant<int, 3>{});
-    }
+    if constexpr (NSTAGES == 2) run_stage(std::integral_constant<int, 1>{});
 
     __builtin_amdgcn_s_setprio(0);
     // what the lane's number decides is formed again: nothing of it is held through the loop
@@ -695,10 +737,10 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) void res_unit_narrow_stream_kern
 
     // ---- Snake on the accumulators; the branch tensor goes to LDS as [column][k-slot]: channel 16 m + 4 q + e of a group of 32 is
     // k-slot 16 m + 8 (q % 2) + 4 (q / 2) + e of the 1x1 weights' K axis
-    uint16_t* ms = reinterpret_cast<uint16_t*>(smem);
+    uint16_t* ms = reinterpret_cast<uint16_t*>(smem + M_OFF);
 #pragma unroll
     for (int mi = 0; mi < TM; ++mi) {
-        const f32x4 al = *reinterpret_cast<const f32x4*>(&prm[3 * CH + ch0 + 16 * mi]), ib = *reinterpret_cast<const f32x4*>(&prm[4 * CH + ch0 + 16 * mi]);
+        const f32x4 al = *reinterpret_cast<const f32x4*>(&late[ch0 + 16 * mi]), ib = *reinterpret_cast<const f32x4*>(&late[CH + ch0 + 16 * mi]);
 #pragma unroll
         for (int ni = 0; ni < TN; ++ni) {
             const f32x4 v = acc[mi][ni];
@@ -710,7 +752,7 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) void res_unit_narrow_stream_kern
     }
 #pragma unroll
     for (int mi = 0; mi < TM; ++mi) {
-        const float b = prm[5 * CH + ec + mi];
+        const float b = late[2 * CH + ec + mi];
 #pragma unroll
         for (int ni = 0; ni < TN; ++ni) acc[mi][ni] = f32x4{b, b, b, b};
     }
@@ -759,8 +801,8 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) void res_unit_narrow_stream_kern
     float a3v[TM], i3v[TM];                                 // Snake of the consumer: the layer that takes the operand, or the head
 #pragma unroll
     for (int mi = 0; mi < TM; ++mi) {
-        a3v[mi] = NPV == 4 ? prm[(NPV == 4 ? 6 : 0) * CH + ec + mi] : 0.f;
-        i3v[mi] = NPV == 4 ? prm[(NPV == 4 ? 7 : 0) * CH + ec + mi] : 0.f;
+        a3v[mi] = NPV == 4 ? late[(NPV == 4 ? 3 : 0) * CH + ec + mi] : 0.f;
+        i3v[mi] = NPV == 4 ? late[(NPV == 4 ? 4 : 0) * CH + ec + mi] : 0.f;
     }
     // ---- residual add and half store to the other buffer.  Rows past out_hi are outside the descriptors and dropped.
     // HEAD: Snake of the (half) value the unit would have stored, in fp32, rounded once to half, goes to an LDS tile, rows shifted by
@@ -876,20 +918,20 @@ hipError_t launch_res_unit_fused(const FusedArgs& a, hipStream_t stream)
     }
     auto tiles = [&](int nt) { return a.hw ? ((long long)a.max_int * a.r + nt - a.hk) / (nt - (a.hk - 1)) : (out_rows + nt - 1) / nt; };
     auto grid = [&](int nt) { return dim3((unsigned)(tiles(nt) + 7) / 8 * 8, (unsigned)a.n_slots); };       // whole groups of 8 tiles; the surplus exits at once
-#define DEMON_NARROW(KX, TM, TN, WM, WN, OCC) { \
-        if (emit) hipLaunchKernelGGL((res_unit_narrow_stream_kernel<KX, TM, TN, WM, WN, OCC, true, false>), grid(16 * TN * WN), dim3(64 * WM * WN), 0, stream, p); \
-        else hipLaunchKernelGGL((res_unit_narrow_stream_kernel<KX, TM, TN, WM, WN, OCC, false, false>), grid(16 * TN * WN), dim3(64 * WM * WN), 0, stream, p); \
+#define DEMON_NARROW(TM, TN, WM, WN, OCC) { \
+        if (emit) hipLaunchKernelGGL((res_unit_narrow_stream_kernel<TM, TN, WM, WN, OCC, true, false>), grid(16 * TN * WN), dim3(64 * WM * WN), 0, stream, p); \
+        else hipLaunchKernelGGL((res_unit_narrow_stream_kernel<TM, TN, WM, WN, OCC, false, false>), grid(16 * TN * WN), dim3(64 * WM * WN), 0, stream, p); \
         return hipGetLastError(); \
     }
     if (a.ntaps == 7 && a.c == 128) {
         // 64 columns a workgroup up to five of them per CU, else 256.  Per unit (dilation 1, 3, 9 with emitted operand) in us, 64 / 256 columns:
         // 13 frames 10, 10, 11 / 20, 20, 21; 40 frames 17, 18, 17 / 21, 20, 21; 75 frames (1133 tiles) 26, 28, 28 / 29, 30, 32; 110 frames (1656)
         // 35, 40, 45 / 32, 32, 35; 375 frames 102, 112, 132 / 90, 92, 107; 60 s clip 457, 445, 533 / 364, 359, 404.
-        if (tiles(64) * a.call_slots <= 1280) DEMON_NARROW(32, 2, 4, 4, 1, 3)
-        DEMON_NARROW(32, 4, 8, 2, 2, 2)
+        if (tiles(64) * a.call_slots <= 1280) DEMON_NARROW(2, 4, 4, 1, 3)
+        DEMON_NARROW(4, 8, 2, 2, 2)
     }
     if (a.ntaps == 7 && a.hw) {
-        hipLaunchKernelGGL((res_unit_narrow_stream_kernel<64, 2, 4, 2, 2, 3, false, true>), grid(128), dim3(256), 0, stream, p);
+        hipLaunchKernelGGL((res_unit_narrow_stream_kernel<2, 4, 2, 2, 3, false, true>), grid(128), dim3(256), 0, stream, p);
         return hipGetLastError();
     }
     // 64 channels: streamed while the tensors read and written fit the 256 MB last-level cache (then its stores go there as well), else
@@ -897,8 +939,8 @@ hipError_t launch_res_unit_fused(const FusedArgs& a, hipStream_t stream)
     // frames 13, 12 / 9, 8 / 10, 10; 75 frames 19 / 17 / 17; 150 frames 30 / 27 / 27; 200 frames 35 / 34 / 32; 500 frames 79 / - / 71; 600 frames
     // 97 / - / 102; 1000 frames 163 / - / 175.
     if (a.ntaps == 7 && a.c == 64 && out_rows * a.call_slots * 64 * 2 * 2 <= 256ll << 20) {
-        if (tiles(128) * a.call_slots <= 2304) DEMON_NARROW(64, 2, 4, 2, 2, 3)
-        DEMON_NARROW(64, 2, 8, 2, 2, 3)
+        if (tiles(128) * a.call_slots <= 2304) DEMON_NARROW(2, 4, 2, 2, 3)
+        DEMON_NARROW(2, 8, 2, 2, 3)
     }
 #undef DEMON_NARROW
     if (a.hw) {

@@ -28,3 +28,21 @@ def test_kernel_sizes(k, dils, width, T):
     ref = oracle.decode_windowed(spec, w, z[0], window=n, halo=max(oracle.receptive_field(spec)), frame_begin=0, frame_end=n)
     assert_close(full[0][:, :2 * n], ref[:, :2 * n], "bf16", f"kernel size {k}")
     vae.close(); large.close()
+
+
+@pytest.mark.parametrize("width", [64, 128, 256, 512])
+@pytest.mark.parametrize("T", [301, 45001])                             # launches of few tiles, and of those that fill the chip
+def test_taps_of_zeros_change_no_bit(width, T):
+    """Seven taps, and the same seven between two of zeros, which run on other kernels (staged weights, taps counted at run time): a zero
+    product leaves a sum as it is, so that the results are the same bits if all kernels add in the same order."""
+    seven, nine = (di.DecoderSpec(64, (2,), (width,), (1, 3, 6), res_kernel=k) for k in (7, 9))
+    vae, w, z = make(seven, "bf16", T, max_extended_frames=T)
+    w9 = np.zeros(di.n_weights(nine), np.float32)
+    padded = di.split_weights(nine, w9)
+    for name, v in di.split_weights(seven, w).items():
+        (padded[name][..., 1:8] if name.endswith("c1.weight") else padded[name])[...] = v
+    other = DemonVAE(nine, w9, dtype="bf16", max_frames=T, max_extended_frames=T)
+    zt = to_device(z, "bf16")
+    got = vae.decode(zt).cpu().numpy()
+    assert np.abs(got).max() > 0 and np.array_equal(got, other.decode(zt).cpu().numpy())
+    vae.close(); other.close()
