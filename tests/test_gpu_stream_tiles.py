@@ -8,6 +8,7 @@ import torch
 import demon_inputs as di
 import oracle
 from gpu_util import assert_close, make, to_device
+import paper_2605_28657_amd as pa
 from paper_2605_28657_amd import DemonVAE, DemonVAEEncoder
 
 pytestmark = pytest.mark.gpu
@@ -106,4 +107,20 @@ def test_two_planes_give_the_same_bits_at_every_size_of_call():
     for begin, n in ((0, 7), (2000, 61), (3900, 400)):
         out = vae.decode_windowed(zt, window=n, halo=-1, frame_begin=begin, frame_end=begin + n)
         assert torch.equal(out[:, :, begin * S:(begin + n) * S], full[:, :, begin * S:(begin + n) * S]), (begin, n)
+    vae.close()
+
+
+def test_tall_tile_on_bf16_operands():
+    """A 256-channel unit on its two-kernel path in more than 512 tiles of 256 x 128: bf16 operands on the tall tile at every span, on
+    windows whose ends fall inside a tile, against a window short enough for a small tile and the oracle."""
+    spec, T = di.DecoderSpec(64, (2,), (256,), (1, 3, 9)), 33100
+    vae, w, z = make(spec, "bf16", T, max_extended_frames=2 * T, flags=pa.DEMON_VAE_FLAG_NO_FUSED)
+    zt = to_device(z, "bf16")
+    full = vae.decode(zt)
+    assert torch.equal(vae.decode_windowed(zt, window=16901, halo=-1), full)
+    for begin in (0, 20011, T - 15):
+        out = vae.decode_windowed(zt, window=15, halo=-1, frame_begin=begin, frame_end=begin + 15)
+        assert torch.equal(out[:, :, 2 * begin:2 * begin + 30], full[:, :, 2 * begin:2 * begin + 30])
+    ref = oracle.decode_windowed(spec, w, z[0], window=60, halo=max(oracle.receptive_field(spec)), frame_begin=T - 60, frame_end=T)
+    assert_close(full[0].cpu().numpy()[:, -120:], ref[:, -120:], "bf16", "256 channels, unfused")
     vae.close()
