@@ -94,25 +94,20 @@ __global__ __launch_bounds__(256) void conv_f32_mfma_kernel(ConvArgs a, int nchu
     extern __shared__ __attribute__((aligned(16))) float xs[];          // [rows][32], 16-byte pieces XOR-swizzled by the row
 
     const Slot s = a.slots[blockIdx.y];
-    const int M = a.stride > 0 ? a.stride * a.cout : a.cout;
+    const int M = a.cout;
     const long long nrows_in = (long long)s.len * a.r_in;
     // output rows that later layers read: the interior widened by `margin`, clamped to the window
-    const long long r_out = a.stride > 0 ? (long long)a.r_in * a.stride : a.down > 0 ? a.r_in / a.down : (long long)a.r_in;
+    const long long r_out = a.down > 0 ? a.r_in / a.down : a.r_in;
     const long long out_lo = max(0ll, s.crop * r_out - a.margin);
     const long long out_hi = min(s.len * r_out, (s.crop + s.n_int) * r_out + a.margin);
-    if (out_hi <= out_lo) return;                        // an empty window (a gated clip)
-    const long long col_lo = a.stride > 0 ? (out_lo + a.stride / 2) / a.stride : out_lo;
-    const long long col_hi = a.stride > 0 ? (out_hi - 1 + a.stride / 2) / a.stride + 1 : out_hi;
-    const long long n0 = uniform64(col_lo + (long long)blockIdx.x * NT);
-    if (n0 >= col_hi) return;
+    const long long n0 = uniform64(out_lo + (long long)blockIdx.x * NT);
+    if (n0 >= out_hi) return;                            // (also an empty window: a gated clip)
     const int m0 = blockIdx.z * MT;
 
     // input row of (column n, tap t): n XS + base + t step
     const int XS = a.down > 0 ? a.down : 1;
-    const int step = a.stride > 0 ? -1 : a.down > 0 ? 1 : a.dil;
-    const int base = a.stride > 0 ? 0 : a.down > 0 ? -(a.down / 2) : -((a.ntaps - 1) / 2) * a.dil;
-    const int last = base + (a.ntaps - 1) * step, minoff = min(base, last);
-    const long long row0 = n0 * XS + minoff;             // first staged row (in the window; may be negative)
+    const int step = a.down > 0 ? 1 : a.dil, base = a.down > 0 ? -(a.down / 2) : -((a.ntaps - 1) / 2) * a.dil;
+    const long long row0 = n0 * XS + base;               // first staged row (in the window; may be negative)
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave / WN, wn = wave % WN, j = lane & 15, q = lane >> 4;
@@ -160,7 +155,7 @@ __global__ __launch_bounds__(256) void conv_f32_mfma_kernel(ConvArgs a, int nchu
     for (int mi = 0; mi < TM; ++mi) {
         const int mu = m0 + (wm * TM + mi) * 16 + 4 * q;
         f32x4 b = {0.f, 0.f, 0.f, 0.f};
-        if (mu < M) b = *reinterpret_cast<const f32x4*>(a.bias + mu % a.cout);
+        if (mu < M) b = *reinterpret_cast<const f32x4*>(a.bias + mu);
 #pragma unroll
         for (int ni = 0; ni < TN; ++ni) acc[mi][ni] = b;
     }
@@ -182,7 +177,7 @@ __global__ __launch_bounds__(256) void conv_f32_mfma_kernel(ConvArgs a, int nchu
             __syncthreads();
             load_x(chunk + 1);
         }
-        const int off = base + tap * step - minoff;
+        const int off = tap * step;
         int row[TN];
 #pragma unroll
         for (int ni = 0; ni < TN; ++ni) row[ni] = ((wn * TN + ni) * 16 + j) * XS + off;
@@ -221,16 +216,14 @@ __global__ __launch_bounds__(256) void conv_f32_mfma_kernel(ConvArgs a, int nchu
 #pragma unroll 1
     for (int i = 0; i < TM * TN; ++i) {
         const int mu = m0 + (wm * TM + i / TN) * 16 + 4 * q;
-        const int phi = a.stride > 0 ? mu / a.cout : 0, o = mu - phi * a.cout;
-        const long long col = n0 + (wn * TN + i % TN) * 16 + j;
-        const long long n = a.stride > 0 ? col * a.stride - a.stride / 2 + phi : col;
-        if (mu >= M || n < 0 || n >= out_hi) continue;
-        const size_t idx = (size_t)(rowbase_o + n) * a.cout + o;
+        const long long n = n0 + (wn * TN + i % TN) * 16 + j;
+        if (mu >= M || n >= out_hi) continue;
+        const size_t idx = (size_t)(rowbase_o + n) * a.cout + mu;
         f32x4 v = own[i * 64];
         if (res) v += *reinterpret_cast<const f32x4*>(res + idx);
         if (a.y) *reinterpret_cast<f32x4*>((float*)a.y + idx) = v;
         if (a.ya) {
-            const f32x4 al = *reinterpret_cast<const f32x4*>(a.out_alpha + o), ib = *reinterpret_cast<const f32x4*>(a.out_inv_beta + o);
+            const f32x4 al = *reinterpret_cast<const f32x4*>(a.out_alpha + mu), ib = *reinterpret_cast<const f32x4*>(a.out_inv_beta + mu);
 #pragma unroll
             for (int e = 0; e < 4; ++e) v[e] = snake_precise(v[e], al[e], ib[e]);
             *reinterpret_cast<f32x4*>((float*)a.ya + idx) = v;
@@ -631,11 +624,11 @@ hipError_t launch_conv_f32(const ConvArgs& a, hipStream_t stream)
         return nchunks % 2 == 0 ? launch_f32_stream<1, 0, 2>(a, stream) : launch_f32_stream<1, 0, 1>(a, stream);
     }
     const unsigned long long w_bytes = (unsigned long long)M * nchunks * a.ntaps * F_KC * 4;
-    if (tiles && w_bytes < 0xf0000000ull) {
+    if (tiles && a.stride == 0 && w_bytes < 0xf0000000ull) {
         struct Tile { int tm, tn, wm, wn; double factor; };
         static const Tile kTiles[5] = {{4, 4, 2, 2, 1.0}, {2, 2, 2, 2, 1.1}, {2, 2, 1, 4, 1.1}, {1, 2, 4, 1, 1.25}, {1, 1, 2, 2, 1.4}};
         const int xs = a.down > 0 ? a.down : 1;
-        const long long span = (long long)(a.ntaps - 1) * (a.stride > 0 || a.down > 0 ? 1 : a.dil);
+        const long long span = (long long)(a.ntaps - 1) * (a.down > 0 ? 1 : a.dil);
         int best = -1;
         double best_cost = 0;
         dim3 grid;
