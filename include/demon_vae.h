@@ -306,7 +306,7 @@ DEMON_API demon_status demon_vae_encode(demon_vae* enc, const float* d_wave, int
 /*
  * For callers that cannot allocate device memory or may not let a library hold a workspace of its own choosing --
  * code under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc: demon_vae_decode_windowed with
- * everything the call needs besides its inputs and outputs (window table, activation buffers, window waveforms) in
+ * everything the call needs besides its inputs and outputs (window table, activation buffers) in
  * a static device array of DEMON_VAE_STATIC_SCRATCH_BYTES that is part of the library's image.  Each GPU the library
  * runs on holds its own copy until the process ends.  The call allocates nothing, copies nothing from the host (a
  * kernel writes the window table) and runs on the given stream only; it can be captured without a preceding call.

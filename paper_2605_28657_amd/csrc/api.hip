@@ -88,8 +88,8 @@ struct Workspace {
     size_t act_elems = 0;              // elements one activation buffer holds (= offset of the lo plane of a split operand)
 };
 
-// Scratch of demon_vae_decode_windowed_static, the entry point for callers that cannot allocate: window table, activation
-// buffers and window waveforms of one call.  Every GPU the library runs on holds its own copy until the process ends.
+// Scratch of demon_vae_decode_windowed_static, the entry point for callers that cannot allocate: window table and activation
+// buffers of one call.  Every GPU the library runs on holds its own copy until the process ends.
 // In host code the array's name is only a handle for hipGetSymbolAddress: kernels get the address looked up there.
 constexpr size_t kStaticScratchBytes = DEMON_VAE_STATIC_SCRATCH_BYTES;
 static __device__ __align__(256) unsigned char scratch[kStaticScratchBytes];
@@ -143,7 +143,7 @@ struct demon_vae {
     // fp32 path: residual stream, activated operand of the next layer, branch tensor / next residual stream, all fp32.
     // bf16 path: buf[0], buf[1] residual stream ping/pong (half), buf[2] bf16 activated branch tensor,
     // buf[3], buf[4] bf16 activated operand of the next layer (each bf16 buffer: hi plane + lo plane).
-    // head_out: planar window waveforms [out_channels, cap_frames*S]; slot_gated: per-call copy of a window table with
+    // head_out: planar window waveforms [out_channels, cap_frames*S], for the 16-bit render only; slot_gated: per-call copy of a window table with
     // the skipped clips emptied (gated decode)
     Workspace ws;
     unsigned char* scratch = nullptr;              // this device's copy of the static scratch array
@@ -1059,7 +1059,7 @@ demon_status demon_vae_decode_windowed_static(demon_vae* v, const void* d_latent
     const demon_status prc = check_plane(v, max_len);
     if (prc != DEMON_OK) return prc;
 
-    // carve the call's memory out of the static array: window table, activation buffers, window waveforms
+    // carve the call's memory out of the static array: window table, activation buffers (the head writes the caller's waveform)
     const bool bf = v->dtype == DEMON_BF16;
     const size_t act_elems = (size_t)total * (size_t)v->per_frame;
     const size_t planes = (bf && v->has_split_operands) ? 2 : 1;
@@ -1068,13 +1068,11 @@ demon_status demon_vae_decode_windowed_static(demon_vae* v, const void* d_latent
     const size_t at_slots = take(sizeof(Slot) * (size_t)(per_clip * n_clips));
     size_t at_buf[5] = {0, 0, 0, 0, 0};
     for (int i = 0; i < (bf ? 5 : 3); ++i) at_buf[i] = take(act_elems * (bf ? (i < 2 ? 2 : 2 * planes) : 4));
-    const size_t at_head = take((size_t)total * (size_t)v->st.total_stride() * v->st.out_channels * sizeof(float));
     if (off > kStaticScratchBytes)
         return fail(DEMON_ERR_WORKSPACE, "the call needs %zu bytes of scratch for %lld extended frames, the static array holds %zu",
                     off, total, kStaticScratchBytes);
     Workspace ws;
     for (int i = 0; i < (bf ? 5 : 3); ++i) ws.buf[i] = v->scratch + at_buf[i];
-    ws.head_out = reinterpret_cast<float*>(v->scratch + at_head);
     ws.act_elems = act_elems;
 
     Plan plan;

@@ -105,3 +105,18 @@ def test_static_scratch_decode_can_be_captured_without_a_warm_up_call():
         torch.cuda.synchronize()
         assert torch.equal(out, ref)
     vae.close()
+
+
+@pytest.mark.parametrize("dtype,spec,per_frame", [("bf16", di.FULL, 10 * 122880), ("f32", di.TINY, 12 * 1024)])
+def test_static_scratch_holds_the_window_table_and_the_activation_buffers_and_nothing_else(dtype, spec, per_frame):
+    """The longest clip whose activation buffers fit the array beside a table of one window is decoded, one frame more is not."""
+    assert per_frame // (10 if dtype == "bf16" else 12) == max(np.cumprod(spec.strides) * np.array(spec.widths))
+    T = ((128 << 20) - 256) // per_frame
+    vae, _, z = make(spec, dtype, T + 1, max_extended_frames=T + 1)
+    zt = to_device(z, dtype)
+    fits = zt[:, :, :T].contiguous()
+    assert torch.equal(vae.decode_windowed_static(fits, window=T, halo=0), vae.decode(fits))
+    with pytest.raises(pa.DemonError) as e:
+        vae.decode_windowed_static(zt, window=T + 1, halo=0)
+    assert e.value.status == pa.DEMON_ERR_WORKSPACE
+    vae.close()
