@@ -101,9 +101,10 @@ typedef struct {
     int flags;            /* DEMON_VAE_FLAG_* */
     int small_tile_wgs;   /* convolutions outside the fused units: launches of at most this many 128 x 128 tiles may use
                              smaller tiles instead (bit-identical results, more workgroups for a single playback
-                             window; strided convolutions of up to 512 merged channels
-                             may use 128 x 64 tiles above it too); default 1024, negative = never, and then the 256-channel unit keeps its
-                             LDS-staged kernel too (any other value leaves that unit its own choice) */
+                             window; strided convolutions of up to 512 merged channels may use 128 x 64 tiles above it
+                             too); default 1024, negative = never, and then the 256-channel unit keeps its LDS-staged
+                             kernel too (any other value leaves that unit its own choice).  Dilated convolutions of seven
+                             taps may use 256 x 128 tiles at any value */
 } demon_vae_config;
 
 /* One window of the grid: interior latent frames [begin, end) of clip `clip`, decoded from the

@@ -125,7 +125,7 @@ struct demon_vae {
     bool has_staged_convs = false;     // bf16 path: some convolution outside the fused units takes an LDS-staged tile
     bool has_split_operands = false;   // bf16 path: some layer carries its operand as hi + lo planes
     bool fuse_f32 = false;             // fp32 path: residual units may run as one kernel
-    long long small_tile_wgs = 1024;   // bf16 path: launches of more 128 x 128 tiles than this take that tile
+    long long small_tile_wgs = 1024;   // bf16 path: launches of more 128 x 128 tiles than this look for no smaller tile (conv_bf16.h)
     bool head_fusable = false;         // bf16 path: the last layer is a fused 64-channel unit that can run the head in its kernel
 
     void* d_params = nullptr;          // one allocation: all packed weights, biases, Snake parameters

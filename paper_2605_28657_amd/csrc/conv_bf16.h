@@ -34,7 +34,8 @@ struct MfmaParams {
 // kernels_bf16_stream.hip: weights streamed to registers, on weights packed for the 128 x 128 tile (variant 0).  `rows` is the
 // GEMM's M, `ncols` the most columns a window needs, `mode`, `in_fmt` and `emit` as the template arguments of the
 // other kernels; `call_slots` the windows of the whole call, `n_slots` those of this launch; launches of more than `max_small`
-// 128 x 128 tiles do not look for a smaller tile.
+// 128 x 128 tiles look for no smaller tile, except strided convs of up to 512 merged channels, which may take 128 x 64 unless
+// `max_small` is 0.  Dilated convs of seven taps may take 256 x 128 whatever `max_small` is.
 hipError_t launch_conv_stream(MfmaParams p, int mode, int in_fmt, int emit, int rows, long long ncols, int n_slots, int call_slots, long long max_small,
                               hipStream_t stream);
 

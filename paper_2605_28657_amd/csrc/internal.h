@@ -83,7 +83,7 @@ struct ConvArgs {
     // bf16 path only: format of the MFMA operand read (x) and of the one emitted (ya), see kernels_bf16.hip
     int in_fmt = OP_BF16, out_fmt = OP_BF16;
     long long in_lo_off = 0, out_lo_off = 0;     // OP_BF16X2: element offset of the lo plane
-    long long small_tile_wgs = 1024;             // bf16 path: launches of more 128 x 128 tiles than this take that tile
+    long long small_tile_wgs = 1024;             // bf16 path: launches of more 128 x 128 tiles than this look for no smaller tile (conv_bf16.h)
 };
 
 // fp32 implicit GEMM on an activated input; y: the residual stream (or nullptr), ya: fp32 operand of the next layer (or nullptr)

@@ -490,10 +490,13 @@ __device__ __forceinline__ void unrolled(std::integer_sequence<int, I...>, Fn&& 
 // branch tensor through LDS.  What bound the kernel above: two barriers per 8 or 16 KB weight block (a launch of few tiles lasts as long as
 // one workgroup's 14 of them), and at 128 channels LDS reads (6 KB per wave and 256 cycles of MFMAs).  Here a stage of 64 channels has all its taps
 // between two barriers and the next stage's Snake runs in the shadow of its MFMAs, a quarter row every other group of TM MFMAs.
+// Times: a launch with an event after it in a call that is waited for (4 to 5 us of each are the events); in back-to-back steps at the power
+// limit the 128-channel units of a 60 s clip take 452 to 494 us.
 //  * 128 channels, large calls: 64 x 128 per wave, 2 x 2 waves, two workgroups per CU (256 registers, 80 KB): a third of the LDS reads.
 //    What bounds it now is the two waves of a SIMD: matrix cores busy 50 %, other VALU work (Snake of 1.25 + 1 values per output) 30 %,
-//    which overlap in part.  Waves in the K loop go first (s_setprio: 390 -> 368 us).  60 s clip 425 -> 360 us per unit, 375 frames 111 -> 91.
-//  * 128 channels, few tiles: 32 x 64 per wave, 4 x 1 waves: window of 13 frames 25 -> 10 us, 75 frames 37 -> 27.
+//    which overlap in part.  Waves in the K loop go first (s_setprio: -5 %).  60 s clip 428 -> 378 us per unit (with the operand 458 -> 424), 375 frames
+//    104 to 121 -> 90 to 106.
+//  * 128 channels, few tiles: 32 x 64 per wave, 4 x 1 waves: window of 13 frames 25 -> 11 us, 75 frames 36 -> 27.
 //  * 64 channels: one stage, two by two waves of 32 channels: 13 frames 13 -> 9 us (with the head 19 -> 11), 75 frames 20 -> 17 (28 -> 23),
 //    375 frames 62 -> 55.
 // K order: (64 channels, tap, channel), as above: the results are the bits of the kernel above.  At 128 channels and 256 columns two stages
@@ -925,8 +928,9 @@ hipError_t launch_res_unit_fused(const FusedArgs& a, hipStream_t stream)
     }
     if (a.ntaps == 7 && a.c == 128) {
         // 64 columns a workgroup up to five of them per CU, else 256.  Per unit (dilation 1, 3, 9 with emitted operand) in us, 64 / 256 columns:
-        // 13 frames 10, 10, 11 / 20, 20, 21; 40 frames 17, 18, 17 / 21, 20, 21; 75 frames (1133 tiles) 26, 28, 28 / 29, 30, 32; 110 frames (1656)
-        // 35, 40, 45 / 32, 32, 35; 375 frames 102, 112, 132 / 90, 92, 107; 60 s clip 457, 445, 533 / 364, 359, 404.
+        // 13 frames 11, 10, 12 / 20, 20, 21; 40 frames 17, 16, 18 / 20, 20, 21; 64 frames 23, 22, 24 / 21, 21, 23; 75 frames (1133 tiles) 26, 25, 28 /
+        // 28, 28, 31; 95 frames 30, 29, 32 / 28, 29, 32; 110 frames (1656) 35, 34, 38 / 29, 30, 33; 150 frames 43, 43, 47 / 47, 50, 56; 200 frames
+        // 57, 56, 61 / 49, 50, 59; 375 frames 104, 102, 111 / 89, 91, 104; 60 s clip 460, 453, 526 / 378, 377, 422.
         if (tiles(64) * a.call_slots <= 1280) DEMON_NARROW(2, 4, 4, 1, 3)
         DEMON_NARROW(4, 8, 2, 2, 2)
     }

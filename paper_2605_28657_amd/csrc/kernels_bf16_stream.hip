@@ -363,8 +363,8 @@ __global__ __launch_bounds__(64 * WM * WN, MODE == MODE_UP && TM * TN == 16 && I
 // Dilated convs of seven taps in launches of many tiles: 256 rows x 128 columns, a wave owning 64 rows of all columns (256 registers, two
 // workgroups per CU).  The 128 x 128 tile above reads 8 KB of LDS per wave and 256 cycles of MFMAs, the most a CU delivers; here it is 8 KB per
 // 512, with 4 KB of weights.  Weights are the row operand, so that a lane ends with 8 consecutive channels of a column and the
-// epilogue needs no LDS.  512 channels, 60 s clip 261 -> 242 us (1.36 PFLOP/s, what the stage loop alone sustains under the power
-// limit); the call 5551 -> 5500.  The same shape for the transposed convs (few k-steps, long epilogues: two workgroups per CU cover them
+// epilogue needs no LDS.  512 channels, 60 s clip 260 -> 241 us in a call that is waited for (1.37 PFLOP/s; in back-to-back steps at the power
+// limit 244 to 258, 1.28 to 1.35); the call 5551 -> 5500.  The same shape for the transposed convs (few k-steps, long epilogues: two workgroups per CU cover them
 // less well than three) is slower: 231 -> 242 us, 205 -> 244.
 template <int SPAN, int IN>
 __global__ __launch_bounds__(256, 2) void conv_tall_kernel(MfmaParams p, StreamGrid sg, bool half_out)
@@ -607,20 +607,24 @@ hipError_t launch_conv_stream(MfmaParams p, int mode, int in_fmt, int emit, int 
     static const Tile kAny[6] = {{32, 32, 75, 45}, {64, 64, 90, 78}, {64, 80, 100, 115}, {64, 96, 105, 132}, {128, 64, 120, 118}, {128, 128, 177, 190}};
     const bool any = mode == MODE_ACT && p.ntaps != 7 && p.ntaps != 1;
     // Seven taps: the tall tile (conv_tall_kernel) where there is more than one round of its two workgroups per CU: below, it is faster by
-    // itself (8 windows of 64 frames, 512 channels: 93 -> 87 us) but not beside the other group's launches (1899 -> 1925 us a call).  Calls
-    // in us, without / with: 700 frames in one window 2622 / 2597, 750 frames 2843 / 2817, 1000 3676 / 3657, 1500 5573 / 5505.
+    // itself (8 windows of 64 frames, 512 channels: 93 -> 87 us) but not beside the other group's launches (1899 -> 1925 us a call).  From 513
+    // to some 640 workgroups in windows it is the other way round: ten windows of 64 frames (620) 108 -> 122 us a launch, the call 2348 -> 2355, which
+    // is within the noise.  Calls in us, without / with: 700 frames in one window 2615 / 2581, in 11 windows of 64 2703 / 2666, 800 frames 2880 / 2855 (4 of
+    // 200: 2901 / 2868), 1000 3660 / 3624, 1024 in 32 of 32 3920 / 3878, 1536 in 24 of 64 5646 / 5572.
     const bool tall_ok = mode == MODE_ACT && p.ntaps == 7 && rows % 256 == 0 && in_fmt != OP_BF16X2 && (emit == 1 || emit == 3);
     // What a K step costs is not all: the 1x1 and transposed convs have few of them and long epilogues, which the 128 x 128 tile has nothing
     // to cover with where a CU has one workgroup, and which 80 and 96 columns (no power of two) make longer; a transposed conv's
     // 64-row tiles write half runs.  Fitted to the fastest tile of 498 1x1 and 280 transposed launches (13 to 1500 frames, windows of 13
     // to 750): 9.89 -> 9.79 and 9.51 -> 9.39 ms in all (9.69 and 9.34 with the fastest each); transposed conv to 512 channels of a 10 s
-    // clip 63 -> 50 us, 1x1 conv of 1024 channels 20 -> 16.
+    // clip 63 -> 50 us, 1x1 conv of 1024 channels 20 -> 16.  Two operand planes take the same tables, not fitted to them: their calls gain what
+    // those of one plane do (3 s window 528 -> 495 us, 10 s clip 1269 -> 1156 with everything else that came with them).
     static const Tile kRes[6] = {{32, 32, 25, 26}, {64, 64, 57, 70}, {64, 80, 65, 90}, {64, 96, 73, 100}, {128, 64, 90, 118}, {128, 128, 245, 190}};
     static const Tile kUp[6] = {{32, 32, 25, 26}, {64, 64, 57, 80}, {64, 80, 65, 95}, {64, 96, 73, 120}, {128, 64, 90, 120}, {128, 128, 240, 190}};
     // Strided convs of up to 512 merged channels: a column is two rows of the activation tile, so 128 columns leave room for two workgroups
     // on a CU and 64 for three, which are faster at any size beyond one round (81 launches: 3.49 -> 3.15 ms; 128 -> 256 channels,
-    // 60 s clip by itself, 347 -> 297 us; the whole 60 s encode, two groups at the power limit, does not change).  Longer K loops (1536 merged channels) hide it: 128 columns 87 us where 64 take 106.  A single chunk
-    // (64 channels) is bound by its output: 97 us against 117.
+    // 60 s clip by itself, 347 -> 297 us; the whole 60 s encode, two groups at the power limit, does not change).  Longer K loops hide it, in us, 64 /
+    // 128 columns, at 48000 columns: 256 merged channels 36 / 38, 384 48 / 50, 512 107 / 110, 640 72 / 71, 768 159 / 154, 1024 203 / 186 and 218 / 200,
+    // 1536 298 / 267 (these to 512 channels, 256, 384 and 640 to 256).  A single chunk (64 channels) is bound by its output: 97 us against 117.
     static const Tile kDown[6] = {{32, 32, 25, 26}, {64, 64, 57, 70}, {64, 80, 65, 85}, {64, 96, 73, 97}, {128, 64, 90, 95}, {128, 128, 185, 212}};
     const bool down = mode == MODE_DOWN && p.nchunks > 1 && p.cin <= 512;
     const Tile* kTiles = any ? kAny : down ? kDown : mode == MODE_RES ? kRes : mode == MODE_UP ? kUp : kFixed;

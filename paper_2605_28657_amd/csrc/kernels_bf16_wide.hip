@@ -501,8 +501,9 @@ __global__ __launch_bounds__(512, 2) void res_unit_wide_stream_kernel(WideParams
 // accumulators (128 registers), four k-steps of weights (64) and the fragments read ahead fit without spills.
 // The dilated conv has the weights as the row operand (a lane ends with four consecutive channels of a column: 8-byte LDS writes of
 // the branch tensor), the 1x1 conv the activations (a lane ends with four channels of a row, 16 lanes with 128 bytes: the
-// epilogue goes straight to memory).  60 s clip 388 -> 313 us per unit (1.2 PFLOP/s; HBM traffic and Snake included), 375 frames
-// 111 -> 80, encode of 60 s 438 -> 353.  Bit-identical to the kernels above.
+// epilogue goes straight to memory).  In calls that are waited for, 60 s clip 389 -> 317 us per unit (1.19 PFLOP/s; HBM traffic and Snake included),
+// 375 frames 111 -> 80, encode of 60 s 438 -> 363; in back-to-back steps at the power limit 366 to 384 (0.98 to 1.03 PFLOP/s).  Bit-identical to
+// the kernels above.
 template <bool EMIT>
 __global__ __launch_bounds__(256, 2) void res_unit_wide_tall_kernel(WideParams p)
 {
@@ -750,7 +751,7 @@ hipError_t launch_res_unit_wide(const WideArgs& a, hipStream_t stream)
     // CUs; larger launches take the tall kernel, two workgroups of 4 waves per CU.  Per unit in us, columns 32, 64, 80, 96 in one round (two
     // rounds in brackets) / tall: 13 frames 18, 21, 23, 26 / 28; 40 frames (30), 22, 24, 27 / 29; 75 frames (44), (39), 28, 29 / 31; 110 frames
     // (55), (40), (46), (52) / 33; 150 frames (70), (59), (50), (55) / 49; four windows of 64 frames 3 rounds and more: 109, 81, 94, 82 / 58.
-    // Against the LDS-staged kernel: 375 frames 111 -> 80, 60 s clip 388 -> 313 (1.2 PFLOP/s).
+    // Against the LDS-staged kernel: 375 frames 111 -> 80, 60 s clip 389 -> 317.
     const bool streamed = a.ntaps == 7 && !a.staged_only;
 #define DEMON_STREAM(TN) \
     if (streamed && tiles(16 * TN) * a.call_slots <= 256) { \

@@ -237,8 +237,9 @@ __global__ __launch_bounds__(256) void conv_f32_mfma_kernel(ConvArgs a, int nchu
 // owns 16 rows of TN column tiles; the weights of the next RS groups wait in registers, the fragments of the next group are
 // requested between the MFMAs of this one, across the stages too (the only barrier of a stage stands before its last group), and the
 // next stage's activations are in the other buffer by then.  TN is chosen per launch so that the rounds of the CUs are full.
-// Per launch of a 75-frame window (dilated / 1x1 / transposed): 1024 channels 148 / 33 / 8 -> 109 / 22 / 8 us, 512 channels 153 / 33 / 97 ->
-// 123 / 25 / 84, 256 channels 148 / 40 / 98 -> 125 / 29 / 78, 128 channels 142 / 46 / 97 -> 129 / 35 / 82; 88 % of the fp32 matrix rate in full rounds.
+// Per launch of a 75-frame window (dilated / 1x1 / transposed), with an event after each, 4 to 5 us: 1024 channels 149 / 37 / 12 -> 119 / 28 / 12 us,
+// 512 channels 154 / 36 / 99 -> 133 / 31 / 96, 256 channels 150 / 43 / 100 -> 133 / 34 / 86, 128 channels 143 / 50 / 102 -> 139 / 41 / 91: 93 to 125
+// TFLOP/s on the dilated ones where a large library product reaches 153.
 // FUSE: a residual unit of 32 or 64 channels in one kernel.  Snake of the accumulators goes to LDS, [column][channel], and is the
 // operand of the 1x1 conv: no branch tensor in memory and one launch instead of two (64 channels, 75 frames: 117 as two before, 100
 // as two streamed ones, 88).  At 128 channels it is no faster (159 against 163) and at 256 slower (172 against 154): a workgroup that holds
