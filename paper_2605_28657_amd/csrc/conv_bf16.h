@@ -21,6 +21,7 @@ struct MfmaParams {
     const uint16_t* w;       // packed weight blocks
     const float* bias;
     hres_t* y;               // residual-stream output; MODE_RES: also the residual source (in place); unused in MODE_ACT
+    bool y_dead;             // MODE_RES: y is read only, nothing after this layer reads the sum
     uint16_t* ya;            // activated output in the kernel's EMIT format; lo plane at ya + out_lo_off
     const float* out_alpha; const float* out_inv_beta;   // Snake applied before writing ya
     const Slot* slots;

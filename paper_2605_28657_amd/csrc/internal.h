@@ -64,6 +64,7 @@ struct ConvArgs {
     void* y;              // output activation [rows_out, cout] (fp32 path: fp32; bf16 path: half); bf16 dilated conv: unused
     void* ya = nullptr;   // activated copy of the output for the next layer (Snake out_alpha/out_inv_beta); fp32 path: fp32
     const void* res;      // residual (same layout as y) or nullptr; bf16 path: must equal y (in place)
+    bool y_dead = false;  // bf16 path, with res: y is only read, the sum goes to ya alone
     const void* w;        // packed weights (layout private to each kernel family)
     const float* bias;    // [cout]
     const float* out_alpha;  const float* out_inv_beta;   // Snake applied before writing ya, or nullptr
@@ -117,7 +118,7 @@ struct HeadOut { float* y = nullptr; long long plane = 0; int n_frames = 0; };
 
 // Fused residual unit (bf16 path, C = 64 or 128): y = x + W1 snake2(W7 (*) snake1(x) + b7) + b1, x != y.
 struct FusedArgs {
-    const void* x; void* y;  // residual stream in its HBM storage type (half)
+    const void* x; void* y;  // residual stream in its HBM storage type (half); y may be nullptr where ya takes all of the output
     uint16_t* ya = nullptr;  // optional: bf16(snake(y; a3, ib3)) for an unfused consumer
     const float* a3 = nullptr; const float* ib3 = nullptr;
     const uint16_t* w7;      // packed as pack_bf16 does for an MT = C, KC = 64 tile
@@ -138,6 +139,7 @@ void pack_w1_fused(const float* w, int C, uint16_t* dst);
 // half residual stream in place
 struct WideArgs {
     const uint16_t* xa; void* y;
+    bool y_dead = false;     // y is only read: its sum goes to the consumer's operand alone (ya)
     uint16_t* ya = nullptr;  // optional: bf16(snake(y; a3, ib3)) for the consumer; must not be the buffer of xa
     const float* a3 = nullptr; const float* ib3 = nullptr;
     const uint16_t* w7;      // packed as pack_bf16 does for variant 3 (MT = 256, KC = 32)

@@ -325,6 +325,7 @@ __global__ __launch_bounds__(64 * WM * WN) void conv_mfma_kernel(MfmaParams p)
     // are used, each of the loads would be waited for in turn (they cannot move above the in-place stores), a chain of
     // memory latencies per tile.
     using pack_t = std::conditional_t<PW == 2, uint32_t, uint16_t>;     // PW 16-bit values
+    const __amdgpu_buffer_rsrc_t rs_ys = MODE == MODE_RES ? make_rsrc(p.y + rowbase_o * p.cout, p.y_dead ? 0u : out_rows * p.cout * (unsigned)sizeof(hres_t)) : rs_y;
     pack_t resv[MODE == MODE_RES ? TN : 1][16];
     auto load_res = [&]() __attribute__((always_inline)) {
 #pragma unroll
@@ -435,12 +436,12 @@ __global__ __launch_bounds__(64 * WM * WN) void conv_mfma_kernel(MfmaParams p)
                 // half store of h; the next layer's operand is Snake of the STORED value
                 if constexpr (PW == 2) {
                     const uint32_t hb = pack_f16x2(v[0], v[1]);           // round to nearest even
-                    __builtin_amdgcn_raw_buffer_store_b32(hb, rs_y, e * 2u, 0, 0);
+                    __builtin_amdgcn_raw_buffer_store_b32(hb, rs_ys, e * 2u, 0, 0);
                     const f16x2 hv = __builtin_bit_cast(f16x2, hb);
                     v[0] = (float)hv[0]; v[1] = (float)hv[1];
                 } else {
                     const _Float16 hv = (_Float16)v[0];
-                    __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(uint16_t, hv), rs_y, e * 2u, 0, 0);
+                    __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(uint16_t, hv), rs_ys, e * 2u, 0, 0);
                     v[0] = (float)hv;
                 }
             }
@@ -508,7 +509,7 @@ hipError_t launch_conv_bf16(const ConvArgs& a, int variant, hipStream_t stream)
     const int cin = a.cin * merge, r_in = a.r_in / merge, ntaps = a.down > 0 ? 4 : a.ntaps;
     MfmaParams p;
     p.xa = (const uint16_t*)a.x; p.w = (const uint16_t*)a.w; p.bias = a.bias;
-    p.y = (hres_t*)a.y; p.ya = (uint16_t*)a.ya;
+    p.y = (hres_t*)a.y; p.y_dead = a.y_dead; p.ya = (uint16_t*)a.ya;
     p.out_alpha = a.out_alpha; p.out_inv_beta = a.out_inv_beta;
     p.slots = a.slots;
     p.r_in = r_in; p.cin = cin; p.cout = a.cout; p.ntaps = ntaps; p.stride = a.stride;
@@ -531,6 +532,7 @@ hipError_t launch_conv_bf16(const ConvArgs& a, int variant, hipStream_t stream)
     if (mode == MODE_ACT && emit == 0) return hipErrorInvalidValue;
     if (emit > 0 && (!a.out_alpha || !a.out_inv_beta)) return hipErrorInvalidValue;
     if (mode != MODE_ACT && !a.y) return hipErrorInvalidValue;
+    if (a.y_dead && (mode != MODE_RES || emit == 0)) return hipErrorInvalidValue;
     if (mode == MODE_RES && a.res != a.y) return hipErrorInvalidValue;            // the residual add is in place
     // one window's activation plane must fit a 32-bit byte offset (buffer descriptors)
     const long long r_out = a.down > 0 ? (long long)a.r_in / a.down : (long long)a.r_in * (a.stride > 0 ? a.stride : 1);

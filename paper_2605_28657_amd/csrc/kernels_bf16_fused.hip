@@ -30,7 +30,7 @@ constexpr int FUSED_MAXSPAN = 64;
 constexpr int FUSED_MAXSPAN7 = FUSED_MAXSPAN / 6 * 6;      // of seven taps
 
 struct FusedParams {
-    const hres_t* x; hres_t* y;
+    const hres_t* x; hres_t* y;  // EMIT: y may be nullptr, nothing after the unit reads the residual stream
     uint16_t* ya;                // optional activated bf16 copy of y (EMIT)
     const uint16_t* w7;          // [chunk][tap] blocks of C x 64 bf16
     const uint16_t* w1;          // [C][C] bf16, K axis permuted (see above)
@@ -136,7 +136,7 @@ __global__ __launch_bounds__(256, (CH == 128 && TN == 2) ? 2 : 3) void res_unit_
 
     // descriptors: one window of the input, the computed part of the window for the outputs
     const __amdgpu_buffer_rsrc_t rs_x = make_rsrc(p.x + rowbase * CH, (unsigned)nrows * CH * (unsigned)sizeof(hres_t));
-    const __amdgpu_buffer_rsrc_t rs_y = make_rsrc(p.y + rowbase * CH, (unsigned)out_hi * CH * (unsigned)sizeof(hres_t));
+    const __amdgpu_buffer_rsrc_t rs_y = make_rsrc(p.y + rowbase * CH, EMIT && !p.y ? 0u : (unsigned)out_hi * CH * (unsigned)sizeof(hres_t));
     const __amdgpu_buffer_rsrc_t rs_a = make_rsrc(p.ya + rowbase * CH, EMIT ? (unsigned)out_hi * CH * 2u : 0u);
     const __amdgpu_buffer_rsrc_t rs_w = weight_rsrc(p.w7, (unsigned)(p.nchunks * p.ntaps) * (A_CH * 16u));
 
@@ -558,7 +558,7 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) void res_unit_narrow_stream_kern
     const int seg = tid % SEGS, xr0 = tid / SEGS;
 
     const __amdgpu_buffer_rsrc_t rs_x = make_rsrc(p.x + rowbase * CH, (unsigned)nrows * CH * (unsigned)sizeof(hres_t));
-    const __amdgpu_buffer_rsrc_t rs_y = make_rsrc(p.y + rowbase * CH, (unsigned)out_hi * CH * (unsigned)sizeof(hres_t));
+    const __amdgpu_buffer_rsrc_t rs_y = make_rsrc(p.y + rowbase * CH, EMIT && !p.y ? 0u : (unsigned)out_hi * CH * (unsigned)sizeof(hres_t));
     const __amdgpu_buffer_rsrc_t rs_a = make_rsrc(p.ya + rowbase * CH, EMIT ? (unsigned)out_hi * CH * 2u : 0u);
     const __amdgpu_buffer_rsrc_t rs_w = weight_rsrc(p.w7, (unsigned)(CH / 64 * NTAPS) * BLOCK);
     const __amdgpu_buffer_rsrc_t rs_w1 = weight_rsrc(p.w1, CH * CH * 2u);
@@ -907,7 +907,7 @@ hipError_t launch_res_unit_fused(const FusedArgs& a, hipStream_t stream)
     p.tap0 = -((a.ntaps - 1) / 2) * a.dil; p.tap_step = a.dil;
     p.nchunks = a.c / 64; p.margin = a.margin;
     if ((a.c != 64 && a.c != 128) || (a.ntaps - 1) * a.dil > FUSED_MAXSPAN || a.margin < 0 || a.x == a.y) return hipErrorInvalidValue;
-    if (a.ya && (!a.a3 || !a.ib3)) return hipErrorInvalidValue;
+    if (a.ya ? !a.a3 || !a.ib3 : !a.y) return hipErrorInvalidValue;
     // one window's activation plane must fit a 32-bit byte offset (buffer descriptors)
     if ((long long)a.max_len * a.r * a.c * (long long)sizeof(hres_t) > 0xf0000000ll) return hipErrorInvalidValue;
     const long long out_rows = std::min((long long)a.max_int * a.r + 2ll * a.margin, (long long)a.max_len * a.r);

@@ -306,6 +306,7 @@ __global__ __launch_bounds__(64 * WM * WN, MODE == MODE_UP && TM * TN == 16 && I
         }
     }
     const __amdgpu_buffer_rsrc_t rs_a = make_rsrc(p.ya + rowbase_o * p.cout, emit > 0 ? out_bytes : 0u);
+    const __amdgpu_buffer_rsrc_t rs_ys = MODE == MODE_RES ? make_rsrc(p.y + rowbase_o * p.cout, p.y_dead ? 0u : out_bytes) : rs_y;
     const __amdgpu_buffer_rsrc_t rs_al = make_rsrc(p.ya + p.out_lo_off + rowbase_o * p.cout, emit == 2 ? out_bytes : 0u);
     float* os = reinterpret_cast<float*>(smem);
 #pragma unroll
@@ -336,7 +337,7 @@ __global__ __launch_bounds__(64 * WM * WN, MODE == MODE_UP && TM * TN == 16 && I
                 f16x8 hv;
 #pragma unroll
                 for (int e = 0; e < 8; ++e) { hv[e] = (_Float16)v[e]; v[e] = (float)hv[e]; }
-                __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, hv), rs_y, off, 0, 0);
+                __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, hv), rs_ys, off, 0, 0);
             }
             if (emit == 0) continue;                                                  // uniform
 #pragma unroll

@@ -36,6 +36,7 @@ constexpr int W_NCHUNKS = W_CH / W_KC;
 struct WideParams {
     const uint16_t* xa;          // activated input, bf16 [rows][256]
     hres_t* y;                   // residual stream, in place
+    bool y_dead;                 // EMIT: y is read only, nothing after the unit reads the sum
     uint16_t* ya;                // optional bf16(snake_next(y)) (EMIT); not the buffer of xa
     const uint16_t* w7;          // [chunk][tap] blocks of 256 x 32 bf16
     const uint16_t* w1;          // [chunk] blocks of 256 x 32 bf16, K axis permuted
@@ -83,6 +84,7 @@ __global__ __launch_bounds__(256) void res_unit_wide_kernel(WideParams p)
 
     const __amdgpu_buffer_rsrc_t rs_x = make_rsrc(p.xa + rowbase * CH, (unsigned)nrows * CH * 2u);
     const __amdgpu_buffer_rsrc_t rs_y = make_rsrc(p.y + rowbase * CH, (unsigned)out_hi * CH * (unsigned)sizeof(hres_t));
+    const __amdgpu_buffer_rsrc_t rs_ys = make_rsrc(p.y + rowbase * CH, EMIT && p.y_dead ? 0u : (unsigned)out_hi * CH * (unsigned)sizeof(hres_t));
     const __amdgpu_buffer_rsrc_t rs_a = make_rsrc(p.ya + rowbase * CH, EMIT ? (unsigned)out_hi * CH * 2u : 0u);
     const int nstages = W_NCHUNKS * p.ntaps;
     const __amdgpu_buffer_rsrc_t rs_w7 = weight_rsrc(p.w7, (unsigned)nstages * (W_A_CH * 16u));
@@ -292,7 +294,7 @@ __global__ __launch_bounds__(256) void res_unit_wide_kernel(WideParams p)
         f16x8 o;
 #pragma unroll
         for (int mo = 0; mo < TM; ++mo) o[mo] = (_Float16)keep_f32(acc[mo][gq] + (float)r[mo]);     // fp32 sum, then one rounding
-        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, o), rs_y, off, 0, 0);
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, o), rs_ys, off, 0, 0);
         if (EMIT) {
             // the next layer's operand is Snake of the STORED value
             u32x4 sh;
@@ -344,6 +346,7 @@ __global__ __launch_bounds__(512, 2) void res_unit_wide_stream_kernel(WideParams
 
     const __amdgpu_buffer_rsrc_t rs_x = make_rsrc(p.xa + rowbase * CH, (unsigned)nrows * CH * 2u);
     const __amdgpu_buffer_rsrc_t rs_y = make_rsrc(p.y + rowbase * CH, (unsigned)out_hi * CH * (unsigned)sizeof(hres_t));
+    const __amdgpu_buffer_rsrc_t rs_ys = make_rsrc(p.y + rowbase * CH, EMIT && p.y_dead ? 0u : (unsigned)out_hi * CH * (unsigned)sizeof(hres_t));
     const __amdgpu_buffer_rsrc_t rs_a = make_rsrc(p.ya + rowbase * CH, EMIT ? (unsigned)out_hi * CH * 2u : 0u);
     const __amdgpu_buffer_rsrc_t rs_w7 = weight_rsrc(p.w7, (unsigned)(W_NCHUNKS * NTAPS) * (W_A_CH * 16u));
     const __amdgpu_buffer_rsrc_t rs_w1 = weight_rsrc(p.w1, (unsigned)W_NCHUNKS * (W_A_CH * 16u));
@@ -482,7 +485,7 @@ __global__ __launch_bounds__(512, 2) void res_unit_wide_stream_kernel(WideParams
         f16x8 o;
 #pragma unroll
         for (int e = 0; e < 8; ++e) o[e] = (_Float16)keep_f32(src[e] + (float)r[e]);
-        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, o), rs_y, off, 0, 0);
+        __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, o), rs_ys, off, 0, 0);
         if (EMIT) {
             u32x4 sh;
 #pragma unroll
@@ -536,6 +539,7 @@ __global__ __launch_bounds__(256, 2) void res_unit_wide_tall_kernel(WideParams p
 
     const __amdgpu_buffer_rsrc_t rs_x = make_rsrc(p.xa + rowbase * CH, (unsigned)nrows * CH * 2u);
     const __amdgpu_buffer_rsrc_t rs_y = make_rsrc(p.y + rowbase * CH, (unsigned)out_hi * CH * (unsigned)sizeof(hres_t));
+    const __amdgpu_buffer_rsrc_t rs_ys = make_rsrc(p.y + rowbase * CH, EMIT && p.y_dead ? 0u : (unsigned)out_hi * CH * (unsigned)sizeof(hres_t));
     const __amdgpu_buffer_rsrc_t rs_a = make_rsrc(p.ya + rowbase * CH, EMIT ? (unsigned)out_hi * CH * 2u : 0u);
     const __amdgpu_buffer_rsrc_t rs_w7 = weight_rsrc(p.w7, (unsigned)(W_NCHUNKS * NTAPS) * (W_A_CH * 16u));
     const __amdgpu_buffer_rsrc_t rs_w1 = weight_rsrc(p.w1, (unsigned)W_NCHUNKS * (W_A_CH * 16u));
@@ -704,7 +708,7 @@ __global__ __launch_bounds__(256, 2) void res_unit_wide_tall_kernel(WideParams p
             f16x4 o;
 #pragma unroll
             for (int mi = 0; mi < TM; ++mi) o[mi] = (_Float16)keep_f32(acc[mi][ni][e] + (float)r[mi]);     // fp32 sum, then one rounding
-            __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, o), rs_y, off, 0, 0);
+            __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, o), rs_ys, off, 0, 0);
             if (EMIT) {
                 // the next layer's operand is Snake of the STORED value
                 u32x2 sh;
@@ -736,12 +740,12 @@ void pack_w1_wide(const float* w, uint16_t* dst)
 hipError_t launch_res_unit_wide(const WideArgs& a, hipStream_t stream)
 {
     WideParams p;
-    p.xa = a.xa; p.y = (hres_t*)a.y; p.ya = a.ya; p.w7 = a.w7; p.w1 = a.w1; p.b7 = a.b7; p.b1 = a.b1;
+    p.xa = a.xa; p.y = (hres_t*)a.y; p.y_dead = a.y_dead; p.ya = a.ya; p.w7 = a.w7; p.w1 = a.w1; p.b7 = a.b7; p.b1 = a.b1;
     p.a2 = a.a2; p.ib2 = a.ib2; p.a3 = a.a3; p.ib3 = a.ib3;
     p.slots = a.slots; p.r = a.r; p.ntaps = a.ntaps;
     p.tap0 = -((a.ntaps - 1) / 2) * a.dil; p.tap_step = a.dil; p.margin = a.margin;
     if (a.c != W_CH || a.ntaps < 1 || (a.ntaps - 1) * a.dil > W_MAXSPAN || a.margin < 0 || !a.xa || !a.y || a.xa == a.ya) return hipErrorInvalidValue;
-    if (a.ya && (!a.a3 || !a.ib3)) return hipErrorInvalidValue;
+    if (a.ya ? !a.a3 || !a.ib3 : a.y_dead) return hipErrorInvalidValue;
     // one window's activation plane must fit a 32-bit byte offset (buffer descriptors)
     if ((long long)a.max_len * a.r * a.c * 2 > 0xf0000000ll) return hipErrorInvalidValue;
     const long long out_rows = std::min((long long)a.max_int * a.r + 2ll * a.margin, (long long)a.max_len * a.r);
