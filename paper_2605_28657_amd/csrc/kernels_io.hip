@@ -86,12 +86,12 @@ hipError_t launch_gather(const void* latent, float* x0, int c0, int n_frames, bo
 // First layer of the encoder (the mirror of the head): Conv1d(k, channels -> C) + bias straight from the planar fp32
 // waveform of every extended window into the time-major residual stream, and with `ya` the activated operand of the
 // next layer as well.  Samples outside the window read as zero (the convolution's zero padding: the window is encoded
-// as if it were a whole clip).  A thread owns one row: it loads its k x channels samples once (consecutive threads,
-// consecutive samples) and walks the C output channels in groups of 8, whose weights are the same for every thread
-// (scalar loads).  It reaches neither its bytes' time nor its FMAs': 64 channels, k = 7, stereo, 60 s clip 0.24 ms (6.2 GFLOP, 0.44 GB: 25 of 157
-// TFLOP/s, 1.8 TB/s), 75 frames 28 us; what is left are the scalar weight loads in the inner loop and 16-byte stores 128 bytes apart.
+// as if it were a whole clip).  Two kernels: on the fp32 MFMA for whole groups of 64 channels and at most 16 taps x channels, a row
+// per thread for the others.
 constexpr int STEM_MAXK = 15 * 8;                 // taps x channels held in registers
 
+// Row per thread: a thread loads its k x channels samples once (consecutive threads, consecutive samples) and walks the C output
+// channels in groups of 8, whose weights are the same for every thread (scalar loads).
 template <typename TY, int KCH>
 __global__ __launch_bounds__(256) void stem_kernel(const float* __restrict__ wave, TY* __restrict__ y, void* __restrict__ ya_,
                                                    int ya_fmt, const float* __restrict__ w /*[k][ch][C]*/,
@@ -158,6 +158,114 @@ __global__ __launch_bounds__(256) void stem_kernel(const float* __restrict__ wav
     }
 }
 
+// Bound by its stores: 64 channels, 7 taps, stereo are 128 bytes out, 8 in and 1.8 kFLOP a row, a third of the stores' time on the fp32 MFMA.
+// The kernel above waits for its scalar weight loads and stores 16 bytes of a row at a time, 128 apart.  From there to here, with an event after the launch:
+// 60 s clip 246 -> 139 us (3.2 TB/s), 75 frames 29 -> 20; the encodes 6.40 -> 6.27 ms, 477 -> 469 us.
+// A wave holds the weights of 64 channels as the row operand of v_mfma_f32_16x16x4 (4 tiles of 16 channels x KS steps of 4 values of
+// K = [tap][channel]); the samples of a workgroup's rows lie in LDS, and a lane reads one per step.  Row 4 q + e of tile mi is
+// channel 32 (mi / 2) + 8 q + 4 (mi % 2) + e, so that a lane ends with 8 consecutive channels of a row twice and four lanes store 64 bytes of it.
+// Sums start at the bias and take the products in the order of K, as above: the same bits.
+constexpr int STEM_ROWS = 512, STEM_KCH = 16;     // rows of a workgroup; taps x channels at most
+
+template <typename TY>
+__global__ __launch_bounds__(256) void stem_mfma_kernel(const float* __restrict__ wave, TY* __restrict__ y, void* __restrict__ ya_,
+                                                        int ya_fmt, const float* __restrict__ w /*[k][ch][C]*/,
+                                                        const float* __restrict__ bias, const float* __restrict__ alpha,
+                                                        const float* __restrict__ inv_beta, int ch, int C, int k, int S,
+                                                        int n_frames, int margin, const Slot* __restrict__ slots)
+{
+    if (sizeof(TY) == 2) fp16_saturate_on();
+    constexpr int KS = STEM_KCH / 4;
+    extern __shared__ float xs[];                  // [channel][STEM_ROWS + k - 1]
+    std::conditional_t<sizeof(TY) == 4, float, uint16_t>* __restrict__ ya = static_cast<std::conditional_t<sizeof(TY) == 4, float, uint16_t>*>(ya_);
+    const Slot s = slots[blockIdx.y];
+    const long long nrows = (long long)s.len * S;
+    const long long out_lo = max(0ll, (long long)s.crop * S - margin);
+    const long long out_hi = min(nrows, (long long)(s.crop + s.n_int) * S + margin);
+    const long long n0 = out_lo + (long long)blockIdx.x * STEM_ROWS;
+    if (n0 >= out_hi) return;
+    const int half = (k - 1) / 2, span = STEM_ROWS + k - 1;
+    const float* clip = wave + (size_t)s.clip * ch * ((size_t)n_frames * S) + (long long)s.lo * S;
+    for (int c = 0; c < ch; ++c)
+        for (int m = threadIdx.x; m < span; m += 256) {
+            const long long at = n0 - half + m;
+            xs[c * span + m] = at >= 0 && at < nrows ? clip[(size_t)c * ((size_t)n_frames * S) + at] : 0.f;
+        }
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, i = lane & 15, q = lane >> 4;
+    const int cg = blockIdx.z * 64;
+    // K value 4 st + q of this lane; past k x ch: 0 x 0
+    float a[KS][4];
+    int off[KS];
+#pragma unroll
+    for (int st = 0; st < KS; ++st) {
+        const int kk = 4 * st + q, t = kk / ch;
+        const bool in = kk < k * ch;
+        off[st] = in ? (kk - t * ch) * span + t : 0;
+#pragma unroll
+        for (int mi = 0; mi < 4; ++mi)
+            a[st][mi] = in ? w[(size_t)kk * C + cg + 32 * (mi >> 1) + 8 * (i >> 2) + 4 * (mi & 1) + (i & 3)] : 0.f;
+    }
+    f32x4 b[4];
+#pragma unroll
+    for (int mi = 0; mi < 4; ++mi) b[mi] = *reinterpret_cast<const f32x4*>(bias + cg + 32 * (mi >> 1) + 8 * q + 4 * (mi & 1));
+    f32x4 al[4], ib[4];
+    if (ya) {
+#pragma unroll
+        for (int mi = 0; mi < 4; ++mi) {
+            al[mi] = *reinterpret_cast<const f32x4*>(alpha + cg + 32 * (mi >> 1) + 8 * q + 4 * (mi & 1));
+            ib[mi] = *reinterpret_cast<const f32x4*>(inv_beta + cg + 32 * (mi >> 1) + 8 * q + 4 * (mi & 1));
+        }
+    }
+    __syncthreads();
+    const int nr = (int)min((long long)STEM_ROWS, out_hi - n0);
+    for (int r0 = wv * 16; r0 < nr; r0 += 64) {
+        float x[KS];
+#pragma unroll
+        for (int st = 0; st < KS; ++st) x[st] = 4 * st + q < k * ch ? xs[off[st] + r0 + i] : 0.f;
+        f32x4 acc[4];
+#pragma unroll
+        for (int mi = 0; mi < 4; ++mi) acc[mi] = b[mi];
+#pragma unroll
+        for (int st = 0; st < KS; ++st)
+#pragma unroll
+            for (int mi = 0; mi < 4; ++mi) acc[mi] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[st][mi], x[st], acc[mi], 0, 0, 0);
+        if (r0 + i >= nr) continue;
+        const size_t idx = ((size_t)s.row0 * S + n0 + r0 + i) * C + cg + 8 * q;
+#pragma unroll
+        for (int p = 0; p < 2; ++p) {
+            if constexpr (sizeof(TY) == 4) {
+                *reinterpret_cast<f32x4*>(&y[idx + 32 * p]) = acc[2 * p];
+                *reinterpret_cast<f32x4*>(&y[idx + 32 * p + 4]) = acc[2 * p + 1];
+                if (ya) {
+#pragma unroll
+                    for (int m = 2 * p; m < 2 * p + 2; ++m)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) acc[m][e] = snake_precise(acc[m][e], al[m][e], ib[m][e]);
+                    *reinterpret_cast<f32x4*>(&ya[idx + 32 * p]) = acc[2 * p];
+                    *reinterpret_cast<f32x4*>(&ya[idx + 32 * p + 4]) = acc[2 * p + 1];
+                }
+            } else {
+                f16x8 hv;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) hv[e] = (_Float16)acc[2 * p + e / 4][e % 4];
+                *reinterpret_cast<f16x8*>(&y[idx + 32 * p]) = hv;
+                if (ya) {
+                    // the next layer's operand is Snake of the STORED value
+                    u32x4 o;
+#pragma unroll
+                    for (int e = 0; e < 8; e += 2) {
+                        const int m = 2 * p + e / 4;
+                        const float a0 = keep_f32(snake_fast((float)hv[e], al[m][e % 4], ib[m][e % 4]));
+                        const float a1 = keep_f32(snake_fast((float)hv[e + 1], al[m][e % 4 + 1], ib[m][e % 4 + 1]));
+                        o[e / 2] = ya_fmt == OP_F16 ? pack_f16x2(a0, a1) : pack_bf16x2(a0, a1);
+                    }
+                    *reinterpret_cast<u32x4*>(&ya[idx + 32 * p]) = o;
+                }
+            }
+        }
+    }
+}
+
 hipError_t launch_stem(const float* wave, void* y, bool y_half, void* ya, int ya_fmt, const float* w, const float* bias,
                        const float* alpha, const float* inv_beta, int ch, int C, int k, int S, int n_frames, int margin,
                        const Slot* slots, int n_slots, int max_len, int max_int, hipStream_t stream)
@@ -165,6 +273,15 @@ hipError_t launch_stem(const float* wave, void* y, bool y_half, void* ya, int ya
     if (C % 8 != 0 || k < 1 || (k & 1) == 0 || margin < 0 || k * ch > STEM_MAXK) return hipErrorInvalidValue;
     if (ya && (ya_fmt == OP_BF16X2 || !alpha || !inv_beta)) return hipErrorInvalidValue;
     const long long rows = std::min((long long)max_int * S + 2ll * margin, (long long)max_len * S);
+    if (C % 64 == 0 && k * ch <= STEM_KCH) {
+        const dim3 tiles((unsigned)((rows + STEM_ROWS - 1) / STEM_ROWS), (unsigned)n_slots, (unsigned)(C / 64));
+        const size_t lds = (size_t)ch * (STEM_ROWS + k - 1) * sizeof(float);
+#define DEMON_STEM(TY_) hipLaunchKernelGGL((stem_mfma_kernel<TY_>), tiles, dim3(256), lds, stream, wave, (TY_*)y, ya, ya_fmt, w, bias, alpha, \
+                                           inv_beta, ch, C, k, S, n_frames, margin, slots)
+        if (y_half) DEMON_STEM(hres_t); else DEMON_STEM(float);
+#undef DEMON_STEM
+        return hipGetLastError();
+    }
     dim3 grid((unsigned)((rows + 255) / 256), (unsigned)n_slots);
     // stereo with a 7-tap stem holds 14 samples per thread; anything up to 15 taps x 8 channels takes the large form
 #define DEMON_STEM(TY_, KCH_) hipLaunchKernelGGL((stem_kernel<TY_, KCH_>), grid, dim3(256), 0, stream, wave, (TY_*)y, ya, ya_fmt, w, bias, alpha, \
