@@ -189,7 +189,8 @@ DEMON_API demon_status demon_vae_decode(demon_vae* vae, const void* d_latent, in
  * windows, run them through the decoder as one batch, trim the halos, write the interiors.
  * Writes only d_out[:, :, frame_begin*S : frame_end*S); the rest of d_out is left untouched, so a
  * partial re-decode splices into an existing waveform.  `halo` in latent frames; -1 = the analytic
- * receptive field; a smaller halo is legal but inexact near window joins.
+ * receptive field; a smaller halo is legal but inexact near window joins.  With the receptive field or more
+ * no sample depends on the grid, and rows that several windows would read are computed once, in fewer, longer windows.
  * frame_end - frame_begin <= window decodes a single playback window.
  * Layouts as for demon_vae_decode (d_latent and d_out are whole-clip buffers).
  * INVALID_ARG: null pointers, n_clips < 1, n_frames < 1, frame_begin < 0, frame_end > n_frames,
@@ -339,7 +340,8 @@ DEMON_API demon_status demon_vae_crossfade(const float* d_prev_tail, long long p
 /*
  * Test aid: after the next decode calls, copy the activation produced by layer `layer` (0-based
  * index into the sequence up_0, res_0_0 .. res_0_{n_res-1}, up_1, ...; -1 disables) of all
- * extended windows to d_dst as fp32, row-major [extended samples at that level, channels].
+ * extended windows to d_dst as fp32, row-major [extended samples at that level, channels].  While it is on, calls compute the
+ * caller's own windows.
  * At most `capacity` floats are written.  d_dst is device memory owned by the caller.
  */
 DEMON_API demon_status demon_vae_debug_tap(demon_vae* vae, int layer, float* d_dst, size_t capacity);

@@ -62,7 +62,9 @@ struct Step { const ConvLayer* conv = nullptr; const ResUnit* unit = nullptr; co
 
 struct Plan {
     bool valid = false;
-    int n_clips = 0, n_frames = 0, frame_begin = 0, frame_end = 0, window = 0, halo = 0;
+    int n_clips = 0, n_frames = 0, frame_begin = 0, frame_end = 0, window = 0, halo = 0;      // as the caller gave them
+    bool verbatim = false;             // the caller's own windows, see computed_grid
+    int grid_window = 0, grid_halo = 0;        // the grid that is computed
     int n_slots = 0, max_len = 0, max_int = 0;
     long long total_frames = 0;
     // where a call that runs as two groups of windows is cut: the window whose first extended frame is nearest to half of all
@@ -252,6 +254,36 @@ demon_status check_plane(const demon_vae* v, int max_len)
     return DEMON_OK;
 }
 
+// The window grid that a call computes.  Where every window carries the whole receptive field (or is the clip), a row does not depend
+// on the grid: the results are the full decode's bits.  Windows side by side would compute the rows that both read twice -- one row in
+// 21 of the decode and one in 6 of the encode with 64 frames, more than half with 16 -- and fill a last tile each, so a call computes each
+// clip's span as one window, or as two where the two groups below would otherwise be unequal.  In us, the caller's windows of 64 frames / one
+// per clip / two (x1920 stack): decode of 250 frames 1085 / 1039 / 1060, 750 frames 2804 / 2713 / 2600, 1500 frames 5474 / 5298 / 5213, four
+// clips of 1500 21614 / 20732 / 20778; encode of 250 frames 1298 / 1071 / 1107, 1500 frames 6185 / 5308 / 5213; fp32 decode of the x32 stack,
+// 1500 frames 293 / 247.  One and two windows, two groups: 330 frames 1348 / 1330, 360 frames 1428 / 1429, 400 frames 1510 / 1509, 440 frames 1778 / 1624, 520 frames
+// 1975 / 1880, encode of 400 frames 1520 / 1605, 440 frames 1790 / 1703; with LDS-staged convolutions 100 frames 994 / 1000, 200 frames 1395 /
+// 1432, 250 frames 1683 / 1582.  A window's plane stays below 1 GB, far from the kernels' 32-bit offsets.
+// The caller's own grid stays where a window carries less (its rows then depend on it), and for the debug tap, whose rows are the caller's windows.
+struct Grid { int window, halo; };
+constexpr long long kRegionBytes = 1ll << 30;
+
+Grid computed_grid(const demon_vae* v, int n_clips, int n_frames, int fb, int fe, int window, int halo, long long frames_held, bool two_streams)
+{
+    const int rf = std::max(v->rf_left, v->rf_right);
+    const bool whole_clip = fb == 0 && fe == n_frames && window >= n_frames;
+    if (halo < rf && !whole_clip) return {window, halo};
+    const long long span = fe - fb;
+    const long long most = kRegionBytes / (v->per_frame * (v->dtype == DEMON_BF16 ? 2 : 4)) - 2ll * rf;
+    long long k = two_streams && n_clips % 2 == 1 && span * n_clips >= (v->has_staged_convs ? 230 : 420) ? 2 : 1;
+    if (most > 0 && (span + most - 1) / most > k) k = (span + most - 1) / most + (span + most - 1) / most % 2;
+    const int w = (int)((span + k - 1) / k);
+    // the halo of the caller's single window is not needed where it is the clip
+    const Grid g = {w, w == span && whole_clip ? 0 : rf};
+    // more extended frames than the caller's grid (a window cut in two): only where they are held
+    if (most < 1 || k * n_clips > kMaxSlots || count_grid(n_frames, fb, fe, g.window, g.halo).clip_frames * n_clips > frames_held) return {window, halo};
+    return g;
+}
+
 // Whether the layer sequence of a call runs as two groups of windows on two streams: the ramp and tail of one group's launches
 // (a last round of workgroups that fills a fraction of the CUs, prologues, epilogues) overlap with the other's.  Both take the
 // tiles that the whole call would take.  One / two groups in us on the x1920 stack, windows of 64 frames: 250 frames (286
@@ -277,18 +309,19 @@ demon_status get_plan(demon_vae* v, int n_clips, int n_frames, int fb, int fe, i
                       hipStream_t stream, Plan** out)
 {
     ++v->use_counter;
+    const bool verbatim = v->tap_layer >= 0 && v->tap_dst;
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     HIP_TRY(hipStreamIsCapturing(stream, &cap), "hipStreamIsCapturing");
     const bool capturing = cap != hipStreamCaptureStatusNone;
     Plan* victim = nullptr;
     for (Plan& p : v->plans) {
         if (p.valid && p.n_clips == n_clips && p.n_frames == n_frames && p.frame_begin == fb && p.frame_end == fe &&
-            p.window == window && p.halo == halo) {
+            p.window == window && p.halo == halo && p.verbatim == verbatim) {
             p.last_use = v->use_counter;
             if (capturing) p.pinned = true;
             if (p.table_pending) {
                 HIP_TRY(launch_plan_slots(p.d_slots, p.n_clips, p.n_slots / p.n_clips, (int)(p.total_frames / p.n_clips), p.n_frames,
-                                          p.frame_begin, p.frame_end, p.window, p.halo, stream), "window table");
+                                          p.frame_begin, p.frame_end, p.grid_window, p.grid_halo, stream), "window table");
                 if (!capturing) p.table_pending = false;
             }
             *out = &p;
@@ -299,34 +332,40 @@ demon_status get_plan(demon_vae* v, int n_clips, int n_frames, int fb, int fe, i
     }
     if (!victim)
         return fail(DEMON_ERR_WORKSPACE, "all %d cached window grids are held by recorded graphs; a further grid needs another handle", kPlanCache);
-    const GridCount gc = count_grid(n_frames, fb, fe, window, halo);
-    const long long n_slots = gc.per_clip * n_clips;
+    // the limits are those of the caller's grid
+    GridCount gc = count_grid(n_frames, fb, fe, window, halo);
+    long long n_slots = gc.per_clip * n_clips;
     if (n_slots > kMaxSlots)
         return fail(DEMON_ERR_WORKSPACE, "%lld windows exceed the limit of %d", n_slots, kMaxSlots);
-    const long long total = gc.clip_frames * n_clips;
+    long long total = gc.clip_frames * n_clips;
     if (total > v->cap_frames)
         return fail(DEMON_ERR_WORKSPACE, "extended windows need %lld frames, the workspace holds %lld", total, v->cap_frames);
     const demon_status prc = check_plane(v, gc.max_len);
     if (prc != DEMON_OK) return prc;
+    const Grid grid = verbatim ? Grid{window, halo} : computed_grid(v, n_clips, n_frames, fb, fe, window, halo, v->cap_frames, v->stream2 != nullptr);
+    gc = count_grid(n_frames, fb, fe, grid.window, grid.halo);
+    n_slots = gc.per_clip * n_clips;
+    total = gc.clip_frames * n_clips;
     const int idx = (int)(victim - v->plans);
     Slot* d = v->d_slot_arena + (size_t)idx * kMaxSlots;
     victim->valid = false;
-    HIP_TRY(launch_plan_slots(d, n_clips, (int)gc.per_clip, (int)gc.clip_frames, n_frames, fb, fe, window, halo, stream), "window table");
+    HIP_TRY(launch_plan_slots(d, n_clips, (int)gc.per_clip, (int)gc.clip_frames, n_frames, fb, fe, grid.window, grid.halo, stream), "window table");
     victim->valid = true;
     victim->pinned = capturing;
     victim->table_pending = capturing;
     victim->n_clips = n_clips; victim->n_frames = n_frames; victim->frame_begin = fb; victim->frame_end = fe;
-    victim->window = window; victim->halo = halo;
+    victim->window = window; victim->halo = halo; victim->verbatim = verbatim;
+    victim->grid_window = grid.window; victim->grid_halo = grid.halo;
     victim->n_slots = (int)n_slots; victim->max_len = gc.max_len; victim->max_int = gc.max_int;
     victim->total_frames = total; victim->d_slots = d; victim->last_use = v->use_counter;
     victim->split = 0; victim->split_frame0 = 0;
     long long best = -1, row = 0, i = 0;
     for (int c = 0; c < n_clips; ++c)
-        for (long long b = fb; b < fe; b += window, ++i) {
-            const long long e = std::min<long long>(b + window, fe);
+        for (long long b = fb; b < fe; b += grid.window, ++i) {
+            const long long e = std::min<long long>(b + grid.window, fe);
             const long long d = std::abs(total - 2 * row);
             if (i >= 1 && (best < 0 || d < best)) { best = d; victim->split = (int)i; victim->split_frame0 = row; }
-            row += std::min<long long>(n_frames, e + halo) - std::max<long long>(0, b - halo);
+            row += std::min<long long>(n_frames, e + grid.halo) - std::max<long long>(0, b - grid.halo);
         }
     *out = victim;
     return DEMON_OK;
@@ -1060,11 +1099,10 @@ demon_status demon_vae_decode_windowed_static(demon_vae* v, const void* d_latent
     // the window grid, counted on the host without building it (the table itself is written by a kernel)
     const GridCount gc = count_grid(n_frames, frame_begin, frame_end, window, halo);
     const long long per_clip = gc.per_clip, clip_frames = gc.clip_frames;
-    const int max_len = gc.max_len, max_int = gc.max_int;
     if (per_clip * n_clips > kMaxSlots)
         return fail(DEMON_ERR_WORKSPACE, "%lld windows exceed the limit of %d", per_clip * n_clips, kMaxSlots);
     const long long total = clip_frames * n_clips;
-    const demon_status prc = check_plane(v, max_len);
+    const demon_status prc = check_plane(v, gc.max_len);
     if (prc != DEMON_OK) return prc;
 
     // carve the call's memory out of the static array: window table, activation buffers (the head writes the caller's waveform)
@@ -1087,10 +1125,12 @@ demon_status demon_vae_decode_windowed_static(demon_vae* v, const void* d_latent
     plan.valid = true;
     plan.n_clips = n_clips; plan.n_frames = n_frames; plan.frame_begin = frame_begin; plan.frame_end = frame_end;
     plan.window = window; plan.halo = halo;
-    plan.n_slots = (int)(per_clip * n_clips); plan.max_len = max_len; plan.max_int = max_int;
-    plan.total_frames = total;
+    const Grid grid = v->tap_layer >= 0 && v->tap_dst ? Grid{window, halo} : computed_grid(v, n_clips, n_frames, frame_begin, frame_end, window, halo, total, false);
+    const GridCount cc = count_grid(n_frames, frame_begin, frame_end, grid.window, grid.halo);
+    plan.n_slots = (int)(cc.per_clip * n_clips); plan.max_len = cc.max_len; plan.max_int = cc.max_int;
+    plan.total_frames = cc.clip_frames * n_clips;
     plan.d_slots = reinterpret_cast<Slot*>(v->scratch + at_slots);
-    HIP_TRY(launch_plan_slots(plan.d_slots, n_clips, (int)per_clip, (int)clip_frames, n_frames, frame_begin, frame_end, window, halo, stream),
+    HIP_TRY(launch_plan_slots(plan.d_slots, n_clips, (int)cc.per_clip, (int)cc.clip_frames, n_frames, frame_begin, frame_end, grid.window, grid.halo, stream),
             "window table");
     Io io;
     io.d_latent = d_latent; io.d_out = d_out; io.n_frames = n_frames;

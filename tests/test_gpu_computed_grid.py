@@ -1,0 +1,124 @@
+"""A call computes each clip's span in as few windows as it can where the grid does not change a row.  The debug tap makes it compute the
+caller's own windows: the same bits, over window lengths from one frame to more than the clip, halos of the receptive field and more,
+spans inside the clip and at its edges, one and several clips, sizes on both sides of the cut into two windows, every entry point.  With
+less than the receptive field the windows are the caller's with and without the tap."""
+import numpy as np
+import pytest
+import torch
+
+import demon_inputs as di
+import oracle
+from gpu_util import TOL, errors, make, to_device
+from paper_2605_28657_amd import DemonError, DemonVAEEncoder, DEMON_ERR_WORKSPACE
+
+pytestmark = pytest.mark.gpu
+
+STACKS = {"narrow": di.DecoderSpec(64, (4, 2), (128, 64)), "wide": di.DecoderSpec(64, (2, 2), (512, 256), (1, 3)),
+          "staged": di.DecoderSpec(32, (4, 2), (96, 32), (1, 3))}
+# clips, frames, begin, end, window
+SPANS = [(1, 130, 0, 130, 1), (1, 130, 0, 130, 37), (1, 130, 5, 117, 16), (3, 90, 11, 90, 64), (2, 75, 0, 75, 500), (1, 700, 0, 700, 64), (1, 700, 0, 700, 700),
+         (1, 900, 3, 881, 130), (3, 300, 0, 299, 50), (4, 200, 0, 200, 9)]
+
+
+def held(spec, clips, T, fb, fe, window):
+    """Extended frames of the caller's grid with the largest halo asked for."""
+    return clips * max(T, -(-(fe - fb) // window) * (min(window, fe - fb) + 2 * (max(oracle.receptive_field(spec)) + 8)))
+
+
+def both(handle, decode):
+    """(the caller's windows, what a call computes)"""
+    scratch = torch.zeros(1, device="cuda:0")
+    handle.tap(0, scratch)
+    ref = decode()
+    handle.tap(-1)
+    return ref, decode()
+
+
+@pytest.mark.parametrize("stack", list(STACKS))
+@pytest.mark.parametrize("clips,T,fb,fe,window", SPANS)
+@pytest.mark.parametrize("dtype,kw", [("bf16", {}), ("bf16", dict(wide_operands=2)), ("f32", {})])
+def test_decode(stack, clips, T, fb, fe, window, dtype, kw):
+    spec = STACKS[stack]
+    vae, _, z = make(spec, dtype, T, n_clips=clips, max_extended_frames=held(spec, clips, T, fb, fe, window), **kw)
+    zt = to_device(z, dtype)
+    rf = max(vae.receptive_field())
+    S = spec.total_stride
+    whole = vae.decode(zt)
+    for halo in (-1, rf, rf + 7, rf - 1, 0):
+        def run(decode=vae.decode_windowed, dt=torch.float32):
+            out = torch.full((clips, spec.out_channels, T * S), 7.0, device="cuda:0")
+            return decode(zt, out=out, window=window, halo=halo, frame_begin=fb, frame_end=fe)
+        ref, got = both(vae, run)
+        assert torch.equal(got, ref), f"halo {halo}"
+        assert (got[:, :, :fb * S] == 7).all() and (got[:, :, fe * S:] == 7).all()
+        if halo == -1 or halo >= rf or (fb == 0 and fe == T and window >= T):
+            assert torch.equal(got[:, :, fb * S:fe * S], whole[:, :, fb * S:fe * S])
+        elif window < fe - fb:
+            assert not torch.equal(got[:, :, fb * S:fe * S], whole[:, :, fb * S:fe * S])
+    args = dict(window=window, halo=-1, frame_begin=fb, frame_end=fe)
+    pcm = both(vae, lambda: vae.decode_windowed_pcm16(zt, **args)[:, fb * S:fe * S].clone())
+    assert torch.equal(*pcm)
+    skip = torch.tensor([0, 1, 0, 1][:clips], dtype=torch.int32, device="cuda:0")
+    gated = both(vae, lambda: vae.decode_windowed_gated(zt, skip, torch.full((clips, spec.out_channels, T * S), 7.0, device="cuda:0"), **args))
+    assert torch.equal(*gated)
+    try:
+        static = both(vae, lambda: vae.decode_windowed_static(zt, out=torch.zeros((clips, spec.out_channels, T * S), device="cuda:0"), **args).clone())
+    except DemonError as e:
+        assert e.status == DEMON_ERR_WORKSPACE
+    else:
+        assert torch.equal(*static)
+    vae.close()
+
+
+@pytest.mark.parametrize("stack", list(STACKS))
+@pytest.mark.parametrize("clips,T,fb,fe,window", SPANS)
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+def test_encode(stack, clips, T, fb, fe, window, dtype):
+    spec = STACKS[stack]
+    w = di.make_encoder_weights(spec, bf16=dtype == "bf16")
+    enc = DemonVAEEncoder(spec, w, dtype=dtype, max_frames=T, max_clips=clips, max_extended_frames=held(spec, clips, T, fb, fe, window))
+    x = torch.from_numpy(np.stack([di.make_waveform(spec.out_channels, T * spec.total_stride, 40 + c) for c in range(clips)])).to("cuda:0")
+    rf = max(enc.receptive_field())
+    whole, _ = enc.encode(x)
+    for halo in (-1, rf + 3, rf - 1):
+        ref, got = both(enc, lambda: enc.encode_windowed(x, window=window, halo=halo, frame_begin=fb, frame_end=fe)[0][:, :, fb:fe].clone())
+        assert torch.equal(got, ref), f"halo {halo}"
+        if halo != rf - 1:
+            assert torch.equal(got, whole[:, :, fb:fe])
+    enc.close()
+
+
+def test_the_limits_are_those_of_the_callers_grid():
+    spec, T = STACKS["narrow"], 500
+    rf = max(oracle.receptive_field(spec))
+    tight, _, z = make(spec, "bf16", T, max_extended_frames=T)
+    zt = to_device(z, "bf16")
+    full = tight.decode(zt)                                  # one window: a cut one would need 2 rf frames more than are held
+    with pytest.raises(DemonError) as e:
+        tight.decode_windowed(zt, window=100, halo=-1)       # 4 joins of 2 rf frames
+    assert e.value.status == DEMON_ERR_WORKSPACE
+    roomy, w, _ = make(spec, "bf16", T, max_extended_frames=T + 2 * rf)
+    assert torch.equal(roomy.decode(zt), full)               # cut in two
+    ma, rl = errors(full[0].cpu().numpy(), oracle.decode(spec, w, z[0]))
+    assert ma <= TOL["bf16"][0] and rl <= TOL["bf16"][1]
+    tight.close(); roomy.close()
+
+
+def test_replay_with_and_without_the_tap():
+    """A recorded grid keeps its table: the caller's windows and the computed ones are two entries."""
+    spec, T = STACKS["narrow"], 600
+    vae, _, z = make(spec, "bf16", T, max_extended_frames=4 * T)
+    zt = to_device(z, "bf16")
+    out = torch.zeros((1, 2, T * spec.total_stride), device="cuda:0")
+    ref = vae.decode(zt)
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        vae.decode_windowed(zt, out=out, window=50, halo=-1)
+    for _ in range(3):
+        out.zero_()
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, ref)
+        a, b = both(vae, lambda: vae.decode_windowed(zt, window=50, halo=-1))
+        assert torch.equal(a, ref) and torch.equal(b, ref)
+    vae.close()
