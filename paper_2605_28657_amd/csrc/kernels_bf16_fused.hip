@@ -182,10 +182,7 @@ __global__ __launch_bounds__(256, (CH == 128 && TN == 2) ? 2 : 3) void res_unit_
             const f16x8 hv = __builtin_bit_cast(f16x8, rx[it]);
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                float e0 = (float)hv[2 * q], e1 = (float)hv[2 * q + 1];
-                e0 = snake_fast(e0, al[2 * q], ib[2 * q]);
-                e1 = snake_fast(e1, al[2 * q + 1], ib[2 * q + 1]);
-                v[q] = pack_bf16x2(e0, e1);
+                v[q] = pack_bf16x2(snake_fast_half(hv[2 * q], al[2 * q], ib[2 * q]), snake_fast_half(hv[2 * q + 1], al[2 * q + 1], ib[2 * q + 1]));
             }
             *reinterpret_cast<u32x4*>(&Xs[xr * LDX + ((seg ^ (xr & 7)) * 8)]) = v;
         }
@@ -366,6 +363,7 @@ __global__ __launch_bounds__(256, (CH == 128 && TN == 2) ? 2 : 3) void res_unit_
         a3v[mo] = EMIT ? p.a3[j * TM + mo] : 0.f;
         i3v[mo] = EMIT ? p.ib3[j * TM + mo] : 0.f;
     }
+    const float one = opaque_one();
     // HEAD: the tile of head operands takes the activation tile's space (nothing reads that after the K loop; every wave
     // has passed the barriers that staged the 1x1 weights), rows shifted by (k-1)/2 so that a tap is a row offset >= 0
     constexpr int LDH = CH + 8;
@@ -395,15 +393,13 @@ __global__ __launch_bounds__(256, (CH == 128 && TN == 2) ? 2 : 3) void res_unit_
 #pragma unroll
         for (int gq = 0; gq < 16; ++gq) {
             const unsigned off = res_offset(ni, gq);
-            float v[TM];
             typedef _Float16 halfs_t __attribute__((ext_vector_type(TM)));
             const halfs_t r = __builtin_bit_cast(halfs_t, resv[ni][gq]);
             static_assert(sizeof(halfs_t) == sizeof(res_t), "TM halves");
             halfs_t o;
 #pragma unroll
             for (int mo = 0; mo < TM; ++mo) {
-                v[mo] = acc[mo][ni][gq] + (float)r[mo];
-                o[mo] = (_Float16)v[mo];                         // round to nearest even
+                o[mo] = (_Float16)keep_f32(add_half(acc[mo][ni][gq], r[mo], one));       // fp32 sum, then one rounding
             }
             if constexpr (HEAD) {
                 // the head's operand: Snake of the (half) value the unit would have stored, in fp32, rounded once to half;
@@ -412,8 +408,8 @@ __global__ __launch_bounds__(256, (CH == 128 && TN == 2) ? 2 : 3) void res_unit_
                 const int n = n0 + col;
                 f16x2 av = {(_Float16)0.f, (_Float16)0.f};
                 if (n >= 0 && n < nrows) {
-                    av[0] = (_Float16)keep_f32(snake_fast((float)o[0], hav[0], hiv[0]));
-                    av[1] = (_Float16)keep_f32(snake_fast((float)o[1], hav[1], hiv[1]));
+                    av[0] = (_Float16)keep_f32(snake_fast_half(o[0], hav[0], hiv[0]));
+                    av[1] = (_Float16)keep_f32(snake_fast_half(o[1], hav[1], hiv[1]));
                 }
                 *reinterpret_cast<f16x2*>(&Hs[(col + hhalf) * LDH + j * TM]) = av;
                 continue;
@@ -425,8 +421,8 @@ __global__ __launch_bounds__(256, (CH == 128 && TN == 2) ? 2 : 3) void res_unit_
                 uint32_t sh[TM / 2];
 #pragma unroll
                 for (int mo = 0; mo < TM; mo += 2) {
-                    const float e0 = snake_fast((float)o[mo], a3v[mo], i3v[mo]);
-                    const float e1 = snake_fast((float)o[mo + 1], a3v[mo + 1], i3v[mo + 1]);
+                    const float e0 = snake_fast_half(o[mo], a3v[mo], i3v[mo]);
+                    const float e1 = snake_fast_half(o[mo + 1], a3v[mo + 1], i3v[mo + 1]);
                     sh[mo / 2] = pack_bf16x2(e0, e1);
                 }
                 if constexpr (TM == 2) __builtin_amdgcn_raw_buffer_store_b32(sh[0], rs_a, off, 0, 2);
