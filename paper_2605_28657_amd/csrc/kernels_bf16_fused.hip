@@ -490,8 +490,9 @@ __device__ __forceinline__ void unrolled(std::integer_sequence<int, I...>, Fn&& 
 // limit the 128-channel units of a 60 s clip take 452 to 494 us.
 //  * 128 channels, large calls: 64 x 128 per wave, 2 x 2 waves, two workgroups per CU (256 registers, 80 KB): a third of the LDS reads.
 //    What bounds it now is the two waves of a SIMD: matrix cores busy 50 %, other VALU work (Snake of 1.25 + 1 values per output) 30 %,
-//    which overlap in part.  Waves in the K loop go first (s_setprio: -5 %).  60 s clip 428 -> 378 us per unit (with the operand 458 -> 424), 375 frames
-//    104 to 121 -> 90 to 106.
+//    which overlap in part.  Waves in the K loop go first (s_setprio: -5 %), those in the 1x1 conv before them: at the default priority its 2 k
+//    cycles of MFMAs took 9 of a workgroup's 60 k beside the other's K loop (366 -> 346 us; the same priority 343, but the call 5090 instead of 5083).
+//    60 s clip 428 -> 346 us per unit (with the operand 458 -> 366), 375 frames 104 to 121 -> 89 to 98.
 //  * 128 channels, few tiles: 32 x 64 per wave, 4 x 1 waves: window of 13 frames 25 -> 11 us, 75 frames 36 -> 27.
 //  * 64 channels: one stage, two by two waves of 32 channels: 13 frames 13 -> 9 us (with the head 19 -> 11), 75 frames 20 -> 17 (28 -> 23),
 //    375 frames 62 -> 55.
@@ -767,6 +768,7 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) void res_unit_narrow_stream_kern
         }
     }
     {
+        __builtin_amdgcn_s_setprio(2);                      // before the waves in the loop: a seventh of its MFMAs, and the workgroup is nearly done
         const uint16_t* mr = ms + (wn * (16 * TN) + i) * LDM + q * 8;
         constexpr int XA = 3, XQ = XA + 1;
         u32x4 x[XQ];
@@ -790,6 +792,7 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) void res_unit_narrow_stream_kern
             __builtin_amdgcn_sched_barrier(0);
         }
     }
+    __builtin_amdgcn_s_setprio(0);
     if (TIGHT) {
 #pragma unroll
         for (int ni = 2 * (KS1 - 1); ni < TN; ++ni) load_res(ni);

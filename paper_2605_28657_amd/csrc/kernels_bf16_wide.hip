@@ -505,8 +505,8 @@ __global__ __launch_bounds__(512, 2) void res_unit_wide_stream_kernel(WideParams
 // The dilated conv has the weights as the row operand (a lane ends with four consecutive channels of a column: 8-byte LDS writes of
 // the branch tensor), the 1x1 conv the activations (a lane ends with four channels of a row, 16 lanes with 128 bytes: the
 // epilogue goes straight to memory).  In calls that are waited for, 60 s clip 389 -> 317 us per unit (1.19 PFLOP/s; HBM traffic and Snake included),
-// 375 frames 111 -> 80, encode of 60 s 438 -> 363; in back-to-back steps at the power limit 366 to 384 (0.98 to 1.03 PFLOP/s).  Bit-identical to
-// the kernels above.
+// 375 frames 111 -> 80, encode of 60 s 438 -> 363.  The 1x1 conv goes before the K loop of the other workgroup (s_setprio 2 and 1: 310 -> 307 us; 1 in the
+// K loop alone: none).  Bit-identical to the kernels above.
 template <bool EMIT>
 __global__ __launch_bounds__(256, 2) void res_unit_wide_tall_kernel(WideParams p)
 {
@@ -583,6 +583,7 @@ __global__ __launch_bounds__(256, 2) void res_unit_wide_tall_kernel(WideParams p
     for (int it = 0; it < X_ITERS; ++it) store_x(0, it);
     __syncthreads();
 
+    __builtin_amdgcn_s_setprio(1);                          // waves in this loop go first, those in the 1x1 conv before them
     const int tap_bytes = p.tap_step * (LDR * 2);
     auto run_stage = [&](int stage, int half, auto last) __attribute__((always_inline)) {
         constexpr bool LAST = decltype(last)::value;
@@ -633,6 +634,7 @@ __global__ __launch_bounds__(256, 2) void res_unit_wide_tall_kernel(WideParams p
     }
     run_stage(NSTAGES - 2, 0, std::true_type{});
     run_stage(NSTAGES - 1, 1, std::true_type{});
+    __builtin_amdgcn_s_setprio(0);
 
     // ---- Snake on the accumulators; the branch tensor goes to LDS as [column][k-slot]: channel 16 m + 4 q + e of a group of 32 is
     // k-slot 16 m + 8 (q % 2) + 4 (q / 2) + e of the 1x1 weights' K axis
@@ -667,6 +669,7 @@ __global__ __launch_bounds__(256, 2) void res_unit_wide_tall_kernel(WideParams p
         for (int e = 0; e < 4; ++e) resv[ni][e] = __builtin_amdgcn_raw_buffer_load_b64(rs_y, e_voff + (unsigned)((16 * ni + e) * CH * 2), 0, 0);
     };
     {
+        __builtin_amdgcn_s_setprio(2);
         const uint16_t* mr = ms + i * LDM + q * 8;
         constexpr int XA = 3, XQ = XA + 1;
         u32x4 x[XQ];
@@ -690,6 +693,7 @@ __global__ __launch_bounds__(256, 2) void res_unit_wide_tall_kernel(WideParams p
             __builtin_amdgcn_sched_barrier(0);
         }
     }
+    __builtin_amdgcn_s_setprio(0);
     load_res(TN - 2);
     load_res(TN - 1);
     asm volatile("" : "+v"(e_voff));                        // the 32 offsets are formed again, not kept
