@@ -1,7 +1,7 @@
 // Fused residual unit for the narrow, high-rate levels (C = 64 or 128 channels):
 //     h_out = h + W1 * snake2(W7 (*) snake1(h) + b7) + b1
 // in one kernel, so that the activated branch tensor never goes to HBM.  Two kernels: the LDS-staged one, first below, for kernel
-// sizes other than 7 and for 64 channels in calls whose tensors exceed the last-level cache, and the streamed one.
+// sizes other than 7, and the streamed one.
 //
 // LDS-staged: the dilated conv runs as in kernels_bf16.hip (implicit GEMM, rows = output channels, columns = time,
 // one weight block in LDS, the next waiting in registers), except that the kernel reads the half-precision residual stream itself and
@@ -597,9 +597,13 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) void res_unit_narrow_stream_kern
     };
 
     // every request of the prologue in the order of use
+    // the last rows are those of the largest dilation (0.5 s window 215.2 -> 212.3 us, 3 s 463 -> 459; the units 3 to 8 % with dilations 1 and 3)
+    const int rows_read = NT + (NTAPS - 1) * p.tap_step;
+    auto staged = [&](int j) __attribute__((always_inline)) { return TIGHT || j < X_ITERS - 1 || j * RPP < rows_read; };
     u32x4 px[X_ITERS], rx[NSTAGES > 1 ? RX : 1];
 #pragma unroll
-    for (int j = 0; j < X_ITERS; ++j) px[j] = load_x(j);
+    for (int j = 0; j < X_ITERS; ++j)
+        if (staged(j)) px[j] = load_x(j);
     f32x4 pal[2], pib[2];                                    // Snake of the first stage's rows
 #pragma unroll
     for (int k = 0; k < 2; ++k) { pal[k] = *reinterpret_cast<const f32x4*>(p.a1 + seg * 8 + 4 * k); pib[k] = *reinterpret_cast<const f32x4*>(p.ib1 + seg * 8 + 4 * k); }
@@ -626,6 +630,7 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) void res_unit_narrow_stream_kern
     }
 #pragma unroll
     for (int j = 0; j < X_ITERS; ++j) {
+        if (!staged(j)) break;
         u32x4 v;
 #pragma unroll
         for (int k = 0; k < 4; ++k) v[k] = snake2(px[j][k], f32x4{pal[k / 2][k % 2 * 2], pib[k / 2][k % 2 * 2], pal[k / 2][k % 2 * 2 + 1], pib[k / 2][k % 2 * 2 + 1]});
@@ -934,14 +939,16 @@ hipError_t launch_res_unit_fused(const FusedArgs& a, hipStream_t stream)
         DEMON_NARROW(4, 8, 2, 2, 2)
     }
     if (a.ntaps == 7 && a.hw) {
-        hipLaunchKernelGGL((res_unit_narrow_stream_kernel<2, 4, 2, 2, 3, false, true>), grid(128), dim3(256), 0, stream, p);
+        // the columns by the rule below: of 128 columns 122 are the head's, of 256 250 (60 s clip 5210 -> 5180 us, 375 frames 1464 -> 1457)
+        if (tiles(128) * a.call_slots <= 2304) hipLaunchKernelGGL((res_unit_narrow_stream_kernel<2, 4, 2, 2, 3, false, true>), grid(128), dim3(256), 0, stream, p);
+        else hipLaunchKernelGGL((res_unit_narrow_stream_kernel<2, 8, 2, 2, 3, false, true>), grid(256), dim3(256), 0, stream, p);
         return hipGetLastError();
     }
-    // 64 channels: streamed while the tensors read and written fit the 256 MB last-level cache (then its stores go there as well), else
-    // the LDS-staged kernel, whose stores of whole rows suit the memory better.  Per unit in us, staged / 128 columns / 256 columns: 13
-    // frames 13, 12 / 9, 8 / 10, 10; 75 frames 19 / 17 / 17; 150 frames 30 / 27 / 27; 200 frames 35 / 34 / 32; 500 frames 79 / - / 71; 600 frames
-    // 97 / - / 102; 1000 frames 163 / - / 175.
-    if (a.ntaps == 7 && a.c == 64 && out_rows * a.call_slots * 64 * 2 * 2 <= 256ll << 20) {
+    // 64 channels.  Per unit in us, LDS-staged / 128 columns / 256 columns: 13 frames 13, 12 / 9, 8 / 10, 10; 75 frames 19 / 17 / 17; 150 frames
+    // 30 / 27 / 27; 200 frames 35 / 34 / 32; 500 frames 79 / - / 71.  Tensors beyond the last-level cache suit the staged kernel's stores of whole
+    // rows better where a launch is waited for (600 frames 97 / - / 102, 1000 frames 163 / - / 175), but not in calls back to back, beside
+    // the other group and at the power limit: 60 s clip 5059 us staged, 5033 streamed, its encode 5078 and 5056.
+    if (a.ntaps == 7 && a.c == 64) {
         if (tiles(128) * a.call_slots <= 2304) DEMON_NARROW(2, 4, 2, 2, 3)
         DEMON_NARROW(2, 8, 2, 2, 3)
     }

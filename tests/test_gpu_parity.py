@@ -731,8 +731,7 @@ def test_transposed_conv_feeding_wide_operands_without_residual_units():
 def test_head_inside_the_last_unit_is_bit_identical_to_the_head_kernel(spec, T, window):
     """When the last layer is the fused 64-channel unit, the head runs inside its kernel (the unit's output never goes
     to memory): the same operands in the same order as the head kernel, so the same bits -- full and windowed, at clip
-    edges, with ragged windows, two clips, partial ranges -- and the oracle's values.  The library does this for calls of at
-    most 256 extended frames (the calls below, except the window-1 grids, which take the head kernel on both sides)."""
+    edges, with ragged windows, two clips, partial ranges -- and the oracle's values."""
     vae, w, z = make(spec, "bf16", T, n_clips=2, max_extended_frames=100 * T)
     ref_vae = pa.DemonVAE(spec, w, dtype="bf16", max_frames=T, max_clips=2, max_extended_frames=100 * T,
                           flags=pa.DEMON_VAE_FLAG_NO_HEAD_FUSION)

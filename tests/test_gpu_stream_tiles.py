@@ -77,7 +77,7 @@ def test_unit_256_stream_tiles(T, dils):
     (512, 32700, 16101),                     # the dilated convolutions' 256 x 128 tile
     (256, 4200, 37), (256, 13000, 6001),     # many ragged windows, two long ones: more tiles than the narrow kernel takes
     (128, 9000, 119), (128, 45000, 20001),   # 64 columns a workgroup; 256
-    (64, 3001, 64), (64, 150001, 60000), (64, 530000, 300000),      # 128 columns (with the head in the short window); 256; LDS-staged
+    (64, 3001, 64), (64, 150001, 60000), (64, 530000, 300000),      # 128 columns (with the head in the short window); 256
 ])
 def test_units_of_large_calls_window_by_window(c, T, window):
     """The residual units' kernels for launches that fill the chip, on windows whose ends fall inside a tile: the same bits as the whole clip,
