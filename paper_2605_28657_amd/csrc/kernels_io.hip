@@ -20,10 +20,13 @@ template <> __device__ __forceinline__ float load_act<_Float16>(const _Float16* 
 
 // ---------------------------------------------------------------------------------- gather
 // The latent is [clip, channel, frame] (frames fastest), the slots are time-major [frame, channel]: a workgroup moves a
-// tile of 64 frames x 64 channels through LDS, reading runs of consecutive frames of one channel and writing runs of
-// consecutive channels of one frame, so both sides are coalesced.  With `xa` (bf16 path) it writes the first layer's
+// tile of 32 frames x 16 channels through LDS, reading runs of consecutive frames of one channel and writing runs of
+// consecutive channels of one frame.  With `xa` (bf16 path) it writes the first layer's
 // MFMA operand directly, snake(latent) in operand format fmt; without it (fp32 path) the same in fp32.
-constexpr int GATHER_TILE = 64;
+// Bound by latencies: window, latent, parameters and flags are all requested before the first is waited for, two elements a thread.
+// (Tiles of 64 x 64, one workgroup for a playback window, went through 16 waits of a load each: 8.1 us for 25 frames, 2.5
+// now; 0.5 s window 212.0 -> 206.6 us, 3 s 438 -> 431, 2 s clip of the x32 stack 105.5 -> 100.6.)
+constexpr int GATHER_R = 32, GATHER_C = 16;
 
 template <typename T>
 __global__ __launch_bounds__(256) void gather_kernel(const T* __restrict__ latent, float* __restrict__ x0,
@@ -33,37 +36,43 @@ __global__ __launch_bounds__(256) void gather_kernel(const T* __restrict__ laten
                                                      const int* __restrict__ skip, Slot* __restrict__ gated)
 {
     fp16_saturate_on();
-    __shared__ float tile[GATHER_TILE][GATHER_TILE + 1];
+    constexpr int RS = 256 / GATHER_R, CS = 256 / GATHER_C;           // channels, frames a pass
+    __shared__ float tile[GATHER_C][GATHER_R + 1];
+    const int cbase = blockIdx.z * GATHER_C, c = cbase + threadIdx.x % GATHER_C;
+    const float al = c < c0 ? alpha[c] : 0.f, ib = c < c0 ? inv_beta[c] : 0.f;
     Slot s = slots[blockIdx.y];
+    const int r0 = blockIdx.x * GATHER_R;
+    const int lane = threadIdx.x % GATHER_R, sub = threadIdx.x / GATHER_R;
+    float v[GATHER_C / RS];
+#pragma unroll
+    for (int u = 0; u < GATHER_C / RS; ++u) {
+        const int cc = cbase + sub + u * RS;
+        v[u] = cc < c0 && r0 + lane < s.len ? load_act<T>(latent + ((size_t)s.clip * c0 + cc) * n_frames + s.lo + r0 + lane) : 0.f;
+    }
     if (skip) {
         // decode gate: the launches after this one read the table that the first workgroup of every window writes here
         if (skip[s.clip] != 0) { s.len = 0; s.n_int = 0; s.crop = 0; }
         if (blockIdx.x == 0 && blockIdx.z == 0 && threadIdx.x == 0) gated[blockIdx.y] = s;
     }
-    const int r0 = blockIdx.x * GATHER_TILE, cbase = blockIdx.z * GATHER_TILE;
     if (r0 >= s.len) return;
-    const int lane = threadIdx.x % GATHER_TILE, sub = threadIdx.x / GATHER_TILE;      // 4 rows of 64 threads
-    for (int cc = sub; cc < GATHER_TILE; cc += 256 / GATHER_TILE) {
-        const int c = cbase + cc, r = r0 + lane;
-        if (c < c0 && r < s.len) tile[cc][lane] = load_act<T>(latent + ((size_t)s.clip * c0 + c) * n_frames + s.lo + r);
-    }
+#pragma unroll
+    for (int u = 0; u < GATHER_C / RS; ++u) tile[sub + u * RS][lane] = v[u];
     __syncthreads();
-    const int c = cbase + lane;
     if (c >= c0) return;
-    const float al = alpha[c], ib = inv_beta[c];
-    for (int rr = sub; rr < GATHER_TILE; rr += 256 / GATHER_TILE) {
-        const int r = r0 + rr;
+#pragma unroll
+    for (int u = 0; u < GATHER_R / CS; ++u) {
+        const int rr = threadIdx.x / GATHER_C + u * CS, r = r0 + rr;
         if (r >= s.len) break;
-        const float raw = tile[lane][rr];
+        const float raw = tile[threadIdx.x % GATHER_C][rr];
         const size_t idx = ((size_t)s.row0 + r) * c0 + c;
         if (!xa) { x0[idx] = snake_precise(raw, al, ib); continue; }
-        const float v = snake_fast(raw, al, ib);
+        const float a = keep_f32(snake_fast(raw, al, ib));
         if (fmt == OP_F16) {
-            xa[idx] = __builtin_bit_cast(uint16_t, (_Float16)v);
+            xa[idx] = __builtin_bit_cast(uint16_t, (_Float16)a);
         } else {
-            const uint16_t hi = f32_to_bf16_bits(v);
+            const uint16_t hi = f32_to_bf16_bits(a);
             xa[idx] = hi;
-            if (fmt == OP_BF16X2) xa[lo_off + idx] = f32_to_bf16_bits(v - bf16_bits_to_f32(hi));
+            if (fmt == OP_BF16X2) xa[lo_off + idx] = f32_to_bf16_bits(a - bf16_bits_to_f32(hi));
         }
     }
 }
@@ -74,7 +83,7 @@ hipError_t launch_gather(const void* latent, float* x0, int c0, int n_frames, bo
                          const int* skip, Slot* gated)
 {
     if (!alpha || !inv_beta || (skip && !gated)) return hipErrorInvalidValue;
-    dim3 grid((unsigned)((max_len + GATHER_TILE - 1) / GATHER_TILE), (unsigned)n_slots, (unsigned)((c0 + GATHER_TILE - 1) / GATHER_TILE));
+    dim3 grid((unsigned)((max_len + GATHER_R - 1) / GATHER_R), (unsigned)n_slots, (unsigned)((c0 + GATHER_C - 1) / GATHER_C));
     if (bf16)
         hipLaunchKernelGGL(gather_kernel<uint16_t>, grid, dim3(256), 0, stream, (const uint16_t*)latent, x0, xa, xa_fmt, xa_lo_off, alpha, inv_beta, c0, n_frames, slots, skip, gated);
     else
