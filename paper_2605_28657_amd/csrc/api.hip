@@ -43,6 +43,7 @@ const long long g_env_small_tile_wgs = [] {
 
 struct ConvLayer {
     int cin = 0, cout = 0, ntaps = 0, dil = 1, stride = 0, variant = -1;
+    bool parts = false;                // K in parts, see kConvParts
     int down = 0;                      // s > 0: strided Conv1d(kernel 2s, stride s, padding s/2) of the encoder (ntaps = 2s)
     int in_fmt = OP_BF16;              // bf16 path: format of the activation operand (the weights are packed to match)
     bool generic = true;               // bf16 path: runs on launch_conv_bf16 (row order of its accumulator tiles)
@@ -553,13 +554,14 @@ demon_status run_pass(demon_vae* v, const Workspace& ws, const Plan* plan, const
                 const ConvLayer* C = T.consumer;
                 if (T.conv) {
                     ConvArgs a = conv_args(*T.conv, acur, other, nullptr);
+                    if (T.conv->parts) { a.y = nullptr; a.part = reinterpret_cast<float*>(at(other, 1, 2 * kConvParts * T.conv->cout)); }
                     if (C) { a.ya = at(aoth, resampled(r, *T.conv), T.conv->cout); a.out_alpha = C->in_alpha; a.out_inv_beta = C->in_inv_beta; a.out_fmt = C->in_fmt; }
                     HIP_TRY(launch_conv_bf16(a, T.conv->variant, gst), "resampling convolution");
                     if (C) std::swap(acur, aoth);
                     HIP_TRY(mark(last ? 1 : 2), "event");
                     std::swap(cur, other);
                     r = resampled(r, *T.conv);
-                    HIP_TRY(tap(cur, T.conv->cout), "debug tap");
+                    if (!T.conv->parts) HIP_TRY(tap(cur, T.conv->cout), "debug tap");     // else after the sampling step
                     continue;
                 }
                 const ResUnit& U = *T.unit;
@@ -634,11 +636,15 @@ demon_status run_pass(demon_vae* v, const Workspace& ws, const Plan* plan, const
     }
     if (enc) {
         // sampling step on the moments, trim and scatter into the caller's [clip, channel, frame] arrays
+        const bool parts = v->steps.back().conv->parts, tapped = parts && v->tap_layer == layer_id && v->tap_dst;
+        void* m = !parts ? cur : tapped ? ws.buf[3] : nullptr;
         for (int gi = 0; gi < n_groups; ++gi) {
             select_group(gi, stream);
-            HIP_TRY(launch_sample(at(cur, r, 2 * v->st.c0), bf, io.d_eps, io.d_moments, io.d_zout, bf, v->st.c0, n_frames, gs, gn,
+            const float* sums = parts ? reinterpret_cast<const float*>(at(cur, 1, 4 * kConvParts * v->st.c0)) : nullptr;
+            HIP_TRY(launch_sample(at(m, r, 2 * v->st.c0), sums, bf, io.d_eps, io.d_moments, io.d_zout, bf, v->st.c0, n_frames, gs, gn,
                                   plan->max_int, stream), "sampling step");
         }
+        if (parts) HIP_TRY(tap(m, 2 * v->st.c0), "debug tap");
         HIP_TRY(mark(1), "event");
         if (v->timing > 0) ++v->timed_calls;
         return DEMON_OK;
@@ -893,6 +899,10 @@ demon_status create_impl(const demon_vae_config* cfg, const float* host_weights,
             pend.push_back(p);
             rate /= s;
             per_frame = std::max(per_frame, rate * cn);
+            // The last one has the longest K (1024 channels, stride 10: 20480) and the fewest columns, one a frame: 12 workgroups for 75 frames and 26 us a
+            // launch in one piece, 9 in parts; 72 and 18 for 60 s.  In parts wherever its chunks divide (whole stages of two chunks), whatever the
+            // call's size, so that a value does not depend on that; up to 256 rows, and where the sums fit where the residual stream would go.
+            L.parts = bf && l == 0 && L.variant == 0 && cn <= 256 && c * (s / 2) % (128 * kConvParts) == 0 && 2ll * kConvParts * cn <= per_frame;
         }
         // Rows each layer must produce beyond a window's interior, walked from the moments back to the stem: a strided
         // conv writing margin m reads inputs up to m s + s/2 rows out, a k-tap conv of dilation d d(k-1)/2 rows further.

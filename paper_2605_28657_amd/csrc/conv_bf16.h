@@ -12,7 +12,8 @@ constexpr int MAXSPAN = 64;    // largest (max tap offset - min tap offset) the 
 enum { MODE_ACT = 0,   // bias + Snake, bf16 out only                     (dilated conv of a residual unit)
        MODE_RES = 1,   // bias + residual add in fp32, half out in place  (1x1 conv of a residual unit)
        MODE_UP  = 2,   // bias, polyphase scatter, half out               (ConvTranspose1d)
-       MODE_DOWN = 3 };// bias, half out; columns step two input rows     (strided Conv1d on merged rows)
+       MODE_DOWN = 3, // bias, half out; columns step two input rows     (strided Conv1d on merged rows)
+       MODE_PART = 4 };// MODE_DOWN with K in kConvParts parts: fp32 sums of each out, the bias in those of the first
 // MODE_RES, MODE_UP and MODE_DOWN may in addition emit the activated operand of the next layer: EMIT = 0 none, else the
 // operand format + 1 (1 bf16, 2 bf16 hi + lo, 3 half).  IN is the operand format of the input.
 
@@ -30,6 +31,7 @@ struct MfmaParams {
     int xcd_group;           // with mtiles_x: 1 = all row tiles of a column tile on one XCD, 0 = row tiles dealt over the XCDs
     unsigned w_bytes;
     long long in_lo_off, out_lo_off;     // element offsets of the lo planes
+    float* part;             // MODE_PART: [row][part][cout]
 };
 
 // kernels_bf16_stream.hip: weights streamed to registers, on weights packed for the 128 x 128 tile (variant 0).  `rows` is the

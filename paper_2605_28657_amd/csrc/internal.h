@@ -65,6 +65,7 @@ struct ConvArgs {
     void* ya = nullptr;   // activated copy of the output for the next layer (Snake out_alpha/out_inv_beta); fp32 path: fp32
     const void* res;      // residual (same layout as y) or nullptr; bf16 path: must equal y (in place)
     bool y_dead = false;  // bf16 path, with res: y is only read, the sum goes to ya alone
+    float* part = nullptr;// bf16 path, strided conv: fp32 sums of the parts of K, [row][kConvParts][cout], instead of y and ya
     const void* w;        // packed weights (layout private to each kernel family)
     const float* bias;    // [cout]
     const float* out_alpha;  const float* out_inv_beta;   // Snake applied before writing ya, or nullptr
@@ -169,9 +170,12 @@ hipError_t launch_gather(const void* latent, float* x0, int c0, int n_frames, bo
 hipError_t launch_stem(const float* wave, void* y, bool y_half, void* ya, int ya_fmt, const float* w, const float* bias,
                        const float* alpha, const float* inv_beta, int ch, int C, int k, int S, int n_frames, int margin,
                        const Slot* slots, int n_slots, int max_len, int max_int, hipStream_t stream);
+// the parts that K of the encoder's last convolution is cut into, each summed by workgroups of its own
+constexpr int kConvParts = 8;
 // encoder: moments of the windows' interior frames -> moments_out fp32 [n_clips, 2 C0, n_frames] and the sampled latent
 // [n_clips, C0, n_frames] (bf16 for the half path, fp32 otherwise); eps fp32 [n_clips, C0, n_frames] or nullptr (z = mean)
-hipError_t launch_sample(const void* m, bool m_half, const float* eps, float* moments_out, void* latent_out, bool latent_bf16,
+// with `parts` (half path) the moments are the sums of the parts there, rounded to half; `m`, if given, takes them as the conv would have left them
+hipError_t launch_sample(void* m, const float* parts, bool m_half, const float* eps, float* moments_out, void* latent_out, bool latent_bf16,
                          int C0, int n_frames, const Slot* slots, int n_slots, int max_int, hipStream_t stream);
 // head: Snake -> Conv1d(k, cin -> oc) -> tanh; output planar fp32 [oc, total_rows]
 // `fast` selects the hardware-sine Snake (alpha given in revolutions) used by the bf16 path.

@@ -514,14 +514,14 @@ hipError_t launch_conv_bf16(const ConvArgs& a, int variant, hipStream_t stream)
     p.slots = a.slots;
     p.r_in = r_in; p.cin = cin; p.cout = a.cout; p.ntaps = ntaps; p.stride = a.stride;
     p.nchunks = cin / v.KC; p.margin = a.margin;
-    p.in_lo_off = a.in_lo_off; p.out_lo_off = a.out_lo_off;
+    p.in_lo_off = a.in_lo_off; p.out_lo_off = a.out_lo_off; p.part = a.part;
     const size_t wb = (size_t)M * ntaps * cin * 2;
     if (wb > 0xffffffffull) return hipErrorInvalidValue;
     // room for the slack in the descriptor.  (Saturated in the kernel, the sum is a vector instruction, the descriptor no longer
     // scalar, and every load a loop over its lanes: the 1024-channel dilated conv of a 60 s clip 206 -> 305 us.)
     p.w_bytes = (unsigned)std::min<size_t>(wb, 0xffffffffu - kWeightSlack);
     int mode;
-    if (a.down > 0) { p.tap0 = -1; p.tap_step = 1; mode = MODE_DOWN; }
+    if (a.down > 0) { p.tap0 = -1; p.tap_step = 1; mode = a.part ? MODE_PART : MODE_DOWN; }
     else if (a.stride > 0) { p.tap0 = 0; p.tap_step = -1; mode = MODE_UP; }
     else { p.tap0 = -((a.ntaps - 1) / 2) * a.dil; p.tap_step = a.dil; mode = a.res ? MODE_RES : MODE_ACT; }
     if (a.in_fmt < OP_BF16 || a.in_fmt > OP_F16 || a.out_fmt < OP_BF16 || a.out_fmt > OP_F16) return hipErrorInvalidValue;
@@ -531,13 +531,14 @@ hipError_t launch_conv_bf16(const ConvArgs& a, int variant, hipStream_t stream)
     if (span > (mode == MODE_ACT ? MAXSPAN : 8) || M % v.MT != 0 || cin % v.KC != 0 || a.cout % 4 != 0 || a.margin < 0) return hipErrorInvalidValue;
     if (mode == MODE_ACT && emit == 0) return hipErrorInvalidValue;
     if (emit > 0 && (!a.out_alpha || !a.out_inv_beta)) return hipErrorInvalidValue;
-    if (mode != MODE_ACT && !a.y) return hipErrorInvalidValue;
+    if (mode != MODE_ACT && mode != MODE_PART && !a.y) return hipErrorInvalidValue;
+    if (a.part && (mode != MODE_PART || variant != 0 || emit != 0)) return hipErrorInvalidValue;
     if (a.y_dead && (mode != MODE_RES || emit == 0)) return hipErrorInvalidValue;
     if (mode == MODE_RES && a.res != a.y) return hipErrorInvalidValue;            // the residual add is in place
     // one window's activation plane must fit a 32-bit byte offset (buffer descriptors)
     const long long r_out = a.down > 0 ? (long long)a.r_in / a.down : (long long)a.r_in * (a.stride > 0 ? a.stride : 1);
     const long long max_in_bytes = (long long)a.max_len * a.r_in * a.cin * 2;
-    const long long max_out_bytes = (long long)a.max_len * r_out * a.cout * (long long)sizeof(hres_t);
+    const long long max_out_bytes = (long long)a.max_len * r_out * a.cout * (a.part ? kConvParts * (long long)sizeof(float) : (long long)sizeof(hres_t));
     if (max_in_bytes > 0xf0000000ll || max_out_bytes > 0xf0000000ll) return hipErrorInvalidValue;
     // most columns any window needs: interior plus margins, never more than the longest window
     long long out_rows = std::min((long long)a.max_int * r_out + 2ll * a.margin, (long long)a.max_len * r_out);

@@ -14,7 +14,9 @@
 // large tile gives every wave 32 rows x 128 columns (8 KB of weights and 32 KB of LDS reads per 288 cycles of MFMAs).
 // Measured, LDS-staged tile -> here: 1024-channel dilated conv 46 -> 9.6 us (200 columns), 47 -> 17 (830), 258 -> 214 (17000);
 // 512 channels 34 -> 21 (4700), 60 s clip 297 (a 128 x 256 tile) -> 266 (1.24 PFLOP/s); 1x1 conv of 1024 channels 13 -> 5 (200), 14 -> 7.6 (830);
-// strided conv 1024 -> 128, stride 10: 146 -> 25 (75 columns).
+// strided conv 1024 -> 128, stride 10: 146 -> 25 (75 columns).  That one, 640 k-steps in a workgroup and a column a frame, lasts as long as one
+// walk at any size: with K in eight parts (MODE_PART), which the sampling step sums, 26 -> 9 us at 75 columns and 72 -> 18 at 1500, with an event after the
+// launch; encode of 75 frames 509 -> 495, of 60 s 5089 -> 5080.  Eight because an XCD then holds a part: its L2 reads an eighth of weights and activations.
 // Every tile adds in the same order (chunk, tap, k-step, for two operand planes hi before lo), so a value does not depend on the tile.
 #include <algorithm>
 #include <type_traits>
@@ -39,7 +41,8 @@ __global__ __launch_bounds__(64 * WM * WN, MODE == MODE_UP && TM * TN == 16 && I
 {
     fp16_saturate_on();
     constexpr int NTH = 64 * WM * WN, MT = 16 * TM * WM, NT = 16 * TN * WN;
-    constexpr int XS = (MODE == MODE_DOWN) ? 2 : 1;        // input rows per GEMM column
+    constexpr bool DOWN = MODE == MODE_DOWN || MODE == MODE_PART;
+    constexpr int XS = DOWN ? 2 : 1;                       // input rows per GEMM column
     constexpr int XROWS = XS * (NT - 1) + 1 + SPAN;
     // channels of a stage; padded LDS row: 16-byte reads of 16 rows x 4 neighbouring pieces are free of bank conflicts (5.3 cycles
     // a wave, else 8 or more) when the rows lie 2 (mod 4) pieces apart
@@ -63,7 +66,7 @@ __global__ __launch_bounds__(64 * WM * WN, MODE == MODE_UP && TM * TN == 16 && I
 
     const Slot s = p.slots[blockIdx.y];
     const int nrows = s.len * p.r_in;
-    const int r_out = (MODE == MODE_UP) ? p.r_in * p.stride : (MODE == MODE_DOWN) ? p.r_in / 2 : p.r_in;
+    const int r_out = (MODE == MODE_UP) ? p.r_in * p.stride : DOWN ? p.r_in / 2 : p.r_in;
     const int nrows_o = s.len * r_out;
     const int out_lo = max(0, s.crop * r_out - p.margin);
     const int out_hi = min(nrows_o, (s.crop + s.n_int) * r_out + p.margin);
@@ -72,9 +75,10 @@ __global__ __launch_bounds__(64 * WM * WN, MODE == MODE_UP && TM * TN == 16 && I
     const int ncols = (MODE == MODE_UP) ? (out_hi - 1 + p.stride / 2) / p.stride + 1 : out_hi;
     // Workgroups are dealt to the 8 XCDs round-robin by linear id (gridDim.x is a multiple of 8), each with its own L2.  XCD
     // (x % xm, x / xm) takes every xm-th panel of 128 rows and every xn-th column tile (rotated by the window): it reads
-    // 1/xm of the weights and 1/xn of the activations.
+    // 1/xm of the weights and 1/xn of the activations.  K in parts: an XCD takes one of the eight parts, and reads an eighth of both.
     constexpr int SUB = 128 / MT;                           // row tiles of a panel
-    const int xcd = (int)((blockIdx.x + blockIdx.y) & 7u), q8 = (int)(blockIdx.x >> 3), mi8 = q8 % sg.mper;
+    const int part = MODE == MODE_PART ? (int)(blockIdx.x & 7u) : 0;
+    const int xcd = MODE == MODE_PART ? 0 : (int)((blockIdx.x + blockIdx.y) & 7u), q8 = (int)(blockIdx.x >> 3), mi8 = q8 % sg.mper;
     const int panel = xcd % sg.xm + sg.xm * (mi8 / SUB), ntile = xcd / sg.xm + sg.xn * (q8 / sg.mper);
     const int n0 = col_lo + ntile * NT;
     if (n0 >= ncols) return;
@@ -114,10 +118,10 @@ __global__ __launch_bounds__(64 * WM * WN, MODE == MODE_UP && TM * TN == 16 && I
     // ---- activations
     const unsigned x_voff = ((unsigned)((XS * n0 + minoff + xr0) * p.cin) + seg * 8u) * 2u;    // may wrap "negative": out of range
     const unsigned x_row_step = (unsigned)(RPP * p.cin) * 2u;
-    const int nstages = p.nchunks / SC;
+    const int nstages = MODE == MODE_PART ? p.nchunks / kConvParts / SC : p.nchunks / SC, stage0 = part * nstages;
     u32x4 rx[X_ITERS][NP];
     auto load_x = [&](int stage) __attribute__((always_inline)) {
-        const unsigned base = stage < nstages ? x_voff + (unsigned)(stage * KX) * 2u : 0xf8000000u;      // past the last stage: out of range
+        const unsigned base = stage < nstages ? x_voff + (unsigned)((stage0 + stage) * KX) * 2u : 0xf8000000u;      // past the last stage: out of range
 #pragma unroll
         for (int it = 0; it < X_ITERS; ++it) {
             // any number of taps: rows that no tap reads are out of range too
@@ -138,10 +142,10 @@ __global__ __launch_bounds__(64 * WM * WN, MODE == MODE_UP && TM * TN == 16 && I
     // every request of the prologue in the order of use
     load_x(0);
 #pragma unroll
-    for (int f = 0; f < RS; ++f) load_a(0, f, ANY ? ahead_voff(w_voff, more_panels || f / 2 < nblocks) : w_voff);
+    for (int f = 0; f < RS; ++f) load_a(stage0 * (F / 2), f, ANY ? ahead_voff(w_voff, more_panels || f / 2 < nblocks) : w_voff);
     float bv[TM];
 #pragma unroll
-    for (int mi = 0; mi < TM; ++mi) bv[mi] = p.bias[(MODE == MODE_UP) ? (m0 + lane_row(mi)) % p.cout : m0 + lane_row(mi)];
+    for (int mi = 0; mi < TM; ++mi) bv[mi] = part > 0 ? 0.f : p.bias[(MODE == MODE_UP) ? (m0 + lane_row(mi)) % p.cout : m0 + lane_row(mi)];
 
     // ---- geometry of the epilogue: piece (row, 8 channels) of the output tile; residual values requested ahead where the
     // registers allow it
@@ -157,7 +161,7 @@ __global__ __launch_bounds__(64 * WM * WN, MODE == MODE_UP && TM * TN == 16 && I
         return (MODE == MODE_UP ? (unsigned)((n * p.stride - p.stride / 2) * p.cout + ec) : (unsigned)(n * p.cout + ec)) * 2u;
     };
     const unsigned out_bytes = (unsigned)out_hi * p.cout * 2u;
-    const __amdgpu_buffer_rsrc_t rs_y = make_rsrc(MODE == MODE_ACT ? nullptr : p.y + rowbase_o * p.cout, MODE == MODE_ACT ? 0u : out_bytes);
+    const __amdgpu_buffer_rsrc_t rs_y = make_rsrc(MODE == MODE_ACT || MODE == MODE_PART ? nullptr : p.y + rowbase_o * p.cout, MODE == MODE_ACT || MODE == MODE_PART ? 0u : out_bytes);
     u32x4 resv[MODE == MODE_RES ? EP : 1][MODE == MODE_RES ? E_ITERS : 1];
     auto load_res = [&]() __attribute__((always_inline)) {
 #pragma unroll
@@ -281,7 +285,7 @@ __global__ __launch_bounds__(64 * WM * WN, MODE == MODE_UP && TM * TN == 16 && I
                     }
                     __builtin_amdgcn_sched_barrier(0);
                 }
-                if (!LAST || f + RS < F) load_a(stage * (F / 2), f + RS, w_voff);
+                if (!LAST || f + RS < F) load_a((stage0 + stage) * (F / 2), f + RS, w_voff);
                 __builtin_amdgcn_sched_barrier(0);
             }
             if (!LAST) store_x((stage + 1) & 1);
@@ -308,6 +312,8 @@ __global__ __launch_bounds__(64 * WM * WN, MODE == MODE_UP && TM * TN == 16 && I
     const __amdgpu_buffer_rsrc_t rs_a = make_rsrc(p.ya + rowbase_o * p.cout, emit > 0 ? out_bytes : 0u);
     const __amdgpu_buffer_rsrc_t rs_ys = MODE == MODE_RES ? make_rsrc(p.y + rowbase_o * p.cout, p.y_dead ? 0u : out_bytes) : rs_y;
     const __amdgpu_buffer_rsrc_t rs_al = make_rsrc(p.ya + p.out_lo_off + rowbase_o * p.cout, emit == 2 ? out_bytes : 0u);
+    // K in parts: this part's sums, rows kConvParts x cout apart; nothing past the last row's
+    const __amdgpu_buffer_rsrc_t rs_p = make_rsrc(p.part + (rowbase_o * kConvParts + part) * p.cout, MODE == MODE_PART ? ((unsigned)(out_hi - 1) * kConvParts + 1u) * p.cout * 4u : 0u);
     float* os = reinterpret_cast<float*>(smem);
 #pragma unroll
     for (int ep = 0; ep < EP; ++ep) {
@@ -327,6 +333,12 @@ __global__ __launch_bounds__(64 * WM * WN, MODE == MODE_UP && TM * TN == 16 && I
 #pragma unroll
             for (int e = 0; e < 8; ++e) v[e] = src[e];
             const unsigned off = eoff(ep, it);
+            if constexpr (MODE == MODE_PART) {
+                const unsigned at = (off - ec * 2u) * (kConvParts * 2u) + ec * 4u;
+                __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, f32x4{v[0], v[1], v[2], v[3]}), rs_p, at, 0, 0);
+                __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, f32x4{v[4], v[5], v[6], v[7]}), rs_p, at + 16u, 0, 0);
+                continue;
+            }
             if (MODE == MODE_RES) {
                 const f16x8 r = __builtin_bit_cast(f16x8, resv[ep][it]);
 #pragma unroll
@@ -568,6 +580,8 @@ hipError_t launch_tile(const MfmaParams& p, const StreamGrid& sg, int mode, int 
         if (p.nchunks == 1) { DEMON_CASE(4, 1, 3, MODE_DOWN, OP_BF16, 1) DEMON_CASE(4, 1, 3, MODE_DOWN, OP_F16, 1) }
         else if (p.nchunks % SD == 0) { DEMON_CASE(4, SD, 3, MODE_DOWN, OP_BF16, 2) DEMON_CASE(4, SD, 3, MODE_DOWN, OP_F16, 2) }
         else { DEMON_CASE(4, 1, 3, MODE_DOWN, OP_BF16, 2) DEMON_CASE(4, 1, 3, MODE_DOWN, OP_F16, 2) }
+    } else if (mode == MODE_PART) {
+        DEMON_CASE(4, SD, 3, MODE_PART, OP_BF16, 2) DEMON_CASE(4, SD, 3, MODE_PART, OP_F16, 2)
     } else {
         if (p.nchunks == 1) { DEMON_CASE(2, 1, 1, MODE_UP, OP_BF16, 1) DEMON_CASE(2, 1, 1, MODE_UP, OP_F16, 1) }
         else if (p.nchunks % SU == 0) { DEMON_CASE(2, SU, 1, MODE_UP, OP_BF16, 2) DEMON_CASE(2, SU, 1, MODE_UP, OP_F16, 2) }
@@ -587,6 +601,7 @@ bool stream_conv_ok(const MfmaParams& p, int mode, int in_fmt)
         case MODE_ACT: return (p.ntaps - 1) * p.tap_step <= MAXSPAN && p.nchunks % 2 == 0 && in_fmt != OP_BF16X2;
         case MODE_RES: return p.ntaps == 1 && p.nchunks % 2 == 0;
         case MODE_DOWN: return p.ntaps == 4 && in_fmt != OP_BF16X2;
+        case MODE_PART: return p.ntaps == 4 && in_fmt != OP_BF16X2 && p.part && p.nchunks % (2 * kConvParts) == 0;
         default: return p.ntaps == 2;
     }
 }
@@ -633,7 +648,7 @@ hipError_t launch_conv_stream(MfmaParams p, int mode, int in_fmt, int emit, int 
     int best = 5;
     double cheapest = 0;
     for (int t = large ? (down && max_small > 0 ? 4 : 5) : 0; t < (tall_ok ? 7 : 6); ++t) {
-        const long long wgs = (ncols + kTiles[t].nt - 1) / kTiles[t].nt * (rows / kTiles[t].mt) * call_slots;
+        const long long wgs = (ncols + kTiles[t].nt - 1) / kTiles[t].nt * (rows / kTiles[t].mt) * call_slots * (mode == MODE_PART ? kConvParts : 1);
         if (t == 6 && wgs <= 512) continue;
         const double cost = wgs <= 256 ? kTiles[t].alone : wgs <= 1024 ? (double)((wgs + 255) / 256) * kTiles[t].shared : (wgs / 256.0 + 0.5) * kTiles[t].shared;
         if (cheapest == 0 || cost < cheapest) { cheapest = cost; best = t; }
@@ -646,16 +661,17 @@ hipError_t launch_conv_stream(MfmaParams p, int mode, int in_fmt, int emit, int 
     const double w = (double)p.w_bytes, x = (double)ncols * n_slots * (mode == MODE_DOWN ? 2 : 1) * p.cin * 2.0;
     double least = 0;
     sg.xm = 0;
-    for (int xm = 1; xm <= 8; xm *= 2) {
+    for (int xm = 1; xm <= (mode == MODE_PART ? 1 : 8); xm *= 2) {
         if (panels % xm != 0) continue;
         const double cost = w / xm + x * xm / 8;
         if (sg.xm == 0 || cost < least) { sg.xm = xm; least = cost; }
     }
-    sg.xn = 8 / sg.xm;
+    sg.xn = mode == MODE_PART ? 1 : 8 / sg.xm;
     sg.mper = panels / sg.xm * std::max(1, 128 / mt);
     const long long ntiles = ((ncols + nt - 1) / nt + sg.xn - 1) / sg.xn * sg.xn;
-    if (ntiles * (rows / mt) > 0x7fffffffll) return hipErrorInvalidValue;
-    const dim3 grid((unsigned)(ntiles * (rows / mt)), (unsigned)n_slots);
+    const long long wgs_x = ntiles * (rows / mt) * (mode == MODE_PART ? kConvParts : 1);
+    if (wgs_x > 0x7fffffffll) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)wgs_x, (unsigned)n_slots);
     if (tall) {
 #define DEMON_TALL(SPAN_, IN_) if (in_fmt == IN_ && 6 * p.tap_step <= SPAN_) { \
         hipLaunchKernelGGL((conv_tall_kernel<SPAN_, IN_>), grid, dim3(256), 0, stream, p, sg, emit == 3); \

@@ -306,19 +306,36 @@ hipError_t launch_stem(const float* wave, void* y, bool y_half, void* ya, int ya
 // interior frames, write them to moments_out [clip, 2 C0, n_frames] (fp32) and the sampled latent
 // z = mean + exp(logvar / 2) eps (the sampling step on the output moments of Table III; eps drawn by the caller, z = mean
 // without eps) to latent_out [clip, C0, n_frames] in the path's latent type.  Either output may be absent.
-template <typename TM, typename TZ>
-__global__ __launch_bounds__(256) void sample_kernel(const TM* __restrict__ m, const float* __restrict__ eps,
+// PARTS: the moments are the sums of the parts that the last convolution's K was cut into (fp32, one rounding to half).
+template <typename TM, typename TZ, bool PARTS>
+__global__ __launch_bounds__(256) void sample_kernel(TM* __restrict__ m, const float* __restrict__ parts, const float* __restrict__ eps,
                                                      float* __restrict__ moments_out, TZ* __restrict__ latent_out,
                                                      int C0, int n_frames, const Slot* __restrict__ slots)
 {
+    if (PARTS) fp16_saturate_on();
     const Slot s = slots[blockIdx.y];
     const int e = blockIdx.x * 256 + threadIdx.x;
     if (e >= s.n_int * C0) return;
     const int fi = e / C0, c = e - fi * C0;
     const size_t row = (size_t)s.row0 + s.crop + fi;
     const int f = s.begin + fi;
-    const float mean = load_act<TM>(m + row * (2 * C0) + c);
-    const float lv = load_act<TM>(m + row * (2 * C0) + C0 + c);
+    float mean, lv;
+    if constexpr (PARTS) {
+        float a[2][kConvParts];
+#pragma unroll
+        for (int k = 0; k < kConvParts; ++k)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) a[h][k] = parts[(row * kConvParts + k) * (2 * C0) + h * C0 + c];
+        mean = a[0][0]; lv = a[1][0];
+#pragma unroll
+        for (int k = 1; k < kConvParts; ++k) { mean += a[0][k]; lv += a[1][k]; }
+        const TM hm = (TM)keep_f32(mean), hl = (TM)keep_f32(lv);
+        mean = (float)hm; lv = (float)hl;
+        if (m) { m[row * (2 * C0) + c] = hm; m[row * (2 * C0) + C0 + c] = hl; }
+    } else {
+        mean = load_act<TM>(m + row * (2 * C0) + c);
+        lv = load_act<TM>(m + row * (2 * C0) + C0 + c);
+    }
     if (moments_out) {
         moments_out[((size_t)s.clip * 2 * C0 + c) * n_frames + f] = mean;
         moments_out[((size_t)s.clip * 2 * C0 + C0 + c) * n_frames + f] = lv;
@@ -331,16 +348,17 @@ __global__ __launch_bounds__(256) void sample_kernel(const TM* __restrict__ m, c
     }
 }
 
-hipError_t launch_sample(const void* m, bool m_half, const float* eps, float* moments_out, void* latent_out, bool latent_bf16,
+hipError_t launch_sample(void* m, const float* parts, bool m_half, const float* eps, float* moments_out, void* latent_out, bool latent_bf16,
                          int C0, int n_frames, const Slot* slots, int n_slots, int max_int, hipStream_t stream)
 {
+    if (m_half != latent_bf16 || (parts ? !m_half : !m)) return hipErrorInvalidValue;
     dim3 grid((unsigned)(((size_t)max_int * C0 + 255) / 256), (unsigned)n_slots);
-    if (m_half && latent_bf16)
-        hipLaunchKernelGGL((sample_kernel<_Float16, uint16_t>), grid, dim3(256), 0, stream, (const _Float16*)m, eps, moments_out, (uint16_t*)latent_out, C0, n_frames, slots);
-    else if (!m_half && !latent_bf16)
-        hipLaunchKernelGGL((sample_kernel<float, float>), grid, dim3(256), 0, stream, (const float*)m, eps, moments_out, (float*)latent_out, C0, n_frames, slots);
-    else
-        return hipErrorInvalidValue;
+#define DEMON_SAMPLE(TM_, TZ_, PARTS_) hipLaunchKernelGGL((sample_kernel<TM_, TZ_, PARTS_>), grid, dim3(256), 0, stream, (TM_*)m, parts, eps, \
+                                                          moments_out, (TZ_*)latent_out, C0, n_frames, slots)
+    if (parts) DEMON_SAMPLE(_Float16, uint16_t, true);
+    else if (m_half) DEMON_SAMPLE(_Float16, uint16_t, false);
+    else DEMON_SAMPLE(float, float, false);
+#undef DEMON_SAMPLE
     return hipGetLastError();
 }
 
