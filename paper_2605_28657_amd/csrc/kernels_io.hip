@@ -367,12 +367,14 @@ hipError_t launch_sample(void* m, const float* parts, bool m_half, const float* 
 // the window read as zero (the conv's zero padding at a clip edge); Snake is applied while staging.
 //
 // Fast kernel (OC output channels, K taps as template arguments): a workgroup owns 256 SPT
-// consecutive samples, each thread SPT of them.  Channels go through LDS in chunks of 16, transposed to
+// consecutive samples (SPT = 1: 128), each thread SPT of them.  Channels go through LDS in chunks of 16, transposed to
 // [channel][row] so that a thread's 4 + K - 1 input rows are consecutive words (three 16-byte reads per
 // channel for K = 7) and feed 4*K*OC FMAs; the weights are wave-uniform (scalar loads).  The row
 // length LDR = 4 mod 16 keeps both the transposing stores and the reads free of bank conflicts.  SPT = 4 reads
-// the fewest LDS words per sample; a launch that would leave CUs idle that way (a few windows) takes SPT = 1, which adds
-// in the same order.
+// the fewest LDS words per sample; a launch that would leave CUs idle that way (a few windows) takes SPT = 1, a thread per sample and
+// output channel, which adds in the same order.  Such a launch is bound by one workgroup's chain, mostly the precise sines of its rows: 128
+// samples a workgroup where it was 256, and a chunk's rows requested together and a chunk ahead where each was waited for in turn.  fp32, 2 s of the x32
+// stack 14.8 -> 10.8 us with an event after the launch (requests alone 13.5), the call 100.4 -> 97.2; 3 s window of the x1920 stack 33.8 -> 30.9.
 constexpr int HEAD_KC = 16;
 constexpr int HEAD_MAXK = 15;
 constexpr int HEAD_MAXOC = 8;
@@ -383,7 +385,9 @@ __global__ __launch_bounds__(256) void head_fast_kernel(const TX* __restrict__ x
                                                         const float* __restrict__ alpha, const float* __restrict__ inv_beta,
                                                         int cin, int r, const Slot* __restrict__ slots)
 {
-    constexpr int HEAD_NT = 256 * HEAD_SPT;
+    constexpr bool SPLIT = HEAD_SPT == 1;                   // a thread per sample and output channel
+    constexpr int HEAD_NT = SPLIT ? 256 / OC : 256 * HEAD_SPT, NO = SPLIT ? 1 : OC;
+    static_assert(HEAD_NT % 64 == 0, "an output channel per wave");
     constexpr int HEAD_LDR = HEAD_NT + 20;                  // >= HEAD_NT + HEAD_MAXK - 1, = 4 (mod 16)
     __shared__ __attribute__((aligned(16))) float xs[HEAD_KC * HEAD_LDR];
     constexpr int HALF = (K - 1) / 2;
@@ -398,39 +402,50 @@ __global__ __launch_bounds__(256) void head_fast_kernel(const TX* __restrict__ x
     const int tid = threadIdx.x;
     const int q = tid & 3, r0 = tid >> 2;                   // staging: 4 lanes per row, 4 channels each
 
-    float acc[HEAD_SPT][OC];
+    const int sample = SPLIT ? tid % HEAD_NT : HEAD_SPT * tid, o0 = SPLIT ? __builtin_amdgcn_readfirstlane(tid / HEAD_NT) : 0;
+    float acc[HEAD_SPT][NO];
 #pragma unroll
     for (int i = 0; i < HEAD_SPT; ++i)
 #pragma unroll
-        for (int o = 0; o < OC; ++o) acc[i][o] = 0.f;
+        for (int o = 0; o < NO; ++o) acc[i][o] = 0.f;
 
+    // every row of a chunk requested before the first is waited for, the next chunk's before this one's sums; rows outside the
+    // window are another's (clamped) and become zeros
+    constexpr int RP = (XR + 63) / 64;
+    using raw_t = std::conditional_t<sizeof(TX) == 4, f32x4, f16x4>;
+    raw_t raw[RP];
+    f32x4 al, ib;
+    auto request = [&](int c0) __attribute__((always_inline)) {
+        al = *reinterpret_cast<const f32x4*>(alpha + c0 + 4 * q);
+        ib = *reinterpret_cast<const f32x4*>(inv_beta + c0 + 4 * q);
+#pragma unroll
+        for (int it = 0; it < RP; ++it) {
+            const long long n = min(max(n0 - HALF + r0 + 64 * it, 0ll), nrows - 1);
+            raw[it] = *reinterpret_cast<const raw_t*>(x + (size_t)(rowbase + n) * cin + c0 + 4 * q);
+        }
+    };
+    request(0);
     for (int c0 = 0; c0 < cin; c0 += HEAD_KC) {
-        const float4 al = *reinterpret_cast<const float4*>(alpha + c0 + 4 * q);
-        const float4 ib = *reinterpret_cast<const float4*>(inv_beta + c0 + 4 * q);
         __syncthreads();
-        for (int row = r0; row < XR; row += 64) {
+#pragma unroll
+        for (int it = 0; it < RP; ++it) {
+            const int row = r0 + 64 * it;
             const long long n = n0 - HALF + row;
-            float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (n >= 0 && n < nrows) {
-                const TX* src = x + (size_t)(rowbase + n) * cin + c0 + 4 * q;
-                if (sizeof(TX) == 4) {
-                    v = *reinterpret_cast<const float4*>(src);
-                } else {
-                    const f16x4 hv = *reinterpret_cast<const f16x4*>(src);
-                    v = make_float4((float)hv[0], (float)hv[1], (float)hv[2], (float)hv[3]);
-                }
-                if (FAST) {
-                    v.x = snake_fast(v.x, al.x, ib.x); v.y = snake_fast(v.y, al.y, ib.y);
-                    v.z = snake_fast(v.z, al.z, ib.z); v.w = snake_fast(v.w, al.w, ib.w);
-                } else {
-                    v.x = snake_precise(v.x, al.x, ib.x); v.y = snake_precise(v.y, al.y, ib.y);
-                    v.z = snake_precise(v.z, al.z, ib.z); v.w = snake_precise(v.w, al.w, ib.w);
-                }
+            if (row >= XR) break;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) xs[(4 * q + e) * HEAD_LDR + row] = n < 0 || n >= nrows ? 0.f : (float)raw[it][e];
+        }
+        const f32x4 a = al, b = ib;
+        if (c0 + HEAD_KC < cin) request(c0 + HEAD_KC);
+        // Snake in place, each thread on what it wrote; one copy of the sine's code
+#pragma unroll 1
+        for (int row = r0; row < XR; row += 64) {
+            if (n0 - HALF + row < 0 || n0 - HALF + row >= nrows) continue;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                float* at = &xs[(4 * q + e) * HEAD_LDR + row];
+                *at = FAST ? snake_fast(*at, a[e], b[e]) : snake_precise(*at, a[e], b[e]);
             }
-            xs[(4 * q + 0) * HEAD_LDR + row] = v.x;
-            xs[(4 * q + 1) * HEAD_LDR + row] = v.y;
-            xs[(4 * q + 2) * HEAD_LDR + row] = v.z;
-            xs[(4 * q + 3) * HEAD_LDR + row] = v.w;
         }
         __syncthreads();
 #pragma unroll 4
@@ -438,7 +453,7 @@ __global__ __launch_bounds__(256) void head_fast_kernel(const TX* __restrict__ x
             float xv[NV * 4];
 #pragma unroll
             for (int i = 0; i < NV; ++i) {
-                const float* src = &xs[c * HEAD_LDR + HEAD_SPT * tid + 4 * i];
+                const float* src = &xs[c * HEAD_LDR + sample + 4 * i];
                 if constexpr (HEAD_SPT == 4) {
                     const float4 t4 = *reinterpret_cast<const float4*>(src);
                     xv[4 * i] = t4.x; xv[4 * i + 1] = t4.y; xv[4 * i + 2] = t4.z; xv[4 * i + 3] = t4.w;
@@ -450,18 +465,18 @@ __global__ __launch_bounds__(256) void head_fast_kernel(const TX* __restrict__ x
 #pragma unroll
             for (int t = 0; t < K; ++t)
 #pragma unroll
-                for (int o = 0; o < OC; ++o) {
-                    const float wv = w[((size_t)t * cin + c0 + c) * OC + o];
+                for (int o = 0; o < NO; ++o) {
+                    const float wv = w[((size_t)t * cin + c0 + c) * OC + o0 + o];
 #pragma unroll
                     for (int i = 0; i < HEAD_SPT; ++i) acc[i][o] = fmaf(wv, xv[i + t], acc[i][o]);
                 }
         }
     }
-    const long long n = n0 + HEAD_SPT * tid, origin = head_origin(out, s, OC, r);
+    const long long n = n0 + sample, origin = head_origin(out, s, OC, r);
 #pragma unroll
-    for (int o = 0; o < OC; ++o) {
-        const float b = bias[o];
-        float* dst = out.y + o * out.plane + origin + n;
+    for (int o = 0; o < NO; ++o) {
+        const float b = bias[o0 + o];
+        float* dst = out.y + (o0 + o) * out.plane + origin + n;
         if (HEAD_SPT == 4 && n + HEAD_SPT <= hi && vec) {
             *reinterpret_cast<float4*>(dst) = make_float4(tanhf(acc[0][o] + b), tanhf(acc[HEAD_SPT / 4][o] + b),
                                                           tanhf(acc[HEAD_SPT / 2][o] + b), tanhf(acc[HEAD_SPT - 1][o] + b));
@@ -700,7 +715,7 @@ hipError_t launch_head(const void* x, bool x_half, const HeadOut& out, const flo
     const long long rows = (long long)max_int * r;
     if (oc == 2 && k == 7 && cin % HEAD_KC == 0) {
         const bool few = (rows + 1023) / 1024 * n_slots < 512;        // two 1024-sample workgroups per CU
-        const int nt = few ? 256 : 1024;
+        const int nt = few ? 128 : 1024;
         // 16-byte stores: rows of a window start at multiples of r in a plane, planes (and clips) are multiples of r apart
         const bool vec = r % 4 == 0 && reinterpret_cast<uintptr_t>(out.y) % 16 == 0;
         dim3 grid((unsigned)((rows + nt - 1) / nt), (unsigned)n_slots);
