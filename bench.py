@@ -182,7 +182,7 @@ def main():
     args = ap.parse_args()
     if args.gpus != 1:
         sys.exit("bench.py: this build runs on one GPU; --gpus N with N > 1 is not supported "
-                 "(windows and clips shard without communication, see DESIGN.md)")
+                 "(windows and clips shard without communication)")
 
     import numpy as np
     import torch
@@ -452,7 +452,7 @@ def main():
 
     if not args.no_cpu_baseline:
         # The oracle (fp32 build, as it stands) beside the GPU, on a bounded sample of this workload's own inputs: the
-        # whole 10 s clip of the same decoder (configs[1]) on all host cores, and a 2 s clip on one thread.
+        # whole 10 s clip of the same decoder on all host cores, and a 2 s clip on one thread.
         import oracle
         os.environ.pop("OMP_DYNAMIC", None)
         wl1 = di.WORKLOADS["full_10s_bf16"] if spec is di.FULL else wl

@@ -48,7 +48,7 @@ class DecoderSpec:
         return s
 
 
-# configs[0]: tiny fp32 decoder (x32); configs[1..4]: 48 kHz stereo decoder (x1920).
+# The tiny fp32 decoder (x32) and the 48 kHz stereo decoder (x1920).
 TINY = DecoderSpec(latent_channels=16, strides=(4, 4, 2), widths=(128, 64, 32))
 FULL = DecoderSpec(latent_channels=64, strides=(10, 6, 4, 4, 2), widths=(1024, 512, 256, 128, 64))
 
