@@ -347,6 +347,12 @@ DEMON_API demon_status demon_vae_crossfade(const float* d_prev_tail, long long p
 DEMON_API demon_status demon_vae_debug_tap(demon_vae* vae, int layer, float* d_dst, size_t capacity);
 
 /*
+ * Test aid (host only): the windows that the last decode or encode call on this handle computed, their extended frames, and
+ * whether its layers ran as one group of windows or as two on two streams.  0 of each before the first call.
+ */
+DEMON_API demon_status demon_vae_debug_last_grid(const demon_vae* vae, int* n_windows, long long* extended_frames, int* n_groups);
+
+/*
  * Benchmark instrumentation.  level 0 = off (default); 1 = HIP events on the decode stream at the
  * boundaries gather | convolutions | head | 16-bit render; 2 = an event after every kernel launch.  The
  * events are created here, not in the decode calls.

@@ -82,6 +82,7 @@ def load_library() -> ctypes.CDLL:
     lib.demon_vae_crossfade.argtypes = [ctypes.c_void_p, ctypes.c_longlong, ctypes.c_void_p, ctypes.c_longlong,
                                         ctypes.c_void_p, ctypes.c_longlong, ctypes.c_int, ctypes.c_int, ctypes.c_void_p]
     lib.demon_vae_debug_tap.argtypes = [ctypes.c_void_p, ctypes.c_int, ctypes.c_void_p, ctypes.c_size_t]
+    lib.demon_vae_debug_last_grid.argtypes = [ctypes.c_void_p, P(ctypes.c_int), P(ctypes.c_longlong), P(ctypes.c_int)]
     lib.demon_vae_set_timing.argtypes = [ctypes.c_void_p, ctypes.c_int]
     lib.demon_vae_get_timing.argtypes = [ctypes.c_void_p, P(ctypes.c_float), ctypes.c_int, P(ctypes.c_int)]
     lib.demon_vae_last_error.restype = ctypes.c_char_p
@@ -290,6 +291,13 @@ def demon_vae_debug_tap(handle: int, layer: int, d_dst: int, capacity: int):
     _check(load_library().demon_vae_debug_tap(handle, layer, d_dst, capacity))
 
 
+def demon_vae_debug_last_grid(handle: int) -> Tuple[int, int, int]:
+    """(windows, extended frames, groups on streams of their own) of the handle's last call."""
+    n, frames, groups = ctypes.c_int(), ctypes.c_longlong(), ctypes.c_int()
+    _check(load_library().demon_vae_debug_last_grid(handle, ctypes.byref(n), ctypes.byref(frames), ctypes.byref(groups)))
+    return n.value, frames.value, groups.value
+
+
 def demon_vae_set_timing(handle: int, level: int):
     _check(load_library().demon_vae_set_timing(handle, level))
 
@@ -414,6 +422,9 @@ class DemonVAE:
         demon_vae_debug_tap(self.handle, layer, dst.data_ptr() if dst is not None else 0,
                             dst.numel() if dst is not None else 0)
 
+    def last_grid(self) -> Tuple[int, int, int]:
+        return demon_vae_debug_last_grid(self.handle)
+
 
 class DemonVAEEncoder:
     """Convenience wrapper of an encoder handle: marshals torch tensors.  No arithmetic happens here."""
@@ -457,6 +468,9 @@ class DemonVAEEncoder:
     def tap(self, layer: int, dst=None):
         demon_vae_debug_tap(self.handle, layer, dst.data_ptr() if dst is not None else 0,
                             dst.numel() if dst is not None else 0)
+
+    def last_grid(self) -> Tuple[int, int, int]:
+        return demon_vae_debug_last_grid(self.handle)
 
     def encode_windowed(self, wave, window: int, halo: int = -1, frame_begin: int = 0, frame_end: Optional[int] = None,
                         eps=None, moments=None, latent=None):

@@ -167,6 +167,9 @@ struct demon_vae {
     int tap_layer = -1;
     float* tap_dst = nullptr;
     size_t tap_cap = 0;
+
+    int last_windows = 0, last_groups = 0;         // what the last call computed (demon_vae_debug_last_grid)
+    long long last_frames = 0;
 };
 
 namespace {
@@ -260,24 +263,37 @@ demon_status check_plane(const demon_vae* v, int max_len)
 // The window grid that a call computes.  Where every window carries the whole receptive field (or is the clip), a row does not depend
 // on the grid: the results are the full decode's bits.  Windows side by side would compute the rows that both read twice -- one row in
 // 21 of the decode and one in 6 of the encode with 64 frames, more than half with 16 -- and fill a last tile each, so a call computes each
-// clip's span as one window, or as two where the two groups below would otherwise be unequal.  In us, the caller's windows of 64 frames / one
+// clip's span as one window, or as two where cut_clips says so.  In us, the caller's windows of 64 frames / one
 // per clip / two (x1920 stack): decode of 250 frames 1085 / 1039 / 1060, 750 frames 2804 / 2713 / 2600, 1500 frames 5474 / 5298 / 5213, four
 // clips of 1500 21614 / 20732 / 20778; encode of 250 frames 1298 / 1071 / 1107, 1500 frames 6185 / 5308 / 5213; fp32 decode of the x32 stack,
-// 1500 frames 293 / 247.  One and two windows, two groups: 330 frames 1348 / 1330, 360 frames 1428 / 1429, 400 frames 1510 / 1509, 440 frames 1778 / 1624, 520 frames
-// 1975 / 1880, encode of 400 frames 1520 / 1605, 440 frames 1790 / 1703; with LDS-staged convolutions 100 frames 994 / 1000, 200 frames 1395 /
-// 1432, 250 frames 1683 / 1582.  A window's plane stays below 1 GB, far from the kernels' 32-bit offsets.
+// 1500 frames 293 / 247.  A window's plane stays below 1 GB, far from the kernels' 32-bit offsets.
 // The caller's own grid stays where a window carries less (its rows then depend on it), and for the debug tap, whose rows are the caller's windows.
 struct Grid { int window, halo; };
 constexpr long long kRegionBytes = 1ll << 30;
 
-Grid computed_grid(const demon_vae* v, int n_clips, int n_frames, int fb, int fe, int window, int halo, long long frames_held, bool two_streams)
+// Whether every clip is cut in two, for calls that may run as the two groups below and would otherwise have unequal ones: an odd number of
+// clips.  A join computes twice the receptive field again (12 frames of the decode, 10 of the encode) in every clip.  In us, one window a clip / two:
+//  * one clip: 330 frames 1348 / 1330, 360 frames 1428 / 1429, 400 frames 1510 / 1509, 440 frames 1778 / 1624, 520 frames 1975 / 1880, encode of 400
+//    frames 1520 / 1605, 440 frames 1790 / 1703; with LDS-staged convolutions 100 frames 994 / 1000, 200 frames 1395 / 1432, 250 frames 1683 / 1582.
+//  * more clips: decode of 3 x 150 frames 1688 / 1693, 3 x 250 2610 / 2674, 3 x 300 3131 / 3093, 3 x 420 4459 / 4349, 3 x 1500 15595 / 15364, 5 x 150 2590 / 2699,
+//    5 x 250 4422 / 4346, 5 x 300 5225 / 5202, 7 x 64 1675 / 1740, 7 x 200 4852 / 4835; encode of 3 x 150 1741 / 1753, 3 x 250 2803 / 2792, 3 x 350 3717 / 3741, 3 x 420
+//    4611 / 4499, 3 x 1500 15602 / 15514, 5 x 90 1724 / 1821, 5 x 300 5389 / 5425, 5 x 420 7428 / 7362, 7 x 64 1670 / 1916, 7 x 200 4912 / 5073.  With LDS-staged
+//    convolutions (960 to 64 channels) decode of 3 x 230 4369 / 4360, 3 x 400 7555 / 7570, encode of 3 x 230 4755 / 4817, 3 x 400 8013 / 8480.
+bool cut_clips(const demon_vae* v, int n_clips, long long span)
+{
+    if (n_clips % 2 == 0) return false;
+    if (n_clips == 1) return span >= (v->has_staged_convs ? 230 : 420);
+    return !v->has_staged_convs && span >= (v->encoder ? 420 : 300);
+}
+
+Grid computed_grid(const demon_vae* v, int n_clips, int n_frames, int fb, int fe, int window, int halo, long long frames_held, bool cut)
 {
     const int rf = std::max(v->rf_left, v->rf_right);
     const bool whole_clip = fb == 0 && fe == n_frames && window >= n_frames;
     if (halo < rf && !whole_clip) return {window, halo};
     const long long span = fe - fb;
     const long long most = kRegionBytes / (v->per_frame * (v->dtype == DEMON_BF16 ? 2 : 4)) - 2ll * rf;
-    long long k = two_streams && n_clips % 2 == 1 && span * n_clips >= (v->has_staged_convs ? 230 : 420) ? 2 : 1;
+    long long k = cut ? 2 : 1;
     if (most > 0 && (span + most - 1) / most > k) k = (span + most - 1) / most + (span + most - 1) / most % 2;
     const int w = (int)((span + k - 1) / k);
     // the halo of the caller's single window is not needed where it is the clip
@@ -345,7 +361,7 @@ demon_status get_plan(demon_vae* v, int n_clips, int n_frames, int fb, int fe, i
         return fail(DEMON_ERR_WORKSPACE, "extended windows need %lld frames, the workspace holds %lld", total, v->cap_frames);
     const demon_status prc = check_plane(v, gc.max_len);
     if (prc != DEMON_OK) return prc;
-    const Grid grid = verbatim ? Grid{window, halo} : computed_grid(v, n_clips, n_frames, fb, fe, window, halo, v->cap_frames, v->stream2 != nullptr);
+    const Grid grid = verbatim ? Grid{window, halo} : computed_grid(v, n_clips, n_frames, fb, fe, window, halo, v->cap_frames, v->stream2 && cut_clips(v, n_clips, fe - fb));
     gc = count_grid(n_frames, fb, fe, grid.window, grid.halo);
     n_slots = gc.per_clip * n_clips;
     total = gc.clip_frames * n_clips;
@@ -403,6 +419,7 @@ demon_status run_pass(demon_vae* v, const Workspace& ws, const Plan* plan, const
     // the launches address a group of windows (gs, gn) on a stream gst: all windows on the caller's stream, or two
     // groups of consecutive windows on two streams (see the bf16 path below)
     const int n_groups = two_groups(v, plan, io.d_skip != nullptr) ? 2 : 1;
+    v->last_windows = ns; v->last_frames = plan->total_frames; v->last_groups = bf ? n_groups : 1;
     const Slot* gs = slots;
     int gn = ns;
     long long frame0 = 0;
@@ -1271,6 +1288,13 @@ demon_status demon_vae_debug_tap(demon_vae* v, int layer, float* d_dst, size_t c
     if (!v) return fail(DEMON_ERR_INVALID_ARG, "NULL handle");
     if (layer >= 0 && !d_dst) return fail(DEMON_ERR_INVALID_ARG, "d_dst is NULL");
     v->tap_layer = layer; v->tap_dst = d_dst; v->tap_cap = capacity;
+    return DEMON_OK;
+}
+
+demon_status demon_vae_debug_last_grid(const demon_vae* v, int* n_windows, long long* extended_frames, int* n_groups)
+{
+    if (!v || !n_windows || !extended_frames || !n_groups) return fail(DEMON_ERR_INVALID_ARG, "NULL argument");
+    *n_windows = v->last_windows; *extended_frames = v->last_frames; *n_groups = v->last_groups;
     return DEMON_OK;
 }
 

@@ -88,6 +88,27 @@ def test_encode(stack, clips, T, fb, fe, window, dtype):
     enc.close()
 
 
+@pytest.mark.parametrize("stack,encode,clips,T,windows", [
+    ("narrow", False, 1, 419, 1), ("narrow", False, 1, 420, 2), ("narrow", False, 2, 500, 2), ("narrow", False, 4, 300, 4),
+    ("narrow", False, 3, 150, 3), ("narrow", False, 3, 299, 3), ("narrow", False, 3, 300, 6), ("narrow", False, 7, 64, 7),
+    ("narrow", True, 1, 419, 1), ("narrow", True, 1, 420, 2), ("narrow", True, 3, 419, 3), ("narrow", True, 3, 420, 6), ("narrow", True, 7, 64, 7),
+    ("staged", False, 1, 229, 1), ("staged", False, 1, 230, 2), ("staged", False, 3, 400, 3), ("staged", True, 3, 400, 3), ("staged", True, 5, 100, 5)])
+def test_calls_that_cut_their_clips(stack, encode, clips, T, windows):
+    """Every clip in two windows only where that is the faster side: the joins of many short clips cost more than equal groups give."""
+    spec = STACKS[stack]
+    if encode:
+        vae = DemonVAEEncoder(spec, di.make_encoder_weights(spec, bf16=True), dtype="bf16", max_frames=T, max_clips=clips)
+        x = torch.zeros((clips, spec.out_channels, T * spec.total_stride), device="cuda:0")
+        vae.encode(x)
+    else:
+        vae, _, z = make(spec, "bf16", T, n_clips=clips)
+        vae.decode(to_device(z, "bf16"))
+    rf = max(vae.receptive_field())
+    frames = clips * T + (windows - clips) * 2 * rf
+    assert vae.last_grid() == (windows, frames, 2 if windows > 1 and frames >= (150 if stack == "staged" else 320) else 1)
+    vae.close()
+
+
 def test_the_limits_are_those_of_the_callers_grid():
     spec, T = STACKS["narrow"], 500
     rf = max(oracle.receptive_field(spec))
