@@ -67,6 +67,7 @@ struct Plan {
     bool valid = false;
     int n_clips = 0, n_frames = 0, frame_begin = 0, frame_end = 0, window = 0, halo = 0;      // as the caller gave them
     bool verbatim = false;             // the caller's own windows, see computed_grid
+    bool cut = false;                  // each clip in two windows, see cut_clips
     int grid_window = 0, grid_halo = 0;        // the grid that is computed
     int n_slots = 0, max_len = 0, max_int = 0;
     long long total_frames = 0;
@@ -272,16 +273,17 @@ struct Grid { int window, halo; };
 constexpr long long kRegionBytes = 1ll << 30;
 
 // Whether every clip is cut in two, for calls that may run as the two groups below and would otherwise have unequal ones: an odd number of
-// clips.  A join computes twice the receptive field again (12 frames of the decode, 10 of the encode) in every clip.  In us, one window a clip / two:
+// clips, with a second stream and no gate (gated, one window a clip / two: one clip of 1500 frames 5191 / 5268, 3 x 150 1730 / 1809).  Per-launch
+// timing, which runs one group, times the launches of the grid that calls compute.  A join computes twice the receptive field again (12 frames of the decode, 10 of the encode) in every clip.  In us, one window a clip / two:
 //  * one clip: 330 frames 1348 / 1330, 360 frames 1428 / 1429, 400 frames 1510 / 1509, 440 frames 1778 / 1624, 520 frames 1975 / 1880, encode of 400
 //    frames 1520 / 1605, 440 frames 1790 / 1703; with LDS-staged convolutions 100 frames 994 / 1000, 200 frames 1395 / 1432, 250 frames 1683 / 1582.
 //  * more clips: decode of 3 x 150 frames 1688 / 1693, 3 x 250 2610 / 2674, 3 x 300 3131 / 3093, 3 x 420 4459 / 4349, 3 x 1500 15595 / 15364, 5 x 150 2590 / 2699,
 //    5 x 250 4422 / 4346, 5 x 300 5225 / 5202, 7 x 64 1675 / 1740, 7 x 200 4852 / 4835; encode of 3 x 150 1741 / 1753, 3 x 250 2803 / 2792, 3 x 350 3717 / 3741, 3 x 420
 //    4611 / 4499, 3 x 1500 15602 / 15514, 5 x 90 1724 / 1821, 5 x 300 5389 / 5425, 5 x 420 7428 / 7362, 7 x 64 1670 / 1916, 7 x 200 4912 / 5073.  With LDS-staged
 //    convolutions (960 to 64 channels) decode of 3 x 230 4369 / 4360, 3 x 400 7555 / 7570, encode of 3 x 230 4755 / 4817, 3 x 400 8013 / 8480.
-bool cut_clips(const demon_vae* v, int n_clips, long long span)
+bool cut_clips(const demon_vae* v, int n_clips, long long span, bool gated)
 {
-    if (n_clips % 2 == 0) return false;
+    if (n_clips % 2 == 0 || !v->stream2 || gated) return false;
     if (n_clips == 1) return span >= (v->has_staged_convs ? 230 : 420);
     return !v->has_staged_convs && span >= (v->encoder ? 420 : 300);
 }
@@ -324,30 +326,40 @@ bool two_groups(const demon_vae* v, const Plan* p, bool gated)
 // Looks the window grid up in the plan cache; on a miss the table of the least recently used entry that no graph holds is
 // rewritten by a small kernel on the decode stream, so the call stays asynchronous (kernels of earlier calls that still
 // read the replaced table precede that kernel on the stream) and can itself be recorded into a graph.
-demon_status get_plan(demon_vae* v, int n_clips, int n_frames, int fb, int fe, int window, int halo,
+demon_status get_plan(demon_vae* v, int n_clips, int n_frames, int fb, int fe, int window, int halo, bool gated,
                       hipStream_t stream, Plan** out)
 {
     ++v->use_counter;
     const bool verbatim = v->tap_layer >= 0 && v->tap_dst;
+    const bool cut = !verbatim && cut_clips(v, n_clips, fe - fb, gated);
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     HIP_TRY(hipStreamIsCapturing(stream, &cap), "hipStreamIsCapturing");
     const bool capturing = cap != hipStreamCaptureStatusNone;
     Plan* victim = nullptr;
+    Plan* hit = nullptr;
+    // the other grid of the same rows: taken where graphs hold every entry, and by a recorded call where a graph holds it already, so that
+    // the graphs of one grid hold one entry
+    Plan* alike = nullptr;
     for (Plan& p : v->plans) {
         if (p.valid && p.n_clips == n_clips && p.n_frames == n_frames && p.frame_begin == fb && p.frame_end == fe &&
             p.window == window && p.halo == halo && p.verbatim == verbatim) {
-            p.last_use = v->use_counter;
-            if (capturing) p.pinned = true;
-            if (p.table_pending) {
-                HIP_TRY(launch_plan_slots(p.d_slots, p.n_clips, p.n_slots / p.n_clips, (int)(p.total_frames / p.n_clips), p.n_frames,
-                                          p.frame_begin, p.frame_end, p.grid_window, p.grid_halo, stream), "window table");
-                if (!capturing) p.table_pending = false;
-            }
-            *out = &p;
-            return DEMON_OK;
+            if (p.cut == cut) { hit = &p; break; }
+            alike = &p;
         }
         if (p.pinned) continue;
         if (!victim || (victim->valid && (!p.valid || p.last_use < victim->last_use))) victim = &p;
+    }
+    if (!hit && alike && (!victim || (capturing && alike->pinned))) hit = alike;
+    if (hit) {
+        hit->last_use = v->use_counter;
+        if (capturing) hit->pinned = true;
+        if (hit->table_pending) {
+            HIP_TRY(launch_plan_slots(hit->d_slots, hit->n_clips, hit->n_slots / hit->n_clips, (int)(hit->total_frames / hit->n_clips), hit->n_frames,
+                                      hit->frame_begin, hit->frame_end, hit->grid_window, hit->grid_halo, stream), "window table");
+            if (!capturing) hit->table_pending = false;
+        }
+        *out = hit;
+        return DEMON_OK;
     }
     if (!victim)
         return fail(DEMON_ERR_WORKSPACE, "all %d cached window grids are held by recorded graphs; a further grid needs another handle", kPlanCache);
@@ -361,7 +373,7 @@ demon_status get_plan(demon_vae* v, int n_clips, int n_frames, int fb, int fe, i
         return fail(DEMON_ERR_WORKSPACE, "extended windows need %lld frames, the workspace holds %lld", total, v->cap_frames);
     const demon_status prc = check_plane(v, gc.max_len);
     if (prc != DEMON_OK) return prc;
-    const Grid grid = verbatim ? Grid{window, halo} : computed_grid(v, n_clips, n_frames, fb, fe, window, halo, v->cap_frames, v->stream2 && cut_clips(v, n_clips, fe - fb));
+    const Grid grid = verbatim ? Grid{window, halo} : computed_grid(v, n_clips, n_frames, fb, fe, window, halo, v->cap_frames, cut);
     gc = count_grid(n_frames, fb, fe, grid.window, grid.halo);
     n_slots = gc.per_clip * n_clips;
     total = gc.clip_frames * n_clips;
@@ -373,7 +385,7 @@ demon_status get_plan(demon_vae* v, int n_clips, int n_frames, int fb, int fe, i
     victim->pinned = capturing;
     victim->table_pending = capturing;
     victim->n_clips = n_clips; victim->n_frames = n_frames; victim->frame_begin = fb; victim->frame_end = fe;
-    victim->window = window; victim->halo = halo; victim->verbatim = verbatim;
+    victim->window = window; victim->halo = halo; victim->verbatim = verbatim; victim->cut = cut;
     victim->grid_window = grid.window; victim->grid_halo = grid.halo;
     victim->n_slots = (int)n_slots; victim->max_len = gc.max_len; victim->max_int = gc.max_int;
     victim->total_frames = total; victim->d_slots = d; victim->last_use = v->use_counter;
@@ -1075,7 +1087,7 @@ static demon_status decode_checked(demon_vae* v, const void* d_latent, int n_cli
     if (n_clips > v->max_clips) return fail(DEMON_ERR_WORKSPACE, "n_clips %d exceeds max_clips %d", n_clips, v->max_clips);
     if (halo == -1) halo = std::max(v->rf_left, v->rf_right);
     Plan* plan = nullptr;
-    const demon_status rc = get_plan(v, n_clips, n_frames, frame_begin, frame_end, window, halo, (hipStream_t)stream, &plan);
+    const demon_status rc = get_plan(v, n_clips, n_frames, frame_begin, frame_end, window, halo, d_skip != nullptr, (hipStream_t)stream, &plan);
     if (rc != DEMON_OK) return rc;
     Io io;
     io.d_latent = d_latent; io.d_skip = d_skip; io.d_out = d_out; io.d_pcm = d_pcm; io.n_frames = n_frames;
@@ -1184,7 +1196,7 @@ demon_status demon_vae_encode_windowed(demon_vae* v, const float* d_wave, int n_
     if ((long long)n_frames * v->st.total_stride() > 0x7fffffffll) return fail(DEMON_ERR_UNSUPPORTED, "clips longer than 2^31 samples");
     if (halo == -1) halo = std::max(v->rf_left, v->rf_right);
     Plan* plan = nullptr;
-    const demon_status rc = get_plan(v, n_clips, n_frames, frame_begin, frame_end, window, halo, (hipStream_t)stream, &plan);
+    const demon_status rc = get_plan(v, n_clips, n_frames, frame_begin, frame_end, window, halo, false, (hipStream_t)stream, &plan);
     if (rc != DEMON_OK) return rc;
     Io io;
     io.d_wave = d_wave; io.d_eps = d_eps; io.d_moments = d_moments; io.d_zout = d_latent; io.n_frames = n_frames;

@@ -109,6 +109,53 @@ def test_calls_that_cut_their_clips(stack, encode, clips, T, windows):
     vae.close()
 
 
+@pytest.mark.parametrize("clips,T", [(1, 500), (3, 350)])
+def test_gated_calls_cut_no_clip(clips, T):
+    """A gated call runs as one group of windows, for which nothing is cut.  16 grids can be recorded whether or not calls on them are gated, and
+    a gated call on a recorded grid takes that one where no entry of the window tables is left."""
+    spec = STACKS["narrow"]
+    vae, _, z = make(spec, "bf16", T, n_clips=clips, max_extended_frames=3 * T * clips)
+    zt = to_device(z, "bf16")
+    S = spec.total_stride
+    ref = vae.decode_windowed(zt, window=64)
+    assert vae.last_grid()[0] == 2 * clips
+    skip = torch.tensor([0, 1, 0][:clips], dtype=torch.int32, device="cuda:0")
+    def gated(fe):
+        out = torch.full_like(ref, 7.0)
+        vae.decode_windowed_gated(zt, skip, out, window=64, frame_end=fe)
+        for c in range(clips):
+            assert (out[c] == 7).all() if skip[c] else torch.equal(out[c, :, :fe * S], ref[c, :, :fe * S])
+    gated(T)
+    assert vae.last_grid() == (clips, clips * T, 1)
+    vae.close()
+    # 16 recorded grids: no entry is left
+    vae, _, _ = make(spec, "bf16", T, n_clips=clips, max_extended_frames=3 * T * clips)
+    graphs, out = [], torch.zeros_like(ref)
+    for i in range(16):
+        graphs.append(torch.cuda.CUDAGraph())
+        with torch.cuda.graph(graphs[-1]):
+            vae.decode_windowed(zt, out=out, window=64, frame_end=T - i)
+        graphs.append(torch.cuda.CUDAGraph())
+        with torch.cuda.graph(graphs[-1]):
+            vae.decode_windowed_gated(zt, skip, out, window=64, frame_end=T - i)
+    for i in (0, 15, 15):
+        gated(T - i)
+        assert vae.last_grid()[0] == 2 * clips
+        out.zero_()
+        graphs[2 * i].replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out[:, :, :(T - i) * S], ref[:, :, :(T - i) * S])
+        out.fill_(7.0)
+        graphs[2 * i + 1].replay()
+        torch.cuda.synchronize()
+        for c in range(clips):
+            assert (out[c] == 7).all() if skip[c] else torch.equal(out[c, :, :(T - i) * S], ref[c, :, :(T - i) * S])
+    with pytest.raises(DemonError) as e:
+        vae.decode_windowed_gated(zt, skip, out, window=65)
+    assert e.value.status == DEMON_ERR_WORKSPACE
+    vae.close()
+
+
 def test_the_limits_are_those_of_the_callers_grid():
     spec, T = STACKS["narrow"], 500
     rf = max(oracle.receptive_field(spec))
