@@ -826,17 +826,19 @@ hipError_t launch_plan_slots(Slot* dst, int n_clips, int per_clip, int clip_fram
 }
 
 // ---------------------------------------------------------------------------------- latent similarity filter
-// One workgroup per clip: squared differences accumulate in double in a fixed order (thread-strided partial sums, then a
-// tree over the workgroup), so the result does not depend on scheduling.  mse and the gate go out as fp32 / int.  Bound by the latency of
-// one workgroup's loads: 16 bytes of each latent at a time, four of them in flight, where both are aligned (else single elements): 64 x 1500
-// in bf16 12.3 -> 7.4 us.  What is left is arithmetic in double on one CU.
+// One workgroup per clip: squared differences accumulate in double in a fixed order (thread-strided partial sums of 16 bytes, then a
+// tree over the workgroup), so the result depends neither on scheduling nor on where the latents lie.  mse and the gate go out as fp32 / int.
+// Bound by the latency of one workgroup's loads: 16 bytes of each latent at a time, four of them in flight.  The loads claim no more than an
+// element's alignment.  64 x 1500 in bf16: single elements 12.2 us, here 7.4 (and from odd addresses, which cost the loads more, 12.4; fp32
+// 12.0 and 7.8 from any address).  What is left is arithmetic in double on one CU.
 template <typename T>
 __global__ __launch_bounds__(1024) void latent_mse_kernel(const T* __restrict__ a, const T* __restrict__ b, long long n,
                                                           float threshold, float* __restrict__ mse, int* __restrict__ unchanged)
 {
     __shared__ double part[16];
-    constexpr int V = 16 / sizeof(T);
+    constexpr int V = 16 / sizeof(T), U = 4;
     typedef T vec_t __attribute__((ext_vector_type(V)));
+    typedef vec_t loose_t __attribute__((aligned(sizeof(T))));
     const T* pa = a + (size_t)blockIdx.x * n;
     const T* pb = b + (size_t)blockIdx.x * n;
     double acc = 0.0;
@@ -844,23 +846,20 @@ __global__ __launch_bounds__(1024) void latent_mse_kernel(const T* __restrict__ 
         const double d = (double)load_act<T>(&x) - (double)load_act<T>(&y);
         acc += d * d;
     };
-    if (n % V == 0 && (reinterpret_cast<uintptr_t>(pa) | reinterpret_cast<uintptr_t>(pb)) % 16 == 0) {
-        constexpr int U = 4;
-        const vec_t* va = reinterpret_cast<const vec_t*>(pa);
-        const vec_t* vb = reinterpret_cast<const vec_t*>(pb);
-        const long long nv = n / V;
-        for (long long i = threadIdx.x; i < nv; i += U * 1024) {
-            vec_t x[U] = {}, y[U] = {};
+    const loose_t* va = reinterpret_cast<const loose_t*>(pa);
+    const loose_t* vb = reinterpret_cast<const loose_t*>(pb);
+    const long long nv = n / V;
+    for (long long i = threadIdx.x; i < nv; i += U * 1024) {
+        vec_t x[U] = {}, y[U] = {};
 #pragma unroll
-            for (int u = 0; u < U; ++u)
-                if (i + u * 1024 < nv) { x[u] = va[i + u * 1024]; y[u] = vb[i + u * 1024]; }
+        for (int u = 0; u < U; ++u)
+            if (i + u * 1024 < nv) { x[u] = va[i + u * 1024]; y[u] = vb[i + u * 1024]; }
 #pragma unroll
-            for (int u = 0; u < U; ++u)
+        for (int u = 0; u < U; ++u)
 #pragma unroll
-                for (int e = 0; e < V; ++e) add(x[u][e], y[u][e]);
-        }
-    } else
-        for (long long i = threadIdx.x; i < n; i += 1024) add(pa[i], pb[i]);
+            for (int e = 0; e < V; ++e) add(x[u][e], y[u][e]);
+    }
+    if (const long long i = nv * V + threadIdx.x; i < n) add(pa[i], pb[i]);
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) acc += __shfl_down(acc, o, 64);
     if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6] = acc;
