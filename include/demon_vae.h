@@ -347,6 +347,12 @@ DEMON_API demon_status demon_vae_crossfade(const float* d_prev_tail, long long p
 DEMON_API demon_status demon_vae_debug_tap(demon_vae* vae, int layer, float* d_dst, size_t capacity);
 
 /*
+ * Test aid (host only): with on != 0 the next calls on this handle compute the caller's own windows also where the halo covers the
+ * receptive field, otherwise as always (streams, fused kernels).  The results are the same bits.
+ */
+DEMON_API demon_status demon_vae_debug_callers_grid(demon_vae* vae, int on);
+
+/*
  * Test aid (host only): the windows that the last decode or encode call on this handle computed, their extended frames, and
  * whether its layers ran as one group of windows or as two on two streams.  0 of each before the first call.
  */

@@ -5,7 +5,7 @@ from .binding import (DemonVAE, DemonVAEEncoder, DemonError, demon_vae_create_en
                       demon_vae_decode_windowed_static,
                       demon_vae_receptive_field,
                       demon_vae_rf_from_config, demon_vae_forward_support, demon_vae_plan_windows,
-                      demon_vae_weight_count, demon_vae_debug_tap, demon_vae_debug_last_grid, demon_vae_last_error,
+                      demon_vae_weight_count, demon_vae_debug_tap, demon_vae_debug_callers_grid, demon_vae_debug_last_grid, demon_vae_last_error,
                       demon_vae_set_timing, demon_vae_get_timing, demon_vae_latent_similarity, demon_vae_crossfade,
                       latent_similarity, crossfade,
                       DEMON_OK, DEMON_ERR_INVALID_ARG, DEMON_ERR_UNSUPPORTED, DEMON_ERR_WORKSPACE, DEMON_ERR_HIP,

@@ -82,6 +82,7 @@ def load_library() -> ctypes.CDLL:
     lib.demon_vae_crossfade.argtypes = [ctypes.c_void_p, ctypes.c_longlong, ctypes.c_void_p, ctypes.c_longlong,
                                         ctypes.c_void_p, ctypes.c_longlong, ctypes.c_int, ctypes.c_int, ctypes.c_void_p]
     lib.demon_vae_debug_tap.argtypes = [ctypes.c_void_p, ctypes.c_int, ctypes.c_void_p, ctypes.c_size_t]
+    lib.demon_vae_debug_callers_grid.argtypes = [ctypes.c_void_p, ctypes.c_int]
     lib.demon_vae_debug_last_grid.argtypes = [ctypes.c_void_p, P(ctypes.c_int), P(ctypes.c_longlong), P(ctypes.c_int)]
     lib.demon_vae_set_timing.argtypes = [ctypes.c_void_p, ctypes.c_int]
     lib.demon_vae_get_timing.argtypes = [ctypes.c_void_p, P(ctypes.c_float), ctypes.c_int, P(ctypes.c_int)]
@@ -291,6 +292,10 @@ def demon_vae_debug_tap(handle: int, layer: int, d_dst: int, capacity: int):
     _check(load_library().demon_vae_debug_tap(handle, layer, d_dst, capacity))
 
 
+def demon_vae_debug_callers_grid(handle: int, on: int):
+    _check(load_library().demon_vae_debug_callers_grid(handle, on))
+
+
 def demon_vae_debug_last_grid(handle: int) -> Tuple[int, int, int]:
     """(windows, extended frames, groups on streams of their own) of the handle's last call."""
     n, frames, groups = ctypes.c_int(), ctypes.c_longlong(), ctypes.c_int()
@@ -422,6 +427,9 @@ class DemonVAE:
         demon_vae_debug_tap(self.handle, layer, dst.data_ptr() if dst is not None else 0,
                             dst.numel() if dst is not None else 0)
 
+    def callers_grid(self, on: bool):
+        demon_vae_debug_callers_grid(self.handle, int(on))
+
     def last_grid(self) -> Tuple[int, int, int]:
         return demon_vae_debug_last_grid(self.handle)
 
@@ -468,6 +476,9 @@ class DemonVAEEncoder:
     def tap(self, layer: int, dst=None):
         demon_vae_debug_tap(self.handle, layer, dst.data_ptr() if dst is not None else 0,
                             dst.numel() if dst is not None else 0)
+
+    def callers_grid(self, on: bool):
+        demon_vae_debug_callers_grid(self.handle, int(on))
 
     def last_grid(self) -> Tuple[int, int, int]:
         return demon_vae_debug_last_grid(self.handle)

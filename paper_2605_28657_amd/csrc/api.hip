@@ -169,6 +169,7 @@ struct demon_vae {
     float* tap_dst = nullptr;
     size_t tap_cap = 0;
 
+    bool callers_grid = false;         // demon_vae_debug_callers_grid
     int last_windows = 0, last_groups = 0;         // what the last call computed (demon_vae_debug_last_grid)
     long long last_frames = 0;
 };
@@ -268,13 +269,17 @@ demon_status check_plane(const demon_vae* v, int max_len)
 // per clip / two (x1920 stack): decode of 250 frames 1085 / 1039 / 1060, 750 frames 2804 / 2713 / 2600, 1500 frames 5474 / 5298 / 5213, four
 // clips of 1500 21614 / 20732 / 20778; encode of 250 frames 1298 / 1071 / 1107, 1500 frames 6185 / 5308 / 5213; fp32 decode of the x32 stack,
 // 1500 frames 293 / 247.  A window's plane stays below 1 GB, far from the kernels' 32-bit offsets.
-// The caller's own grid stays where a window carries less (its rows then depend on it), and for the debug tap, whose rows are the caller's windows.
+// The caller's own grid stays where a window carries less (its rows then depend on it), for the debug tap, whose rows are the caller's windows, and
+// where a test asks for it.
 struct Grid { int window, halo; };
 constexpr long long kRegionBytes = 1ll << 30;
 
+bool callers_own(const demon_vae* v) { return v->callers_grid || (v->tap_layer >= 0 && v->tap_dst); }
+
 // Whether every clip is cut in two, for calls that may run as the two groups below and would otherwise have unequal ones: an odd number of
 // clips, with a second stream and no gate (gated, one window a clip / two: one clip of 1500 frames 5191 / 5268, 3 x 150 1730 / 1809).  Per-launch
-// timing, which runs one group, times the launches of the grid that calls compute.  A join computes twice the receptive field again (12 frames of the decode, 10 of the encode) in every clip.  In us, one window a clip / two:
+// timing, which runs one group, times the launches of the grid that calls compute.  A join
+// computes twice the receptive field again (12 frames on the x1920 stack) in every clip.  In us, one window a clip / two:
 //  * one clip: 330 frames 1348 / 1330, 360 frames 1428 / 1429, 400 frames 1510 / 1509, 440 frames 1778 / 1624, 520 frames 1975 / 1880, encode of 400
 //    frames 1520 / 1605, 440 frames 1790 / 1703; with LDS-staged convolutions 100 frames 994 / 1000, 200 frames 1395 / 1432, 250 frames 1683 / 1582.
 //  * more clips: decode of 3 x 150 frames 1688 / 1693, 3 x 250 2610 / 2674, 3 x 300 3131 / 3093, 3 x 420 4459 / 4349, 3 x 1500 15595 / 15364, 5 x 150 2590 / 2699,
@@ -330,7 +335,7 @@ demon_status get_plan(demon_vae* v, int n_clips, int n_frames, int fb, int fe, i
                       hipStream_t stream, Plan** out)
 {
     ++v->use_counter;
-    const bool verbatim = v->tap_layer >= 0 && v->tap_dst;
+    const bool verbatim = callers_own(v);
     const bool cut = !verbatim && cut_clips(v, n_clips, fe - fb, gated);
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     HIP_TRY(hipStreamIsCapturing(stream, &cap), "hipStreamIsCapturing");
@@ -1165,7 +1170,7 @@ demon_status demon_vae_decode_windowed_static(demon_vae* v, const void* d_latent
     plan.valid = true;
     plan.n_clips = n_clips; plan.n_frames = n_frames; plan.frame_begin = frame_begin; plan.frame_end = frame_end;
     plan.window = window; plan.halo = halo;
-    const Grid grid = v->tap_layer >= 0 && v->tap_dst ? Grid{window, halo} : computed_grid(v, n_clips, n_frames, frame_begin, frame_end, window, halo, total, false);
+    const Grid grid = callers_own(v) ? Grid{window, halo} : computed_grid(v, n_clips, n_frames, frame_begin, frame_end, window, halo, total, false);
     const GridCount cc = count_grid(n_frames, frame_begin, frame_end, grid.window, grid.halo);
     plan.n_slots = (int)(cc.per_clip * n_clips); plan.max_len = cc.max_len; plan.max_int = cc.max_int;
     plan.total_frames = cc.clip_frames * n_clips;
@@ -1300,6 +1305,13 @@ demon_status demon_vae_debug_tap(demon_vae* v, int layer, float* d_dst, size_t c
     if (!v) return fail(DEMON_ERR_INVALID_ARG, "NULL handle");
     if (layer >= 0 && !d_dst) return fail(DEMON_ERR_INVALID_ARG, "d_dst is NULL");
     v->tap_layer = layer; v->tap_dst = d_dst; v->tap_cap = capacity;
+    return DEMON_OK;
+}
+
+demon_status demon_vae_debug_callers_grid(demon_vae* v, int on)
+{
+    if (!v) return fail(DEMON_ERR_INVALID_ARG, "NULL handle");
+    v->callers_grid = on != 0;
     return DEMON_OK;
 }
 

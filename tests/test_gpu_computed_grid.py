@@ -1,5 +1,5 @@
 """A call computes each clip's span in as few windows as it can where the grid does not change a row.  The debug tap makes it compute the
-caller's own windows: the same bits, over window lengths from one frame to more than the clip, halos of the receptive field and more,
+caller's own windows, and so does a test aid that leaves streams and kernels as they are: the same bits, over window lengths from one frame to more than the clip, halos of the receptive field and more,
 spans inside the clip and at its edges, one and several clips, sizes on both sides of the cut into two windows, every entry point.  With
 less than the receptive field the windows are the caller's with and without the tap."""
 import numpy as np
@@ -31,6 +31,9 @@ def both(handle, decode):
     handle.tap(0, scratch)
     ref = decode()
     handle.tap(-1)
+    handle.callers_grid(True)
+    assert torch.equal(decode(), ref)
+    handle.callers_grid(False)
     return ref, decode()
 
 

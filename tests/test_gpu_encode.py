@@ -11,7 +11,7 @@ import oracle
 import paper_2605_28657_amd as pa
 from gpu_util import errors
 
-pytestmark = pytest.mark.gpu
+pytestmark = [pytest.mark.gpu, pytest.mark.usefixtures("grid")]
 
 TOL_REL = {"f32": 1e-4, "bf16": 1e-2}
 TOL_ABS = {"f32": 1e-4, "bf16": 2e-2}

@@ -8,7 +8,7 @@ import oracle
 import paper_2605_28657_amd as pa
 from gpu_util import assert_close, make, to_device
 
-pytestmark = pytest.mark.gpu
+pytestmark = [pytest.mark.gpu, pytest.mark.usefixtures("grid")]
 
 
 @pytest.mark.parametrize("spec,T,window", [

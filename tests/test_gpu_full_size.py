@@ -1,5 +1,5 @@
-"""GPU parity at the full benchmark sizes, in the launch configuration bench.py times (window 64,
-analytic halo, all windows in one batch).  The oracle cannot decode whole clips in seconds, so it is
+"""GPU parity at the full benchmark sizes, in the calls bench.py times (window 64, analytic halo), on the windows that a call
+computes and on the caller's.  The oracle cannot decode whole clips in seconds, so it is
 evaluated on sampled blocks of output frames through its own windowed decode (whose equality with the
 full decode is pinned on the CPU); the rest is covered by properties that hold at any size: windowed ==
 full bit for bit, batch of clips == clip by clip, partial re-decode + splice == full re-decode."""
@@ -12,7 +12,7 @@ import oracle
 from gpu_util import TOL_WINDOWED_VS_FULL, assert_close, to_device
 from paper_2605_28657_amd import DemonVAE, DEMON_VAE_FLAG_NO_FUSED, DEMON_VAE_FLAG_ONE_STREAM
 
-pytestmark = pytest.mark.gpu
+pytestmark = [pytest.mark.gpu, pytest.mark.usefixtures("grid")]
 
 SPEC = di.FULL
 S = SPEC.total_stride
@@ -42,12 +42,13 @@ def make_vae(wl, extra=0):
 
 
 @pytest.mark.parametrize("name,starts", [("full_10s_bf16", (0, 62, 123, 246)), ("full_60s_bf16", (0, 638, 1470, 1496))])
-def test_single_clip_windowed_full_and_oracle_samples(name, starts):
+def test_single_clip_windowed_full_and_oracle_samples(name, starts, grid):
     wl = di.WORKLOADS[name]
     vae, weights, lat = make_vae(wl)
     assert vae.receptive_field() == (H, H)
     zt = to_device(lat, "bf16")
     win = vae.decode_windowed(zt, window=wl.window, halo=-1)
+    assert vae.last_grid()[0] == (-(-wl.n_frames // wl.window) if grid == "callers" else 1 if wl.n_frames < 420 else 2)
     full = vae.decode(zt)
     assert float((win - full).abs().max()) <= TOL_WINDOWED_VS_FULL
     assert torch.equal(win, full)
@@ -57,11 +58,11 @@ def test_single_clip_windowed_full_and_oracle_samples(name, starts):
     vae.close()
 
 
-def test_10s_clip_whole_against_the_oracle_with_every_kernel_variant():
-    """configs[1] element by element over the whole clip (the f64 oracle decodes 10 s in seconds), for the default
+def test_10s_clip_whole_against_the_oracle_with_every_kernel_variant(grid):
+    """A 10 s clip element by element over the whole clip (the f64 oracle decodes 10 s in seconds), for the default
     kernels and for each alternative the config selects: hi + lo bf16 operands on the wide levels, unfused residual
     units, one stream, no small tiles.  Each variant also reproduces its own full decode bit for bit, in windows of 64 frames
-    and in windows of 32, which are enough frames for two groups of windows on two streams (but with the one-stream flag)."""
+    and in windows of 32, which as the caller's own are enough frames for two groups of windows on two streams (but with the one-stream flag)."""
     wl = di.WORKLOADS["full_10s_bf16"]
     weights, lat = di.workload_inputs(wl)
     ref = oracle.decode(SPEC, weights, lat[0])
@@ -75,6 +76,8 @@ def test_10s_clip_whole_against_the_oracle_with_every_kernel_variant():
         full = vae.decode(zt)
         assert torch.equal(win, full), name
         assert torch.equal(vae.decode_windowed(zt, window=wl.window // 2, halo=-1), full), name
+        # on the computed grid the clip is one window, two only where its 64-channel convolutions are LDS-staged
+        assert vae.last_grid()[2] == (1 if name == "one stream" or (grid == "computed" and name != "unfused") else 2), name
         g = win[0].cpu().numpy()
         ma, rl = assert_close(g, ref, "bf16", name)
         print(f"10 s clip, {name}: max-abs {ma:.3e} rel-L2 {rl:.3e} over {g.size} samples")
@@ -85,7 +88,7 @@ def test_10s_clip_whole_against_the_oracle_with_every_kernel_variant():
         vae.close()
 
 
-def test_four_clips_in_one_call():
+def test_four_clips_in_one_call(grid):
     wl = di.WORKLOADS["full_4x60s_bf16"]
     vae, weights, lat = make_vae(wl)
     zt = to_device(lat, "bf16")
@@ -93,7 +96,8 @@ def test_four_clips_in_one_call():
     assert win.shape == (4, 2, 1500 * S)
     for c, b in enumerate((0, 63, 700, 1496)):          # one oracle block per clip
         check_blocks(win[c].cpu().numpy(), oracle_blocks(weights, lat[c], (b,)), f"clip {c}")
-    # the batch of 96 windows equals clip-by-clip decodes
+    assert vae.last_grid()[0] == (96 if grid == "callers" else 4)
+    # the batch of all windows equals clip-by-clip decodes
     for c in (0, 3):
         one = vae.decode_windowed(zt[c:c + 1].contiguous(), window=wl.window, halo=-1)
         assert torch.equal(one[0], win[c])

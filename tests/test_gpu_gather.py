@@ -8,7 +8,7 @@ import demon_inputs as di
 import oracle
 from gpu_util import assert_close, make, to_device
 
-pytestmark = pytest.mark.gpu
+pytestmark = [pytest.mark.gpu, pytest.mark.usefixtures("grid")]
 
 
 @pytest.mark.parametrize("c0,width,dtype,kw", [(1, 8, "f32", {}), (17, 16, "f32", {}), (40, 32, "f32", {}), (16, 32, "bf16", {}), (48, 64, "bf16", {}),

@@ -10,7 +10,7 @@ import oracle
 import paper_2605_28657_amd as pa
 from gpu_util import TOL_WINDOWED_VS_FULL, assert_close, errors, make, pcm16, to_device
 
-pytestmark = pytest.mark.gpu
+pytestmark = [pytest.mark.gpu, pytest.mark.usefixtures("grid")]
 
 # small stacks that select each MFMA tile variant: (128x128, K64), (64x256, K64), (32x128, K16)
 STACK_V0 = di.DecoderSpec(64, (2,), (128,), (1, 3, 9))
@@ -284,7 +284,7 @@ def test_workspace_and_argument_errors():
     vae.close()
 
 
-def test_unfused_kernels_for_64_128_and_256_channels_in_a_subprocess():
+def test_unfused_kernels_for_64_128_and_256_channels_in_a_subprocess(grid):
     """DEMON_VAE_NO_FUSED=1 (read when the library loads) keeps the 64-, 128- and 256-channel residual units on the
     two-kernel path; same parity bar, and bit-identical windowed == full there too."""
     import os
@@ -296,24 +296,25 @@ sys.path.insert(0, os.path.join(os.getcwd(), "tests")); sys.path.insert(0, os.ge
 import numpy as np
 import demon_inputs as di, oracle
 from gpu_util import make, to_device, assert_close
+grid = sys.argv[1]
 for spec, T in ((di.DecoderSpec(64, (2,), (128,), (1, 3, 9)), 150), (di.DecoderSpec(64, (4,), (64,), (1, 3, 9)), 150),
                 (di.DecoderSpec(64, (2, 2), (256, 64), (1, 3, 9)), 150)):
     vae, w, z = make(spec, "bf16", T, snake="uniform", max_extended_frames=8 * T)
     zt = to_device(z, "bf16")
     full = vae.decode(zt).cpu().numpy()
-    win = vae.decode_windowed(zt, window=37, halo=-1).cpu().numpy()
     assert_close(full, oracle.decode(spec, w, z), "bf16", "unfused")
-    assert np.array_equal(win, full)
+    vae.callers_grid(grid == "callers")
+    assert np.array_equal(vae.decode_windowed(zt, window=37, halo=-1).cpu().numpy(), full)
     vae.close()
 print("ok")
 '''
     root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
     env = dict(os.environ, DEMON_VAE_NO_FUSED="1")
-    r = subprocess.run([sys.executable, "-c", code], cwd=root, env=env, capture_output=True, text=True, timeout=240)
+    r = subprocess.run([sys.executable, "-c", code, grid], cwd=root, env=env, capture_output=True, text=True, timeout=240)
     assert r.returncode == 0 and "ok" in r.stdout, r.stdout + r.stderr
 
 
-def test_small_grid_tile_is_bit_identical_to_the_large_tile(tmp_path):
+def test_small_grid_tile_is_bit_identical_to_the_large_tile(tmp_path, grid):
     """Launches with few workgroups use smaller tiles on the same packed weights (here: every generic launch, the inputs
     are short); DEMON_VAE_SMALL_TILE_WGS=0 in a subprocess keeps the 128 x 128 tile (and the LDS-staged 256-channel unit).
     Same K order, so the two decodes must agree bit for bit."""
@@ -330,6 +331,7 @@ outs = []
 for spec, T in ((di.DecoderSpec(64, (2, 2), (512, 128), (1, 9)), 60), (di.DecoderSpec(64, (10, 6, 2), (1024, 512, 64), (1, 3, 9)), 12),
                 (di.DecoderSpec(64, (2, 2), (256, 128), (1, 3)), 50)):
     vae, w, z = make(spec, "bf16", T, n_clips=2, max_extended_frames=8 * T)
+    vae.callers_grid(sys.argv[2] == "callers")
     outs.append(vae.decode_windowed(to_device(z, "bf16"), window=T // 2 + 1, halo=-1).cpu().numpy().ravel())
     vae.close()
 np.save(sys.argv[1], np.concatenate(outs))
@@ -343,7 +345,7 @@ print("ok")
         if wgs is not None:
             env["DEMON_VAE_SMALL_TILE_WGS"] = wgs
         path = str(tmp_path / (name + ".npy"))
-        r = subprocess.run([sys.executable, "-c", code, path], cwd=root, env=env, capture_output=True, text=True, timeout=240)
+        r = subprocess.run([sys.executable, "-c", code, path, grid], cwd=root, env=env, capture_output=True, text=True, timeout=240)
         assert r.returncode == 0 and "ok" in r.stdout, r.stdout + r.stderr
         got[name] = np.load(path)
     assert got["small"].shape == got["large"].shape and np.array_equal(got["small"], got["large"])
@@ -373,7 +375,7 @@ def test_one_window_of_a_long_clip_equals_its_small_windows():
     vae.close(); ref_vae.close()
 
 
-def test_wide_levels_with_hi_lo_bf16_operands_in_a_subprocess():
+def test_wide_levels_with_hi_lo_bf16_operands_in_a_subprocess(grid):
     """DEMON_VAE_WIDE_OPERANDS=bf16x2 (read when the library loads) carries the operands of the levels that are at least
     512 channels wide as hi + lo bf16 pairs instead of half; same parity bar, bit-identical windowed == full, also on
     the first two levels of the x1920 stack and on a stack whose width grows into the wide range."""
@@ -386,21 +388,22 @@ sys.path.insert(0, os.path.join(os.getcwd(), "tests")); sys.path.insert(0, os.ge
 import numpy as np
 import demon_inputs as di, oracle
 from gpu_util import make, to_device, assert_close
+grid = sys.argv[1]
 for spec, T, window in ((di.DecoderSpec(64, (2, 2), (512, 128), (1, 9)), 60, 23),
                         (di.DecoderSpec(32, (2, 2, 2), (128, 256, 512), (1, 3)), 40, 17),
                         (di.DecoderSpec(64, (10, 6, 2), (1024, 512, 64), (1, 3, 9)), 12, 5)):
     vae, w, z = make(spec, "bf16", T, max_extended_frames=8 * T)
     zt = to_device(z, "bf16")
     full = vae.decode(zt).cpu().numpy()
-    win = vae.decode_windowed(zt, window=window, halo=-1).cpu().numpy()
     assert_close(full, oracle.decode(spec, w, z), "bf16", "hi + lo operands")
-    assert np.array_equal(win, full)
+    vae.callers_grid(grid == "callers")
+    assert np.array_equal(vae.decode_windowed(zt, window=window, halo=-1).cpu().numpy(), full)
     vae.close()
 print("ok")
 '''
     root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
     env = dict(os.environ, DEMON_VAE_WIDE_OPERANDS="bf16x2")
-    r = subprocess.run([sys.executable, "-c", code], cwd=root, env=env, capture_output=True, text=True, timeout=240)
+    r = subprocess.run([sys.executable, "-c", code, grid], cwd=root, env=env, capture_output=True, text=True, timeout=240)
     assert r.returncode == 0 and "ok" in r.stdout, r.stdout + r.stderr
 
 

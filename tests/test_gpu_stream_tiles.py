@@ -11,7 +11,7 @@ from gpu_util import assert_close, make, to_device
 import paper_2605_28657_amd as pa
 from paper_2605_28657_amd import DemonVAE, DemonVAEEncoder
 
-pytestmark = pytest.mark.gpu
+pytestmark = [pytest.mark.gpu, pytest.mark.usefixtures("grid")]
 
 
 @pytest.mark.parametrize("spec,T,kw", [
@@ -79,7 +79,7 @@ def test_unit_256_stream_tiles(T, dils):
     (128, 9000, 119), (128, 45000, 20001),   # 64 columns a workgroup; 256
     (64, 3001, 64), (64, 150001, 60000), (64, 530000, 300000),      # 128 columns (with the head in the short window); 256
 ])
-def test_units_of_large_calls_window_by_window(c, T, window):
+def test_units_of_large_calls_window_by_window(c, T, window, grid):
     """The residual units' kernels for launches that fill the chip, on windows whose ends fall inside a tile: the same bits as the whole clip,
     and as a window short enough for the kernel of few tiles."""
     spec = di.DecoderSpec(64, (2,), (c,), (1, 3, 9))
@@ -88,6 +88,7 @@ def test_units_of_large_calls_window_by_window(c, T, window):
     zt = to_device(z, "bf16")
     full = vae.decode_windowed(zt, window=T, halo=-1)
     assert torch.equal(vae.decode_windowed(zt, window=window, halo=-1), full)
+    assert vae.last_grid()[0] == (-(-T // window) if grid == "callers" else 2)
     out = vae.decode_windowed(zt, window=15, halo=-1, frame_begin=T // 2, frame_end=T // 2 + 15)
     S = spec.total_stride
     assert torch.equal(out[:, :, T // 2 * S:(T // 2 + 15) * S], full[:, :, T // 2 * S:(T // 2 + 15) * S])

@@ -9,7 +9,7 @@ import demon_inputs as di
 import paper_2605_28657_amd as pa
 from gpu_util import make, to_device
 
-pytestmark = pytest.mark.gpu
+pytestmark = [pytest.mark.gpu, pytest.mark.usefixtures("grid")]
 
 STACK_WIDE = di.DecoderSpec(64, (2, 2), (256, 64), (1, 3, 9))
 
