@@ -2,8 +2,9 @@
 """Benchmark of the windowed VAE decode on one MI355X.
 
 One step = one windowed decode (gather -> transposed/dilated/1x1 convolutions -> head) of the
-60 s, 48 kHz stereo workload: a 64 x 1500 latent cut into 24 windows of 64 frames plus a 6-frame halo,
-all windows in one batch.  Inputs are synthetic (seeded) and resident in HBM before the timed region.
+60 s, 48 kHz stereo workload: a 64 x 1500 latent, asked for in 24 windows of 64 frames plus a 6-frame halo.  With a halo of the
+receptive field no sample depends on the grid, and the library computes the clip in fewer, longer windows (two of 750 frames;
+config.computed says what the last timed step ran).  Inputs are synthetic (seeded) and resident in HBM before the timed region.
 Prints ONE JSON line.
 
   python bench.py [--gpus 1] [--steps K] [--warmup W] [--workload NAME] [--no-cpu-baseline]
@@ -20,6 +21,12 @@ if ROOT not in sys.path:
 
 PEAK_BF16_TFLOPS = 2500.0      # MI355X dense bf16 MFMA
 PEAK_HBM_GBS = 8000.0
+
+
+def grid_of(handle):
+    """The windows that the handle's last call computed, which need not be those asked for."""
+    windows, frames, groups = handle.last_grid()
+    return {"windows": windows, "extended_frames": frames, "groups_on_streams": groups}
 
 
 def kernel_sources_digest():
@@ -229,6 +236,7 @@ def main():
     t1 = time.perf_counter()
     groups = np.array(vae.get_timing())                # average over the timed steps (the last 32 at most)
     ms_per_step = (t1 - t0) * 1e3 / args.steps
+    computed = grid_of(vae)
     audio_s = wl.n_clips * wl.n_frames / 25.0
 
     conv_f, head_f = conv_flops_per_frame(spec)
@@ -246,7 +254,7 @@ def main():
         "higher_is_better": True, "scaling": "weak", "vs_baseline": None,
         "dtype": dtype, "data": "synthetic",
         "config": {"workload": args.workload, "latent": [wl.n_clips, spec.latent_channels, wl.n_frames],
-                   "window": wl.window, "halo": halo, "n_windows": n_windows,
+                   "window": wl.window, "halo": halo, "n_windows": n_windows, "computed": computed,
                    "strides": list(spec.strides), "widths": list(spec.widths),
                    # the 16-bit formats of the bf16 path (bf16 and f16 MFMA have the same peak rate)
                    "operands": ("weights: bf16 values; activation operands: bf16 below 512 channels, IEEE half from 512 "
@@ -275,7 +283,7 @@ def main():
         result["hbm_kernels"]["head"] = {"GB/s": head_bytes / (groups[2] * 1e-3) / 1e9,
                                          "frac": head_bytes / (groups[2] * 1e-3) / 1e9 / PEAK_HBM_GBS}
     else:
-        # calls of a few windows run the head inside the last residual unit's kernel: no launch of its own
+        # the head inside the last residual unit's kernel: no launch of its own
         result["hbm_kernels"]["head"] = {"note": "ran inside the last 64-channel unit's kernel (counted under convolutions)"}
 
     if args.detail:
@@ -429,7 +437,8 @@ def main():
                             "stage_ms": {"stem": float(eg[0]), "convolutions": float(eg[1]), "sampling_step": float(eg[2])},
                             "roofline_frac": enc_f * frames / (float(eg[1]) * 1e-3) / 1e12 / PEAK_BF16_TFLOPS,
                             "algorithmic_flop": enc_f * frames,
-                            "config": "windowed encode of the same shape: %d windows of %d frames + halo 6, one batch" % (n_windows, wl.window)}
+                            "config": {"note": "windowed encode of the same shape", "window": wl.window, "halo": halo, "n_windows": n_windows,
+                                       "computed": grid_of(enc)}}
         if args.detail:
             enc.set_timing(2)
             enc.encode_windowed(wave, window=wl.window, halo=-1, eps=eps, moments=mom, latent=zl)
