@@ -125,6 +125,7 @@ struct demon_vae {
     demon_dtype dtype = DEMON_F32;
     int max_frames = 0, max_clips = 0;
     long long cap_frames = 0;
+    double frame_flop = 0;             // operations of the convolutions for one latent frame
     long long per_frame = 0;           // largest rate x width of a layer: elements of one latent frame at its widest
     int rf_left = 0, rf_right = 0;
     int device = 0;
@@ -278,19 +279,24 @@ bool callers_own(const demon_vae* v) { return v->callers_grid || (v->tap_layer >
 
 // Whether every clip is cut in two, for calls that may run as the two groups below and would otherwise have unequal ones: an odd number of
 // clips, with a second stream and no gate (gated, one window a clip / two: one clip of 1500 frames 5191 / 5268, 3 x 150 1730 / 1809).  Per-launch
-// timing, which runs one group, times the launches of the grid that calls compute.  A join
-// computes twice the receptive field again (12 frames on the x1920 stack) in every clip.  In us, one window a clip / two:
+// timing, which runs one group, times the launches of the grid that calls compute.  A join computes twice the receptive field again (12 frames
+// on the x1920 stack) in every clip, and two groups are twice the launches.  In us, one window a clip / two:
 //  * one clip: 330 frames 1348 / 1330, 360 frames 1428 / 1429, 400 frames 1510 / 1509, 440 frames 1778 / 1624, 520 frames 1975 / 1880, encode of 400
 //    frames 1520 / 1605, 440 frames 1790 / 1703; with LDS-staged convolutions 100 frames 994 / 1000, 200 frames 1395 / 1432, 250 frames 1683 / 1582.
+//  * one clip of a smaller stack: what two groups cover is a share of each launch, so it takes as much work to be worth it.  512 to 64
+//    channels at 768 samples a frame (0.63 GFLOP a frame): 440 frames 429 / 444, 700 631 / 581; with LDS-staged convolutions (0.43) 330 frames 396 / 410, 440 486 / 511,
+//    700 701 / 670; 512 to 96 at 32 samples (0.12) 700 frames 215 / 258, 1500 319 / 331; 128 to 64 at 8 samples, bound by the launches, 700 frames 53 / 106.
 //  * more clips: decode of 3 x 150 frames 1688 / 1693, 3 x 250 2610 / 2674, 3 x 300 3131 / 3093, 3 x 420 4459 / 4349, 3 x 1500 15595 / 15364, 5 x 150 2590 / 2699,
 //    5 x 250 4422 / 4346, 5 x 300 5225 / 5202, 7 x 64 1675 / 1740, 7 x 200 4852 / 4835; encode of 3 x 150 1741 / 1753, 3 x 250 2803 / 2792, 3 x 350 3717 / 3741, 3 x 420
 //    4611 / 4499, 3 x 1500 15602 / 15514, 5 x 90 1724 / 1821, 5 x 300 5389 / 5425, 5 x 420 7428 / 7362, 7 x 64 1670 / 1916, 7 x 200 4912 / 5073.  With LDS-staged
-//    convolutions (960 to 64 channels) decode of 3 x 230 4369 / 4360, 3 x 400 7555 / 7570, encode of 3 x 230 4755 / 4817, 3 x 400 8013 / 8480.
+//    convolutions (960 to 64 channels) decode of 3 x 230 4369 / 4360, 3 x 300 5732 / 5704, 3 x 400 7555 / 7570, encode of 3 x 230 4755 / 4817, 3 x 400 8013 / 8480.
+constexpr double kCutFlop = 300e9;
+
 bool cut_clips(const demon_vae* v, int n_clips, long long span, bool gated)
 {
-    if (n_clips % 2 == 0 || !v->stream2 || gated) return false;
+    if (n_clips % 2 == 0 || !v->stream2 || gated || v->frame_flop * span * n_clips < kCutFlop) return false;
     if (n_clips == 1) return span >= (v->has_staged_convs ? 230 : 420);
-    return !v->has_staged_convs && span >= (v->encoder ? 420 : 300);
+    return v->encoder ? !v->has_staged_convs && span >= 420 : span >= 300;
 }
 
 Grid computed_grid(const demon_vae* v, int n_clips, int n_frames, int fb, int fe, int window, int halo, long long frames_held, bool cut)
@@ -1020,6 +1026,15 @@ demon_status create_impl(const demon_vae_config* cfg, const float* host_weights,
         if (!encoder) { Step t; t.conv = &B.up; v->steps.push_back(t); }
         for (int j = 0; j < nres; ++j) { Step t; t.unit = &B.res[j]; v->steps.push_back(t); }
         if (encoder) { Step t; t.conv = &B.up; v->steps.push_back(t); }
+    }
+    {
+        double r = 1;
+        if (encoder) for (int s : st.strides) r *= s;
+        for (const Step& t : v->steps) {
+            const ConvLayer& L = t.conv ? *t.conv : t.unit->dilated;
+            if (t.conv) r = L.down > 0 ? r / L.down : r * L.stride;
+            v->frame_flop += 2.0 * r * L.cin * L.cout * (t.conv ? L.ntaps : L.ntaps + 1);
+        }
     }
     auto operand_layer = [](const Step& t) -> const ConvLayer* {
         if (t.conv) return t.conv;

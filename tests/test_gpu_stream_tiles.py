@@ -88,7 +88,7 @@ def test_units_of_large_calls_window_by_window(c, T, window, grid):
     zt = to_device(z, "bf16")
     full = vae.decode_windowed(zt, window=T, halo=-1)
     assert torch.equal(vae.decode_windowed(zt, window=window, halo=-1), full)
-    assert vae.last_grid()[0] == (-(-T // window) if grid == "callers" else 2)
+    assert vae.last_grid()[0] == (-(-T // window) if grid == "callers" else 2 if c == 512 else 1)
     out = vae.decode_windowed(zt, window=15, halo=-1, frame_begin=T // 2, frame_end=T // 2 + 15)
     S = spec.total_stride
     assert torch.equal(out[:, :, T // 2 * S:(T // 2 + 15) * S], full[:, :, T // 2 * S:(T // 2 + 15) * S])
