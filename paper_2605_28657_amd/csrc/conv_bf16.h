@@ -34,6 +34,15 @@ struct MfmaParams {
     float* part;             // MODE_PART: [row][part][cout]
 };
 
+// MODE_PART: byte offset of a piece's sums in rows of kConvParts x cout floats, from its offset in rows of cout halves and its first
+// channel.  A surplus piece of a tile stays out of range: the row of kOutOfRange, times sixteen, would wrap to an offset near
+// 2 GiB, inside the sums of a large window.
+constexpr unsigned kOutOfRange = 0xf8000000u;
+__host__ __device__ constexpr unsigned part_voff(unsigned off, unsigned ch)
+{
+    return off >= kOutOfRange ? off : (off - ch * 2u) * (kConvParts * 2u) + ch * 4u;
+}
+
 // kernels_bf16_stream.hip: weights streamed to registers, on weights packed for the 128 x 128 tile (variant 0).  `rows` is the
 // GEMM's M, `ncols` the most columns a window needs, `mode`, `in_fmt` and `emit` as the template arguments of the
 // other kernels; `call_slots` the windows of the whole call, `n_slots` those of this launch; launches of more than `max_small`

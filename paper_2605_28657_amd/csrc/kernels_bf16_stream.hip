@@ -155,7 +155,7 @@ __global__ __launch_bounds__(64 * WM * WN, MODE == MODE_UP && TM * TN == 16 && I
     const int ec = m0 + (tid % PPR) * 8, er0 = tid / PPR;
     auto eoff = [&](int ep, int it) __attribute__((always_inline)) -> unsigned {
         const int r = er0 + it * ERPP;
-        if (NT / EP % ERPP != 0 && r >= NT / EP) return 0xf8000000u;         // out of range
+        if (NT / EP % ERPP != 0 && r >= NT / EP) return kOutOfRange;
         const int n = n0 + r / WROWS * (16 * TN) + ep * WROWS + r % WROWS;
         // transposed conv: column n, row mu lands on the run starting at (n s - p) cout + mu; a negative row wraps: out of range
         return (MODE == MODE_UP ? (unsigned)((n * p.stride - p.stride / 2) * p.cout + ec) : (unsigned)(n * p.cout + ec)) * 2u;
@@ -334,7 +334,7 @@ __global__ __launch_bounds__(64 * WM * WN, MODE == MODE_UP && TM * TN == 16 && I
             for (int e = 0; e < 8; ++e) v[e] = src[e];
             const unsigned off = eoff(ep, it);
             if constexpr (MODE == MODE_PART) {
-                const unsigned at = (off - ec * 2u) * (kConvParts * 2u) + ec * 4u;
+                const unsigned at = part_voff(off, (unsigned)ec);
                 __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, f32x4{v[0], v[1], v[2], v[3]}), rs_p, at, 0, 0);
                 __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, f32x4{v[4], v[5], v[6], v[7]}), rs_p, at + 16u, 0, 0);
                 continue;

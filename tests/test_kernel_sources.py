@@ -56,6 +56,36 @@ def test_the_parameter_allocation_ends_with_the_slack():
     assert re.search(r"ar\.reserve\(kWeightSlack\);\s*hipError_t e = hipMalloc\(&v->d_params, ar\.bytes\.size\(\)\)", text)
 
 
+def test_surplus_pieces_of_sums_in_parts_stay_out_of_range():
+    """The offset of a tile's surplus piece, scaled to rows of sums, lies past every descriptor the launch accepts; other offsets are the
+    row's, as far as a window's sums reach."""
+    import ctypes
+    import subprocess
+    import tempfile
+    text = open(os.path.join(b.CSRC, "conv_bf16.h")).read()
+    stream = open(os.path.join(b.CSRC, "kernels_bf16_stream.hip")).read()
+    (parts,) = re.findall(r"constexpr int kConvParts = (\d+);", open(os.path.join(b.CSRC, "internal.h")).read())
+    (limit,) = re.findall(r"max_out_bytes > (0x\w+)ll\) return hipErrorInvalidValue;", open(os.path.join(b.CSRC, "kernels_bf16.hip")).read())
+    parts, limit = int(parts), int(limit, 16)
+    assert "part_voff(off, (unsigned)ec)" in stream and "return kOutOfRange;" in stream
+    out_of_range = int(re.search(r"kOutOfRange = (0x\w+)u;", text).group(1), 16)
+    fn = re.search(r"__host__ __device__ (constexpr unsigned part_voff\(.*?\n})", text, re.S).group(1)
+    with tempfile.TemporaryDirectory() as d:
+        src, lib = os.path.join(d, "f.cpp"), os.path.join(d, "f.so")
+        open(src, "w").write(f"constexpr int kConvParts = {parts};\nconstexpr unsigned kOutOfRange = {out_of_range}u;\n{fn}\n"
+                             "extern \"C\" unsigned f(unsigned off, unsigned ch) { return part_voff(off, ch); }\n")
+        subprocess.run(["g++", "-std=c++17", "-shared", "-fPIC", "-o", lib, src], check=True)
+        f = ctypes.CDLL(lib).f
+        f.restype, f.argtypes = ctypes.c_uint, [ctypes.c_uint, ctypes.c_uint]
+        for cout in (128, 256):
+            last = limit // (4 * parts * cout) - 1                      # last row of the largest window
+            for ch in range(0, cout, 8):
+                assert f(out_of_range, ch) >= limit
+                for row in (0, 1, 97, last - 1, last, last + 127):      # a tile's columns run past the last row
+                    at = f((row * cout + ch) * 2, ch)
+                    assert at == row * parts * cout * 4 + ch * 4 and (row <= last) == (at + 32 <= limit)
+
+
 def _resources():
     """{kernel: (bytes of scratch memory, spilled registers)} of the gfx950 code in the built library."""
     import subprocess
