@@ -17,21 +17,26 @@ enum { MODE_ACT = 0,   // bias + Snake, bf16 out only                     (dilat
 // MODE_RES, MODE_UP and MODE_DOWN may in addition emit the activated operand of the next layer: EMIT = 0 none, else the
 // operand format + 1 (1 bf16, 2 bf16 hi + lo, 3 half).  IN is the operand format of the input.
 
+// No larger than it needs to be: the host bounds a call of empty launches (a gated call whose clips are skipped), and where it is slow to
+// issue them (some processes are, from their start to their end) such a call of a 3 s window takes 82 to 84 us with the 144
+// bytes that this and the grid come to, 86 to 88 with 152 and with 160, in turn in one process.
 struct MfmaParams {
     const uint16_t* xa;      // activated input, 16-bit [rows][cin] in the kernel's IN format; lo plane at xa + in_lo_off
     const uint16_t* w;       // packed weight blocks
     const float* bias;
     hres_t* y;               // residual-stream output; MODE_RES: also the residual source (in place); unused in MODE_ACT
-    bool y_dead;             // MODE_RES: y is read only, nothing after this layer reads the sum
-    uint16_t* ya;            // activated output in the kernel's EMIT format; lo plane at ya + out_lo_off
+    union {
+        uint16_t* ya;        // activated output in the kernel's EMIT format; lo plane at ya + out_lo_off
+        float* part;         // MODE_PART: [row][part][cout]
+    };
     const float* out_alpha; const float* out_inv_beta;   // Snake applied before writing ya
     const Slot* slots;
     int r_in, cin, cout, ntaps, tap0, tap_step, stride, nchunks, margin;
     int mtiles_x;            // > 0: blockIdx.x enumerates (column tile, row tile), see the kernel; 0: blockIdx.z = row tile
-    int xcd_group;           // with mtiles_x: 1 = all row tiles of a column tile on one XCD, 0 = row tiles dealt over the XCDs
+    bool y_dead;             // MODE_RES: y is read only, nothing after this layer reads the sum
+    bool xcd_group;          // with mtiles_x: 1 = all row tiles of a column tile on one XCD, 0 = row tiles dealt over the XCDs
     unsigned w_bytes;
     long long in_lo_off, out_lo_off;     // element offsets of the lo planes
-    float* part;             // MODE_PART: [row][part][cout]
 };
 
 // MODE_PART: byte offset of a piece's sums in rows of kConvParts x cout floats, from its offset in rows of cout halves and its first

@@ -509,12 +509,13 @@ hipError_t launch_conv_bf16(const ConvArgs& a, int variant, hipStream_t stream)
     const int cin = a.cin * merge, r_in = a.r_in / merge, ntaps = a.down > 0 ? 4 : a.ntaps;
     MfmaParams p;
     p.xa = (const uint16_t*)a.x; p.w = (const uint16_t*)a.w; p.bias = a.bias;
-    p.y = (hres_t*)a.y; p.y_dead = a.y_dead; p.ya = (uint16_t*)a.ya;
+    p.y = (hres_t*)a.y; p.y_dead = a.y_dead;
+    if (a.part) p.part = a.part; else p.ya = (uint16_t*)a.ya;
     p.out_alpha = a.out_alpha; p.out_inv_beta = a.out_inv_beta;
     p.slots = a.slots;
     p.r_in = r_in; p.cin = cin; p.cout = a.cout; p.ntaps = ntaps; p.stride = a.stride;
     p.nchunks = cin / v.KC; p.margin = a.margin;
-    p.in_lo_off = a.in_lo_off; p.out_lo_off = a.out_lo_off; p.part = a.part;
+    p.in_lo_off = a.in_lo_off; p.out_lo_off = a.out_lo_off;
     const size_t wb = (size_t)M * ntaps * cin * 2;
     if (wb > 0xffffffffull) return hipErrorInvalidValue;
     // room for the slack in the descriptor.  (Saturated in the kernel, the sum is a vector instruction, the descriptor no longer

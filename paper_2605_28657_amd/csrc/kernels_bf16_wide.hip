@@ -36,7 +36,6 @@ constexpr int W_NCHUNKS = W_CH / W_KC;
 struct WideParams {
     const uint16_t* xa;          // activated input, bf16 [rows][256]
     hres_t* y;                   // residual stream, in place
-    bool y_dead;                 // EMIT: y is read only, nothing after the unit reads the sum
     uint16_t* ya;                // optional bf16(snake_next(y)) (EMIT); not the buffer of xa
     const uint16_t* w7;          // [chunk][tap] blocks of 256 x 32 bf16
     const uint16_t* w1;          // [chunk] blocks of 256 x 32 bf16, K axis permuted
@@ -45,6 +44,7 @@ struct WideParams {
     const float* a3; const float* ib3;    // Snake of the consumer (EMIT)
     const Slot* slots;
     int r, ntaps, tap0, tap_step, margin;
+    bool y_dead;                 // EMIT: y is read only, nothing after the unit reads the sum
 };
 
 template <bool EMIT>

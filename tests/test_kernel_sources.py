@@ -86,8 +86,8 @@ def test_surplus_pieces_of_sums_in_parts_stay_out_of_range():
                     assert at == row * parts * cout * 4 + ch * 4 and (row <= last) == (at + 32 <= limit)
 
 
-def _resources():
-    """{kernel: (bytes of scratch memory, spilled registers)} of the gfx950 code in the built library."""
+def _resources(fields=("private_segment_fixed_size", "vgpr_spill_count")):
+    """{kernel: (bytes of scratch memory, spilled registers)}, or other fields, of the gfx950 code in the built library."""
     import subprocess
     import tempfile
     llvm = "/opt/rocm/llvm/bin"
@@ -106,7 +106,7 @@ def _resources():
             notes = subprocess.run([f"{llvm}/llvm-readelf", "--notes", elf], capture_output=True, text=True, check=True).stdout
             for k in notes.split("- .agpr_count:")[1:]:
                 field = lambda f: re.search(rf"\.{f}:\s+(\S+)", k).group(1)
-                out[field("name")] = int(field("private_segment_fixed_size")), int(field("vgpr_spill_count"))
+                out[field("name")] = tuple(int(field(f)) for f in fields)
     return out
 
 
@@ -115,6 +115,19 @@ def test_convolution_kernels_keep_their_accumulators_in_registers():
     res = {n: r for n, r in _resources().items() if "conv_" in n or "res_unit_wide" in n or "res_unit_narrow" in n}
     assert len(res) > 100
     assert {n: r for n, r in res.items() if r != (0, 0)} == {}
+
+
+def test_kernel_arguments_do_not_grow():
+    """The host bounds a call of empty launches (a gated call whose clips are skipped), and issues the launches with longer arguments later."""
+    limit = {"conv_stream_kernel": 144, "conv_tall_kernel": 144, "conv_mfma_kernel": 128, "res_unit_fused_kernel": 456,
+             "res_unit_narrow_stream_kernel": 456, "res_unit_wide": 376}
+    seen = set()
+    for name, (size,) in _resources(("kernarg_segment_size",)).items():
+        for k, most in limit.items():
+            if re.search(rf"\d{k}", name):
+                seen.add(k)
+                assert size <= most, (name, size)
+    assert seen == set(limit)
 
 
 def test_descriptors_are_scalar():
