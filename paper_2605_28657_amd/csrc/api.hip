@@ -283,14 +283,17 @@ bool callers_own(const demon_vae* v) { return v->callers_grid || (v->tap_layer >
 // on the x1920 stack) in every clip, and two groups are twice the launches.  In us, one window a clip / two:
 //  * one clip: 330 frames 1348 / 1330, 360 frames 1428 / 1429, 400 frames 1510 / 1509, 440 frames 1778 / 1624, 520 frames 1975 / 1880, encode of 400
 //    frames 1520 / 1605, 440 frames 1790 / 1703; with LDS-staged convolutions 100 frames 994 / 1000, 200 frames 1395 / 1432, 250 frames 1683 / 1582.
-//  * one clip of a smaller stack: what two groups cover is a share of each launch, so it takes as much work to be worth it.  512 to 64
-//    channels at 768 samples a frame (0.63 GFLOP a frame): 440 frames 429 / 444, 700 631 / 581; with LDS-staged convolutions (0.43) 330 frames 396 / 410, 440 486 / 511,
-//    700 701 / 670; 512 to 96 at 32 samples (0.12) 700 frames 215 / 258, 1500 319 / 331; 128 to 64 at 8 samples, bound by the launches, 700 frames 53 / 106.
+//  * one clip of a smaller stack: what two groups cover is a share of each launch, so it takes as much work to be worth it, and a call that is waited
+//    for pays for fork and join as well.  Back to back / waited for, one window, two: 512 to 64 channels at 768 samples a frame (0.63 GFLOP a frame)
+//    480 frames 434 / 453, 455 / 513; 600 frames 503 / 520, 520 / 601; 700 frames 631 / 647, 584 / 680; its encode 642 / 659, 610 / 653; with LDS-staged
+//    convolutions (0.43) 700 frames 694 / 714, 665 / 761; 900 frames 801 / 824, 771 / 877; 1000 frames 866 / 887, 836 / 899; 1200 frames 1061 / 1073, 967 / 1036, its
+//    encode 1075 / 1086, 1005 / 1016.  512 to 96 channels at 32 samples (0.12) 700 frames 215, 258, 1500 frames 319, 331; 128 to 64 at 8 samples, bound by the
+//    launches, 700 frames 53, 106.
 //  * more clips: decode of 3 x 150 frames 1688 / 1693, 3 x 250 2610 / 2674, 3 x 300 3131 / 3093, 3 x 420 4459 / 4349, 3 x 1500 15595 / 15364, 5 x 150 2590 / 2699,
 //    5 x 250 4422 / 4346, 5 x 300 5225 / 5202, 7 x 64 1675 / 1740, 7 x 200 4852 / 4835; encode of 3 x 150 1741 / 1753, 3 x 250 2803 / 2792, 3 x 350 3717 / 3741, 3 x 420
 //    4611 / 4499, 3 x 1500 15602 / 15514, 5 x 90 1724 / 1821, 5 x 300 5389 / 5425, 5 x 420 7428 / 7362, 7 x 64 1670 / 1916, 7 x 200 4912 / 5073.  With LDS-staged
 //    convolutions (960 to 64 channels) decode of 3 x 230 4369 / 4360, 3 x 300 5732 / 5704, 3 x 400 7555 / 7570, encode of 3 x 230 4755 / 4817, 3 x 400 8013 / 8480.
-constexpr double kCutFlop = 300e9;
+constexpr double kCutFlop = 430e9;
 
 bool cut_clips(const demon_vae* v, int n_clips, long long span, bool gated)
 {

@@ -21,8 +21,8 @@ pytestmark = [pytest.mark.gpu, pytest.mark.usefixtures("grid")]
     (di.DecoderSpec(64, (4, 2), (128, 64)), 310, 64, 3, {}),                    # so here
     (di.DecoderSpec(32, (4, 2), (96, 32)), 240, 37, 1, {}),                     # LDS-staged tiles
     (di.DecoderSpec(64, (4, 2), (96, 64), (1, 3)), 230, 60, 1, {}),             # LDS-staged tiles, the head inside the last unit
-    (di.DecoderSpec(64, (8, 6, 4, 4), (512, 256, 128, 64)), 480, 64, 1, {}),    # one clip, cut in two
-    (di.DecoderSpec(32, (8, 6, 4, 4), (512, 256, 96, 32)), 710, 90, 1, {}),     # so, LDS-staged tiles
+    (di.DecoderSpec(64, (8, 6, 4, 4), (512, 256, 128, 64)), 690, 64, 1, {}),    # one clip, cut in two
+    (di.DecoderSpec(32, (8, 6, 4, 4), (512, 256, 96, 32)), 1010, 90, 1, {}),     # so, LDS-staged tiles
 ])
 def test_two_groups_equal_one_stream(spec, T, window, clips, kw, grid):
     vae, w, z = make(spec, "bf16", T, n_clips=clips, max_extended_frames=8 * T * clips, **kw)
@@ -72,7 +72,7 @@ def test_two_groups_equal_one_stream(spec, T, window, clips, kw, grid):
     vae.close(); one.close()
 
 
-@pytest.mark.parametrize("spec,T,clips", [(di.DecoderSpec(64, (4, 2), (128, 64)), 250, 2), (di.DecoderSpec(64, (8, 6, 4, 4), (512, 256, 128, 64)), 480, 1),
+@pytest.mark.parametrize("spec,T,clips", [(di.DecoderSpec(64, (4, 2), (128, 64)), 250, 2), (di.DecoderSpec(64, (8, 6, 4, 4), (512, 256, 128, 64)), 690, 1),
                                           (di.DecoderSpec(64, (32,), (64,)), 250, 2)])          # the last convolution's K in parts
 @pytest.mark.parametrize("short", [0, 1])
 def test_encode_in_two_groups_equals_one_stream(spec, T, clips, short):
