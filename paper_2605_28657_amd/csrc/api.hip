@@ -943,8 +943,11 @@ demon_status create_impl(const demon_vae_config* cfg, const float* host_weights,
             rate /= s;
             per_frame = std::max(per_frame, rate * cn);
             // The last one has the longest K (1024 channels, stride 10: 20480) and the fewest columns, one a frame: 12 workgroups for 75 frames and 26 us a
-            // launch in one piece, 9 in parts; 72 and 18 for 60 s.  In parts wherever its chunks divide (whole stages of two chunks), whatever the
-            // call's size, so that a value does not depend on that; up to 256 rows, and where the sums fit where the residual stream would go.
+            // launch in one piece, 9 in parts; 72 and 18 for 60 s.  In parts whatever the call's size, so that a value does not depend on that, although very long
+            // calls lose by the sums' traffic, in us with an event after the launch, conv and sampling step, one piece / parts: K of 20480 27 + 6 / 8 + 6 up to 400
+            // frames, 68 + 13 / 46 + 15 at 6000, 169 + 36 / 170 + 50 at 24000; K of 4096 to 128 rows 9 + 6 / 7 + 6, 15 + 12 / 19 + 14, 40 + 35 / 59 + 40 (that whole
+            // encode 354 us before, 314 with the stem's gain).  For K whose 64-channel chunks divide into eight parts of whole stages of two chunks (others, 75 chunks of
+            // 960 channels at stride 10, go in one piece), up to 256 rows, and where the sums fit where the residual stream would go.
             L.parts = bf && l == 0 && L.variant == 0 && cn <= 256 && c * (s / 2) % (128 * kConvParts) == 0 && 2ll * kConvParts * cn <= per_frame;
         }
         // Rows each layer must produce beyond a window's interior, walked from the moments back to the stem: a strided

@@ -486,12 +486,13 @@ __device__ __forceinline__ void unrolled(std::integer_sequence<int, I...>, Fn&& 
 // branch tensor through LDS.  What bound the kernel above: two barriers per 8 or 16 KB weight block (a launch of few tiles lasts as long as
 // one workgroup's 14 of them), and at 128 channels LDS reads (6 KB per wave and 256 cycles of MFMAs).  Here a stage of 64 channels has all its taps
 // between two barriers and the next stage's Snake runs in the shadow of its MFMAs, a quarter row every other group of TM MFMAs.
-// Times: a launch with an event after it in a call that is waited for (4 to 5 us of each are the events); in back-to-back steps at the power
-// limit the 128-channel units of a 60 s clip take 452 to 494 us.
+// Times: a launch with an event after it in a call that is waited for (4 to 5 us of each are the events; in back-to-back steps at the power
+// limit the 128-channel units of a 60 s clip take 376 to 399 us on one stream).
 //  * 128 channels, large calls: 64 x 128 per wave, 2 x 2 waves, two workgroups per CU (256 registers, 80 KB): a third of the LDS reads.
 //    What bounds it now is the two waves of a SIMD: matrix cores busy 50 %, other VALU work (Snake of 1.25 + 1 values per output) 30 %,
 //    which overlap in part.  Waves in the K loop go first (s_setprio: -5 %), those in the 1x1 conv before them: at the default priority its 2 k
-//    cycles of MFMAs took 9 of a workgroup's 60 k beside the other's K loop (366 -> 346 us; the same priority 343, but the call 5090 instead of 5083).
+//    cycles of MFMAs took 9 of a workgroup's 60 k beside the other's K loop (366 -> 346 us; at the loop's own priority 343, and calls the same within
+//    0.1 %: 60 s clip 4808 to 4818 us in eight runs of either).
 //    60 s clip 428 -> 346 us per unit (with the operand 458 -> 366), 375 frames 104 to 121 -> 89 to 98.
 //  * 128 channels, few tiles: 32 x 64 per wave, 4 x 1 waves: window of 13 frames 25 -> 11 us, 75 frames 36 -> 27.
 //  * 64 channels: one stage, two by two waves of 32 channels: 13 frames 13 -> 9 us (with the head 19 -> 11), 75 frames 20 -> 17 (28 -> 23),
@@ -945,9 +946,10 @@ hipError_t launch_res_unit_fused(const FusedArgs& a, hipStream_t stream)
         return hipGetLastError();
     }
     // 64 channels.  Per unit in us, LDS-staged / 128 columns / 256 columns: 13 frames 13, 12 / 9, 8 / 10, 10; 75 frames 19 / 17 / 17; 150 frames
-    // 30 / 27 / 27; 200 frames 35 / 34 / 32; 500 frames 79 / - / 71.  Tensors beyond the last-level cache suit the staged kernel's stores of whole
-    // rows better where a launch is waited for (600 frames 97 / - / 102, 1000 frames 163 / - / 175), but not in calls back to back, beside
-    // the other group and at the power limit: 60 s clip 5059 us staged, 5033 streamed, its encode 5078 and 5056.
+    // 30 / 27 / 27; 200 frames 35 / 34 / 32.  Beyond the last-level cache the stores of whole rows of the staged kernel gain nothing: on one
+    // stream with an event after the launch (gated calls run so), staged / 256 columns: 375 frames 60 / 55, 500 frames 77 / 72, 600 frames 92 / 93, 1000 frames 160 /
+    // 159, 1500 frames 242 / 240, the whole calls 1332 / 1309, 1835 / 1815, 2070 / 2067, 3334 / 3332, 4931 / 4926 (encodes 1356 / 1319, 1852 / 1831, 2163 / 2155, 3449 / 3440,
+    // 5037 / 5036); in two groups 60 s 5059 / 5033, its encode 5078 / 5056.
     if (a.ntaps == 7 && a.c == 64) {
         if (tiles(128) * a.call_slots <= 2304) DEMON_NARROW(2, 4, 2, 2, 3)
         DEMON_NARROW(2, 8, 2, 2, 3)
